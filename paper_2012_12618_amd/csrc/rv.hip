@@ -105,7 +105,8 @@ constexpr int kRefitWaves = kRefitBlock / 64;  // clusters per refit workgroup
 constexpr int kRefitBigClass = 41;             // size class of 1024 points: a workgroup each
 constexpr int kXcds = 8;                // MI355X: 8 XCDs, workgroups dealt round-robin
 constexpr int kPrepBlock = 256;
-constexpr int kRowsMax = 16;            // rows of 64 points held in registers per pass
+constexpr int kRowsMax = 16;            // register rows per pass, the most a tuning may name
+constexpr int kPassRows = 12;           // register rows per pass, the most the float32 loop holds
 constexpr int kHypGroup = 4;            // hypotheses per LDS fetch in the scoring loop
 constexpr int kSizeClasses = 128;       // quarter-octave size classes for the dispatch order
 constexpr int64_t kPlanMaxClusters = 1 << 16;  // above this, clusters run in index order
@@ -113,14 +114,21 @@ constexpr int64_t kPlanMaxClusters = 1 << 16;  // above this, clusters run in in
 // Device helpers
 // ---------------------------------------------------------------------------
 
-// Staged points: float32 (cos, sin) and v_d for scoring (v_d = +inf marks a
-// point whose azimuth or Doppler value is not finite), the float32 low parts of
-// the FP64 (cos, sin) for the solves and the refit (cs64() below), and the
-// caller's azimuths for the seed-separation test.
+// One staged point: float32 (cos, sin) and v_d for scoring (v_d = +inf marks a
+// point whose azimuth or Doppler value is not finite) and the float32 low parts
+// of the FP64 (cos, sin) for the solves and the refit (cs64() below).  All
+// twenty bytes in one record: a hypothesis's seeds are gathered at random, and
+// what a gather costs is the cache lines it touches.
+struct StagedPoint {
+    float c, s, v;
+    float clo, slo;
+};
+static_assert(sizeof(StagedPoint) == 20, "packed");
+
+// A frame's staged points and the caller's azimuths (for the seed-separation
+// test).
 struct Points {
-    const float2 *cs32;
-    const float *v32;
-    const float2 *cslo;
+    const StagedPoint *staged;
     const float *theta;
 };
 
@@ -128,8 +136,8 @@ struct Points {
 // part, c = hi + lo (an exact FP64 sum), within 2^-49 of the FP64 sincos.
 // Staging 8 bytes per point for the low parts instead of 16 for the FP64 pair
 // shortens the staging kernel, which is bound by its bytes.
-__device__ __forceinline__ double2 cs64(float2 hi, float2 lo) {
-    return make_double2((double)hi.x + (double)lo.x, (double)hi.y + (double)lo.y);
+__device__ __forceinline__ double2 cs64(const StagedPoint &p) {
+    return make_double2((double)p.c + (double)p.clo, (double)p.s + (double)p.slo);
 }
 
 struct Hypothesis {
@@ -145,17 +153,21 @@ __device__ __forceinline__ Hypothesis make_hypothesis(const Points &pts, Span sp
     uint32_t i, j;
     seed_pair(u.x, u.y, (uint32_t)sp.n, i, j);
     const int64_t pi = sp.lo + i, pj = sp.lo + j;
-    // No branch before the solve: all six loads are in flight together, and
-    // an invalid pair's solve (possibly inf or NaN) is replaced by NaN.
-    const float vi = pts.v32[pi], vj = pts.v32[pj];
-    const float ti = pts.theta[pi], tj = pts.theta[pj];
-    const double2 ai = cs64(pts.cs32[pi], pts.cslo[pi]), bj = cs64(pts.cs32[pj], pts.cslo[pj]);
-    Hypothesis hy;
-    hy.valid = ((int)isfinite(vi) & (int)isfinite(vj) &
-                (int)(fabs((double)tj - (double)ti) >= RV_MIN_SEED_SEPARATION)) != 0;
+    // No branch before the solve: all loads are in flight together, and an
+    // invalid pair's solve (possibly inf or NaN) is replaced by NaN.
+    const StagedPoint pa = pts.staged[pi], pb = pts.staged[pj];
+    const double2 ai = cs64(pa), bj = cs64(pb);
     const double ci = ai.x, si = ai.y, cj = bj.x, sj = bj.y;
-    const double dvi = vi, dvj = vj;
-    const double inv_det = 1.0 / (ci * sj - si * cj);
+    const double dvi = pa.v, dvj = pb.v;
+    const double det = ci * sj - si * cj;
+    Hypothesis hy;
+    hy.valid = ((int)isfinite(pa.v) & (int)isfinite(pb.v)) != 0;
+    // The determinant is sin(theta_j - theta_i) within 2^-46, and |sin x| <=
+    // |x|: above the separation limit (with room for that error) the pair is
+    // separated.  Only below it are the azimuths themselves read.
+    if (!(fabs(det) > 1.0005 * RV_MIN_SEED_SEPARATION) && hy.valid)
+        hy.valid = fabs((double)pts.theta[pj] - (double)pts.theta[pi]) >= RV_MIN_SEED_SEPARATION;
+    const double inv_det = 1.0 / det;
     const double vx = (dvi * sj - dvj * si) * inv_det;
     const double vy = (ci * dvj - cj * dvi) * inv_det;
     hy.vx = hy.valid ? vx : __builtin_nan("");
@@ -289,16 +301,19 @@ __device__ void plan_order(const int32_t *__restrict__ off, int64_t point_base, 
 // below tau, and +inf marks it for the solves and the refit.
 __device__ __forceinline__ void stage_point(const float *__restrict__ theta,
                                             const float *__restrict__ vd, int64_t p,
-                                            float2 *__restrict__ cs32, float *__restrict__ v32,
-                                            float2 *__restrict__ cslo) {
+                                            StagedPoint *__restrict__ staged) {
     const float t = theta[p], v = vd[p];
     double s, c;
     sincos((double)t, &s, &c);
     const bool ok = isfinite(t) && isfinite(v);
     const float ch = ok ? (float)c : 0.0f, sh = ok ? (float)s : 0.0f;
-    cs32[p] = make_float2(ch, sh);
-    v32[p] = ok ? v : __builtin_inff();
-    cslo[p] = make_float2(ok ? (float)(c - (double)ch) : 0.0f, ok ? (float)(s - (double)sh) : 0.0f);
+    StagedPoint q;
+    q.c = ch;
+    q.s = sh;
+    q.v = ok ? v : __builtin_inff();
+    q.clo = ok ? (float)(c - (double)ch) : 0.0f;
+    q.slo = ok ? (float)(s - (double)sh) : 0.0f;
+    staged[p] = q;
 }
 
 // Block 0 plans the order (when `order` is non-null); it is dispatched first,
@@ -306,8 +321,7 @@ __device__ __forceinline__ void stage_point(const float *__restrict__ theta,
 // points and clear the per-cluster best keys.
 __global__ __launch_bounds__(kPrepBlock) void prep_kernel(
     const float *__restrict__ theta, const float *__restrict__ vd, int64_t n_points,
-    float2 *__restrict__ cs32, float *__restrict__ v32, float2 *__restrict__ cslo,
-    uint32_t *__restrict__ bits,
+    StagedPoint *__restrict__ staged, uint32_t *__restrict__ bits,
     int64_t n_words, const int32_t *__restrict__ off, int64_t point_base, int64_t n_clusters,
     int32_t *__restrict__ order, int64_t *__restrict__ n_big,
     unsigned long long *__restrict__ best_key) {
@@ -317,7 +331,7 @@ __global__ __launch_bounds__(kPrepBlock) void prep_kernel(
     }
     const int64_t p = (int64_t)(blockIdx.x - 1) * kPrepBlock + threadIdx.x;
     if (p < n_clusters) best_key[p] = 0;
-    if (p < n_points) stage_point(theta, vd, p, cs32, v32, cslo);
+    if (p < n_points) stage_point(theta, vd, p, staged);
     if (bits != nullptr && p < n_words) bits[p] = 0u;
 }
 
@@ -327,26 +341,10 @@ __global__ __launch_bounds__(kPrepBlock) void prep_kernel(
 // group count is read as a wave-uniform value, which keeps the loop counter on
 // the scalar unit (measured 1 % faster in the persistent batched kernel, 0.5 %
 // slower in the single-frame kernel, whose schedule it changes).
-template <int R, bool kScalarLoop = false>
-__device__ __forceinline__ uint32_t score_rows(const float2 *__restrict__ cs_chunk,
-                                               const float *__restrict__ v_chunk, int npts,
-                                               int lane, const float4 *hp, int ng, float tau) {
-    float c[R], s[R], v[R];
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-        // Uniform row base and row length, one lane offset: no per-row address
-        // registers.
-        const int len = npts - r * kWave;
-        c[r] = 0.0f;
-        s[r] = 0.0f;
-        v[r] = __builtin_inff();
-        if (lane < len) {
-            const float2 q = cs_chunk[r * kWave + lane];
-            c[r] = q.x;
-            s[r] = q.y;
-            v[r] = v_chunk[r * kWave + lane];
-        }
-    }
+template <int R, bool kScalarLoop>
+__device__ __forceinline__ uint32_t count_rows(const float (&c)[R], const float (&s)[R],
+                                               const float (&v)[R], const float4 *hp, int ng,
+                                               float tau) {
     uint32_t counts = 0;
     const int n_groups = kScalarLoop ? __builtin_amdgcn_readfirstlane(ng) : ng;
     for (int g = 0; g < n_groups; ++g) {
@@ -372,32 +370,79 @@ __device__ __forceinline__ uint32_t score_rows(const float2 *__restrict__ cs_chu
     return counts;
 }
 
+// count_rows on the points from cs_chunk, v_chunk on (npts of them, the rest of
+// the rows padded with a point that never counts).
+template <int R, bool kScalarLoop = false>
+__device__ __forceinline__ uint32_t score_rows(const float2 *__restrict__ cs_chunk,
+                                               const float *__restrict__ v_chunk, int npts,
+                                               int lane, const float4 *hp, int ng, float tau) {
+    float c[R], s[R], v[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        // Uniform row base and row length, one lane offset: no per-row address
+        // registers.
+        const int len = npts - r * kWave;
+        c[r] = 0.0f;
+        s[r] = 0.0f;
+        v[r] = __builtin_inff();
+        if (lane < len) {
+            const float2 q = cs_chunk[r * kWave + lane];
+            c[r] = q.x;
+            s[r] = q.y;
+            v[r] = v_chunk[r * kWave + lane];
+        }
+    }
+    return count_rows<R, kScalarLoop>(c, s, v, hp, ng, tau);
+}
+
+// count_rows on the npts points from `chunk` on (the rest of the rows padded with
+// a point that never counts).
+template <int R, bool kScalarLoop = false>
+__device__ __forceinline__ uint32_t score_rows(const StagedPoint *__restrict__ chunk, int npts,
+                                               int lane, const float4 *hp, int ng, float tau) {
+    float c[R], s[R], v[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        // Uniform row base and row length, one lane offset: no per-row address
+        // registers.
+        const int len = npts - r * kWave;
+        c[r] = 0.0f;
+        s[r] = 0.0f;
+        v[r] = __builtin_inff();
+        if (lane < len) {
+            const StagedPoint &q = chunk[r * kWave + lane];
+            c[r] = q.c;
+            s[r] = q.s;
+            v[r] = q.v;
+        }
+    }
+    return count_rows<R, kScalarLoop>(c, s, v, hp, ng, tau);
+}
+
 // Inlier counts of the wave's nh hypotheses (LDS at hp) over all points of the
-// cluster, rows_max (<= kMaxRows) register rows of points per pass; lane q
-// returns the count of hypothesis q.
-template <int kMaxRows = kRowsMax, bool kScalarLoop = false>
+// cluster, rows_max (at most kMaxRows are used) register rows of points per
+// pass; lane q returns the count of hypothesis q.
+template <int kMaxRows = kPassRows, bool kScalarLoop = false>
 __device__ __forceinline__ uint32_t score_cluster(const Points &pts, Span sp, int lane,
                                                   const float4 *hp, int nh, float tau,
                                                   int rows_max) {
     const int ng = (nh + kHypGroup - 1) / kHypGroup;
     const int64_t end = sp.lo + sp.n;
-    const int64_t pass = (int64_t)rows_max * kWave;
+    const int64_t pass = (int64_t)(rows_max < kMaxRows ? rows_max : kMaxRows) * kWave;
     uint32_t total = 0;
     for (int64_t base = sp.lo; base < end; base += pass) {
         const int64_t left = end - base;
         const int npts = (int)(left < pass ? left : pass);
         const int rows = (npts + kWave - 1) / kWave;
-        const float2 *cs_chunk = pts.cs32 + base;
-        const float *v_chunk = pts.v32 + base;
+        const StagedPoint *chunk = pts.staged + base;
         switch (rows) {
 #define RV_ROWS(R)                                                                   \
     case R:                                                                          \
         if constexpr (R <= kMaxRows)                                                 \
-            total += score_rows<R, kScalarLoop>(cs_chunk, v_chunk, npts, lane, hp, ng, tau); \
+            total += score_rows<R, kScalarLoop>(chunk, npts, lane, hp, ng, tau); \
         break;
             RV_ROWS(1) RV_ROWS(2) RV_ROWS(3) RV_ROWS(4) RV_ROWS(5) RV_ROWS(6) RV_ROWS(7)
-            RV_ROWS(8) RV_ROWS(9) RV_ROWS(10) RV_ROWS(11) RV_ROWS(12) RV_ROWS(13)
-            RV_ROWS(14) RV_ROWS(15) RV_ROWS(16)
+            RV_ROWS(8) RV_ROWS(9) RV_ROWS(10) RV_ROWS(11) RV_ROWS(12)
 #undef RV_ROWS
             default: break;
         }
@@ -431,8 +476,7 @@ __device__ __forceinline__ int lanes_tail(int64_t n) {
 // that the loads can be issued before other long-latency work (a hypothesis's
 // seed loads) and stored after it.
 struct PointLoad {
-    float2 cs;
-    float v;
+    float c, s, v;
 };
 
 // Thread tid's point among the `count` points from `first` (a valid point of
@@ -440,9 +484,11 @@ struct PointLoad {
 __device__ __forceinline__ PointLoad load_point(const Points &pts, int64_t first, int count) {
     const int tid = threadIdx.x;
     const int64_t p = first + (tid < count ? tid : 0);
+    const StagedPoint &q = pts.staged[p];
     PointLoad L;
-    L.cs = pts.cs32[p];
-    L.v = pts.v32[p];
+    L.c = q.c;
+    L.s = q.s;
+    L.v = q.v;
     return L;
 }
 
@@ -454,8 +500,8 @@ __device__ __forceinline__ void store_points(const PointLoad &L, int count, floa
     const int tid = threadIdx.x;
     if (tid < ((count + 3) & ~3)) {
         const bool real = tid < count;
-        reinterpret_cast<float *>(c)[tid] = real ? L.cs.x : 0.0f;
-        reinterpret_cast<float *>(s)[tid] = real ? L.cs.y : 0.0f;
+        reinterpret_cast<float *>(c)[tid] = real ? L.c : 0.0f;
+        reinterpret_cast<float *>(s)[tid] = real ? L.s : 0.0f;
         reinterpret_cast<float *>(v)[tid] = real ? L.v : __builtin_inff();
     }
 }
@@ -533,7 +579,7 @@ __device__ __forceinline__ void score_block(Span sp, ClusterId id, int b, int32_
         const int nh = (int64_t)n_hyp - h0 < kWave ? (int)((int64_t)n_hyp - h0) : kWave;
         Span rows = sp;
         rows.n -= tail;
-        uint32_t cnt = score_cluster<kRowsMax, kUniformTail>(
+        uint32_t cnt = score_cluster<kPassRows, kUniformTail>(
             pts, rows, lane, s_hyp + wave * (kWave / 2), nh, tau, rows_max);
         // The lane's own hypothesis is re-read from LDS rather than kept in
         // registers through the scoring loop.
@@ -659,8 +705,7 @@ __device__ __forceinline__ uint32_t fp16_count4(uint32_t c0, uint32_t c1, uint32
 // score_rows in the FP16 form: returns hi of hypothesis q of the wave in lane q.
 // R is a multiple of four; rows past the points are padding (w = +inf).
 template <int R>
-__device__ __forceinline__ uint32_t score_rows_fp16(const float2 *__restrict__ cs_chunk,
-                                                    const float *__restrict__ v_chunk, int npts,
+__device__ __forceinline__ uint32_t score_rows_fp16(const StagedPoint *__restrict__ chunk, int npts,
                                                     int lane, const float4 *hp, int ng, float rx,
                                                     float ry) {
     static_assert(R % 4 == 0, "rows come in blocks of four");
@@ -672,10 +717,9 @@ __device__ __forceinline__ uint32_t score_rows_fp16(const float2 *__restrict__ c
         cs[r] = 0u;
         w[r] = __builtin_inff();
         if (lane < len) {
-            const float2 q = cs_chunk[r * kWave + lane];
-            const float v = v_chunk[r * kWave + lane];
-            cs[r] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(q.x, q.y));
-            w[r] = __builtin_fmaf(-ry, q.y, __builtin_fmaf(-rx, q.x, v));
+            const StagedPoint &q = chunk[r * kWave + lane];
+            cs[r] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(q.c, q.s));
+            w[r] = __builtin_fmaf(-ry, q.s, __builtin_fmaf(-rx, q.c, q.v));
         }
     }
     uint32_t counts = 0;
@@ -711,12 +755,11 @@ __device__ __forceinline__ uint32_t score_cluster_fp16(const Points &pts, Span s
         const int64_t left = end - base;
         const int npts = (int)(left < pass ? left : pass);
         const int blocks = (npts + 4 * kWave - 1) / (4 * kWave);
-        const float2 *cs_chunk = pts.cs32 + base;
-        const float *v_chunk = pts.v32 + base;
+        const StagedPoint *chunk = pts.staged + base;
         switch (blocks) {
 #define RV_ROWS16(B)                                                                       \
     case B:                                                                                \
-        total += score_rows_fp16<4 * B>(cs_chunk, v_chunk, npts, lane, hp, ng, rx, ry);    \
+        total += score_rows_fp16<4 * B>(chunk, npts, lane, hp, ng, rx, ry);                 \
         break;
             RV_ROWS16(1) RV_ROWS16(2) RV_ROWS16(3) RV_ROWS16(4)
 #undef RV_ROWS16
@@ -818,11 +861,12 @@ __device__ __forceinline__ void score_block_lanes(Span sp, ClusterId id, int b, 
     // block barriers, which every wave reaches after its last read of it.
 }
 
-// Exact float32 counts of the nl (<= 64) hypotheses in sh.list over the whole
-// cluster; wave w scores rows [w rows/4, (w+1) rows/4) of the cluster.  Lane q
-// of every wave returns the count of list entry q.  Contains barriers.
+// Exact float32 counts of the nl (<= 64) hypotheses in `list` (LDS) over the
+// whole cluster; wave w scores rows [w rows/4, (w+1) rows/4) of the cluster.
+// Lane q of every wave returns the count of list entry q.  Contains barriers.
 __device__ __forceinline__ uint32_t exact_counts(Span sp, const Points &pts, float tau, int nl,
-                                                 Fp16Shared &sh, int wave, int lane) {
+                                                 const float4 *list, uint32_t (*part_sums)[kWave],
+                                                 int wave, int lane) {
     const int64_t rows = (sp.n + kWave - 1) / kWave;
     const int64_t r0 = rows * wave / (kScoreBlock / kWave);
     const int64_t r1 = rows * (wave + 1) / (kScoreBlock / kWave);
@@ -831,14 +875,407 @@ __device__ __forceinline__ uint32_t exact_counts(Span sp, const Points &pts, flo
     part.lo = sp.lo + r0 * kWave;
     part.n = p1 - r0 * kWave;
     part.ok = true;
-    sh.part[wave][lane] = score_cluster<kExactRows>(pts, part, lane, sh.list, nl, tau, kExactRows);
+    part_sums[wave][lane] = score_cluster<kExactRows>(pts, part, lane, list, nl, tau, kExactRows);
     __syncthreads();
     uint32_t total = 0;
 #pragma unroll
-    for (int w = 0; w < kScoreBlock / kWave; ++w) total += sh.part[w][lane];
+    for (int w = 0; w < kScoreBlock / kWave; ++w) total += part_sums[w][lane];
     __syncthreads();
     return total;
 }
+
+// ---------------------------------------------------------------------------
+// Large clusters: counting only the hypotheses that can still win.
+//
+// Only the hypothesis with the most inliers is kept, so a hypothesis need not
+// be counted once its count is known to be below another's.  Per workgroup
+// (one cluster, up to kPruneHyp hypotheses):
+//   1. reference r: among the first 256 hypotheses, the one with the most
+//      inliers in a strided sample of the points;
+//   2. one sweep over the cluster counts r exactly (T) and sorts the points
+//      into a table of direction (kAngleBins) x signed residual under r;
+//   3. every hypothesis h gets an upper bound of its count from the table: a
+//      point with direction u is an inlier of h only if its residual under r
+//      lies within tau of (h - r).u, and over one direction bin (h - r).u
+//      stays in a known interval, so h's inliers in the bin are at most the
+//      bin's points in that interval widened by tau: two prefix-sum lookups;
+//   4. the four hypotheses with the largest bounds (one per wave) are counted,
+//      which raises the best known count;
+//   5. every hypothesis whose bound still reaches the best known (count, lowest
+//      index) is counted in float32 over all points.
+// A hypothesis left out has count <= bound and loses to a counted one, so the
+// best key, and every output, is the full count's bit for bit.  (Calls that ask
+// for every hypothesis's count take the full count.)
+//
+// With 20 to 40 % outliers about one hypothesis in eight reaches r's count in
+// step 3 and one in twenty the best key in step 5.  What remains is per
+// hypothesis: the draw and solve (about 230 vector instructions per 64
+// hypotheses) and the bound (16 table lookups and about 170), against 3.7 per
+// 64 hypotheses and point of the full count.  Scoring stage before and after on
+// frames of equal clusters, 4.2M hypotheses: 4096 clusters of 512 points 152 and
+// 78 us, 1024 of 2048 points 151 and 52 us; the 4096-cluster frame of 8 to 4096
+// points 193 and 84 us; 64 clusters of 65,536 points at 4096 hypotheses 1.40 and
+// 0.33 ms.
+//
+// Rounding.  A point with |float32 residual under h| < tau has an exact
+// residual (of the float32 cos, sin, v_d and velocities) within
+// 2^-24 (2 tau + |hy|) of it; its float32 residual under r is within
+// 2^-24 (2 (tau + |hx - rx| + |hy - ry|) + |ry|) of the exact one; the float32
+// evaluation of (h - r).u at a bin's centre, the bin's centre direction and the
+// staged direction's length add at most 2^-21 (|hx - rx| + |hy - ry|).  All of
+// it is below 2^-19 (tau + M), M = |hx| + |hy| + |rx| + |ry|; the interval is
+// widened by 2^-18 (tau + M).
+// ---------------------------------------------------------------------------
+
+constexpr int kPruneHyp = 1024;     // hypotheses per workgroup, at most
+constexpr int kPruneRounds = kPruneHyp / kScoreBlock;
+
+// Smallest cluster scored this way, by blocks of 256 hypotheses per workgroup
+// (at least 1).  The table is made once per workgroup, so with several blocks
+// sharing it the bound pays from 128 points on (16,384 clusters of 128 points at
+// 1024 hypotheses: scoring stage 247 us counted in full, 212 us this way; 8192 of
+// 256 points 183 and 125 us); with one block per table only from about 320
+// points on (a frame of 1021 clusters in 3-degree windows: 37, 35 and 34 us with
+// the line at 128, 192 and 320).
+__host__ __device__ constexpr int prune_min(int rounds) {
+    return rounds == 1 ? 320 : 128;
+}
+constexpr int kAngleBins = 8;
+constexpr int kResidualBins = 256;  // 128 per sign, 16 per octave of |e| + unit (residual_bin)
+constexpr int kResidualRow = kResidualBins + 1;
+constexpr int kSampleRows = 1;      // rows of 64 points in the sample
+constexpr float kPruneMaxSpeed = 1e15f;  // references beyond it are not used
+
+struct PruneShared {
+    float4 hyp[kPruneHyp / 2];  // (vx, vy) pairs
+    float4 dir[kAngleBins];     // centre (cos, sin), half width w, w^2 / 2
+    union {
+        uint32_t hist[kAngleBins * kResidualRow];
+        struct {
+            uint32_t part[kScoreBlock / kWave][kWave];
+            float list[2 * kWave] __attribute__((aligned(16)));
+            uint16_t idx[kPruneHyp];
+        } count;
+    } u;
+    unsigned long long key[kScoreBlock / kWave];
+    float lo[kScoreBlock / kWave], hi[kScoreBlock / kWave];
+    uint32_t n[kScoreBlock / kWave];
+    uint32_t top[kScoreBlock / kWave];
+};
+
+// Position of a direction on the circle, monotone in its angle over (-pi, pi]:
+// s / (|c| + |s|) in the right half plane, continued to +-2 at the left.
+__device__ __forceinline__ float direction_key(float c, float s) {
+    const float y = s * __builtin_amdgcn_rcpf(__builtin_fabsf(c) + __builtin_fabsf(s));
+    return c >= 0.0f ? y : __builtin_copysignf(2.0f, s) - y;
+}
+
+// The unit vector of a direction key.
+__device__ __forceinline__ float2 key_direction(float q) {
+    const float a = __builtin_fabsf(q);
+    const float c = 1.0f - a;
+    const float s = __builtin_copysignf(a <= 1.0f ? a : 2.0f - a, q);
+    const float inv = 1.0f / sqrtf(c * c + s * s);
+    return make_float2(c * inv, s * inv);
+}
+
+// Residual bin of e' = e sigma, with sigma the power of two that takes tau into
+// [4, 8) (residual_scale): the octaves of |e'| + 2 in sixteen bins each, eight
+// octaves, beyond them the last bin.  Monotone in e' (the float addition, the
+// minimum and the bit pattern of a positive float are), so a window [lo, hi] of
+// residuals holds only points of bins residual_bin(lo) to residual_bin(hi).
+__device__ __forceinline__ int residual_bin(float e) {
+    const float t = fminf(__builtin_fabsf(e) + 2.0f, 511.0f);
+    // exponent field 128 to 135: its low bits and four of the mantissa
+    const uint32_t k = (__builtin_bit_cast(uint32_t, t) >> 19) & 127u;
+    return (int)(k ^ (uint32_t)(__builtin_bit_cast(int32_t, e) >> 31)) + kResidualBins / 2;
+}
+
+__device__ __forceinline__ float residual_scale(float tau) {
+    const uint32_t exponent = (__builtin_bit_cast(uint32_t, tau) >> 23) & 255u;  // tau is normal
+    return __builtin_bit_cast(float, (127u + 127u + 2u - exponent) << 23);
+}
+
+__device__ __forceinline__ float uniform_f(float v) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, v)));
+}
+
+// Scoring of hypotheses [h_first, h_first + nh), nh <= kPruneHyp, of a cluster
+// with at least kWave points.  Called by all threads of the block, also
+// from the persistent loop: every branch around a barrier is on a wave-uniform
+// value.
+__device__ __forceinline__ void score_pruned(Span sp, ClusterId id, int64_t h_first, int nh,
+                                             const Points &pts, float tau, PruneShared &sh,
+                                             unsigned long long *__restrict__ best_key,
+                                             unsigned long long *block_best = nullptr) {
+    const int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int lane = tid % kWave;
+    const uint32_t n = (uint32_t)sp.n;
+    const int rounds = (nh + kScoreBlock - 1) / kScoreBlock;
+    const StagedPoint *points = pts.staged + sp.lo;
+    float2 *hyp = reinterpret_cast<float2 *>(sh.hyp);
+
+    // Range of the points' directions.
+    float qlo = __builtin_inff(), qhi = -__builtin_inff();
+#pragma unroll 4
+    for (uint32_t p = tid; p < n; p += kScoreBlock) {
+        const float q = direction_key(points[p].c, points[p].s);  // NaN for a non-finite point (0, 0)
+        qlo = fminf(qlo, q);
+        qhi = fmaxf(qhi, q);
+    }
+    for (int i = tid; i < kAngleBins * kResidualRow; i += kScoreBlock) sh.u.hist[i] = 0;
+    for (int q = 0; q < rounds; ++q) {
+        const int hl = q * kScoreBlock + tid;
+        float2 hv = make_float2(__builtin_nanf(""), __builtin_nanf(""));
+        if (hl < nh) {
+            const Hypothesis y =
+                make_hypothesis(pts, sp, (uint32_t)(h_first + hl), id.local, id.key0, id.key1);
+            hv = make_float2((float)y.vx, (float)y.vy);  // NaN exactly when degenerate
+        }
+        hyp[hl] = hv;
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        qlo = fminf(qlo, __shfl_xor(qlo, o, kWave));
+        qhi = fmaxf(qhi, __shfl_xor(qhi, o, kWave));
+    }
+    if (lane == 0) {
+        sh.lo[wave] = qlo;
+        sh.hi[wave] = qhi;
+    }
+    __syncthreads();
+
+    // 1. Reference.
+    {
+        float c[kSampleRows], s[kSampleRows], v[kSampleRows];
+#pragma unroll
+        for (int r = 0; r < kSampleRows; ++r) {
+            const uint32_t p = (uint32_t)(((uint64_t)(r * kWave + lane) * n) / (kSampleRows * kWave));
+            const StagedPoint &u = points[p];
+            c[r] = u.c;
+            s[r] = u.s;
+            v[r] = u.v;
+        }
+        const int left = nh - wave * kWave;
+        const int ng = ((left < kWave ? left : kWave) + kHypGroup - 1) / kHypGroup;
+        const uint32_t cnt = count_rows<kSampleRows, true>(c, s, v, sh.hyp + wave * (kWave / 2), ng, tau);
+        const float2 own = hyp[tid];
+        unsigned long long key = 0;
+        if (__builtin_fabsf(own.x) + __builtin_fabsf(own.y) < kPruneMaxSpeed)  // false for NaN
+            key = hyp_key(cnt, tid);
+        key = wave_max_u64(key);
+        if (lane == 0) sh.key[wave] = key;
+    }
+    const float q0 = fminf(fminf(sh.lo[0], sh.lo[1]), fminf(sh.lo[2], sh.lo[3]));
+    const float q1 = fmaxf(fmaxf(sh.hi[0], sh.hi[1]), fmaxf(sh.hi[2], sh.hi[3]));
+    const float width = fmaxf(q1 - q0, 1e-6f) * (1.0f / kAngleBins);
+    if (tid < kAngleBins) {
+        // A direction bin's centre and half width (asin x <= 1.05 x up to half
+        // a radian: bins are narrower than 60 degrees), widened for the
+        // rounding of direction_key.
+        const float2 a = key_direction(q0 + tid * width);
+        const float2 b = key_direction(tid == kAngleBins - 1 ? q1 : q0 + (tid + 1) * width);
+        const float dx = b.x - a.x, dy = b.y - a.y;
+        const float w = 0.53f * sqrtf(dx * dx + dy * dy) + 0x1p-15f;
+        const float mx = a.x + b.x, my = a.y + b.y;
+        const float inv = 1.0f / sqrtf(mx * mx + my * my);
+        sh.dir[tid] = make_float4(mx * inv, my * inv, w, 0.5f * w * w);
+    }
+    __syncthreads();
+    unsigned long long ref = 0;
+#pragma unroll
+    for (int w = 0; w < kScoreBlock / kWave; ++w) ref = sh.key[w] > ref ? sh.key[w] : ref;
+    ref = uniform_u64(ref);
+
+    unsigned long long best = 0;  // best known (count, hypothesis) key, the same in every lane
+    uint32_t ub[kPruneRounds];
+    if (ref != 0) {
+        // 2. Table of the points under r.
+        const uint32_t r_local = 0xFFFFFFFFu - (uint32_t)ref;
+        const float rx = uniform_f(hyp[r_local].x), ry = uniform_f(hyp[r_local].y);
+        const float sigma = uniform_f(residual_scale(tau));
+        const float scale = 1.0f / width;
+        uint32_t t = 0;
+#pragma unroll 4
+        for (uint32_t p = tid; p < n; p += kScoreBlock) {
+            const StagedPoint &u = points[p];
+            const float e = __builtin_fmaf(-ry, u.s, __builtin_fmaf(-rx, u.c, u.v));
+            t += __builtin_fabsf(e) < tau ? 1u : 0u;
+            int b = (int)((direction_key(u.c, u.s) - q0) * scale);
+            b = b < kAngleBins - 1 ? b : kAngleBins - 1;
+            b = b > 0 ? b : 0;
+            if (u.v < __builtin_inff()) atomicAdd(&sh.u.hist[b * kResidualRow + residual_bin(e * sigma)], 1u);
+        }
+        t = (uint32_t)wave_sum_i((int)t);
+        if (lane == 0) sh.n[wave] = t;
+        __syncthreads();
+        best = hyp_key(sh.n[0] + sh.n[1] + sh.n[2] + sh.n[3], h_first + r_local);
+        best = uniform_u64(best);
+        // Prefix sums along each row: 32 threads per row, eight bins each.
+        {
+            constexpr int kRowThreads = 32;
+            static_assert(kAngleBins * kRowThreads == kScoreBlock &&
+                          kResidualBins == kRowThreads * 8, "one pass");
+            uint32_t *row =
+                sh.u.hist + (tid / kRowThreads) * kResidualRow + (tid % kRowThreads) * 8;
+            uint32_t x[8], sum = 0;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                x[i] = sum;
+                sum += row[i];
+            }
+            uint32_t incl = sum;
+#pragma unroll
+            for (int d = 1; d < kRowThreads; d <<= 1) {
+                const uint32_t y = __shfl_up(incl, d, kRowThreads);
+                if (tid % kRowThreads >= d) incl += y;
+            }
+#pragma unroll
+            for (int i = 0; i < 8; ++i) row[i] = incl - sum + x[i];
+            if (tid % kRowThreads == kRowThreads - 1) row[8] = incl;
+        }
+        __syncthreads();
+        // 3. Bounds.
+        float w2 = sh.dir[0].w;
+#pragma unroll
+        for (int b = 1; b < kAngleBins; ++b) w2 = fmaxf(w2, sh.dir[b].w);
+#pragma unroll
+        for (int q = 0; q < kPruneRounds; ++q) {
+            ub[q] = 0;
+            if (q < rounds) {
+                const float2 h = hyp[q * kScoreBlock + tid];
+                const float m = __builtin_fabsf(h.x) + __builtin_fabsf(h.y) + __builtin_fabsf(rx) +
+                                __builtin_fabsf(ry);
+                const float dx = (h.x - rx) * sigma, dy = (h.y - ry) * sigma;
+                const float band = __builtin_fmaf(__builtin_fabsf(dx) + __builtin_fabsf(dy), w2,
+                                                  (tau + 0x1p-18f * (tau + m)) * sigma);
+                uint32_t bound = 0;
+                for (int b = 0; b < kAngleBins; ++b) {
+                    const float4 d = sh.dir[b];
+                    const float f = __builtin_fmaf(dx, d.x, dy * d.y);
+                    const float g = __builtin_fmaf(dy, d.x, -dx * d.y);
+                    const float rad = __builtin_fmaf(__builtin_fabsf(g), d.z, band);
+                    const uint32_t *row = sh.u.hist + b * kResidualRow;
+                    bound += row[residual_bin(f + rad) + 1] - row[residual_bin(f - rad)];
+                }
+                // Beyond this magnitude the interval arithmetic may overflow.
+                if (!(m < 2.0f * kPruneMaxSpeed)) bound = n;
+                // r itself is already counted.
+                ub[q] = __builtin_isnan(h.x) || (q == 0 && tid == (int)r_local) ? 0u : bound;
+            }
+        }
+    } else {
+#pragma unroll
+        for (int q = 0; q < kPruneRounds; ++q)
+            ub[q] = q < rounds && !__builtin_isnan(hyp[q * kScoreBlock + tid].x) ? n : 0u;
+    }
+
+    // 4. The largest bound of each wave's hypotheses above the best key known
+    // (this workgroup's r, or another workgroup's of the same cluster).
+    const unsigned long long other = uniform_u64(
+        __hip_atomic_load(&best_key[id.out], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+    unsigned long long floor_key = other > best ? other : best;
+    unsigned long long top = 0;
+#pragma unroll
+    for (int q = 0; q < kPruneRounds; ++q) {
+        const unsigned long long k = ub[q] != 0 ? hyp_key(ub[q], h_first + q * kScoreBlock + tid) : 0ull;
+        if (k > floor_key && k > top) top = k;
+    }
+    top = wave_max_u64(top);
+    if (lane == 0) sh.key[wave] = top;
+    __syncthreads();  // also the last use of the table
+    int nl = 0;
+    {
+        int before = 0;
+#pragma unroll
+        for (int w = 0; w < kScoreBlock / kWave; ++w) {
+            const int has = sh.key[w] != 0 ? 1 : 0;
+            before += w < wave ? has : 0;
+            nl += has;
+        }
+        nl = __builtin_amdgcn_readfirstlane(nl);
+        if (lane == 0 && top != 0) {
+            const uint32_t h = 0xFFFFFFFFu - (uint32_t)top - (uint32_t)h_first;
+            reinterpret_cast<float2 *>(sh.u.count.list)[before] = hyp[h];
+            sh.top[before] = h;
+        }
+    }
+    // 5. Exact counts: the tops, then every hypothesis whose bound still
+    // reaches the best key, 64 per pass.
+    uint32_t n_cand = 0, c0 = 0;
+    bool tops = true;
+    while (nl > 0) {
+        __syncthreads();
+        const uint32_t cnt = exact_counts(sp, pts, tau, nl,
+                                          reinterpret_cast<const float4 *>(sh.u.count.list),
+                                          sh.u.count.part, wave, lane);
+        unsigned long long k = 0;
+        if (lane < nl) k = hyp_key(cnt, h_first + (tops ? sh.top[lane & 3] : sh.u.count.idx[c0 - kWave + lane]));
+        k = uniform_u64(wave_max_u64(k));
+        best = k > best ? k : best;
+        floor_key = best > floor_key ? best : floor_key;
+        if (tops) {
+            tops = false;
+            uint32_t mine = 0;
+            uint64_t masks[kPruneRounds];
+#pragma unroll
+            for (int q = 0; q < kPruneRounds; ++q) {
+                const unsigned long long kq =
+                    ub[q] != 0 ? hyp_key(ub[q], h_first + q * kScoreBlock + tid) : 0ull;
+                masks[q] = __builtin_amdgcn_ballot_w64(kq > floor_key && kq != top);
+                mine += (uint32_t)__builtin_popcountll(masks[q]);
+            }
+            if (lane == 0) sh.n[wave] = mine;
+            __syncthreads();
+            uint32_t at = 0;
+            n_cand = 0;
+#pragma unroll
+            for (int w = 0; w < kScoreBlock / kWave; ++w) {
+                const uint32_t x = sh.n[w];
+                at += w < wave ? x : 0u;
+                n_cand += x;
+            }
+            n_cand = __builtin_amdgcn_readfirstlane(n_cand);
+#pragma unroll
+            for (int q = 0; q < kPruneRounds; ++q) {
+                const uint32_t rank = __builtin_amdgcn_mbcnt_hi(
+                    (uint32_t)(masks[q] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)masks[q], 0u));
+                if ((masks[q] >> lane) & 1) sh.u.count.idx[at + rank] = (uint16_t)(q * kScoreBlock + tid);
+                at += (uint32_t)__builtin_popcountll(masks[q]);
+            }
+            __syncthreads();
+        }
+        const uint32_t rest = n_cand > c0 ? n_cand - c0 : 0u;
+        nl = rest < (uint32_t)kWave ? (int)rest : kWave;
+        if (tid < nl) reinterpret_cast<float2 *>(sh.u.count.list)[tid] = hyp[sh.u.count.idx[c0 + tid]];
+        c0 += kWave;
+    }
+    if (block_best != nullptr) {
+        *block_best = best;
+    } else if (wave == 0) {
+        if (lane == 0 && best != 0) atomicMax(&best_key[id.out], best);
+    }
+}
+
+// Workgroup LDS of the rows form.
+struct RowsShared {
+    float4 hyp[kScoreBlock / 2];  // (vx, vy) pairs, two per float4
+    unsigned long long key[kScoreBlock / kWave];
+    TailShared tail;
+};
+
+// Workgroup LDS of the scoring forms: a workgroup uses one at a time.
+struct ScoreShared {
+    static constexpr size_t kBytes = sizeof(PruneShared);
+    static_assert(sizeof(RowsShared) <= kBytes && sizeof(LaneShared) <= kBytes &&
+                  sizeof(Fp16Shared) <= kBytes, "the largest");
+    alignas(16) unsigned char bytes[kBytes];
+    __device__ RowsShared &rows() { return *reinterpret_cast<RowsShared *>(bytes); }
+    __device__ LaneShared &lanes() { return *reinterpret_cast<LaneShared *>(bytes); }
+    __device__ Fp16Shared &fp16() { return *reinterpret_cast<Fp16Shared *>(bytes); }
+    __device__ PruneShared &prune() { return *reinterpret_cast<PruneShared *>(bytes); }
+};
 
 // One scoring block in the FP16 form (sp.ok and sp.n >= 2; called from the
 // persistent loop: every branch around a barrier is on a wave-uniform value).
@@ -949,7 +1386,7 @@ __device__ __forceinline__ void score_block_fp16(Span sp, ClusterId id, int b, i
     }
     __syncthreads();
     const uint32_t n1 = has_top + n_wide < (uint32_t)kWave ? has_top + n_wide : (uint32_t)kWave;
-    const uint32_t c1 = exact_counts(sp, pts, tau, (int)n1, sh, wave, lane);
+    const uint32_t c1 = exact_counts(sp, pts, tau, (int)n1, sh.list, sh.part, wave, lane);
     const uint32_t t_exact = has_top ? __builtin_amdgcn_readfirstlane(c1) : 0u;
     unsigned long long best = lane < (int)n1 ? hyp_key(c1, base + sh.idx[lane]) : 0ull;
     best = wave_max_u64(best);
@@ -976,7 +1413,7 @@ __device__ __forceinline__ void score_block_fp16(Span sp, ClusterId id, int b, i
         const int nl = n_cand - c0 < (uint32_t)kWave ? (int)(n_cand - c0) : kWave;
         if (tid < nl) reinterpret_cast<float2 *>(sh.list)[tid] = h32[sh.idx[c0 + tid]];
         __syncthreads();
-        const uint32_t cnt = exact_counts(sp, pts, tau, nl, sh, wave, lane);
+        const uint32_t cnt = exact_counts(sp, pts, tau, nl, sh.list, sh.part, wave, lane);
         unsigned long long k2 = 0;
         if (lane < nl) k2 = hyp_key(cnt, base + sh.idx[c0 + lane]);
         k2 = wave_max_u64(k2);
@@ -1055,8 +1492,7 @@ __device__ __forceinline__ void refit_points(int64_t p0, bool in_range, float v,
 constexpr int kRefitUnroll = 4;
 
 struct RefitLoads {
-    float v[kRefitUnroll];
-    float2 hi[kRefitUnroll], lo[kRefitUnroll];
+    StagedPoint p[kRefitUnroll];
     bool in[kRefitUnroll];
 };
 
@@ -1068,10 +1504,7 @@ __device__ __forceinline__ RefitLoads refit_load(Span sp, int64_t p0, int64_t st
     for (int u = 0; u < kRefitUnroll; ++u) {
         const int64_t p = p0 + u * stride + lane;
         L.in[u] = p >= sp.lo && p < end;
-        const int64_t q = L.in[u] ? p : sp.lo;
-        L.v[u] = pts.v32[q];
-        L.hi[u] = pts.cs32[q];
-        L.lo[u] = pts.cslo[q];
+        L.p[u] = pts.staged[L.in[u] ? p : sp.lo];
     }
     return L;
 }
@@ -1082,7 +1515,7 @@ __device__ __forceinline__ void refit_group(const RefitLoads &L, int64_t p0, int
 #pragma unroll
     for (int u = 0; u < kRefitUnroll; ++u)
         if (p0 + u * stride < end)
-            refit_points(p0 + u * stride, L.in[u], L.v[u], cs64(L.hi[u], L.lo[u]), hy, dtau, a, o,
+            refit_points(p0 + u * stride, L.in[u], L.p[u].v, cs64(L.p[u]), hy, dtau, a, o,
                          lane);
 }
 
@@ -1252,12 +1685,9 @@ __device__ __forceinline__ void refit_wave(Span sp, ClusterId id, unsigned long 
 __global__ __launch_bounds__(kScoreBlock) __attribute__((amdgpu_waves_per_eu(8))) void score_kernel(
     const int32_t *__restrict__ off, const int32_t *__restrict__ order, int64_t n_clusters,
     int64_t n_points, int32_t n_hyp, int32_t blocks_per_cluster, uint32_t key0, uint32_t key1,
-    uint32_t cluster_base, int64_t point_base, Points pts, float tau,
+    uint32_t cluster_base, int64_t point_base, int32_t prune_rounds, Points pts, float tau,
     unsigned long long *__restrict__ best_key, int32_t *__restrict__ hyp_counts) {
-    __shared__ float4 s_hyp[kScoreBlock / 2];  // (vx, vy) pairs, two per float4
-    __shared__ unsigned long long s_key[kScoreBlock / kWave];
-    __shared__ LaneShared s_lanes;
-    __shared__ TailShared s_tail;
+    __shared__ ScoreShared s;
     const uint32_t xcd = blockIdx.x % kXcds;
     const uint32_t r = blockIdx.x / kXcds;
     const int64_t j = xcd + (int64_t)kXcds * (r / (uint32_t)blocks_per_cluster);
@@ -1271,11 +1701,26 @@ __global__ __launch_bounds__(kScoreBlock) __attribute__((amdgpu_waves_per_eu(8))
     id.key1 = key1;
     const Span sp = cluster_span(off, k, n_points, point_base);
     if (sp.ok && sp.n >= 2 && sp.n <= kSingleLanesMax) {  // the same for the whole block
-        score_block_lanes(sp, id, b, n_hyp, pts, tau, s_lanes, best_key, hyp_counts);
+        score_block_lanes(sp, id, b, n_hyp, pts, tau, s.lanes(), best_key, hyp_counts);
         return;
     }
-    score_block<false>(sp, id, b, n_hyp, pts, tau, kRowsMax, s_hyp, s_key, s_tail, best_key,
-                       hyp_counts);
+    if (prune_rounds > 0 && sp.n >= prune_min(prune_rounds)) {
+        // One workgroup of each group of prune_rounds works, and which one turns
+        // from cluster to cluster: workgroups go to the compute units in
+        // rotation, so always taking the first would leave most units idle.
+        const int part = b / prune_rounds;
+        const int in_part = blocks_per_cluster - part * prune_rounds < prune_rounds
+                                ? blocks_per_cluster - part * prune_rounds : prune_rounds;
+        const int turn = (int)((r / (uint32_t)blocks_per_cluster) % (uint32_t)in_part);
+        if (b - part * prune_rounds != turn) return;
+        const int64_t first = (int64_t)part * prune_rounds * kScoreBlock;
+        const int64_t left = n_hyp - first;
+        const int most = prune_rounds * kScoreBlock;
+        score_pruned(sp, id, first, left < most ? (int)left : most, pts, tau, s.prune(), best_key);
+        return;
+    }
+    score_block<false>(sp, id, b, n_hyp, pts, tau, kRowsMax, s.rows().hyp, s.rows().key,
+                       s.rows().tail, best_key, hyp_counts);
 }
 
 // Refit of a frame's or batch's clusters over their planned (largest-first)
@@ -1359,19 +1804,15 @@ __global__ __launch_bounds__(kRefitBlock) void refit_kernel(
 __global__ __launch_bounds__(kScoreBlock) __attribute__((amdgpu_waves_per_eu(8))) void small_frame_kernel(
     const float *__restrict__ theta, const float *__restrict__ vd, const int32_t *__restrict__ off,
     int64_t n_points, int32_t n_hyp, uint32_t key0, uint32_t key1, uint32_t cluster_base,
-    int64_t point_base, Points pts, float tau,
-    float2 *__restrict__ cs32, float *__restrict__ v32, float2 *__restrict__ cslo,
-    unsigned long long *__restrict__ best_key, Outputs o) {
-    __shared__ float4 s_hyp[kScoreBlock / 2];
-    __shared__ unsigned long long s_key[kScoreBlock / kWave];
+    int64_t point_base, int32_t prune, Points pts, float tau,
+    StagedPoint *__restrict__ staged, unsigned long long *__restrict__ best_key, Outputs o) {
+    __shared__ ScoreShared s;
     __shared__ double s_sum[kRefitBlock / kWave][5];
     __shared__ int s_cnt[kRefitBlock / kWave][2];
-    __shared__ LaneShared s_lanes;
-    __shared__ TailShared s_tail;
     const int64_t k = blockIdx.x;
     const Span sp = cluster_span(off, k, n_points, point_base);
     for (int64_t p = sp.lo + threadIdx.x; p < sp.lo + sp.n; p += kScoreBlock)
-        stage_point(theta, vd, p, cs32, v32, cslo);
+        stage_point(theta, vd, p, staged);
     if (threadIdx.x == 0) best_key[k] = 0;
     __syncthreads();
     ClusterId id;
@@ -1382,15 +1823,19 @@ __global__ __launch_bounds__(kScoreBlock) __attribute__((amdgpu_waves_per_eu(8))
     // The workgroup's own block key is the cluster's best (one block per
     // cluster); the per-wave keys are still in LDS after the scoring's barrier.
     const bool lanes = sp.ok && sp.n >= 2 && sp.n <= kSingleLanesMax;  // block-uniform
-    if (lanes)
-        score_block_lanes(sp, id, 0, n_hyp, pts, tau, s_lanes, best_key, o.hyp_counts);
-    else
-        score_block<false>(sp, id, 0, n_hyp, pts, tau, kRowsMax, s_hyp, s_key, s_tail,
-                           best_key, o.hyp_counts);
-    const unsigned long long *keys = lanes ? s_lanes.key : s_key;
     unsigned long long best = 0;
+    if (prune > 0 && sp.n >= prune_min(prune)) {
+        score_pruned(sp, id, 0, n_hyp, pts, tau, s.prune(), best_key, &best);
+    } else {
+        if (lanes)
+            score_block_lanes(sp, id, 0, n_hyp, pts, tau, s.lanes(), best_key, o.hyp_counts);
+        else
+            score_block<false>(sp, id, 0, n_hyp, pts, tau, kRowsMax, s.rows().hyp, s.rows().key,
+                               s.rows().tail, best_key, o.hyp_counts);
+        const unsigned long long *keys = lanes ? s.lanes().key : s.rows().key;
 #pragma unroll
-    for (int w = 0; w < kScoreBlock / kWave; ++w) best = keys[w] > best ? keys[w] : best;
+        for (int w = 0; w < kScoreBlock / kWave; ++w) best = keys[w] > best ? keys[w] : best;
+    }
     refit_block(sp, id, uniform_u64(best), pts, tau, o, s_sum, s_cnt);
 }
 
@@ -1406,10 +1851,11 @@ struct Tuning {
     int32_t rows[RV_TUNE_BUCKETS];
     int32_t fp16_min;   // clusters of at least this many points use the FP16 form; 0: none
     int32_t lanes_max;  // clusters of at most this many points score with lanes = hypotheses
+    int32_t prune_rounds;  // see prune_rounds(); 0: every hypothesis is counted
 };
 
 // Scoring form of a cluster (ItemDesc::form).
-enum : int16_t { kFormRows = 0, kFormFp16 = 1, kFormLanes = 2 };
+enum : int16_t { kFormRows = 0, kFormFp16 = 1, kFormLanes = 2, kFormPruned = 3 };
 
 // Everything the scoring and refit workgroups need about one cluster, at its
 // position in the dispatch order: one 32-byte load instead of a chain of
@@ -1476,14 +1922,13 @@ __global__ __launch_bounds__(kSizeClasses) void batch_init_kernel(
 // one global atomic per class and block).
 __global__ __launch_bounds__(kPrepBlock) void batch_prep_kernel(
     const float *__restrict__ theta, const float *__restrict__ vd, int64_t n_points,
-    float2 *__restrict__ cs32, float *__restrict__ v32, float2 *__restrict__ cslo,
-    uint32_t *__restrict__ bits, int64_t n_words, const int32_t *__restrict__ off,
-    int64_t n_clusters, unsigned long long *__restrict__ best_key, uint32_t *__restrict__ hist) {
+    StagedPoint *__restrict__ staged, uint32_t *__restrict__ bits, int64_t n_words,
+    const int32_t *__restrict__ off, int64_t n_clusters, unsigned long long *__restrict__ best_key, uint32_t *__restrict__ hist) {
     __shared__ uint32_t local[kSizeClasses];
     for (int c = threadIdx.x; c < kSizeClasses; c += kPrepBlock) local[c] = 0;
     __syncthreads();
     const int64_t p = (int64_t)blockIdx.x * kPrepBlock + threadIdx.x;
-    if (p < n_points) stage_point(theta, vd, p, cs32, v32, cslo);
+    if (p < n_points) stage_point(theta, vd, p, staged);
     if (bits != nullptr && p < n_words) bits[p] = 0u;
     if (p < n_clusters) {
         best_key[p] = 0;
@@ -1550,6 +1995,8 @@ __global__ __launch_bounds__(kPrepBlock) void batch_scatter_kernel(
         d.form = kFormLanes;
     else if (tune.fp16_min > 0 && sp.ok && sp.n >= 2 && sp.n >= tune.fp16_min)
         d.form = kFormFp16;
+    else if (tune.prune_rounds > 0 && sp.n >= prune_min(tune.prune_rounds))
+        d.form = kFormPruned;
     desc[base[cls] + rank] = d;
 }
 
@@ -1567,14 +2014,11 @@ __global__ __launch_bounds__(kPrepBlock) void batch_scatter_kernel(
 template <bool kFp16>
 __global__ __launch_bounds__(kScoreBlock) __attribute__((amdgpu_waves_per_eu(kFp16 ? 7 : 8))) void batch_score_kernel(
     const ItemDesc *__restrict__ desc, int64_t n_clusters, int32_t n_hyp,
-    int32_t blocks_per_cluster, Points pts, float tau, unsigned long long *__restrict__ queues,
+    int32_t blocks_per_cluster, int32_t prune_rounds, Points pts, float tau,
+    unsigned long long *__restrict__ queues,
     unsigned long long *__restrict__ best_key, int32_t *__restrict__ hyp_counts) {
-    __shared__ float4 s_hyp[kScoreBlock / 2];
-    __shared__ unsigned long long s_key[kScoreBlock / kWave];
+    __shared__ ScoreShared s;
     __shared__ unsigned long long s_item;
-    __shared__ Fp16Shared s_fp16;  // unreferenced, so not allocated, when !kFp16
-    __shared__ LaneShared s_lanes;
-    __shared__ TailShared s_tail;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int lane = threadIdx.x % kWave;
     const uint32_t home = blockIdx.x % kXcds;
@@ -1597,19 +2041,28 @@ __global__ __launch_bounds__(kScoreBlock) __attribute__((amdgpu_waves_per_eu(kFp
             const int b = (int)(item % bpc);
             const ItemDesc d = desc[j];
             if (d.form == kFormLanes) {
-                score_block_lanes(desc_span(d), desc_id(d), b, n_hyp, pts, tau, s_lanes, best_key,
+                score_block_lanes(desc_span(d), desc_id(d), b, n_hyp, pts, tau, s.lanes(), best_key,
                                   hyp_counts);
+                continue;
+            }
+            if (d.form == kFormPruned) {
+                if (b % prune_rounds != 0) continue;
+                const int64_t first = (int64_t)b * kScoreBlock;
+                const int64_t left = n_hyp - first;
+                const int most = prune_rounds * kScoreBlock;
+                score_pruned(desc_span(d), desc_id(d), first, left < most ? (int)left : most, pts,
+                             tau, s.prune(), best_key);
                 continue;
             }
             if constexpr (kFp16) {
                 if (d.form == kFormFp16) {
-                    score_block_fp16(desc_span(d), desc_id(d), b, n_hyp, pts, tau, d.rows, s_fp16,
+                    score_block_fp16(desc_span(d), desc_id(d), b, n_hyp, pts, tau, d.rows, s.fp16(),
                                      best_key, hyp_counts);
                     continue;
                 }
             }
-            score_block<true>(desc_span(d), desc_id(d), b, n_hyp, pts, tau, d.rows, s_hyp, s_key,
-                              s_tail, best_key, hyp_counts);
+            score_block<true>(desc_span(d), desc_id(d), b, n_hyp, pts, tau, d.rows, s.rows().hyp,
+                              s.rows().key, s.rows().tail, best_key, hyp_counts);
         }
     }
 }
@@ -1667,16 +2120,14 @@ constexpr size_t kAlign = 256;
 size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
 struct Layout {
-    size_t cs32, v32, cslo, order, best_key, n_big, total;
+    size_t staged, order, best_key, n_big, total;
 };
 
 Layout make_layout(int64_t n_clusters, int64_t n_points) {
     Layout L;
     const size_t np = (size_t)n_points;
     size_t at = 0;
-    L.cs32 = at; at = align_up(at + np * sizeof(float2));
-    L.v32 = at; at = align_up(at + np * sizeof(float));
-    L.cslo = at; at = align_up(at + np * sizeof(float2));
+    L.staged = at; at = align_up(at + np * sizeof(StagedPoint));
     L.order = at; at = align_up(at + (size_t)n_clusters * sizeof(int32_t));
     L.best_key = at; at = align_up(at + (size_t)n_clusters * sizeof(unsigned long long));
     L.n_big = at; at = align_up(at + sizeof(int64_t));
@@ -1688,16 +2139,14 @@ Layout make_layout(int64_t n_clusters, int64_t n_points) {
 
 
 struct BatchLayout {
-    size_t cs32, v32, cslo, desc, best_key, hist, queues, n_big, total;
+    size_t staged, desc, best_key, hist, queues, n_big, total;
 };
 
 BatchLayout make_batch_layout(int64_t n_clusters, int64_t n_points) {
     BatchLayout L;
     const size_t np = (size_t)n_points, nc = (size_t)n_clusters;
     size_t at = 0;
-    L.cs32 = at; at = align_up(at + np * sizeof(float2));
-    L.v32 = at; at = align_up(at + np * sizeof(float));
-    L.cslo = at; at = align_up(at + np * sizeof(float2));
+    L.staged = at; at = align_up(at + np * sizeof(StagedPoint));
     L.desc = at; at = align_up(at + nc * sizeof(ItemDesc));
     L.best_key = at; at = align_up(at + nc * sizeof(unsigned long long));
     L.hist = at; at = align_up(at + kSizeClasses * sizeof(uint32_t));
@@ -1774,6 +2223,23 @@ int device_cus() {
     return cus;
 }
 
+// Hypotheses of a large cluster per scoring workgroup, in blocks of 256
+// (score_pruned), or 0 for the full count: when the caller asks for every
+// hypothesis's count, or tau is so extreme that the residual bins' scale leaves
+// the normal range.  As many as leave 2048 workgroups (eight per compute unit):
+// scoring stage with 1, 2 and 4 at 1024 hypotheses: 4096 mixed clusters 116, 88
+// and 83 us; 1024 clusters of 2048 points 68, 55 and 68 us; 512 of 4096 points
+// 56, 66 and 90 us.
+int32_t prune_rounds(int64_t n_clusters, int64_t blocks_per_cluster, float tau,
+                     const int32_t *hyp_counts) {
+    if (hyp_counts != nullptr || !(tau > 1e-15f) || !(tau < 1e15f)) return 0;
+    int32_t rounds = 1;
+    while (rounds < kPruneRounds && rounds < blocks_per_cluster &&
+           n_clusters * ((blocks_per_cluster + 2 * rounds - 1) / (2 * rounds)) >= 2048)
+        rounds *= 2;
+    return rounds;
+}
+
 // The refit kernel over planned positions; n_big (device, nullable) is the
 // ordering pass's count of big clusters.
 void launch_refit(bool batch, const int32_t *off, const int32_t *order, const ItemDesc *desc,
@@ -1813,18 +2279,14 @@ int launch_batch(const BatchArgs &a, unsigned grid, hipStream_t st, bool allow_t
     if (a.n_clusters == 0) return RV_OK;
     const BatchLayout L = make_batch_layout(a.n_clusters, a.n_points);
     char *ws = (char *)a.workspace;
-    float2 *cs32 = (float2 *)(ws + L.cs32);
-    float *v32 = (float *)(ws + L.v32);
-    float2 *cslo = (float2 *)(ws + L.cslo);
+    StagedPoint *staged = (StagedPoint *)(ws + L.staged);
     ItemDesc *desc = (ItemDesc *)(ws + L.desc);
     unsigned long long *best_key = (unsigned long long *)(ws + L.best_key);
     uint32_t *hist = (uint32_t *)(ws + L.hist);
     unsigned long long *queues = (unsigned long long *)(ws + L.queues);
     int64_t *n_big = (int64_t *)(ws + L.n_big);
     Points pts;
-    pts.cs32 = cs32;
-    pts.v32 = v32;
-    pts.cslo = cslo;
+    pts.staged = staged;
     pts.theta = a.theta;
     Batch bt;
     bt.frame_off = a.frame_off;
@@ -1835,6 +2297,8 @@ int launch_batch(const BatchArgs &a, unsigned grid, hipStream_t st, bool allow_t
     tune.fp16_min = a.tuning.fp16_min_points;
     tune.lanes_max = a.tuning.lanes_max_points;
     const int64_t bpc = batch_blocks_per_cluster(a);
+    const int32_t rounds = prune_rounds(a.n_clusters, bpc, a.tau, a.o.hyp_counts);
+    tune.prune_rounds = rounds;
     const int64_t n_words = a.o.bits != nullptr ? (a.n_points + 31) / 32 : 0;
     int64_t prep_items = a.n_points > n_words ? a.n_points : n_words;
     prep_items = prep_items > a.n_clusters ? prep_items : a.n_clusters;
@@ -1844,7 +2308,7 @@ int launch_batch(const BatchArgs &a, unsigned grid, hipStream_t st, bool allow_t
     if (timed) (void)hipEventRecord(tc.ev[0], st);
     hipLaunchKernelGGL(batch_init_kernel, dim3(1), dim3(kSizeClasses), 0, st, hist, queues);
     hipLaunchKernelGGL(batch_prep_kernel, dim3((unsigned)((prep_items + kPrepBlock - 1) / kPrepBlock)),
-                       dim3(kPrepBlock), 0, st, a.theta, a.vd, a.n_points, cs32, v32, cslo,
+                       dim3(kPrepBlock), 0, st, a.theta, a.vd, a.n_points, staged,
                        a.o.bits, n_words, a.off, a.n_clusters, best_key, hist);
     hipLaunchKernelGGL(batch_scan_kernel, dim3(1), dim3(64), 0, st, hist, n_big);
     hipLaunchKernelGGL(batch_scatter_kernel,
@@ -1853,11 +2317,11 @@ int launch_batch(const BatchArgs &a, unsigned grid, hipStream_t st, bool allow_t
     if (timed) (void)hipEventRecord(tc.ev[1], st);
     if (a.tuning.fp16_min_points > 0)
         hipLaunchKernelGGL(batch_score_kernel<true>, dim3(grid), dim3(kScoreBlock), 0, st,
-                           (const ItemDesc *)desc, a.n_clusters, a.n_hyp, (int32_t)bpc, pts, a.tau,
+                           (const ItemDesc *)desc, a.n_clusters, a.n_hyp, (int32_t)bpc, rounds, pts, a.tau,
                            queues, best_key, a.o.hyp_counts);
     else
         hipLaunchKernelGGL(batch_score_kernel<false>, dim3(grid), dim3(kScoreBlock), 0, st,
-                           (const ItemDesc *)desc, a.n_clusters, a.n_hyp, (int32_t)bpc, pts, a.tau,
+                           (const ItemDesc *)desc, a.n_clusters, a.n_hyp, (int32_t)bpc, rounds, pts, a.tau,
                            queues, best_key, a.o.hyp_counts);
     if (timed) (void)hipEventRecord(tc.ev[2], st);
     launch_refit(true, nullptr, nullptr, (const ItemDesc *)desc, a.n_clusters, n_big, a.n_points,
@@ -1959,13 +2423,9 @@ int estimate_frame(const float *theta, const float *vd, const int32_t *cluster_o
     if (n_clusters == 0) return RV_OK;
 
     char *ws = (char *)workspace;
-    float2 *cs32 = (float2 *)(ws + L.cs32);
-    float *v32 = (float *)(ws + L.v32);
-    float2 *cslo = (float2 *)(ws + L.cslo);
+    StagedPoint *staged = (StagedPoint *)(ws + L.staged);
     Points pts;
-    pts.cs32 = cs32;
-    pts.v32 = v32;
-    pts.cslo = cslo;
+    pts.staged = staged;
     pts.theta = theta;
     int32_t *order = n_clusters <= kPlanMaxClusters ? (int32_t *)(ws + L.order) : nullptr;
     int64_t *n_big = (int64_t *)(ws + L.n_big);
@@ -1993,7 +2453,8 @@ int estimate_frame(const float *theta, const float *vd, const int32_t *cluster_o
         if (timed) (void)hipEventRecord(tc.ev[1], st);
         hipLaunchKernelGGL(small_frame_kernel, dim3((unsigned)n_clusters), dim3(kScoreBlock), 0, st,
                            theta, vd, cluster_offsets, n_points, n_hyp, key0, key1, first_cluster,
-                           first_point, pts, tau, cs32, v32, cslo, best_key, o);
+                           first_point, prune_rounds(n_clusters, 1, tau, hyp_counts), pts, tau,
+                           staged, best_key, o);
         if (timed) {
             (void)hipEventRecord(tc.ev[2], st);
             (void)hipEventRecord(tc.ev[3], st);
@@ -2007,13 +2468,15 @@ int estimate_frame(const float *theta, const float *vd, const int32_t *cluster_o
     prep_items = prep_items > n_clusters ? prep_items : n_clusters;
     const int64_t prep_blocks = (prep_items + kPrepBlock - 1) / kPrepBlock + 1;  // + planner
     hipLaunchKernelGGL(prep_kernel, dim3((unsigned)prep_blocks), dim3(kPrepBlock), 0, st, theta,
-                       vd, n_points, cs32, v32, cslo, inlier_bits, n_words, cluster_offsets,
+                       vd, n_points, staged, inlier_bits, n_words, cluster_offsets,
                        first_point, n_clusters, order, n_big, best_key);
     if (timed) (void)hipEventRecord(tc.ev[1], st);
     hipLaunchKernelGGL(score_kernel, dim3((unsigned)(clusters_xcd * blocks_per_cluster)),
                        dim3(kScoreBlock), 0, st, cluster_offsets, (const int32_t *)order,
                        n_clusters, n_points, n_hyp, (int32_t)blocks_per_cluster, key0, key1,
-                       first_cluster, first_point, pts, tau, best_key, hyp_counts);
+                       first_cluster, first_point,
+                       prune_rounds(n_clusters, blocks_per_cluster, tau, hyp_counts), pts, tau,
+                       best_key, hyp_counts);
     if (timed) (void)hipEventRecord(tc.ev[2], st);
     launch_refit(false, cluster_offsets, order, nullptr, n_clusters,
                  order != nullptr ? (const int64_t *)n_big : nullptr, n_points, key0, key1,
