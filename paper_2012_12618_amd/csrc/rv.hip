@@ -27,7 +27,7 @@
 //           1024 points or more: FP64 re-classification under the kept
 //           hypothesis, FP64 normal-equation sums in a fixed reduction tree,
 //           2x2 solve (Sec. 3.2, Eq. 7, Alg. 2) and atan2 heading (Eq. 8).
-// Small frames without an inlier mask take one launch (small_frame_kernel)
+// Small frames without an inlier mask take one launch (cluster_kernel)
 // that runs the same three steps per cluster in one workgroup.  A part of a
 // frame (its clusters drawing with their whole-frame indexes, its points found
 // through the frame's offsets minus a point base) runs the same kernels; a
@@ -145,34 +145,54 @@ struct Hypothesis {
     bool valid;
 };
 
-// Hypothesis h of cluster k: seed pair, validity and the FP64 2x2 solve of
-// v_d = vx cos + vy sin at the two seeds (Cramer's rule).
-__device__ __forceinline__ Hypothesis make_hypothesis(const Points &pts, Span sp, uint32_t h,
-                                                      uint32_t k, uint32_t key0, uint32_t key1) {
+// The two seed points of a hypothesis.
+struct Seeds {
+    int64_t pi, pj;
+    StagedPoint a, b;
+};
+
+// Seed pair of hypothesis h of cluster k.  No branch: all loads are in flight
+// together.
+__device__ __forceinline__ Seeds draw_seeds(const Points &pts, Span sp, uint32_t h, uint32_t k,
+                                            uint32_t key0, uint32_t key1) {
     const uint4 u = philox4x32_10(make_uint4(h, k, 0u, 0u), key0, key1);
     uint32_t i, j;
     seed_pair(u.x, u.y, (uint32_t)sp.n, i, j);
-    const int64_t pi = sp.lo + i, pj = sp.lo + j;
-    // No branch before the solve: all loads are in flight together, and an
-    // invalid pair's solve (possibly inf or NaN) is replaced by NaN.
-    const StagedPoint pa = pts.staged[pi], pb = pts.staged[pj];
-    const double2 ai = cs64(pa), bj = cs64(pb);
+    Seeds d;
+    d.pi = sp.lo + i;
+    d.pj = sp.lo + j;
+    d.a = pts.staged[d.pi];
+    d.b = pts.staged[d.pj];
+    return d;
+}
+
+// Validity and the FP64 2x2 solve of v_d = vx cos + vy sin at the two seeds
+// (Cramer's rule); an invalid pair's solve (possibly inf or NaN) is replaced by
+// NaN.
+__device__ __forceinline__ Hypothesis solve_seeds(const Points &pts, const Seeds &d) {
+    const double2 ai = cs64(d.a), bj = cs64(d.b);
     const double ci = ai.x, si = ai.y, cj = bj.x, sj = bj.y;
-    const double dvi = pa.v, dvj = pb.v;
+    const double dvi = d.a.v, dvj = d.b.v;
     const double det = ci * sj - si * cj;
     Hypothesis hy;
-    hy.valid = ((int)isfinite(pa.v) & (int)isfinite(pb.v)) != 0;
+    hy.valid = ((int)isfinite(d.a.v) & (int)isfinite(d.b.v)) != 0;
     // The determinant is sin(theta_j - theta_i) within 2^-46, and |sin x| <=
     // |x|: above the separation limit (with room for that error) the pair is
     // separated.  Only below it are the azimuths themselves read.
     if (!(fabs(det) > 1.0005 * RV_MIN_SEED_SEPARATION) && hy.valid)
-        hy.valid = fabs((double)pts.theta[pj] - (double)pts.theta[pi]) >= RV_MIN_SEED_SEPARATION;
+        hy.valid = fabs((double)pts.theta[d.pj] - (double)pts.theta[d.pi]) >= RV_MIN_SEED_SEPARATION;
     const double inv_det = 1.0 / det;
     const double vx = (dvi * sj - dvj * si) * inv_det;
     const double vy = (ci * dvj - cj * dvi) * inv_det;
     hy.vx = hy.valid ? vx : __builtin_nan("");
     hy.vy = hy.valid ? vy : __builtin_nan("");
     return hy;
+}
+
+// Hypothesis h of cluster k.
+__device__ __forceinline__ Hypothesis make_hypothesis(const Points &pts, Span sp, uint32_t h,
+                                                      uint32_t k, uint32_t key0, uint32_t key1) {
+    return solve_seeds(pts, draw_seeds(pts, sp, h, k, key0, key1));
 }
 
 // ---------------------------------------------------------------------------
@@ -198,7 +218,6 @@ __device__ __forceinline__ int size_class(int64_t n) {
 // over the classes (largest first) is one wave's prefix sum, two classes per
 // lane.  This workgroup runs beside the staging workgroups and sets the prep
 // kernel's length when it is the slower one.
-constexpr int kPlanUnroll = 16;
 static_assert(kSizeClasses == 2 * kWave, "the class scan takes two classes per lane");
 
 // Exclusive prefix sum of x over the lanes of one full wave.
@@ -230,6 +249,7 @@ __device__ __forceinline__ void plan_scan(const uint32_t *count, uint32_t *start
     }
 }
 
+constexpr int kPlanUnroll = 16;
 __device__ void plan_order(const int32_t *__restrict__ off, int64_t point_base, int64_t n_clusters,
                            int64_t n_points, int32_t *__restrict__ order,
                            int64_t *__restrict__ n_big) {
@@ -463,8 +483,13 @@ __device__ __forceinline__ uint32_t score_cluster(const Points &pts, Span sp, in
 // for bit.
 constexpr int kTailLanesMax = 32;
 
-struct TailShared {
-    float4 c[kWave / 4], s[kWave / 4], v[kWave / 4];  // padded with (0, 0, +inf)
+
+// Points held in LDS for scoring with lanes = hypotheses: a cluster's tail, a
+// whole small cluster, or a sample.
+constexpr int kLaneTile = 256;  // the largest cluster scored whole this way
+template <int N>
+struct LaneTile {
+    float4 c[N / 4], s[N / 4], v[N / 4];  // padded with (0, 0, +inf)
 };
 
 __device__ __forceinline__ int lanes_tail(int64_t n) {
@@ -506,10 +531,13 @@ __device__ __forceinline__ void store_points(const PointLoad &L, int count, floa
     }
 }
 
-// Inliers of hypothesis (hx, hy) among the staged tail points (LDS broadcasts).
-__device__ __forceinline__ uint32_t tail_count(const TailShared &sh, int tail, float hx, float hy,
+// Inliers of hypothesis (hx, hy) among the first `tail` points of the tile (LDS
+// broadcasts).
+template <int N>
+__device__ __forceinline__ uint32_t tail_count(const LaneTile<N> &sh, int tail, float hx, float hy,
                                                float tau) {
     uint32_t cnt = 0;
+#pragma unroll 1
     for (int q = 0; q < (tail + 3) / 4; ++q) {
         const float4 c = sh.c[q], sn = sh.s[q], v = sh.v[q];
         const float cc[4] = {c.x, c.y, c.z, c.w}, ss[4] = {sn.x, sn.y, sn.z, sn.w};
@@ -531,79 +559,106 @@ struct ClusterId {
     uint32_t key0, key1;
 };
 
-// One scoring block: hypotheses [b * 256, b * 256 + 256) of one cluster.  Each
+// Key of the wave's best hypothesis, the same in every lane: val = its count + 1
+// (0: none), the lowest h among the largest; 0 when no lane has one.
+__device__ __forceinline__ unsigned long long wave_best(uint32_t val, uint32_t h) {
+    const uint32_t most = wave_max_u32(val);
+    if (most == 0) return 0;
+    const uint32_t low = ~wave_max_u32(val == most ? ~h : 0u);
+    return ((unsigned long long)(most - 1u) << 32) | (0xFFFFFFFFull - low);
+}
+
+// The largest of the block's per-wave keys (LDS), the same in every thread.
+template <int B>
+__device__ __forceinline__ unsigned long long block_key(const unsigned long long *keys) {
+    unsigned long long key = keys[0];
+#pragma unroll
+    for (int w = 1; w < B / kWave; ++w) key = keys[w] > key ? keys[w] : key;
+    return uniform_u64(key);
+}
+
+// Merges a block's best key into the cluster's: a 64-bit atomic maximum, whose
+// result does not depend on the order of the blocks.  Called by the whole block
+// (the guard is wave-uniform: it may sit in a loop with barriers, see
+// batch_score_kernel).
+__device__ __forceinline__ void merge_key(unsigned long long *best_key, unsigned long long key,
+                                          int wave, int lane) {
+    if (wave == 0) {
+        if (lane == 0 && key != 0) atomicMax(best_key, key);
+    }
+}
+
+// Workgroup LDS of the rows form.
+template <int B>
+struct RowsShared {
+    float4 hyp[B / 2];  // (vx, vy) pairs, two per float4
+    unsigned long long key[B / kWave];
+    LaneTile<kLaneTile> tile;
+};
+
+// One scoring block: hypotheses [b B, b B + B) of one cluster, B threads.  Each
 // thread draws and solves one hypothesis into LDS; each wave then scores 64 of
-// them against every point of the cluster.  The block's best (count, lowest
-// index) key over its valid hypotheses is merged into best_key with a 64-bit
-// atomic maximum, whose result does not depend on the order of the blocks.
-// Called by all threads of the block; contains block barriers.
-// kUniformTail: the block's key is merged under a wave-uniform guard (needed
-// where score_block runs inside a loop with barriers, see batch_score_kernel);
-// otherwise under threadIdx.x == 0, which leaves the single-pass kernel's
-// register allocation free of spills.
-template <bool kUniformTail>
-__device__ __forceinline__ void score_block(Span sp, ClusterId id, int b, int32_t n_hyp,
-                                            const Points &pts, float tau, int rows_max,
-                                            float4 *s_hyp, unsigned long long *s_key,
-                                            TailShared &s_tail,
-                                            unsigned long long *__restrict__ best_key,
-                                            int32_t *__restrict__ hyp_counts) {
+// them against every point of the cluster: lanes = points over the cluster's full
+// rows, lanes = hypotheses over its tail, or over the whole cluster when it has at
+// most lanes_max (<= kLaneTile) points.  Returns the block's best (count, lowest
+// index) key over its valid hypotheses, the same in every thread.  Called by all
+// threads of the block, also from the persistent loop (every branch around a
+// barrier is on a wave-uniform value).
+template <int B>
+__device__ __forceinline__ unsigned long long score_block(Span sp, ClusterId id, int b,
+                                                          int32_t n_hyp, const Points &pts,
+                                                          float tau, int rows_max, int lanes_max,
+                                                          RowsShared<B> &sh,
+                                                          int32_t *__restrict__ hyp_counts) {
+    static_assert(kLaneTile <= B, "a thread stages a point");
     const int tid = threadIdx.x;
-    const int64_t h = (int64_t)b * kScoreBlock + tid;
+    const int64_t h = (int64_t)b * B + tid;
     if (!sp.ok || sp.n < 2) {
         if (hyp_counts != nullptr && h < n_hyp) hyp_counts[id.out * n_hyp + h] = 0;
-        return;
+        return 0;
     }
-    const int tail = lanes_tail(sp.n);  // the same for the whole block
+    const int tail = sp.n <= lanes_max ? (int)sp.n : lanes_tail(sp.n);  // the same for the block
+    float2 own = make_float2(__builtin_nanf(""), __builtin_nanf(""));
     {
         // The tail points' loads go out before the hypothesis's seed loads and
         // are stored after its solve, so the two latencies overlap.
         PointLoad tl;
         if (tail > 0) tl = load_point(pts, sp.lo + sp.n - tail, tail);
-        float hx = __builtin_nanf(""), hy = __builtin_nanf("");
         if (h < n_hyp) {
             const Hypothesis hyp = make_hypothesis(pts, sp, (uint32_t)h, id.local, id.key0, id.key1);
-            hx = (float)hyp.vx;  // NaN exactly when the pair is degenerate
-            hy = (float)hyp.vy;
+            own = make_float2((float)hyp.vx, (float)hyp.vy);  // NaN exactly when degenerate
         }
-        reinterpret_cast<float2 *>(s_hyp)[tid] = make_float2(hx, hy);
-        if (tail > 0) store_points(tl, tail, s_tail.c, s_tail.s, s_tail.v);
+        reinterpret_cast<float2 *>(sh.hyp)[tid] = own;
+        if (tail > 0) store_points(tl, tail, sh.tile.c, sh.tile.s, sh.tile.v);
     }
     __syncthreads();
 
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int lane = tid % kWave;
-    const int64_t h0 = (int64_t)b * kScoreBlock + wave * kWave;
-    unsigned long long key = 0;
+    const int64_t h0 = (int64_t)b * B + wave * kWave;
+    uint32_t val = 0;  // count + 1 of a valid hypothesis
     if (h0 < n_hyp) {
         const int nh = (int64_t)n_hyp - h0 < kWave ? (int)((int64_t)n_hyp - h0) : kWave;
         Span rows = sp;
         rows.n -= tail;
-        uint32_t cnt = score_cluster<kPassRows, kUniformTail>(
-            pts, rows, lane, s_hyp + wave * (kWave / 2), nh, tau, rows_max);
-        // The lane's own hypothesis is re-read from LDS rather than kept in
-        // registers through the scoring loop.
-        const float2 own = reinterpret_cast<const float2 *>(s_hyp)[tid];
-        if (tail > 0) cnt += tail_count(s_tail, tail, own.x, own.y, tau);
-        const int64_t hl = h0 + lane;
+        uint32_t cnt = 0;
+        if (rows.n > 0) {
+            cnt = score_cluster<kPassRows, true>(pts, rows, lane, sh.hyp + wave * (kWave / 2), nh,
+                                                 tau, rows_max);
+            // The lane's own hypothesis is re-read from LDS rather than kept in
+            // registers through the scoring loop.
+            own = reinterpret_cast<const float2 *>(sh.hyp)[tid];
+        }
+        cnt += tail_count(sh.tile, tail, own.x, own.y, tau);
         if (lane < nh) {
-            if (hyp_counts != nullptr) hyp_counts[id.out * n_hyp + hl] = (int32_t)cnt;
-            if (!__builtin_isnan(own.x))
-                key = ((unsigned long long)cnt << 32) | (0xFFFFFFFFull - (uint32_t)hl);
+            if (hyp_counts != nullptr) hyp_counts[id.out * n_hyp + h] = (int32_t)cnt;
+            if (!__builtin_isnan(own.x)) val = cnt + 1u;
         }
     }
-    key = wave_max_u64(key);
-    if (lane == 0) s_key[wave] = key;
+    const unsigned long long key = wave_best(val, (uint32_t)h);
+    if (lane == 0) sh.key[wave] = key;
     __syncthreads();
-    if (kUniformTail) {
-        if (wave == 0) {  // wave-uniform guard; one lane merges the block's key
-            for (int w = 1; w < kScoreBlock / kWave; ++w) key = s_key[w] > key ? s_key[w] : key;
-            if (lane == 0 && key != 0) atomicMax(&best_key[id.out], key);
-        }
-    } else if (tid == 0) {
-        for (int w = 1; w < kScoreBlock / kWave; ++w) key = s_key[w] > key ? s_key[w] : key;
-        if (key != 0) atomicMax(&best_key[id.out], key);
-    }
+    return block_key<B>(sh.key);
 }
 
 // ---------------------------------------------------------------------------
@@ -786,90 +841,24 @@ __device__ __forceinline__ unsigned long long hyp_key(uint32_t count, int64_t h)
     return ((unsigned long long)count << 32) | (0xFFFFFFFFull - (uint32_t)h);
 }
 
-// ---------------------------------------------------------------------------
-// Small clusters with lanes = hypotheses (batched form, clusters of at most
-// Tuning::lanes_max points, at most kLaneTile).  With lanes = points a cluster
-// of n < 64 points leaves 64 - n lanes of every compare idle; here each thread
-// keeps the hypothesis it solved in registers, the cluster's points are staged
-// in LDS and read by every lane at the same address (a broadcast), and each
-// lane counts its own inliers with one compare and one add per point: four
-// vector instructions per point and 64 hypotheses, none on the scalar unit.
-// The residual and the test are the float32 loop's, fma(-hy, s, fma(-hx, c,
-// v_d)) and |.| < tau, so every count, and the block's key, is the same bit for
-// bit.
-// ---------------------------------------------------------------------------
-
-constexpr int kLaneTile = 256;        // points staged in LDS: the largest cluster of this form
+// Small clusters score with lanes = hypotheses: with lanes = points a cluster of
+// n < 64 points leaves 64 - n lanes of every compare idle and pays the
+// per-hypothesis overhead on a single row.  The residual and the test are the
+// rows form's, fma(-hy, s, fma(-hx, c, v_d)) and |.| < tau, so every count, and
+// the block's key, is the same bit for bit.
 constexpr int kDefaultLanesMax = 64;  // default Tuning::lanes_max
-// Single-frame calls (score_kernel, small_frame_kernel): clusters of at most
-// this many points score with lanes = hypotheses.
-constexpr int kSingleLanesMax = 64;
-
-struct LaneShared {
-    float4 c[kLaneTile / 4], s[kLaneTile / 4], v[kLaneTile / 4];  // padded with (0, 0, +inf)
-    unsigned long long key[kScoreBlock / kWave];
-};
-
-// One scoring block of a cluster with 2 <= n <= kLaneTile points, lanes =
-// hypotheses.  Called by all threads of the block from the persistent loop
-// (every branch around a barrier is on a wave-uniform value).
-__device__ __forceinline__ void score_block_lanes(Span sp, ClusterId id, int b, int32_t n_hyp,
-                                                  const Points &pts, float tau, LaneShared &sh,
-                                                  unsigned long long *__restrict__ best_key,
-                                                  int32_t *__restrict__ hyp_counts) {
-    const int tid = threadIdx.x;
-    const int n = (int)sp.n;
-    const int n4 = (n + 3) / 4;
-    // The point loads go out before the hypothesis's seed loads and are stored
-    // after its solve, so the two latencies overlap.
-    const PointLoad pl = load_point(pts, sp.lo, n);
-    const int64_t h = (int64_t)b * kScoreBlock + tid;
-    float hx = __builtin_nanf(""), hy = __builtin_nanf("");
-    if (h < n_hyp) {
-        const Hypothesis hyp = make_hypothesis(pts, sp, (uint32_t)h, id.local, id.key0, id.key1);
-        hx = (float)hyp.vx;  // NaN exactly when the pair is degenerate: counts 0
-        hy = (float)hyp.vy;
-    }
-    store_points(pl, n, sh.c, sh.s, sh.v);
-    __syncthreads();
-    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
-    const int lane = tid % kWave;
-    uint32_t cnt = 0;
-    for (int q = 0; q < n4; ++q) {
-        const float4 c = sh.c[q], sn = sh.s[q], v = sh.v[q];
-        const float cc[4] = {c.x, c.y, c.z, c.w}, ss[4] = {sn.x, sn.y, sn.z, sn.w};
-        const float vv[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const float e = __builtin_fmaf(-hy, ss[u], __builtin_fmaf(-hx, cc[u], vv[u]));
-            cnt += __builtin_fabsf(e) < tau ? 1u : 0u;
-        }
-    }
-    unsigned long long key = 0;
-    if (h < n_hyp) {
-        if (hyp_counts != nullptr) hyp_counts[id.out * n_hyp + h] = (int32_t)cnt;
-        if (!__builtin_isnan(hx)) key = hyp_key(cnt, h);
-    }
-    key = wave_max_u64(key);
-    if (lane == 0) sh.key[wave] = key;
-    __syncthreads();
-    if (wave == 0) {  // wave-uniform guard; one lane merges the block's key
-        for (int w = 1; w < kScoreBlock / kWave; ++w) key = sh.key[w] > key ? sh.key[w] : key;
-        if (lane == 0 && key != 0) atomicMax(&best_key[id.out], key);
-    }
-    // The next item restages the tile only after the work-queue fetch's two
-    // block barriers, which every wave reaches after its last read of it.
-}
+constexpr int kSingleLanesMax = 64;   // single-frame calls
 
 // Exact float32 counts of the nl (<= 64) hypotheses in `list` (LDS) over the
-// whole cluster; wave w scores rows [w rows/4, (w+1) rows/4) of the cluster.
+// whole cluster; the block's waves share the cluster's rows.
 // Lane q of every wave returns the count of list entry q.  Contains barriers.
+template <int B>
 __device__ __forceinline__ uint32_t exact_counts(Span sp, const Points &pts, float tau, int nl,
                                                  const float4 *list, uint32_t (*part_sums)[kWave],
                                                  int wave, int lane) {
     const int64_t rows = (sp.n + kWave - 1) / kWave;
-    const int64_t r0 = rows * wave / (kScoreBlock / kWave);
-    const int64_t r1 = rows * (wave + 1) / (kScoreBlock / kWave);
+    const int64_t r0 = rows * wave / (B / kWave);
+    const int64_t r1 = rows * (wave + 1) / (B / kWave);
     const int64_t p1 = r1 * kWave < sp.n ? r1 * kWave : sp.n;
     Span part;
     part.lo = sp.lo + r0 * kWave;
@@ -879,7 +868,7 @@ __device__ __forceinline__ uint32_t exact_counts(Span sp, const Points &pts, flo
     __syncthreads();
     uint32_t total = 0;
 #pragma unroll
-    for (int w = 0; w < kScoreBlock / kWave; ++w) total += part_sums[w][lane];
+    for (int w = 0; w < B / kWave; ++w) total += part_sums[w][lane];
     __syncthreads();
     return total;
 }
@@ -890,8 +879,8 @@ __device__ __forceinline__ uint32_t exact_counts(Span sp, const Points &pts, flo
 // Only the hypothesis with the most inliers is kept, so a hypothesis need not
 // be counted once its count is known to be below another's.  Per workgroup
 // (one cluster, up to kPruneHyp hypotheses):
-//   1. reference r: among the first 256 hypotheses, the one with the most
-//      inliers in a strided sample of the points;
+//   1. reference r: among the first hypotheses, one per thread, the one with the
+//      most inliers in a strided sample of the points;
 //   2. one sweep over the cluster counts r exactly (T) and sorts the points
 //      into a table of direction (kAngleBins) x signed residual under r;
 //   3. every hypothesis h gets an upper bound of its count from the table: a
@@ -899,8 +888,8 @@ __device__ __forceinline__ uint32_t exact_counts(Span sp, const Points &pts, flo
 //      lies within tau of (h - r).u, and over one direction bin (h - r).u
 //      stays in a known interval, so h's inliers in the bin are at most the
 //      bin's points in that interval widened by tau: two prefix-sum lookups;
-//   4. the four hypotheses with the largest bounds (one per wave) are counted,
-//      which raises the best known count;
+//   4. the hypotheses with the largest bounds (one per wave) are counted, which
+//      raises the best known count;
 //   5. every hypothesis whose bound still reaches the best known (count, lowest
 //      index) is counted in float32 over all points.
 // A hypothesis left out has count <= bound and loses to a counted one, so the
@@ -928,40 +917,41 @@ __device__ __forceinline__ uint32_t exact_counts(Span sp, const Points &pts, flo
 // ---------------------------------------------------------------------------
 
 constexpr int kPruneHyp = 1024;     // hypotheses per workgroup, at most
-constexpr int kPruneRounds = kPruneHyp / kScoreBlock;
 
 // Smallest cluster scored this way, by blocks of 256 hypotheses per workgroup
-// (at least 1).  The table is made once per workgroup, so with several blocks
-// sharing it the bound pays from 128 points on (16,384 clusters of 128 points at
-// 1024 hypotheses: scoring stage 247 us counted in full, 212 us this way; 8192 of
-// 256 points 183 and 125 us); with one block per table only from about 320
-// points on (a frame of 1021 clusters in 3-degree windows: 37, 35 and 34 us with
-// the line at 128, 192 and 320).
+// (at least 1).  The table is made once per workgroup, so the more blocks share it
+// the sooner the bound pays: with four from 128 points on (16,384 clusters of 128
+// points at 1024 hypotheses: scoring stage 247 us counted in full, 212 us this
+// way), with two a little later (32,768 clusters of 128 points at 512 hypotheses:
+// 256 and 264 us), with one from about 320 points on (a frame of 1021 clusters in
+// 3-degree windows: 37, 35 and 34 us with the line at 128, 192 and 320).
 __host__ __device__ constexpr int prune_min(int rounds) {
-    return rounds == 1 ? 320 : 128;
+    return rounds == 1 ? 320 : rounds == 2 ? 160 : 128;
 }
 constexpr int kAngleBins = 8;
 constexpr int kResidualBins = 256;  // 128 per sign, 16 per octave of |e| + unit (residual_bin)
 constexpr int kResidualRow = kResidualBins + 1;
-constexpr int kSampleRows = 1;      // rows of 64 points in the sample
 constexpr float kPruneMaxSpeed = 1e15f;  // references beyond it are not used
 
+template <int B>
 struct PruneShared {
     float4 hyp[kPruneHyp / 2];  // (vx, vy) pairs
+    LaneTile<kWave> sample;
     float4 dir[kAngleBins];     // centre (cos, sin), half width w, w^2 / 2
     union {
         uint32_t hist[kAngleBins * kResidualRow];
         struct {
-            uint32_t part[kScoreBlock / kWave][kWave];
+            uint32_t part[B / kWave][kWave];
             float list[2 * kWave] __attribute__((aligned(16)));
             uint16_t idx[kPruneHyp];
         } count;
     } u;
-    unsigned long long key[kScoreBlock / kWave];
-    float lo[kScoreBlock / kWave], hi[kScoreBlock / kWave];
-    uint32_t n[kScoreBlock / kWave];
-    uint32_t top[kScoreBlock / kWave];
+    unsigned long long key[B / kWave];
+    float lo[B / kWave], hi[B / kWave];
+    uint32_t n[B / kWave];
+    uint32_t top[B / kWave];
 };
+static_assert(1024 / kWave <= kWave, "a lane per wave's top");
 
 // Position of a direction on the circle, monotone in its angle over (-pi, pi]:
 // s / (|c| + |s|) in the right half plane, continued to +-2 at the left.
@@ -975,7 +965,7 @@ __device__ __forceinline__ float2 key_direction(float q) {
     const float a = __builtin_fabsf(q);
     const float c = 1.0f - a;
     const float s = __builtin_copysignf(a <= 1.0f ? a : 2.0f - a, q);
-    const float inv = 1.0f / sqrtf(c * c + s * s);
+    const float inv = __builtin_amdgcn_rsqf(c * c + s * s);
     return make_float2(c * inv, s * inv);
 }
 
@@ -1001,45 +991,61 @@ __device__ __forceinline__ float uniform_f(float v) {
 }
 
 // Scoring of hypotheses [h_first, h_first + nh), nh <= kPruneHyp, of a cluster
-// with at least kWave points.  Called by all threads of the block, also
-// from the persistent loop: every branch around a barrier is on a wave-uniform
-// value.
-__device__ __forceinline__ void score_pruned(Span sp, ClusterId id, int64_t h_first, int nh,
-                                             const Points &pts, float tau, PruneShared &sh,
-                                             unsigned long long *__restrict__ best_key,
-                                             unsigned long long *block_best = nullptr) {
+// with at least kWave points.  Returns the best key among the hypotheses, or,
+// where a key of best_key (the cluster's so far, shared by its workgroups;
+// nullptr: none) beats them all, some key not above it.  Called by all threads
+// of the block, also from the persistent loop: every branch around a barrier is
+// on a wave-uniform value.
+template <int B>
+__device__ __forceinline__ unsigned long long score_pruned(
+    Span sp, ClusterId id, int64_t h_first, int nh, const Points &pts, float tau,
+    PruneShared<B> &sh, const unsigned long long *best_key) {
+    constexpr int kPruneRounds = kPruneHyp / B;
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int lane = tid % kWave;
     const uint32_t n = (uint32_t)sp.n;
-    const int rounds = (nh + kScoreBlock - 1) / kScoreBlock;
+    const int rounds = (nh + B - 1) / B;
     const StagedPoint *points = pts.staged + sp.lo;
     float2 *hyp = reinterpret_cast<float2 *>(sh.hyp);
 
+    // The sample: 64 points spread over the cluster.
+    if (wave == 0) {
+        const StagedPoint &u = points[(uint32_t)(((uint64_t)lane * n) / kWave)];
+        PointLoad L;
+        L.c = u.c;
+        L.s = u.s;
+        L.v = u.v;
+        store_points(L, kWave, sh.sample.c, sh.sample.s, sh.sample.v);
+    }
     // Range of the points' directions.
     float qlo = __builtin_inff(), qhi = -__builtin_inff();
-#pragma unroll 4
-    for (uint32_t p = tid; p < n; p += kScoreBlock) {
+#pragma unroll 2
+    for (uint32_t p = tid; p < n; p += B) {
         const float q = direction_key(points[p].c, points[p].s);  // NaN for a non-finite point (0, 0)
         qlo = fminf(qlo, q);
         qhi = fmaxf(qhi, q);
     }
-    for (int i = tid; i < kAngleBins * kResidualRow; i += kScoreBlock) sh.u.hist[i] = 0;
-    for (int q = 0; q < rounds; ++q) {
-        const int hl = q * kScoreBlock + tid;
-        float2 hv = make_float2(__builtin_nanf(""), __builtin_nanf(""));
-        if (hl < nh) {
-            const Hypothesis y =
-                make_hypothesis(pts, sp, (uint32_t)(h_first + hl), id.local, id.key0, id.key1);
-            hv = make_float2((float)y.vx, (float)y.vy);  // NaN exactly when degenerate
+    for (int i = tid; i < kAngleBins * kResidualRow; i += B) sh.u.hist[i] = 0;
+    // The hypotheses, two at a time so that their seed loads overlap (NaN for a
+    // degenerate pair and past the last).
+    float2 own = make_float2(0.0f, 0.0f);  // the thread's first
+    for (int q = 0; q < rounds; q += 2) {
+        const int h0 = q * B + tid, h1 = h0 + B;
+        const Seeds d0 = draw_seeds(pts, sp, (uint32_t)(h_first + h0), id.local, id.key0, id.key1);
+        const Seeds d1 = draw_seeds(pts, sp, (uint32_t)(h_first + h1), id.local, id.key0, id.key1);
+        const Hypothesis y0 = solve_seeds(pts, d0);
+        const float qnan = __builtin_nanf("");
+        const float2 f0 = h0 < nh ? make_float2((float)y0.vx, (float)y0.vy) : make_float2(qnan, qnan);
+        hyp[h0] = f0;
+        if (q == 0) own = f0;
+        if (q + 1 < rounds) {
+            const Hypothesis y1 = solve_seeds(pts, d1);
+            hyp[h1] = h1 < nh ? make_float2((float)y1.vx, (float)y1.vy) : make_float2(qnan, qnan);
         }
-        hyp[hl] = hv;
     }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        qlo = fminf(qlo, __shfl_xor(qlo, o, kWave));
-        qhi = fmaxf(qhi, __shfl_xor(qhi, o, kWave));
-    }
+    qlo = wave_min_f(qlo);
+    qhi = wave_max_f(qhi);
     if (lane == 0) {
         sh.lo[wave] = qlo;
         sh.hi[wave] = qhi;
@@ -1048,27 +1054,17 @@ __device__ __forceinline__ void score_pruned(Span sp, ClusterId id, int64_t h_fi
 
     // 1. Reference.
     {
-        float c[kSampleRows], s[kSampleRows], v[kSampleRows];
-#pragma unroll
-        for (int r = 0; r < kSampleRows; ++r) {
-            const uint32_t p = (uint32_t)(((uint64_t)(r * kWave + lane) * n) / (kSampleRows * kWave));
-            const StagedPoint &u = points[p];
-            c[r] = u.c;
-            s[r] = u.s;
-            v[r] = u.v;
-        }
-        const int left = nh - wave * kWave;
-        const int ng = ((left < kWave ? left : kWave) + kHypGroup - 1) / kHypGroup;
-        const uint32_t cnt = count_rows<kSampleRows, true>(c, s, v, sh.hyp + wave * (kWave / 2), ng, tau);
-        const float2 own = hyp[tid];
-        unsigned long long key = 0;
-        if (__builtin_fabsf(own.x) + __builtin_fabsf(own.y) < kPruneMaxSpeed)  // false for NaN
-            key = hyp_key(cnt, tid);
-        key = wave_max_u64(key);
+        const uint32_t cnt = tail_count(sh.sample, kWave, own.x, own.y, tau);
+        const bool usable = __builtin_fabsf(own.x) + __builtin_fabsf(own.y) < kPruneMaxSpeed;  // not NaN
+        const unsigned long long key = wave_best(usable ? cnt + 1u : 0u, (uint32_t)tid);
         if (lane == 0) sh.key[wave] = key;
     }
-    const float q0 = fminf(fminf(sh.lo[0], sh.lo[1]), fminf(sh.lo[2], sh.lo[3]));
-    const float q1 = fmaxf(fmaxf(sh.hi[0], sh.hi[1]), fmaxf(sh.hi[2], sh.hi[3]));
+    float q0 = sh.lo[0], q1 = sh.hi[0];
+#pragma unroll
+    for (int w = 1; w < B / kWave; ++w) {
+        q0 = fminf(q0, sh.lo[w]);
+        q1 = fmaxf(q1, sh.hi[w]);
+    }
     const float width = fmaxf(q1 - q0, 1e-6f) * (1.0f / kAngleBins);
     if (tid < kAngleBins) {
         // A direction bin's centre and half width (asin x <= 1.05 x up to half
@@ -1077,15 +1073,15 @@ __device__ __forceinline__ void score_pruned(Span sp, ClusterId id, int64_t h_fi
         const float2 a = key_direction(q0 + tid * width);
         const float2 b = key_direction(tid == kAngleBins - 1 ? q1 : q0 + (tid + 1) * width);
         const float dx = b.x - a.x, dy = b.y - a.y;
-        const float w = 0.53f * sqrtf(dx * dx + dy * dy) + 0x1p-15f;
+        const float w = 0.53f * __builtin_amdgcn_sqrtf(dx * dx + dy * dy) + 0x1p-15f;
         const float mx = a.x + b.x, my = a.y + b.y;
-        const float inv = 1.0f / sqrtf(mx * mx + my * my);
+        const float inv = __builtin_amdgcn_rsqf(mx * mx + my * my);
         sh.dir[tid] = make_float4(mx * inv, my * inv, w, 0.5f * w * w);
     }
     __syncthreads();
     unsigned long long ref = 0;
 #pragma unroll
-    for (int w = 0; w < kScoreBlock / kWave; ++w) ref = sh.key[w] > ref ? sh.key[w] : ref;
+    for (int w = 0; w < B / kWave; ++w) ref = sh.key[w] > ref ? sh.key[w] : ref;
     ref = uniform_u64(ref);
 
     unsigned long long best = 0;  // best known (count, hypothesis) key, the same in every lane
@@ -1097,8 +1093,8 @@ __device__ __forceinline__ void score_pruned(Span sp, ClusterId id, int64_t h_fi
         const float sigma = uniform_f(residual_scale(tau));
         const float scale = 1.0f / width;
         uint32_t t = 0;
-#pragma unroll 4
-        for (uint32_t p = tid; p < n; p += kScoreBlock) {
+#pragma unroll 2
+        for (uint32_t p = tid; p < n; p += B) {
             const StagedPoint &u = points[p];
             const float e = __builtin_fmaf(-ry, u.s, __builtin_fmaf(-rx, u.c, u.v));
             t += __builtin_fabsf(e) < tau ? 1u : 0u;
@@ -1110,13 +1106,15 @@ __device__ __forceinline__ void score_pruned(Span sp, ClusterId id, int64_t h_fi
         t = (uint32_t)wave_sum_i((int)t);
         if (lane == 0) sh.n[wave] = t;
         __syncthreads();
-        best = hyp_key(sh.n[0] + sh.n[1] + sh.n[2] + sh.n[3], h_first + r_local);
-        best = uniform_u64(best);
+        t = sh.n[0];
+#pragma unroll
+        for (int w = 1; w < B / kWave; ++w) t += sh.n[w];
+        best = uniform_u64(hyp_key(t, h_first + r_local));
         // Prefix sums along each row: 32 threads per row, eight bins each.
-        {
-            constexpr int kRowThreads = 32;
-            static_assert(kAngleBins * kRowThreads == kScoreBlock &&
-                          kResidualBins == kRowThreads * 8, "one pass");
+        constexpr int kRowThreads = 32;
+        static_assert(kAngleBins * kRowThreads <= B && kAngleBins * kRowThreads % kWave == 0 &&
+                      kResidualBins == kRowThreads * 8, "one pass of whole waves");
+        if (wave < kAngleBins * kRowThreads / kWave) {
             uint32_t *row =
                 sh.u.hist + (tid / kRowThreads) * kResidualRow + (tid % kRowThreads) * 8;
             uint32_t x[8], sum = 0;
@@ -1144,13 +1142,14 @@ __device__ __forceinline__ void score_pruned(Span sp, ClusterId id, int64_t h_fi
         for (int q = 0; q < kPruneRounds; ++q) {
             ub[q] = 0;
             if (q < rounds) {
-                const float2 h = hyp[q * kScoreBlock + tid];
+                const float2 h = hyp[q * B + tid];
                 const float m = __builtin_fabsf(h.x) + __builtin_fabsf(h.y) + __builtin_fabsf(rx) +
                                 __builtin_fabsf(ry);
                 const float dx = (h.x - rx) * sigma, dy = (h.y - ry) * sigma;
                 const float band = __builtin_fmaf(__builtin_fabsf(dx) + __builtin_fabsf(dy), w2,
                                                   (tau + 0x1p-18f * (tau + m)) * sigma);
                 uint32_t bound = 0;
+#pragma unroll 1
                 for (int b = 0; b < kAngleBins; ++b) {
                     const float4 d = sh.dir[b];
                     const float f = __builtin_fmaf(dx, d.x, dy * d.y);
@@ -1168,28 +1167,37 @@ __device__ __forceinline__ void score_pruned(Span sp, ClusterId id, int64_t h_fi
     } else {
 #pragma unroll
         for (int q = 0; q < kPruneRounds; ++q)
-            ub[q] = q < rounds && !__builtin_isnan(hyp[q * kScoreBlock + tid].x) ? n : 0u;
+            ub[q] = q < rounds && !__builtin_isnan(hyp[q * B + tid].x) ? n : 0u;
     }
 
     // 4. The largest bound of each wave's hypotheses above the best key known
     // (this workgroup's r, or another workgroup's of the same cluster).
-    const unsigned long long other = uniform_u64(
-        __hip_atomic_load(&best_key[id.out], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-    unsigned long long floor_key = other > best ? other : best;
-    unsigned long long top = 0;
-#pragma unroll
-    for (int q = 0; q < kPruneRounds; ++q) {
-        const unsigned long long k = ub[q] != 0 ? hyp_key(ub[q], h_first + q * kScoreBlock + tid) : 0ull;
-        if (k > floor_key && k > top) top = k;
+    unsigned long long floor_key = best;
+    if (best_key != nullptr) {
+        const unsigned long long other = uniform_u64(
+            __hip_atomic_load(best_key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+        floor_key = other > best ? other : best;
     }
-    top = wave_max_u64(top);
+    unsigned long long top = 0;
+    {
+        uint32_t most = 0, at = 0;
+#pragma unroll
+        for (int q = 0; q < kPruneRounds; ++q) {
+            if (ub[q] > most) {
+                most = ub[q];
+                at = (uint32_t)(q * B + tid);
+            }
+        }
+        top = wave_best(most != 0 ? most + 1u : 0u, (uint32_t)h_first + at);
+        top = top > floor_key ? top : 0ull;
+    }
     if (lane == 0) sh.key[wave] = top;
     __syncthreads();  // also the last use of the table
     int nl = 0;
     {
         int before = 0;
 #pragma unroll
-        for (int w = 0; w < kScoreBlock / kWave; ++w) {
+        for (int w = 0; w < B / kWave; ++w) {
             const int has = sh.key[w] != 0 ? 1 : 0;
             before += w < wave ? has : 0;
             nl += has;
@@ -1207,12 +1215,12 @@ __device__ __forceinline__ void score_pruned(Span sp, ClusterId id, int64_t h_fi
     bool tops = true;
     while (nl > 0) {
         __syncthreads();
-        const uint32_t cnt = exact_counts(sp, pts, tau, nl,
+        const uint32_t cnt = exact_counts<B>(sp, pts, tau, nl,
                                           reinterpret_cast<const float4 *>(sh.u.count.list),
                                           sh.u.count.part, wave, lane);
-        unsigned long long k = 0;
-        if (lane < nl) k = hyp_key(cnt, h_first + (tops ? sh.top[lane & 3] : sh.u.count.idx[c0 - kWave + lane]));
-        k = uniform_u64(wave_max_u64(k));
+        uint32_t h = 0;
+        if (lane < nl) h = tops ? sh.top[lane] : sh.u.count.idx[c0 - kWave + lane];
+        const unsigned long long k = wave_best(lane < nl ? cnt + 1u : 0u, (uint32_t)h_first + h);
         best = k > best ? k : best;
         floor_key = best > floor_key ? best : floor_key;
         if (tops) {
@@ -1222,7 +1230,7 @@ __device__ __forceinline__ void score_pruned(Span sp, ClusterId id, int64_t h_fi
 #pragma unroll
             for (int q = 0; q < kPruneRounds; ++q) {
                 const unsigned long long kq =
-                    ub[q] != 0 ? hyp_key(ub[q], h_first + q * kScoreBlock + tid) : 0ull;
+                    ub[q] != 0 ? hyp_key(ub[q], h_first + q * B + tid) : 0ull;
                 masks[q] = __builtin_amdgcn_ballot_w64(kq > floor_key && kq != top);
                 mine += (uint32_t)__builtin_popcountll(masks[q]);
             }
@@ -1231,7 +1239,7 @@ __device__ __forceinline__ void score_pruned(Span sp, ClusterId id, int64_t h_fi
             uint32_t at = 0;
             n_cand = 0;
 #pragma unroll
-            for (int w = 0; w < kScoreBlock / kWave; ++w) {
+            for (int w = 0; w < B / kWave; ++w) {
                 const uint32_t x = sh.n[w];
                 at += w < wave ? x : 0u;
                 n_cand += x;
@@ -1241,7 +1249,7 @@ __device__ __forceinline__ void score_pruned(Span sp, ClusterId id, int64_t h_fi
             for (int q = 0; q < kPruneRounds; ++q) {
                 const uint32_t rank = __builtin_amdgcn_mbcnt_hi(
                     (uint32_t)(masks[q] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)masks[q], 0u));
-                if ((masks[q] >> lane) & 1) sh.u.count.idx[at + rank] = (uint16_t)(q * kScoreBlock + tid);
+                if ((masks[q] >> lane) & 1) sh.u.count.idx[at + rank] = (uint16_t)(q * B + tid);
                 at += (uint32_t)__builtin_popcountll(masks[q]);
             }
             __syncthreads();
@@ -1251,31 +1259,40 @@ __device__ __forceinline__ void score_pruned(Span sp, ClusterId id, int64_t h_fi
         if (tid < nl) reinterpret_cast<float2 *>(sh.u.count.list)[tid] = hyp[sh.u.count.idx[c0 + tid]];
         c0 += kWave;
     }
-    if (block_best != nullptr) {
-        *block_best = best;
-    } else if (wave == 0) {
-        if (lane == 0 && best != 0) atomicMax(&best_key[id.out], best);
-    }
+    return best;
 }
 
-// Workgroup LDS of the rows form.
-struct RowsShared {
-    float4 hyp[kScoreBlock / 2];  // (vx, vy) pairs, two per float4
-    unsigned long long key[kScoreBlock / kWave];
-    TailShared tail;
+// Workgroup LDS of the scoring forms: a workgroup uses one at a time.
+template <int B>
+struct ScoreShared {
+    static constexpr size_t kBytes = sizeof(PruneShared<B>);
+    static_assert(sizeof(RowsShared<B>) <= kBytes && sizeof(Fp16Shared) <= kBytes, "the largest");
+    alignas(16) unsigned char bytes[kBytes];
+    __device__ RowsShared<B> &rows() { return *reinterpret_cast<RowsShared<B> *>(bytes); }
+    __device__ Fp16Shared &fp16() { return *reinterpret_cast<Fp16Shared *>(bytes); }
+    __device__ PruneShared<B> &prune() { return *reinterpret_cast<PruneShared<B> *>(bytes); }
 };
 
-// Workgroup LDS of the scoring forms: a workgroup uses one at a time.
-struct ScoreShared {
-    static constexpr size_t kBytes = sizeof(PruneShared);
-    static_assert(sizeof(RowsShared) <= kBytes && sizeof(LaneShared) <= kBytes &&
-                  sizeof(Fp16Shared) <= kBytes, "the largest");
-    alignas(16) unsigned char bytes[kBytes];
-    __device__ RowsShared &rows() { return *reinterpret_cast<RowsShared *>(bytes); }
-    __device__ LaneShared &lanes() { return *reinterpret_cast<LaneShared *>(bytes); }
-    __device__ Fp16Shared &fp16() { return *reinterpret_cast<Fp16Shared *>(bytes); }
-    __device__ PruneShared &prune() { return *reinterpret_cast<PruneShared *>(bytes); }
-};
+// Float32 scoring of hypotheses [h_first, h_first + nh) of one cluster by one
+// workgroup (h_first a multiple of B), in the form its size asks for; the best
+// key, the same in every thread.  lanes_max: clusters of at most this many points
+// take lanes = hypotheses; prune: clusters of at least this many points count
+// only possible winners (nh <= kPruneHyp).
+template <int B>
+__device__ __forceinline__ unsigned long long score_hypotheses(
+    Span sp, ClusterId id, int64_t h_first, int nh, int32_t n_hyp, const Points &pts, float tau,
+    int rows_max, int lanes_max, int64_t prune, ScoreShared<B> &sh,
+    const unsigned long long *best_key, int32_t *__restrict__ hyp_counts) {
+    if (sp.n >= prune) return score_pruned<B>(sp, id, h_first, nh, pts, tau, sh.prune(), best_key);
+    const int b0 = (int)(h_first / B), blocks = (nh + B - 1) / B;
+    unsigned long long best = 0;
+    for (int b = b0; b < b0 + blocks; ++b) {
+        const unsigned long long key = score_block<B>(sp, id, b, n_hyp, pts, tau, rows_max,
+                                                      lanes_max, sh.rows(), hyp_counts);
+        best = key > best ? key : best;
+    }
+    return best;
+}
 
 // One scoring block in the FP16 form (sp.ok and sp.n >= 2; called from the
 // persistent loop: every branch around a barrier is on a wave-uniform value).
@@ -1386,7 +1403,7 @@ __device__ __forceinline__ void score_block_fp16(Span sp, ClusterId id, int b, i
     }
     __syncthreads();
     const uint32_t n1 = has_top + n_wide < (uint32_t)kWave ? has_top + n_wide : (uint32_t)kWave;
-    const uint32_t c1 = exact_counts(sp, pts, tau, (int)n1, sh.list, sh.part, wave, lane);
+    const uint32_t c1 = exact_counts<kScoreBlock>(sp, pts, tau, (int)n1, sh.list, sh.part, wave, lane);
     const uint32_t t_exact = has_top ? __builtin_amdgcn_readfirstlane(c1) : 0u;
     unsigned long long best = lane < (int)n1 ? hyp_key(c1, base + sh.idx[lane]) : 0ull;
     best = wave_max_u64(best);
@@ -1413,7 +1430,7 @@ __device__ __forceinline__ void score_block_fp16(Span sp, ClusterId id, int b, i
         const int nl = n_cand - c0 < (uint32_t)kWave ? (int)(n_cand - c0) : kWave;
         if (tid < nl) reinterpret_cast<float2 *>(sh.list)[tid] = h32[sh.idx[c0 + tid]];
         __syncthreads();
-        const uint32_t cnt = exact_counts(sp, pts, tau, nl, sh.list, sh.part, wave, lane);
+        const uint32_t cnt = exact_counts<kScoreBlock>(sp, pts, tau, nl, sh.list, sh.part, wave, lane);
         unsigned long long k2 = 0;
         if (lane < nl) k2 = hyp_key(cnt, base + sh.idx[c0 + lane]);
         k2 = wave_max_u64(k2);
@@ -1441,6 +1458,30 @@ __device__ __forceinline__ void write_failed(const Outputs &o, int64_t k, uint8_
     o.status[k] = st;
     if (o.n_near) o.n_near[k] = 0;
     if (o.best) o.best[k] = -1;
+}
+
+// A cluster's results from its inliers' normal-equation sums.
+__device__ __forceinline__ void write_refit(const Outputs &o, int64_t k, uint32_t hbest, int n_in,
+                                            int n_near, double scc, double scs, double sss,
+                                            double scv, double ssv) {
+    o.n_inliers[k] = n_in;
+    if (o.n_near) o.n_near[k] = n_near;
+    if (o.best) o.best[k] = (int32_t)hbest;
+    const double det = scc * sss - scs * scs;
+    if (n_in < 2 || !(det > 0.0)) {
+        const float qnan = __builtin_nanf("");
+        o.vx[k] = qnan;
+        o.vy[k] = qnan;
+        o.heading[k] = qnan;
+        o.status[k] = RV_CLUSTER_SINGULAR_REFIT;
+        return;
+    }
+    const double fvx = (sss * scv - scs * ssv) / det;
+    const double fvy = (scc * ssv - scs * scv) / det;
+    o.vx[k] = (float)fvx;
+    o.vy[k] = (float)fvy;
+    o.heading[k] = (float)atan2(fvy, fvx);
+    o.status[k] = RV_CLUSTER_OK;
 }
 
 // FP64 sums of a refit, per lane.
@@ -1482,217 +1523,134 @@ __device__ __forceinline__ void refit_points(int64_t p0, bool in_range, float v,
     }
 }
 
-// All points of a cluster under h*, 64-aligned blocks from first_block in
-// steps of `stride`, kRefitUnroll blocks per iteration: the loads of all of
-// them are issued (from a clamped, always valid index) before any block is
-// used.  Each lane visits its points in the same order as one block per
-// iteration, so the sums are the same.  The first iteration's loads do not
-// depend on h*: the callers issue them (refit_load) before solving h*, so
-// their latency overlaps the hypothesis's.
-constexpr int kRefitUnroll = 4;
-
-struct RefitLoads {
-    StagedPoint p[kRefitUnroll];
-    bool in[kRefitUnroll];
+// One point of a wave's 64-point block from p0 on, loaded from a clamped, always
+// valid index.
+struct RefitLoad {
+    StagedPoint p;
+    bool in;
 };
 
-__device__ __forceinline__ RefitLoads refit_load(Span sp, int64_t p0, int64_t stride,
-                                                 const Points &pts, int lane) {
-    RefitLoads L;
-    const int64_t end = sp.lo + sp.n;
-#pragma unroll
-    for (int u = 0; u < kRefitUnroll; ++u) {
-        const int64_t p = p0 + u * stride + lane;
-        L.in[u] = p >= sp.lo && p < end;
-        L.p[u] = pts.staged[L.in[u] ? p : sp.lo];
-    }
+__device__ __forceinline__ RefitLoad refit_load(Span sp, int64_t p0, const Points &pts, int lane) {
+    const int64_t p = p0 + lane;
+    RefitLoad L;
+    L.in = p >= sp.lo && p < sp.lo + sp.n;
+    L.p = pts.staged[L.in ? p : sp.lo];
     return L;
 }
 
-__device__ __forceinline__ void refit_group(const RefitLoads &L, int64_t p0, int64_t stride,
-                                            int64_t end, const Hypothesis &hy, double dtau,
-                                            RefitSums &a, const Outputs &o, int lane) {
-#pragma unroll
-    for (int u = 0; u < kRefitUnroll; ++u)
-        if (p0 + u * stride < end)
-            refit_points(p0 + u * stride, L.in[u], L.p[u].v, cs64(L.p[u]), hy, dtau, a, o,
-                         lane);
-}
-
-// The first group's loads come from the caller (issued before the hypothesis
-// solve); the first group is taken apart from the loop so that no copy of a
-// whole group of loads is selected at run time (such a select puts the group
-// in scratch memory).
-__device__ __forceinline__ RefitSums refit_sweep(Span sp, int64_t first_block, int64_t stride,
-                                                 const RefitLoads &first, const Points &pts,
-                                                 const Hypothesis &hy, double dtau,
-                                                 const Outputs &o, int lane) {
-    RefitSums a;
-    const int64_t end = sp.lo + sp.n;
-    refit_group(first, first_block, stride, end, hy, dtau, a, o, lane);
-    for (int64_t p0 = first_block + kRefitUnroll * stride; p0 < end; p0 += kRefitUnroll * stride)
-        refit_group(refit_load(sp, p0, stride, pts, lane), p0, stride, end, hy, dtau, a, o, lane);
-    return a;
-}
-
-// Refit of one cluster by one workgroup of kRefitBlock threads: the kept
-// hypothesis (from its best key), FP64 re-classification of every point under
-// it, least-squares refit on its inliers (Sec. 3.2, Eq. 7, Alg. 2: normal
-// equations A^T A v = A^T v_d, summed per thread and reduced in a fixed tree)
-// and heading atan2(vy, vx) (Eq. 8).
-__device__ __forceinline__ void refit_block(Span sp, ClusterId id, unsigned long long best,
-                                            const Points &pts, float tau, const Outputs &o,
-                                            double (*s_sum)[5], int (*s_cnt)[2]) {
-    const int tid = threadIdx.x;
-    const int wave = tid / kWave;
-    const int lane = tid % kWave;
-    const int64_t k = id.out;
-    if (!sp.ok || sp.n < 2) {
-        if (tid == 0) write_failed(o, k, sp.ok ? RV_CLUSTER_TOO_FEW_POINTS : RV_CLUSTER_BAD_OFFSETS);
-        return;
+// Sum over the wave in the fixed tree of lane distances 32, 16, ..., 1, all sums
+// together, one distance per iteration of a rolled loop (code size: see
+// refit_cluster).
+__device__ __forceinline__ void wave_sum_all(RefitSums &a) {
+#pragma unroll 1
+    for (int o = kWave / 2; o > 0; o >>= 1) {
+        a.scc += __shfl_xor(a.scc, o, kWave);
+        a.scs += __shfl_xor(a.scs, o, kWave);
+        a.sss += __shfl_xor(a.sss, o, kWave);
+        a.scv += __shfl_xor(a.scv, o, kWave);
+        a.ssv += __shfl_xor(a.ssv, o, kWave);
+        a.n_in += __shfl_xor(a.n_in, o, kWave);
+        a.n_near += __shfl_xor(a.n_near, o, kWave);
     }
-    if (best == 0) {
-        if (tid == 0) write_failed(o, k, RV_CLUSTER_ALL_DEGENERATE);
+}
+
+// Refit of one cluster by `waves` waves (1, or all of the workgroup's at most
+// kMaxWaves; `wave` is this one's index among them): the kept hypothesis (from its
+// best key), FP64 re-classification of every point under it, least-squares refit
+// on its inliers (Sec. 3.2, Eq. 7, Alg. 2: normal equations A^T A v = A^T v_d,
+// summed per lane over the wave's 64-point blocks, across the wave in a fixed
+// tree, then over the waves in order) and heading atan2(vy, vx) (Eq. 8).
+//
+// What bounds it on a few clusters is the code: every compute unit that runs it
+// once fetches each of its lines once, at more than a hundred cycles a line.  So
+// the sums and the point loop are rolled and both workgroup shapes share one copy.
+// Wave-uniform branches only around the barrier (it is called from the persistent
+// loop, see batch_score_kernel).
+struct RefitShared {
+    double sum[1024 / kWave][5];
+    int cnt[1024 / kWave][2];
+};
+
+__device__ __forceinline__ void refit_cluster(Span sp, ClusterId id, unsigned long long best,
+                                              const Points &pts, float tau, const Outputs &o,
+                                              int wave, int waves, RefitShared &sh) {
+    const int lane = threadIdx.x % kWave;
+    const int64_t k = id.out;
+    if (!sp.ok || sp.n < 2 || best == 0) {
+        if (wave == 0) {
+            if (lane == 0)
+                write_failed(o, k, !sp.ok ? RV_CLUSTER_BAD_OFFSETS
+                                          : sp.n < 2 ? RV_CLUSTER_TOO_FEW_POINTS
+                                                     : RV_CLUSTER_ALL_DEGENERATE);
+        }
         return;
     }
     // Waves walk 64-aligned global blocks so one wave ballot maps onto two
     // words of the frame-wide bitmask.
-    const int64_t first_block = (sp.lo & ~(int64_t)(kWave - 1)) + (int64_t)wave * kWave;
-    const RefitLoads first = refit_load(sp, first_block, kRefitBlock, pts, lane);
+    const int64_t end = sp.lo + sp.n, stride = (int64_t)waves * kWave;
+    int64_t p0 = (sp.lo & ~(int64_t)(kWave - 1)) + (int64_t)wave * kWave;
+    // Two blocks' loads in flight while the two before them are summed (the first
+    // pair during the solve).
+    RefitLoad a0 = refit_load(sp, p0, pts, lane), a1 = refit_load(sp, p0 + stride, pts, lane);
     const uint32_t hbest = 0xFFFFFFFFu - (uint32_t)(best & 0xFFFFFFFFull);
     const Hypothesis hy = make_hypothesis(pts, sp, hbest, id.local, id.key0, id.key1);
-    const double dtau = tau;
-    const RefitSums a = refit_sweep(sp, first_block, kRefitBlock, first, pts, hy, dtau, o, lane);
-    double scc = a.scc, scs = a.scs, sss = a.sss, scv = a.scv, ssv = a.ssv;
-    int n_in = a.n_in, n_near = a.n_near;
-    scc = wave_sum(scc);
-    scs = wave_sum(scs);
-    sss = wave_sum(sss);
-    scv = wave_sum(scv);
-    ssv = wave_sum(ssv);
-    n_in = wave_sum_i(n_in);
-    n_near = wave_sum_i(n_near);
-    if (lane == 0) {
-        s_sum[wave][0] = scc;
-        s_sum[wave][1] = scs;
-        s_sum[wave][2] = sss;
-        s_sum[wave][3] = scv;
-        s_sum[wave][4] = ssv;
-        s_cnt[wave][0] = n_in;
-        s_cnt[wave][1] = n_near;
+    RefitSums a;
+#pragma unroll 1
+    for (; p0 < end; p0 += 2 * stride) {
+        const RefitLoad b0 = refit_load(sp, p0 + 2 * stride, pts, lane);
+        const RefitLoad b1 = refit_load(sp, p0 + 3 * stride, pts, lane);
+        refit_points(p0, a0.in, a0.p.v, cs64(a0.p), hy, (double)tau, a, o, lane);
+        if (p0 + stride < end)
+            refit_points(p0 + stride, a1.in, a1.p.v, cs64(a1.p), hy, (double)tau, a, o, lane);
+        a0 = b0;
+        a1 = b1;
     }
-    __syncthreads();
-    if (tid != 0) return;
-    scc = s_sum[0][0];
-    scs = s_sum[0][1];
-    sss = s_sum[0][2];
-    scv = s_sum[0][3];
-    ssv = s_sum[0][4];
-    n_in = s_cnt[0][0];
-    n_near = s_cnt[0][1];
-    for (int w = 1; w < kRefitBlock / kWave; ++w) {
-        scc += s_sum[w][0];
-        scs += s_sum[w][1];
-        sss += s_sum[w][2];
-        scv += s_sum[w][3];
-        ssv += s_sum[w][4];
-        n_in += s_cnt[w][0];
-        n_near += s_cnt[w][1];
+    wave_sum_all(a);
+    if (waves > 1) {
+        if (lane == 0) {
+            sh.sum[wave][0] = a.scc;
+            sh.sum[wave][1] = a.scs;
+            sh.sum[wave][2] = a.sss;
+            sh.sum[wave][3] = a.scv;
+            sh.sum[wave][4] = a.ssv;
+            sh.cnt[wave][0] = a.n_in;
+            sh.cnt[wave][1] = a.n_near;
+        }
+        __syncthreads();
+#pragma unroll 1
+        for (int w = 1; w < waves; ++w) {
+            a.scc += sh.sum[w][0];
+            a.scs += sh.sum[w][1];
+            a.sss += sh.sum[w][2];
+            a.scv += sh.sum[w][3];
+            a.ssv += sh.sum[w][4];
+            a.n_in += sh.cnt[w][0];
+            a.n_near += sh.cnt[w][1];
+        }
     }
-    o.n_inliers[k] = n_in;
-    if (o.n_near) o.n_near[k] = n_near;
-    if (o.best) o.best[k] = (int32_t)hbest;
-    const double det = scc * sss - scs * scs;
-    if (n_in < 2 || !(det > 0.0)) {
-        const float qnan = __builtin_nanf("");
-        o.vx[k] = qnan;
-        o.vy[k] = qnan;
-        o.heading[k] = qnan;
-        o.status[k] = RV_CLUSTER_SINGULAR_REFIT;
-        return;
+    if (wave == 0) {
+        if (lane == 0)
+            write_refit(o, k, hbest, a.n_in, a.n_near, a.scc, a.scs, a.sss, a.scv, a.ssv);
     }
-    const double fvx = (sss * scv - scs * ssv) / det;
-    const double fvy = (scc * ssv - scs * scv) / det;
-    o.vx[k] = (float)fvx;
-    o.vy[k] = (float)fvy;
-    o.heading[k] = (float)atan2(fvy, fvx);
-    o.status[k] = RV_CLUSTER_OK;
-}
-
-// Refit of one cluster by one wave: the kept hypothesis (from its best key),
-// FP64 re-classification of every point under it, least-squares refit on its
-// inliers (Sec. 3.2, Eq. 7, Alg. 2: normal equations A^T A v = A^T v_d, summed
-// per lane over the cluster's 64-point blocks and reduced across the wave in a
-// fixed tree) and heading atan2(vy, vx) (Eq. 8).  One wave per cluster keeps
-// small clusters from idling a whole workgroup and needs no barrier.
-__device__ __forceinline__ void refit_wave(Span sp, ClusterId id, unsigned long long best,
-                                           const Points &pts, float tau, const Outputs &o) {
-    const int lane = threadIdx.x % kWave;
-    const int64_t k = id.out;
-    if (!sp.ok || sp.n < 2) {
-        if (lane == 0) write_failed(o, k, sp.ok ? RV_CLUSTER_TOO_FEW_POINTS : RV_CLUSTER_BAD_OFFSETS);
-        return;
-    }
-    if (best == 0) {
-        if (lane == 0) write_failed(o, k, RV_CLUSTER_ALL_DEGENERATE);
-        return;
-    }
-    // 64-aligned global blocks of points, so one ballot maps onto two words of
-    // the frame-wide bitmask.
-    const int64_t first_block = sp.lo & ~(int64_t)(kWave - 1);
-    const RefitLoads first = refit_load(sp, first_block, kWave, pts, lane);
-    const uint32_t hbest = 0xFFFFFFFFu - (uint32_t)(best & 0xFFFFFFFFull);
-    const Hypothesis hy = make_hypothesis(pts, sp, hbest, id.local, id.key0, id.key1);
-    const double dtau = tau;
-    const RefitSums a = refit_sweep(sp, first_block, kWave, first, pts, hy, dtau, o, lane);
-    double scc = a.scc, scs = a.scs, sss = a.sss, scv = a.scv, ssv = a.ssv;
-    int n_in = a.n_in, n_near = a.n_near;
-    scc = wave_sum(scc);
-    scs = wave_sum(scs);
-    sss = wave_sum(sss);
-    scv = wave_sum(scv);
-    ssv = wave_sum(ssv);
-    n_in = wave_sum_i(n_in);
-    n_near = wave_sum_i(n_near);
-    if (lane != 0) return;
-    o.n_inliers[k] = n_in;
-    if (o.n_near) o.n_near[k] = n_near;
-    if (o.best) o.best[k] = (int32_t)hbest;
-    const double det = scc * sss - scs * scs;
-    if (n_in < 2 || !(det > 0.0)) {
-        const float qnan = __builtin_nanf("");
-        o.vx[k] = qnan;
-        o.vy[k] = qnan;
-        o.heading[k] = qnan;
-        o.status[k] = RV_CLUSTER_SINGULAR_REFIT;
-        return;
-    }
-    const double fvx = (sss * scv - scs * ssv) / det;
-    const double fvy = (scc * ssv - scs * scv) / det;
-    o.vx[k] = (float)fvx;
-    o.vy[k] = (float)fvy;
-    o.heading[k] = (float)atan2(fvy, fvx);
-    o.status[k] = RV_CLUSTER_OK;
 }
 
 // ---- single frame ---------------------------------------------------------
 
-// Work item = (cluster, block of 256 hypotheses).  Block i takes the item that
-// keeps clusters in the planned order while all items of one cluster run on the
-// same XCD (blocks are dealt to the 8 XCDs round-robin), sharing that XCD's L2
-// copy of the cluster's points.  Eight waves per SIMD: the scoring loop fits in
-// 64 VGPRs.
+// Work item = (cluster, `rounds` blocks of 256 hypotheses).  Block i takes the
+// item that keeps clusters in the planned order while all items of one cluster
+// run on the same XCD (blocks are dealt to the 8 XCDs round-robin), sharing that
+// XCD's L2 copy of the cluster's points.  Eight waves per SIMD: the scoring loop
+// fits in 64 VGPRs.
 __global__ __launch_bounds__(kScoreBlock) __attribute__((amdgpu_waves_per_eu(8))) void score_kernel(
     const int32_t *__restrict__ off, const int32_t *__restrict__ order, int64_t n_clusters,
-    int64_t n_points, int32_t n_hyp, int32_t blocks_per_cluster, uint32_t key0, uint32_t key1,
-    uint32_t cluster_base, int64_t point_base, int32_t prune_rounds, Points pts, float tau,
+    int64_t n_points, int32_t n_hyp, int32_t rounds, int32_t parts, uint32_t key0, uint32_t key1,
+    uint32_t cluster_base, int64_t point_base, int64_t prune, Points pts, float tau,
     unsigned long long *__restrict__ best_key, int32_t *__restrict__ hyp_counts) {
-    __shared__ ScoreShared s;
+    __shared__ ScoreShared<kScoreBlock> s;
     const uint32_t xcd = blockIdx.x % kXcds;
     const uint32_t r = blockIdx.x / kXcds;
-    const int64_t j = xcd + (int64_t)kXcds * (r / (uint32_t)blocks_per_cluster);
+    const int64_t j = xcd + (int64_t)kXcds * (r / (uint32_t)parts);
     if (j >= n_clusters) return;
-    const int b = (int)(r % (uint32_t)blocks_per_cluster);
     const int64_t k = order != nullptr ? order[j] : j;
     ClusterId id;
     id.out = k;
@@ -1700,51 +1658,36 @@ __global__ __launch_bounds__(kScoreBlock) __attribute__((amdgpu_waves_per_eu(8))
     id.key0 = key0;
     id.key1 = key1;
     const Span sp = cluster_span(off, k, n_points, point_base);
-    if (sp.ok && sp.n >= 2 && sp.n <= kSingleLanesMax) {  // the same for the whole block
-        score_block_lanes(sp, id, b, n_hyp, pts, tau, s.lanes(), best_key, hyp_counts);
-        return;
-    }
-    if (prune_rounds > 0 && sp.n >= prune_min(prune_rounds)) {
-        // One workgroup of each group of prune_rounds works, and which one turns
-        // from cluster to cluster: workgroups go to the compute units in
-        // rotation, so always taking the first would leave most units idle.
-        const int part = b / prune_rounds;
-        const int in_part = blocks_per_cluster - part * prune_rounds < prune_rounds
-                                ? blocks_per_cluster - part * prune_rounds : prune_rounds;
-        const int turn = (int)((r / (uint32_t)blocks_per_cluster) % (uint32_t)in_part);
-        if (b - part * prune_rounds != turn) return;
-        const int64_t first = (int64_t)part * prune_rounds * kScoreBlock;
-        const int64_t left = n_hyp - first;
-        const int most = prune_rounds * kScoreBlock;
-        score_pruned(sp, id, first, left < most ? (int)left : most, pts, tau, s.prune(), best_key);
-        return;
-    }
-    score_block<false>(sp, id, b, n_hyp, pts, tau, kRowsMax, s.rows().hyp, s.rows().key,
-                       s.rows().tail, best_key, hyp_counts);
+    const int most = rounds * kScoreBlock;
+    const int64_t first = (int64_t)(r % (uint32_t)parts) * most;
+    const int64_t left = n_hyp - first;
+    const unsigned long long key = score_hypotheses<kScoreBlock>(
+        sp, id, first, left < most ? (int)left : most, n_hyp, pts, tau, kRowsMax, kSingleLanesMax,
+        prune, s, &best_key[k], hyp_counts);
+    merge_key(&best_key[k], key, __builtin_amdgcn_readfirstlane(threadIdx.x / kWave),
+              threadIdx.x % kWave);
 }
 
 // Refit of a frame's or batch's clusters over their planned (largest-first)
 // positions, in one launch: workgroups [0, n_big) take the first n_big
 // clusters (size class >= kRefitBigClass, i.e. >= 1024 points), one each with
-// all four waves (refit_block); the following workgroups take the other
-// clusters four at a time, one per wave (refit_wave).  n_big is counted on the
+// all four waves; the following workgroups take the other
+// clusters four at a time, one per wave.  n_big is counted on the
 // device by the ordering pass; without an order (n_big == nullptr) every
 // cluster gets a workgroup.  The grid is an upper bound (one workgroup per
 // cluster); surplus workgroups exit at once.
 template <typename ClusterAt>
 __device__ __forceinline__ void refit_planned(int64_t n_clusters, const int64_t *n_big,
                                               const ClusterAt &at, const Points &pts, float tau,
-                                              const Outputs &o, double (*s_sum)[5],
-                                              int (*s_cnt)[2]) {
+                                              const Outputs &o, RefitShared &sh) {
     const int64_t b = blockIdx.x;
     const int64_t big = n_big != nullptr ? *n_big : n_clusters;
-    if (b < big) {
-        refit_block(at.span(b), at.id(b), at.best(b), pts, tau, o, s_sum, s_cnt);
-        return;
-    }
-    const int64_t j = big + (b - big) * kRefitWaves + threadIdx.x / kWave;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const bool all = b < big;  // the whole workgroup on one cluster
+    const int64_t j = all ? b : big + (b - big) * kRefitWaves + wave;
     if (j >= n_clusters) return;
-    refit_wave(at.span(j), at.id(j), at.best(j), pts, tau, o);
+    refit_cluster(at.span(j), at.id(j), at.best(j), pts, tau, o, all ? wave : 0,
+                  all ? kRefitWaves : 1, sh);
 }
 
 // Cluster at planned position j of a single frame.
@@ -1774,11 +1717,10 @@ __global__ __launch_bounds__(kRefitBlock) void refit_kernel(
     const int64_t *__restrict__ n_big, int64_t n_points, uint32_t key0, uint32_t key1,
     uint32_t cluster_base, int64_t point_base, Points pts,
     const unsigned long long *__restrict__ best_key, float tau, Outputs o) {
-    __shared__ double s_sum[kRefitBlock / kWave][5];
-    __shared__ int s_cnt[kRefitBlock / kWave][2];
+    __shared__ RefitShared s_refit;
     const FrameClusterAt at = {off, order, n_points, key0, key1, cluster_base, point_base,
                                best_key};
-    refit_planned(n_clusters, n_big, at, pts, tau, o, s_sum, s_cnt);
+    refit_planned(n_clusters, n_big, at, pts, tau, o, s_refit);
 }
 
 // ---- many frames in one launch sequence ----------------------------------
@@ -1794,49 +1736,36 @@ __global__ __launch_bounds__(kRefitBlock) void refit_kernel(
 // and no counter is hammered by the whole chip; a workgroup whose queue is
 // empty takes items from the others.
 
-// Small frames (see use_small_frame_path): one workgroup per cluster stages the
-// cluster's own points, scores its hypotheses (at most 256: one block), keeps
-// the best and refits, in a single launch.  The arithmetic is the three-kernel
-// path's, so every output is bitwise the same; these frames are bound by
-// launch latency, and one launch replaces three.  A workgroup reads back only
-// points it staged itself, after a workgroup barrier (its waves share the
-// compute unit's L1, which its own stores keep current).
-__global__ __launch_bounds__(kScoreBlock) __attribute__((amdgpu_waves_per_eu(8))) void small_frame_kernel(
+// Small frames (see use_cluster_path): one workgroup per cluster stages the
+// cluster's own points, scores its hypotheses (at most 256) and refits, in a
+// single launch.  The arithmetic is the three-kernel path's, so every output is
+// the same; these frames are bound by launch latency, and one launch replaces
+// three.  A workgroup reads back only points it staged itself, after a workgroup
+// barrier (its waves share the compute unit's L1, which its own stores keep
+// current; the staged points are written and read through one pointer, so no read
+// of them goes through the scalar cache).
+__global__ __launch_bounds__(kScoreBlock) __attribute__((amdgpu_waves_per_eu(8))) void cluster_kernel(
     const float *__restrict__ theta, const float *__restrict__ vd, const int32_t *__restrict__ off,
     int64_t n_points, int32_t n_hyp, uint32_t key0, uint32_t key1, uint32_t cluster_base,
-    int64_t point_base, int32_t prune, Points pts, float tau,
-    StagedPoint *__restrict__ staged, unsigned long long *__restrict__ best_key, Outputs o) {
-    __shared__ ScoreShared s;
-    __shared__ double s_sum[kRefitBlock / kWave][5];
-    __shared__ int s_cnt[kRefitBlock / kWave][2];
+    int64_t point_base, int64_t prune, float tau, StagedPoint *staged, Outputs o) {
+    const Points pts = {staged, theta};
+    __shared__ ScoreShared<kScoreBlock> s;
+    __shared__ RefitShared s_refit;
     const int64_t k = blockIdx.x;
     const Span sp = cluster_span(off, k, n_points, point_base);
     for (int64_t p = sp.lo + threadIdx.x; p < sp.lo + sp.n; p += kScoreBlock)
         stage_point(theta, vd, p, staged);
-    if (threadIdx.x == 0) best_key[k] = 0;
     __syncthreads();
     ClusterId id;
     id.out = k;
     id.local = cluster_base + (uint32_t)k;
     id.key0 = key0;
     id.key1 = key1;
-    // The workgroup's own block key is the cluster's best (one block per
-    // cluster); the per-wave keys are still in LDS after the scoring's barrier.
-    const bool lanes = sp.ok && sp.n >= 2 && sp.n <= kSingleLanesMax;  // block-uniform
-    unsigned long long best = 0;
-    if (prune > 0 && sp.n >= prune_min(prune)) {
-        score_pruned(sp, id, 0, n_hyp, pts, tau, s.prune(), best_key, &best);
-    } else {
-        if (lanes)
-            score_block_lanes(sp, id, 0, n_hyp, pts, tau, s.lanes(), best_key, o.hyp_counts);
-        else
-            score_block<false>(sp, id, 0, n_hyp, pts, tau, kRowsMax, s.rows().hyp, s.rows().key,
-                               s.rows().tail, best_key, o.hyp_counts);
-        const unsigned long long *keys = lanes ? s.lanes().key : s.rows().key;
-#pragma unroll
-        for (int w = 0; w < kScoreBlock / kWave; ++w) best = keys[w] > best ? keys[w] : best;
-    }
-    refit_block(sp, id, uniform_u64(best), pts, tau, o, s_sum, s_cnt);
+    const unsigned long long best =
+        score_hypotheses<kScoreBlock>(sp, id, 0, n_hyp, n_hyp, pts, tau, kRowsMax, kSingleLanesMax,
+                                      prune, s, nullptr, o.hyp_counts);
+    refit_cluster(sp, id, best, pts, tau, o, __builtin_amdgcn_readfirstlane(threadIdx.x / kWave),
+                  kScoreBlock / kWave, s_refit);
 }
 
 struct Batch {
@@ -1851,7 +1780,7 @@ struct Tuning {
     int32_t rows[RV_TUNE_BUCKETS];
     int32_t fp16_min;   // clusters of at least this many points use the FP16 form; 0: none
     int32_t lanes_max;  // clusters of at most this many points score with lanes = hypotheses
-    int32_t prune_rounds;  // see prune_rounds(); 0: every hypothesis is counted
+    int64_t prune;      // clusters of at least this many points count only possible winners
 };
 
 // Scoring form of a cluster (ItemDesc::form).
@@ -1908,6 +1837,43 @@ __device__ __forceinline__ ClusterId desc_id(const ItemDesc &d) {
     id.key0 = d.key0;
     id.key1 = d.key1;
     return id;
+}
+
+__device__ __forceinline__ int desc_lanes(const ItemDesc &d) {
+    return d.form == kFormLanes ? kLaneTile : 0;
+}
+
+__device__ __forceinline__ int64_t desc_prune(const ItemDesc &d) {
+    return d.form == kFormPruned ? 0 : INT64_MAX;
+}
+
+// Runs body(cluster position, part) for every item this workgroup takes from the
+// queues: cluster j of the dispatch order belongs to queue j % 8, `parts` items
+// each; a workgroup serves its home queue first, then the others.  The body is
+// called by the whole workgroup and may hold barriers (see batch_score_kernel).
+template <typename Body>
+__device__ __forceinline__ void for_each_item(unsigned long long *__restrict__ queues,
+                                              int64_t n_clusters, int32_t parts, uint32_t home,
+                                              int wave, int lane, unsigned long long &s_item,
+                                              const Body &body) {
+    for (uint32_t step = 0; step < kXcds; ++step) {
+        const uint32_t q = (home + step) % kXcds;
+        const int64_t clusters_q = n_clusters > (int64_t)q ? (n_clusters - q + kXcds - 1) / kXcds : 0;
+        const unsigned long long total = (unsigned long long)clusters_q * (uint64_t)parts;
+        for (;;) {
+            if (wave == 0) {
+                unsigned long long got = 0;
+                if (lane == 0) got = atomicAdd(&queues[q * kQueueStride], 1ull);
+                s_item = uniform_u64(got);  // the same value from every lane of wave 0
+            }
+            __syncthreads();
+            const unsigned long long item = uniform_u64(s_item);
+            __syncthreads();
+            if (item >= total) break;
+            const unsigned long long at = item / (uint64_t)parts;
+            body((int64_t)q + (int64_t)kXcds * (int64_t)at, (int)(item - at * (uint64_t)parts));
+        }
+    }
 }
 
 // Clears the size-class histogram and the work queues.
@@ -1995,7 +1961,7 @@ __global__ __launch_bounds__(kPrepBlock) void batch_scatter_kernel(
         d.form = kFormLanes;
     else if (tune.fp16_min > 0 && sp.ok && sp.n >= 2 && sp.n >= tune.fp16_min)
         d.form = kFormFp16;
-    else if (tune.prune_rounds > 0 && sp.n >= prune_min(tune.prune_rounds))
+    else if (sp.n >= tune.prune)
         d.form = kFormPruned;
     desc[base[cls] + rank] = d;
 }
@@ -2014,57 +1980,35 @@ __global__ __launch_bounds__(kPrepBlock) void batch_scatter_kernel(
 template <bool kFp16>
 __global__ __launch_bounds__(kScoreBlock) __attribute__((amdgpu_waves_per_eu(kFp16 ? 7 : 8))) void batch_score_kernel(
     const ItemDesc *__restrict__ desc, int64_t n_clusters, int32_t n_hyp,
-    int32_t blocks_per_cluster, int32_t prune_rounds, Points pts, float tau,
-    unsigned long long *__restrict__ queues,
+    int32_t rounds, int32_t parts, Points pts, float tau, unsigned long long *__restrict__ queues,
     unsigned long long *__restrict__ best_key, int32_t *__restrict__ hyp_counts) {
-    __shared__ ScoreShared s;
+    __shared__ ScoreShared<kScoreBlock> s;
     __shared__ unsigned long long s_item;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int lane = threadIdx.x % kWave;
     const uint32_t home = blockIdx.x % kXcds;
-    const uint64_t bpc = (uint64_t)blocks_per_cluster;
-    for (uint32_t step = 0; step < kXcds; ++step) {
-        const uint32_t q = (home + step) % kXcds;
-        const int64_t clusters_q = n_clusters > (int64_t)q ? (n_clusters - q + kXcds - 1) / kXcds : 0;
-        const unsigned long long total = (unsigned long long)clusters_q * bpc;
-        for (;;) {
-            if (wave == 0) {
-                unsigned long long got = 0;
-                if (lane == 0) got = atomicAdd(&queues[q * kQueueStride], 1ull);
-                s_item = uniform_u64(got);  // the same value from every lane of wave 0
-            }
-            __syncthreads();
-            const unsigned long long item = uniform_u64(s_item);
-            __syncthreads();
-            if (item >= total) break;
-            const int64_t j = (int64_t)q + (int64_t)kXcds * (int64_t)(item / bpc);
-            const int b = (int)(item % bpc);
-            const ItemDesc d = desc[j];
-            if (d.form == kFormLanes) {
-                score_block_lanes(desc_span(d), desc_id(d), b, n_hyp, pts, tau, s.lanes(), best_key,
-                                  hyp_counts);
-                continue;
-            }
-            if (d.form == kFormPruned) {
-                if (b % prune_rounds != 0) continue;
-                const int64_t first = (int64_t)b * kScoreBlock;
-                const int64_t left = n_hyp - first;
-                const int most = prune_rounds * kScoreBlock;
-                score_pruned(desc_span(d), desc_id(d), first, left < most ? (int)left : most, pts,
-                             tau, s.prune(), best_key);
-                continue;
-            }
-            if constexpr (kFp16) {
-                if (d.form == kFormFp16) {
+    for_each_item(queues, n_clusters, parts, home, wave, lane, s_item, [&](int64_t j, int part) {
+        const ItemDesc d = desc[j];
+        const int most = rounds * kScoreBlock;
+        const int64_t first = (int64_t)part * most;
+        const int64_t left = n_hyp - first;
+        const int nh = left < most ? (int)left : most;
+        if constexpr (kFp16) {
+            if (d.form == kFormFp16) {
+                const int b0 = part * rounds;
+                for (int b = b0; b < b0 + (nh + kScoreBlock - 1) / kScoreBlock; ++b) {
                     score_block_fp16(desc_span(d), desc_id(d), b, n_hyp, pts, tau, d.rows, s.fp16(),
                                      best_key, hyp_counts);
-                    continue;
+                    __syncthreads();
                 }
+                return;
             }
-            score_block<true>(desc_span(d), desc_id(d), b, n_hyp, pts, tau, d.rows, s.rows().hyp,
-                              s.rows().key, s.rows().tail, best_key, hyp_counts);
         }
-    }
+        const unsigned long long key = score_hypotheses<kScoreBlock>(
+            desc_span(d), desc_id(d), first, nh, n_hyp, pts, tau, d.rows, desc_lanes(d),
+            desc_prune(d), s, &best_key[d.out], hyp_counts);
+        merge_key(&best_key[d.out], key, wave, lane);
+    });
 }
 
 // Cluster at dispatch position j of a batch (its descriptor).
@@ -2079,10 +2023,9 @@ struct BatchClusterAt {
 __global__ __launch_bounds__(kRefitBlock) void batch_refit_kernel(
     const ItemDesc *__restrict__ desc, int64_t n_clusters, const int64_t *__restrict__ n_big,
     Points pts, const unsigned long long *__restrict__ best_key, float tau, Outputs o) {
-    __shared__ double s_sum[kRefitBlock / kWave][5];
-    __shared__ int s_cnt[kRefitBlock / kWave][2];
+    __shared__ RefitShared s_refit;
     const BatchClusterAt at = {desc, best_key};
-    refit_planned(n_clusters, n_big, at, pts, tau, o, s_sum, s_cnt);
+    refit_planned(n_clusters, n_big, at, pts, tau, o, s_refit);
 }
 
 __global__ __launch_bounds__(kPrepBlock) void philox_kernel(const uint32_t *__restrict__ ctr,
@@ -2116,7 +2059,6 @@ using rv_internal::take_timed_call;
 using rv_internal::TimedCall;
 
 constexpr size_t kAlign = 256;
-
 size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
 struct Layout {
@@ -2205,9 +2147,7 @@ int check_batch(const BatchArgs &a) {
     return RV_OK;
 }
 
-int64_t batch_blocks_per_cluster(const BatchArgs &a) {
-    return ((int64_t)a.n_hyp + kScoreBlock - 1) / kScoreBlock;
-}
+int64_t blocks_of(int32_t n_hyp) { return ((int64_t)n_hyp + kScoreBlock - 1) / kScoreBlock; }
 
 // Compute units of the current device, queried once per device (a launch that
 // is being captured into a graph only reads the cache, filled by the caller's
@@ -2223,21 +2163,48 @@ int device_cus() {
     return cus;
 }
 
-// Hypotheses of a large cluster per scoring workgroup, in blocks of 256
-// (score_pruned), or 0 for the full count: when the caller asks for every
-// hypothesis's count, or tau is so extreme that the residual bins' scale leaves
-// the normal range.  As many as leave 2048 workgroups (eight per compute unit):
-// scoring stage with 1, 2 and 4 at 1024 hypotheses: 4096 mixed clusters 116, 88
-// and 83 us; 1024 clusters of 2048 points 68, 55 and 68 us; 512 of 4096 points
-// 56, 66 and 90 us.
-int32_t prune_rounds(int64_t n_clusters, int64_t blocks_per_cluster, float tau,
-                     const int32_t *hyp_counts) {
-    if (hyp_counts != nullptr || !(tau > 1e-15f) || !(tau < 1e15f)) return 0;
+// Hypotheses per scoring workgroup, in blocks of 256 (at most kPruneHyp).  A
+// large cluster's table is made once per workgroup, so as many as leave 2048
+// workgroups (eight per compute unit): scoring stage with 1, 2 and 4 at 1024
+// hypotheses: 4096 mixed clusters 116, 88 and 83 us; 1024 clusters of 2048 points
+// 68, 55 and 68 us; 512 of 4096 points 56, 66 and 90 us.
+int32_t score_rounds(int64_t n_clusters, int64_t blocks_per_cluster) {
     int32_t rounds = 1;
-    while (rounds < kPruneRounds && rounds < blocks_per_cluster &&
+    while (rounds < kPruneHyp / kScoreBlock && rounds < blocks_per_cluster &&
            n_clusters * ((blocks_per_cluster + 2 * rounds - 1) / (2 * rounds)) >= 2048)
         rounds *= 2;
     return rounds;
+}
+
+// Smallest cluster that counts only possible winners: none when the caller asks
+// for every hypothesis's count, or tau is so extreme that the residual bins'
+// scale leaves the normal range.
+int64_t prune_from(int32_t rounds, float tau, const int32_t *hyp_counts) {
+    if (hyp_counts != nullptr || !(tau > 1e-15f) || !(tau < 1e15f)) return INT64_MAX;
+    return prune_min(rounds);
+}
+
+// Frames small enough that launch latency dominates take one launch
+// (cluster_kernel): at most 256 hypotheses, at most 65,536 points (each workgroup
+// stages its own cluster) and no frame-wide inlier mask (its words are shared by
+// neighbouring clusters and are cleared by the staging kernel).
+constexpr int64_t kSmallFrameMaxPoints = 1 << 16;
+constexpr int64_t kSmallFrameMaxClusters = 1 << 16;
+
+bool use_cluster_path(int64_t n_clusters, int64_t n_points, int32_t n_hyp,
+                      const uint32_t *inlier_bits) {
+    return inlier_bits == nullptr && n_hyp <= kScoreBlock && n_points <= kSmallFrameMaxPoints &&
+           n_clusters <= kSmallFrameMaxClusters;
+}
+
+int32_t batch_rounds(const BatchArgs &a) {
+    return score_rounds(a.n_clusters, blocks_of(a.n_hyp));
+}
+
+// Work items per cluster.
+int32_t batch_parts(const BatchArgs &a) {
+    const int32_t rounds = batch_rounds(a);
+    return (int32_t)((blocks_of(a.n_hyp) + rounds - 1) / rounds);
 }
 
 // The refit kernel over planned positions; n_big (device, nullable) is the
@@ -2257,16 +2224,21 @@ void launch_refit(bool batch, const int32_t *off, const int32_t *order, const It
 }
 
 // Persistent grid of the batched scoring kernel on the current device.
-int persistent_blocks(int blocks_per_cu, bool fp16, int64_t items, unsigned *grid) {
+int persistent_blocks(const BatchArgs &a, unsigned *grid) {
+    *grid = 1;
+    if (a.n_clusters == 0) return RV_OK;
     int fit = 0;
     const int cus = device_cus();
     const hipError_t e =
-        fp16 ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&fit, batch_score_kernel<true>, kScoreBlock, 0)
-             : hipOccupancyMaxActiveBlocksPerMultiprocessor(&fit, batch_score_kernel<false>, kScoreBlock, 0);
+        a.tuning.fp16_min_points > 0
+            ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&fit, batch_score_kernel<true>, kScoreBlock, 0)
+            : hipOccupancyMaxActiveBlocksPerMultiprocessor(&fit, batch_score_kernel<false>, kScoreBlock, 0);
     if (cus <= 0 || e != hipSuccess)
         return fail(RV_ERR_HIP, "device query failed");
-    int per_cu = blocks_per_cu > 0 && blocks_per_cu < fit ? blocks_per_cu : fit;
+    const int asked = a.tuning.blocks_per_cu;
+    int per_cu = asked > 0 && asked < fit ? asked : fit;
     if (per_cu < 1) per_cu = 1;
+    const int64_t items = a.n_clusters * batch_parts(a);
     int64_t g = (int64_t)cus * per_cu;
     if (g > items) g = items;
     *grid = (unsigned)(g > 0 ? g : 1);
@@ -2296,9 +2268,8 @@ int launch_batch(const BatchArgs &a, unsigned grid, hipStream_t st, bool allow_t
     for (int b = 0; b < RV_TUNE_BUCKETS; ++b) tune.rows[b] = a.tuning.rows_max[b];
     tune.fp16_min = a.tuning.fp16_min_points;
     tune.lanes_max = a.tuning.lanes_max_points;
-    const int64_t bpc = batch_blocks_per_cluster(a);
-    const int32_t rounds = prune_rounds(a.n_clusters, bpc, a.tau, a.o.hyp_counts);
-    tune.prune_rounds = rounds;
+    const int32_t rounds = batch_rounds(a), parts = batch_parts(a);
+    tune.prune = prune_from(rounds, a.tau, a.o.hyp_counts);
     const int64_t n_words = a.o.bits != nullptr ? (a.n_points + 31) / 32 : 0;
     int64_t prep_items = a.n_points > n_words ? a.n_points : n_words;
     prep_items = prep_items > a.n_clusters ? prep_items : a.n_clusters;
@@ -2317,15 +2288,15 @@ int launch_batch(const BatchArgs &a, unsigned grid, hipStream_t st, bool allow_t
     if (timed) (void)hipEventRecord(tc.ev[1], st);
     if (a.tuning.fp16_min_points > 0)
         hipLaunchKernelGGL(batch_score_kernel<true>, dim3(grid), dim3(kScoreBlock), 0, st,
-                           (const ItemDesc *)desc, a.n_clusters, a.n_hyp, (int32_t)bpc, rounds, pts, a.tau,
-                           queues, best_key, a.o.hyp_counts);
+                           (const ItemDesc *)desc, a.n_clusters, a.n_hyp, rounds, parts, pts,
+                           a.tau, queues, best_key, a.o.hyp_counts);
     else
         hipLaunchKernelGGL(batch_score_kernel<false>, dim3(grid), dim3(kScoreBlock), 0, st,
-                           (const ItemDesc *)desc, a.n_clusters, a.n_hyp, (int32_t)bpc, rounds, pts, a.tau,
-                           queues, best_key, a.o.hyp_counts);
+                           (const ItemDesc *)desc, a.n_clusters, a.n_hyp, rounds, parts, pts,
+                           a.tau, queues, best_key, a.o.hyp_counts);
     if (timed) (void)hipEventRecord(tc.ev[2], st);
-    launch_refit(true, nullptr, nullptr, (const ItemDesc *)desc, a.n_clusters, n_big, a.n_points,
-                 0, 0, 0, 0, pts, best_key, a.tau, a.o, st);
+    launch_refit(true, nullptr, nullptr, (const ItemDesc *)desc, a.n_clusters, n_big,
+                 a.n_points, 0, 0, 0, 0, pts, best_key, a.tau, a.o, st);
     if (timed) {
         (void)hipEventRecord(tc.ev[3], st);
         keep_timed_call(tc);
@@ -2333,20 +2304,6 @@ int launch_batch(const BatchArgs &a, unsigned grid, hipStream_t st, bool allow_t
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail(RV_ERR_HIP, "kernel launch failed: %s", hipGetErrorString(e));
     return RV_OK;
-}
-
-// Frames small enough that launch latency dominates take the one-launch path
-// (small_frame_kernel): at most 256 hypotheses (one scoring block per cluster,
-// as on the three-kernel path), at most 65,536 points (each workgroup stages
-// its own cluster) and no frame-wide inlier mask (its words are shared by
-// neighbouring clusters and are cleared by the staging kernel).
-constexpr int64_t kSmallFrameMaxPoints = 1 << 16;
-constexpr int64_t kSmallFrameMaxClusters = 1 << 16;
-
-bool use_small_frame_path(int64_t n_clusters, int64_t n_points, int32_t n_hyp,
-                          const uint32_t *inlier_bits) {
-    return inlier_bits == nullptr && n_hyp <= kScoreBlock && n_points <= kSmallFrameMaxPoints &&
-           n_clusters <= kSmallFrameMaxClusters;
 }
 
 BatchArgs make_batch_args(const float *theta, const float *vd, const int32_t *cluster_offsets,
@@ -2410,7 +2367,7 @@ int estimate_frame(const float *theta, const float *vd, const int32_t *cluster_o
         (vx == nullptr || vy == nullptr || heading == nullptr || n_inliers == nullptr ||
          status == nullptr))
         return fail(RV_ERR_INVALID_ARG, "a required output is NULL");
-    const int64_t blocks_per_cluster = ((int64_t)n_hyp + kScoreBlock - 1) / kScoreBlock;
+    const int64_t blocks_per_cluster = blocks_of(n_hyp);
     const int64_t clusters_xcd = (n_clusters + kXcds - 1) / kXcds * kXcds;
     if (clusters_xcd > (int64_t)INT32_MAX / blocks_per_cluster)
         return fail(RV_ERR_INVALID_ARG, "n_clusters * ceil(n_hyp / 256) exceeds 2^31 - 1");
@@ -2448,13 +2405,12 @@ int estimate_frame(const float *theta, const float *vd, const int32_t *cluster_o
     TimedCall tc;
     const bool timed = allow_timing && take_timed_call(tc);
     if (timed) (void)hipEventRecord(tc.ev[0], st);
-    if (use_small_frame_path(n_clusters, n_points, n_hyp, inlier_bits)) {
+    if (use_cluster_path(n_clusters, n_points, n_hyp, inlier_bits)) {
         // One launch; its time counts as the scoring stage.
         if (timed) (void)hipEventRecord(tc.ev[1], st);
-        hipLaunchKernelGGL(small_frame_kernel, dim3((unsigned)n_clusters), dim3(kScoreBlock), 0, st,
+        hipLaunchKernelGGL(cluster_kernel, dim3((unsigned)n_clusters), dim3(kScoreBlock), 0, st,
                            theta, vd, cluster_offsets, n_points, n_hyp, key0, key1, first_cluster,
-                           first_point, prune_rounds(n_clusters, 1, tau, hyp_counts), pts, tau,
-                           staged, best_key, o);
+                           first_point, prune_from(1, tau, hyp_counts), tau, staged, o);
         if (timed) {
             (void)hipEventRecord(tc.ev[2], st);
             (void)hipEventRecord(tc.ev[3], st);
@@ -2464,6 +2420,8 @@ int estimate_frame(const float *theta, const float *vd, const int32_t *cluster_o
         if (e != hipSuccess) return fail(RV_ERR_HIP, "kernel launch failed: %s", hipGetErrorString(e));
         return RV_OK;
     }
+    const int32_t rounds = score_rounds(n_clusters, blocks_per_cluster);
+    const int64_t parts = (blocks_per_cluster + rounds - 1) / rounds;
     int64_t prep_items = n_points > n_words ? n_points : n_words;
     prep_items = prep_items > n_clusters ? prep_items : n_clusters;
     const int64_t prep_blocks = (prep_items + kPrepBlock - 1) / kPrepBlock + 1;  // + planner
@@ -2471,12 +2429,10 @@ int estimate_frame(const float *theta, const float *vd, const int32_t *cluster_o
                        vd, n_points, staged, inlier_bits, n_words, cluster_offsets,
                        first_point, n_clusters, order, n_big, best_key);
     if (timed) (void)hipEventRecord(tc.ev[1], st);
-    hipLaunchKernelGGL(score_kernel, dim3((unsigned)(clusters_xcd * blocks_per_cluster)),
-                       dim3(kScoreBlock), 0, st, cluster_offsets, (const int32_t *)order,
-                       n_clusters, n_points, n_hyp, (int32_t)blocks_per_cluster, key0, key1,
-                       first_cluster, first_point,
-                       prune_rounds(n_clusters, blocks_per_cluster, tau, hyp_counts), pts, tau,
-                       best_key, hyp_counts);
+    hipLaunchKernelGGL(score_kernel, dim3((unsigned)(clusters_xcd * parts)), dim3(kScoreBlock), 0,
+                       st, cluster_offsets, (const int32_t *)order, n_clusters, n_points, n_hyp,
+                       rounds, (int32_t)parts, key0, key1, first_cluster, first_point,
+                       prune_from(rounds, tau, hyp_counts), pts, tau, best_key, hyp_counts);
     if (timed) (void)hipEventRecord(tc.ev[2], st);
     launch_refit(false, cluster_offsets, order, nullptr, n_clusters,
                  order != nullptr ? (const int64_t *)n_big : nullptr, n_points, key0, key1,
@@ -2848,10 +2804,7 @@ int rv_estimate_velocity_batch(const float *theta, const float *vd, const int32_
                                         hyp_counts, best_hyp, tuning, workspace, workspace_bytes);
     if (int rc = check_batch(a)) return rc;
     unsigned grid = 1;
-    if (a.n_clusters > 0)
-        if (int rc = persistent_blocks(a.tuning.blocks_per_cu, a.tuning.fp16_min_points > 0,
-                                     a.n_clusters * batch_blocks_per_cluster(a), &grid))
-            return rc;
+    if (int rc = persistent_blocks(a, &grid)) return rc;
     return launch_batch(a, grid, (hipStream_t)stream, true);
 }
 
@@ -2876,10 +2829,7 @@ int rv_graph_capture_batch(const float *theta, const float *vd, const int32_t *c
                                         hyp_counts, best_hyp, tuning, workspace, workspace_bytes);
     if (int rc = check_batch(a)) return rc;
     unsigned grid = 1;
-    if (a.n_clusters > 0)
-        if (int rc = persistent_blocks(a.tuning.blocks_per_cu, a.tuning.fp16_min_points > 0,
-                                     a.n_clusters * batch_blocks_per_cluster(a), &grid))
-            return rc;
+    if (int rc = persistent_blocks(a, &grid)) return rc;
     hipStream_t cap = nullptr;
     if (hipStreamCreateWithFlags(&cap, hipStreamNonBlocking) != hipSuccess)
         return fail(RV_ERR_HIP, "hipStreamCreate failed");

@@ -69,6 +69,48 @@ __device__ __forceinline__ unsigned long long uniform_u64(unsigned long long v) 
     return ((unsigned long long)hi << 32) | lo;
 }
 
+// One step of a reduction towards lane 63: the value kCtrl lanes below within the
+// row (row_shr 0x111, 0x112, 0x114, 0x118) or the last lane of the row below
+// (row_bcast 0x142, 0x143) in the rows of kRows, `none` where there is none.
+template <int kCtrl, int kRows>
+__device__ __forceinline__ uint32_t dpp_from(uint32_t v, uint32_t none) {
+    return (uint32_t)__builtin_amdgcn_update_dpp((int)none, (int)v, kCtrl, kRows, 0xF, false);
+}
+
+// Maximum over the wave, the same in every lane (data-parallel moves: a tenth of
+// the latency of six lane shuffles through LDS).  Every lane active.
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
+    uint32_t w = v;
+#define RV_STEP(ctrl, rows)                              \
+    {                                                    \
+        const uint32_t x = dpp_from<ctrl, rows>(w, 0u);  \
+        w = x > w ? x : w;                               \
+    }
+    RV_STEP(0x111, 0xF) RV_STEP(0x112, 0xF) RV_STEP(0x114, 0xF) RV_STEP(0x118, 0xF)
+    RV_STEP(0x142, 0xA) RV_STEP(0x143, 0xC)
+#undef RV_STEP
+    return (uint32_t)__builtin_amdgcn_readlane((int)w, kWave - 1);
+}
+
+// Bit pattern of a float as an unsigned integer in the same order.
+__device__ __forceinline__ uint32_t ordered_bits(float v) {
+    const uint32_t u = __builtin_bit_cast(uint32_t, v);
+    return u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u);
+}
+
+__device__ __forceinline__ float from_ordered(uint32_t u) {
+    return __builtin_bit_cast(float, u ^ ((uint32_t)((int32_t)~u >> 31) | 0x80000000u));
+}
+
+// Largest and smallest value over the wave (no NaN), the same in every lane.
+__device__ __forceinline__ float wave_max_f(float v) {
+    return from_ordered(wave_max_u32(ordered_bits(v)));
+}
+
+__device__ __forceinline__ float wave_min_f(float v) {
+    return from_ordered(~wave_max_u32(~ordered_bits(v)));
+}
+
 __device__ __forceinline__ uint64_t wave_max_u64(uint64_t v) {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
