@@ -873,6 +873,29 @@ __device__ __forceinline__ uint32_t exact_counts(Span sp, const Points &pts, flo
     return total;
 }
 
+// exact_counts in the FP16 form: upper bounds of the counts of the nl hypotheses
+// in `list` (fp16_hypothesis pairs against (rx, ry)).
+template <int B>
+__device__ __forceinline__ uint32_t fp16_counts(Span sp, const Points &pts, int nl,
+                                                const float4 *list, uint32_t (*part_sums)[kWave],
+                                                int wave, int lane, float rx, float ry) {
+    const int64_t rows = (sp.n + kWave - 1) / kWave;
+    const int64_t r0 = rows * wave / (B / kWave);
+    const int64_t r1 = rows * (wave + 1) / (B / kWave);
+    const int64_t p1 = r1 * kWave < sp.n ? r1 * kWave : sp.n;
+    Span part;
+    part.lo = sp.lo + r0 * kWave;
+    part.n = p1 - r0 * kWave;
+    part.ok = true;
+    part_sums[wave][lane] = score_cluster_fp16(pts, part, lane, list, nl, kExactRows, rx, ry);
+    __syncthreads();
+    uint32_t total = 0;
+#pragma unroll
+    for (int w = 0; w < B / kWave; ++w) total += part_sums[w][lane];
+    __syncthreads();
+    return total;
+}
+
 // ---------------------------------------------------------------------------
 // Large clusters: counting only the hypotheses that can still win.
 //
@@ -944,6 +967,8 @@ struct PruneShared {
             uint32_t part[B / kWave][kWave];
             float list[2 * kWave] __attribute__((aligned(16)));
             uint16_t idx[kPruneHyp];
+            float half_list[2 * kWave] __attribute__((aligned(16)));  // FP16 form
+            uint16_t kept[kWave];
         } count;
     } u;
     unsigned long long key[B / kWave];
@@ -996,7 +1021,10 @@ __device__ __forceinline__ float uniform_f(float v) {
 // nullptr: none) beats them all, some key not above it.  Called by all threads
 // of the block, also from the persistent loop: every branch around a barrier is
 // on a wave-uniform value.
-template <int B>
+// kHalf: the remaining hypotheses are first counted in the FP16 residual form (see
+// below; r as its reference velocity), 64 at a time, and only those whose upper
+// count still reaches the best key are counted in float32.
+template <int B, bool kHalf = false>
 __device__ __forceinline__ unsigned long long score_pruned(
     Span sp, ClusterId id, int64_t h_first, int nh, const Points &pts, float tau,
     PruneShared<B> &sh, const unsigned long long *best_key) {
@@ -1086,10 +1114,12 @@ __device__ __forceinline__ unsigned long long score_pruned(
 
     unsigned long long best = 0;  // best known (count, hypothesis) key, the same in every lane
     uint32_t ub[kPruneRounds];
+    float rx = 0.0f, ry = 0.0f;
     if (ref != 0) {
         // 2. Table of the points under r.
         const uint32_t r_local = 0xFFFFFFFFu - (uint32_t)ref;
-        const float rx = uniform_f(hyp[r_local].x), ry = uniform_f(hyp[r_local].y);
+        rx = uniform_f(hyp[r_local].x);
+        ry = uniform_f(hyp[r_local].y);
         const float sigma = uniform_f(residual_scale(tau));
         const float scale = 1.0f / width;
         uint32_t t = 0;
@@ -1215,11 +1245,37 @@ __device__ __forceinline__ unsigned long long score_pruned(
     bool tops = true;
     while (nl > 0) {
         __syncthreads();
-        const uint32_t cnt = exact_counts<B>(sp, pts, tau, nl,
-                                          reinterpret_cast<const float4 *>(sh.u.count.list),
-                                          sh.u.count.part, wave, lane);
         uint32_t h = 0;
         if (lane < nl) h = tops ? sh.top[lane] : sh.u.count.idx[c0 - kWave + lane];
+        if constexpr (kHalf) {
+            if (!tops) {
+                const float2 own = reinterpret_cast<const float2 *>(sh.u.count.list)[lane];
+                const bool near = __builtin_fabsf(rx) + __builtin_fabsf(ry) < kFp16MaxOffset;
+                const float fx = near ? rx : 0.0f, fy = near ? ry : 0.0f;
+                reinterpret_cast<float2 *>(sh.u.count.half_list)[lane] =
+                    fp16_hypothesis(own.x, own.y, fx, fy, tau);  // the same from every wave
+                __syncthreads();
+                const uint32_t hi = fp16_counts<B>(
+                    sp, pts, nl, reinterpret_cast<const float4 *>(sh.u.count.half_list),
+                    sh.u.count.part, wave, lane, fx, fy);
+                const bool keep = lane < nl && hyp_key(hi, h_first + h) > floor_key;
+                const uint64_t m = __builtin_amdgcn_ballot_w64(keep);  // the same in every wave
+                if (wave == 0) {
+                    const uint32_t rank = __builtin_amdgcn_mbcnt_hi(
+                        (uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+                    if (keep) {
+                        reinterpret_cast<float2 *>(sh.u.count.list)[rank] = own;
+                        sh.u.count.kept[rank] = (uint16_t)h;
+                    }
+                }
+                nl = __builtin_popcountll(m);
+                __syncthreads();
+                h = lane < nl ? sh.u.count.kept[lane] : 0u;
+            }
+        }
+        const uint32_t cnt = exact_counts<B>(sp, pts, tau, nl,
+                                             reinterpret_cast<const float4 *>(sh.u.count.list),
+                                             sh.u.count.part, wave, lane);
         const unsigned long long k = wave_best(lane < nl ? cnt + 1u : 0u, (uint32_t)h_first + h);
         best = k > best ? k : best;
         floor_key = best > floor_key ? best : floor_key;
@@ -1980,8 +2036,9 @@ __global__ __launch_bounds__(kPrepBlock) void batch_scatter_kernel(
 template <bool kFp16>
 __global__ __launch_bounds__(kScoreBlock) __attribute__((amdgpu_waves_per_eu(kFp16 ? 7 : 8))) void batch_score_kernel(
     const ItemDesc *__restrict__ desc, int64_t n_clusters, int32_t n_hyp,
-    int32_t rounds, int32_t parts, Points pts, float tau, unsigned long long *__restrict__ queues,
-    unsigned long long *__restrict__ best_key, int32_t *__restrict__ hyp_counts) {
+    int32_t rounds, int32_t parts, int64_t prune, Points pts, float tau,
+    unsigned long long *__restrict__ queues, unsigned long long *__restrict__ best_key,
+    int32_t *__restrict__ hyp_counts) {
     __shared__ ScoreShared<kScoreBlock> s;
     __shared__ unsigned long long s_item;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
@@ -1994,6 +2051,13 @@ __global__ __launch_bounds__(kScoreBlock) __attribute__((amdgpu_waves_per_eu(kFp
         const int64_t left = n_hyp - first;
         const int nh = left < most ? (int)left : most;
         if constexpr (kFp16) {
+            if (d.form == kFormFp16 && d.n >= prune) {
+                const unsigned long long key =
+                    score_pruned<kScoreBlock, true>(desc_span(d), desc_id(d), first, nh, pts, tau,
+                                                    s.prune(), &best_key[d.out]);
+                merge_key(&best_key[d.out], key, wave, lane);
+                return;
+            }
             if (d.form == kFormFp16) {
                 const int b0 = part * rounds;
                 for (int b = b0; b < b0 + (nh + kScoreBlock - 1) / kScoreBlock; ++b) {
@@ -2288,11 +2352,11 @@ int launch_batch(const BatchArgs &a, unsigned grid, hipStream_t st, bool allow_t
     if (timed) (void)hipEventRecord(tc.ev[1], st);
     if (a.tuning.fp16_min_points > 0)
         hipLaunchKernelGGL(batch_score_kernel<true>, dim3(grid), dim3(kScoreBlock), 0, st,
-                           (const ItemDesc *)desc, a.n_clusters, a.n_hyp, rounds, parts, pts,
+                           (const ItemDesc *)desc, a.n_clusters, a.n_hyp, rounds, parts, tune.prune, pts,
                            a.tau, queues, best_key, a.o.hyp_counts);
     else
         hipLaunchKernelGGL(batch_score_kernel<false>, dim3(grid), dim3(kScoreBlock), 0, st,
-                           (const ItemDesc *)desc, a.n_clusters, a.n_hyp, rounds, parts, pts,
+                           (const ItemDesc *)desc, a.n_clusters, a.n_hyp, rounds, parts, tune.prune, pts,
                            a.tau, queues, best_key, a.o.hyp_counts);
     if (timed) (void)hipEventRecord(tc.ev[2], st);
     launch_refit(true, nullptr, nullptr, (const ItemDesc *)desc, a.n_clusters, n_big,
