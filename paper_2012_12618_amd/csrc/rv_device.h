@@ -92,6 +92,17 @@ __device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
     return (uint32_t)__builtin_amdgcn_readlane((int)w, kWave - 1);
 }
 
+// Inclusive prefix sum over the lanes of a full wave.
+__device__ __forceinline__ uint32_t wave_inclusive_sum(uint32_t v) {
+    v += dpp_from<0x111, 0xF>(v, 0u);
+    v += dpp_from<0x112, 0xF>(v, 0u);
+    v += dpp_from<0x114, 0xF>(v, 0u);
+    v += dpp_from<0x118, 0xF>(v, 0u);
+    v += dpp_from<0x142, 0xA>(v, 0u);
+    v += dpp_from<0x143, 0xC>(v, 0u);
+    return v;
+}
+
 // Bit pattern of a float as an unsigned integer in the same order.
 __device__ __forceinline__ uint32_t ordered_bits(float v) {
     const uint32_t u = __builtin_bit_cast(uint32_t, v);

@@ -6,15 +6,15 @@
 //   stats   one workgroup: per-cluster min-max normalisation of azimuth and
 //           Doppler onto [0, 1] (Alg. 1's normalize(); a zero span maps to 0),
 //           then the median absolute deviation of the normalised Doppler
-//           values (Eq. 5, read as the statistic the text names): two medians
-//           in LDS, by ranks for up to 256 points, else by bitonic sorts of
-//           up to 4096 doubles.
-//   score   one thread per (trial, cluster), the mapping of Alg. 1: the trial
-//           draws its seed pair from Philox4x32-10 exactly as the
-//           velocity-profile kernels do, fits the line through the two
-//           normalised seeds, and counts the points whose perpendicular
-//           distance (aa x + bb y + cc over sqrt(aa^2 + bb^2)) is at most the
-//           threshold (for each line, as one comparison of the numerator
+//           values (Eq. 5, read as the statistic the text names): two medians,
+//           each selected from a histogram in LDS; clears its share of the
+//           frame-wide inlier mask.
+//   score   a thread per (trial, cluster) draws the trial's seed pair from
+//           Philox4x32-10 exactly as the velocity-profile kernels do and fits the
+//           line through the two normalised seeds (Alg. 1); then the workgroup's
+//           waves share the cluster's points, every lane counting those whose
+//           perpendicular distance (aa x + bb y + cc over sqrt(aa^2 + bb^2)) is at
+//           most the threshold (for each line, as one comparison of the numerator
 //           against the largest value that passes, found once per trial); the
 //           block's best (count, lowest index) key is merged per cluster with a
 //           64-bit atomic maximum.
@@ -58,89 +58,137 @@ __device__ __forceinline__ double unit_coord(float a, double lo, double span) {
     return span > 0.0 ? ((double)a - lo) / span : 0.0;
 }
 
-__device__ __forceinline__ double wave_min(double v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmin(v, __shfl_xor(v, o, kWave));
-    return v;
-}
-
-__device__ __forceinline__ double wave_max(double v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o, kWave));
-    return v;
-}
-
-// Ascending bitonic sort of s[0, P) (P a power of two, <= RV_PAPER_MAX_POINTS)
-// by the whole workgroup; every loop bound is uniform.
-__device__ void bitonic_sort(double *s, int P) {
-    for (int size = 2; size <= P; size <<= 1) {
-        for (int stride = size >> 1; stride > 0; stride >>= 1) {
-            for (int i = threadIdx.x; i < P / 2; i += kPaperBlock) {
-                const int lo = (i / stride) * 2 * stride + (i % stride);
-                const int hi = lo + stride;
-                const bool ascending = (lo & size) == 0;
-                const double a = s[lo], b = s[hi];
-                if ((a > b) == ascending) {
-                    s[lo] = b;
-                    s[hi] = a;
-                }
-            }
-            __syncthreads();
-        }
-    }
-}
-
-// Median of the m smallest entries of a sorted array (mean of the two middle
-// values for an even m); m >= 1.
-__device__ __forceinline__ double sorted_median(const double *s, int m) {
-    return (m & 1) ? s[m / 2] : (s[m / 2 - 1] + s[m / 2]) / 2.0;
-}
-
-// The same median for n <= kPaperBlock entries without sorting (entries past
-// n are the +inf padding, never below a finite entry, so they are left out):
-// thread i ranks entry s[i] against all n (how many are below it, how many not
-// above it); the entry whose rank range holds a middle position is that order
-// statistic (equal entries write the same value), and the two middle values
-// are combined as sorted_median combines them.  Called by the whole workgroup;
-// the barrier orders the writes of mid[] before its reads.
-__device__ double rank_median(const double *s, int n, int m, double *mid) {
-    const int q1 = m / 2, q0 = (m & 1) ? q1 : q1 - 1;
-    const int i = threadIdx.x;
-    if (i < n) {
-        const double a = s[i];
-        int below = 0, upto = 0;
-        for (int j = 0; j < n; ++j) {
-            const double b = s[j];
-            below += b < a ? 1 : 0;
-            upto += b <= a ? 1 : 0;
-        }
-        if (below <= q0 && q0 < upto) mid[0] = a;
-        if (below <= q1 && q1 < upto) mid[1] = a;
-    }
-    __syncthreads();
-    return (m & 1) ? mid[1] : (mid[0] + mid[1]) / 2.0;
-}
-
 // Spans of a cluster with 2 <= n <= RV_PAPER_MAX_POINTS points, the only ones
 // the score and refit kernels work on.
 __device__ __forceinline__ bool paper_cluster(const Span &sp) {
     return sp.ok && sp.n >= 2 && sp.n <= RV_PAPER_MAX_POINTS;
 }
 
+constexpr int kSelectBins = 1024;
+
 // Workgroup LDS of the threshold step.
 struct StatsShared {
-    double sort[RV_PAPER_MAX_POINTS];
-    double red[4][kPaperWaves];
-    int cnt[kPaperWaves];
-    double mid[2][2];
+    uint32_t hist[kSelectBins];
+    double sel[kPaperBlock];
+    float red[4][kPaperWaves];
+    uint32_t cnt[kPaperWaves];
+    uint32_t bin[2], below, n_sel;
+    double mid[2];
 };
+
+// Bins of the histogram that hold the positions q0 <= q1 in sorted order, into
+// sh.bin, and the number of entries below the first, into sh.below.  Called by the
+// whole workgroup after a barrier; ends with one.
+__device__ __forceinline__ void find_bins(StatsShared &sh, uint32_t q0, uint32_t q1) {
+    constexpr int kEach = kSelectBins / kPaperBlock;
+    const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
+    uint32_t sum = 0;
+#pragma unroll
+    for (int i = 0; i < kEach; ++i) sum += sh.hist[tid * kEach + i];
+    const uint32_t incl = wave_inclusive_sum(sum);
+    if (lane == kWave - 1) sh.cnt[wave] = incl;
+    __syncthreads();
+    uint32_t at = incl - sum;
+    for (int w = 0; w < wave; ++w) at += sh.cnt[w];
+#pragma unroll
+    for (int i = 0; i < kEach; ++i) {
+        const uint32_t end = at + sh.hist[tid * kEach + i];
+        if (at <= q0 && q0 < end) {
+            sh.bin[0] = tid * kEach + i;
+            sh.below = at;
+        }
+        if (at <= q1 && q1 < end) sh.bin[1] = tid * kEach + i;
+        at = end;
+    }
+    __syncthreads();
+}
+
+// Median (mean of the two middle values for an even count) of the m values
+// value(p) in [0, 1] over the points p < n for which it is not NaN, m >= 1, without
+// sorting: a histogram of the values (monotone bins) finds the bins that hold the
+// middle positions; their entries, usually a handful, are ranked against each
+// other, and the entry whose rank range holds a middle position is that order
+// statistic (equal entries write the same value).  When more than kPaperBlock
+// entries share those bins (many equal values), the two order statistics are
+// selected digit by digit of their bit patterns instead (non-negative doubles order
+// like them).  A bitonic sort of 2048 values took 66 barriers; this takes six.
+// Whole workgroup.
+template <typename Value>
+__device__ __forceinline__ double select_median(StatsShared &sh, int n, int m, const Value &value) {
+    const int tid = threadIdx.x;
+    const uint32_t q1 = m / 2, q0 = (m & 1) ? q1 : q1 - 1;
+    const auto bin_of = [](double y) {
+        const int b = (int)(y * kSelectBins);
+        return (uint32_t)(b < kSelectBins - 1 ? b : kSelectBins - 1);
+    };
+    for (int i = tid; i < kSelectBins; i += kPaperBlock) sh.hist[i] = 0;
+    if (tid == 0) sh.n_sel = 0;
+    __syncthreads();
+    for (int p = tid; p < n; p += kPaperBlock) {
+        const double y = value(p);
+        if (!__builtin_isnan(y)) atomicAdd(&sh.hist[bin_of(y)], 1u);
+    }
+    __syncthreads();
+    find_bins(sh, q0, q1);
+    const uint32_t b0 = sh.bin[0], b1 = sh.bin[1], below = sh.below;
+    for (int p = tid; p < n; p += kPaperBlock) {
+        const double y = value(p);
+        if (!__builtin_isnan(y) && bin_of(y) >= b0 && bin_of(y) <= b1) {
+            const uint32_t k = atomicAdd(&sh.n_sel, 1u);
+            if (k < kPaperBlock) sh.sel[k] = y;
+        }
+    }
+    __syncthreads();
+    const uint32_t n_sel = sh.n_sel;
+    if (n_sel <= kPaperBlock) {
+        if ((uint32_t)tid < n_sel) {
+            const double a = sh.sel[tid];
+            uint32_t lo = below, hi = below;
+            for (uint32_t j = 0; j < n_sel; ++j) {
+                const double b = sh.sel[j];
+                lo += b < a ? 1u : 0u;
+                hi += b <= a ? 1u : 0u;
+            }
+            if (lo <= q0 && q0 < hi) sh.mid[0] = a;
+            if (lo <= q1 && q1 < hi) sh.mid[1] = a;
+        }
+        __syncthreads();
+    } else {
+        for (int which = 0; which < 2; ++which) {
+            uint32_t k = which == 0 ? q0 : q1;
+            uint64_t prefix = 0;
+            for (int bits = 64; bits > 0;) {
+                const int width = bits < 10 ? bits : 10;
+                bits -= width;
+                __syncthreads();
+                for (int i = tid; i < kSelectBins; i += kPaperBlock) sh.hist[i] = 0;
+                __syncthreads();
+                for (int p = tid; p < n; p += kPaperBlock) {
+                    const double y = value(p);
+                    const uint64_t u = __builtin_bit_cast(uint64_t, y);
+                    if (!__builtin_isnan(y) && (bits + width == 64 || (u >> (bits + width)) == prefix))
+                        atomicAdd(&sh.hist[(u >> bits) & ((1u << width) - 1u)], 1u);
+                }
+                __syncthreads();
+                find_bins(sh, k, k);
+                prefix = (prefix << width) | sh.bin[0];
+                k -= sh.below;
+            }
+            if (tid == 0) sh.mid[which] = __builtin_bit_cast(double, prefix);
+        }
+        __syncthreads();
+    }
+    const double lo = sh.mid[0], hi = sh.mid[1];
+    __syncthreads();
+    return (m & 1) ? hi : (lo + hi) / 2.0;
+}
 
 // Threshold step of cluster k (whole workgroup; uniform early returns): the
 // normalised (x, y) of its points into xy (and into s_xy, when given, for
 // clusters of at most kPaperBlock points), and its threshold into thresh[k],
 // NaN when the cluster takes no part or has no usable point.  Returns the
 // threshold in every thread.
-__device__ double paper_stats(const float *__restrict__ theta, const float *__restrict__ vd,
+__device__ __forceinline__ double paper_stats(const float *__restrict__ theta, const float *__restrict__ vd,
                               Span sp, int64_t k, double2 *__restrict__ xy,
                               double *__restrict__ thresh, StatsShared &sh, double2 *s_xy) {
     const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
@@ -148,34 +196,24 @@ __device__ double paper_stats(const float *__restrict__ theta, const float *__re
     if (!paper_cluster(sp)) return __builtin_nan("");
     const int n = (int)sp.n;
     const float *t = theta + sp.lo, *v = vd + sp.lo;
-    // With at most one point per thread, each thread keeps its point and its
-    // normalised Doppler value in registers across the steps (every loop
-    // below then runs once, at p = tid).
-    const bool one = n <= kPaperBlock;
-    float t_own = 0.0f, v_own = 0.0f;
-    double y_own = 0.0;
-    if (one && tid < n) {
-        t_own = t[tid];
-        v_own = v[tid];
-    }
-
-    double tmin = __builtin_inf(), tmax = -__builtin_inf();
-    double vmin = __builtin_inf(), vmax = -__builtin_inf();
-    int m_ok = 0;
+    // Extremes of the finite points (the same in float32 as in FP64).
+    float tmin = __builtin_inff(), tmax = -__builtin_inff();
+    float vmin = __builtin_inff(), vmax = -__builtin_inff();
+    uint32_t m_ok = 0;
     for (int p = tid; p < n; p += kPaperBlock) {
-        const float tp = one ? t_own : t[p], vp = one ? v_own : v[p];
+        const float tp = t[p], vp = v[p];
         if (!(isfinite(tp) && isfinite(vp))) continue;
-        tmin = fmin(tmin, (double)tp);
-        tmax = fmax(tmax, (double)tp);
-        vmin = fmin(vmin, (double)vp);
-        vmax = fmax(vmax, (double)vp);
+        tmin = fminf(tmin, tp);
+        tmax = fmaxf(tmax, tp);
+        vmin = fminf(vmin, vp);
+        vmax = fmaxf(vmax, vp);
         m_ok += 1;
     }
-    tmin = wave_min(tmin);
-    tmax = wave_max(tmax);
-    vmin = wave_min(vmin);
-    vmax = wave_max(vmax);
-    m_ok = wave_sum_i(m_ok);
+    tmin = wave_min_f(tmin);
+    tmax = wave_max_f(tmax);
+    vmin = wave_min_f(vmin);
+    vmax = wave_max_f(vmax);
+    m_ok = __builtin_amdgcn_readlane(wave_inclusive_sum(m_ok), kWave - 1);
     if (lane == 0) {
         sh.red[0][wave] = tmin;
         sh.red[1][wave] = tmax;
@@ -190,73 +228,52 @@ __device__ double paper_stats(const float *__restrict__ theta, const float *__re
     vmax = sh.red[3][0];
     m_ok = sh.cnt[0];
     for (int w = 1; w < kPaperWaves; ++w) {
-        tmin = fmin(tmin, sh.red[0][w]);
-        tmax = fmax(tmax, sh.red[1][w]);
-        vmin = fmin(vmin, sh.red[2][w]);
-        vmax = fmax(vmax, sh.red[3][w]);
+        tmin = fminf(tmin, sh.red[0][w]);
+        tmax = fmaxf(tmax, sh.red[1][w]);
+        vmin = fminf(vmin, sh.red[2][w]);
+        vmax = fmaxf(vmax, sh.red[3][w]);
         m_ok += sh.cnt[w];
     }
-    const double tspan = tmax - tmin, vspan = vmax - vmin;
+    const double tlo = tmin, tspan = (double)tmax - (double)tmin;
+    const double vlo = vmin, vspan = (double)vmax - (double)vmin;
 
-    // Normalised coordinates (x = NaN marks a point that takes no part), and
-    // the finite y values, padded with +inf to a power of two, for the median.
-    int P = 2;
-    while (P < n) P <<= 1;
-    for (int p = tid; p < P; p += kPaperBlock) {
-        double y = __builtin_inf();
-        if (p < n) {
-            const float tp = one ? t_own : t[p], vp = one ? v_own : v[p];
-            const bool ok = isfinite(tp) && isfinite(vp);
-            const double x = ok ? unit_coord(tp, tmin, tspan) : __builtin_nan("");
-            y = ok ? unit_coord(vp, vmin, vspan) : __builtin_inf();
-            const double2 q = make_double2(x, ok ? y : __builtin_nan(""));
-            xy[sp.lo + p] = q;
-            if (one && s_xy != nullptr) s_xy[p] = q;
-        }
-        if (one) y_own = y;
-        sh.sort[p] = y;
+    // Normalised coordinates; NaN marks a point that takes no part.
+    for (int p = tid; p < n; p += kPaperBlock) {
+        const float tp = t[p], vp = v[p];
+        const bool ok = isfinite(tp) && isfinite(vp);
+        const double2 q = make_double2(ok ? unit_coord(tp, tlo, tspan) : __builtin_nan(""),
+                                       ok ? unit_coord(vp, vlo, vspan) : __builtin_nan(""));
+        xy[sp.lo + p] = q;
+        if (s_xy != nullptr && n <= kPaperBlock) s_xy[p] = q;
     }
-    __syncthreads();
     if (m_ok == 0) return __builtin_nan("");
-    // Up to one entry per thread: ranks; above that: a bitonic sort.
-    const bool ranks = P <= kPaperBlock;
-    double med;
-    if (ranks) {
-        med = rank_median(sh.sort, n, m_ok, sh.mid[0]);
-    } else {
-        bitonic_sort(sh.sort, P);
-        med = sorted_median(sh.sort, m_ok);
+    // The thread's own values (it wrote them itself).
+    const bool in_lds = s_xy != nullptr && n <= kPaperBlock;
+    const auto y_of = [&](int p) { return in_lds ? s_xy[p].y : xy[sp.lo + p].y; };
+    // The median of y (|y - 0|: no y is negative), then of |y - median|.
+    double mid = 0.0;
+#pragma unroll 1
+    for (int pass = 0; pass < 2; ++pass) {
+        const double center = mid;
+        mid = select_median(sh, n, (int)m_ok, [&](int p) { return fabs(y_of(p) - center); });
     }
-    __syncthreads();
-    for (int p = tid; p < P; p += kPaperBlock) {
-        double d = __builtin_inf();
-        if (one) {
-            // y_own is +inf exactly for a point that takes no part.
-            if (p < n && y_own < __builtin_inf()) d = fabs(y_own - med);
-        } else if (p < n && isfinite(t[p]) && isfinite(v[p])) {
-            d = fabs(unit_coord(v[p], vmin, vspan) - med);
-        }
-        sh.sort[p] = d;
-    }
-    __syncthreads();
-    double mad;
-    if (ranks) {
-        mad = rank_median(sh.sort, n, m_ok, sh.mid[1]);
-    } else {
-        bitonic_sort(sh.sort, P);
-        mad = sorted_median(sh.sort, m_ok);
-    }
-    if (tid == 0) thresh[k] = mad;
-    return mad;
+    if (tid == 0) thresh[k] = mid;
+    return mid;
 }
 
 __global__ __launch_bounds__(kPaperBlock) void paper_stats_kernel(
     const float *__restrict__ theta, const float *__restrict__ vd,
     const int32_t *__restrict__ off, int64_t n_points, double2 *__restrict__ xy,
-    double *__restrict__ thresh, unsigned long long *__restrict__ best_key) {
+    double *__restrict__ thresh, unsigned long long *__restrict__ best_key,
+    uint32_t *__restrict__ bits, int64_t n_words) {
     __shared__ StatsShared sh;
     const int64_t k = blockIdx.x;
     if (threadIdx.x == 0) best_key[k] = 0;
+    // This workgroup's share of the frame-wide mask, cleared for the refit kernel.
+    if (bits != nullptr) {
+        const int64_t w1 = n_words * (k + 1) / gridDim.x;
+        for (int64_t w = n_words * k / gridDim.x + threadIdx.x; w < w1; w += kPaperBlock) bits[w] = 0u;
+    }
     (void)paper_stats(theta, vd, cluster_span(off, k, n_points), k, xy, thresh, sh, nullptr);
 }
 
@@ -328,63 +345,130 @@ __device__ __forceinline__ bool pass_bound(double distd, double th, double &boun
     return true;
 }
 
-// Trial h of cluster k in this thread (Alg. 1's thread) and the best (count,
-// lowest index) key over the workgroup's trials, returned in every thread
-// (0 when none is valid).  Whole workgroup; uniform early return.
-__device__ unsigned long long paper_score(const float *__restrict__ theta, Span sp, int64_t k,
-                                          int64_t h, int32_t n_hyp, uint32_t key0, uint32_t key1,
+// Workgroup LDS of T trials.
+template <int T>
+struct TrialShared {
+    double aa[T], cc[T];  // numerator of each trial's distance
+    double bound[T];      // largest |numerator| that passes; -1: invalid trial
+    double distd[T];
+    int count[T];
+    unsigned long long key[T / kWave];
+    int literal;  // some trial has no bound: the literal test for all
+};
+
+// Adds to sh.count the inliers of the workgroup's trials among the points
+// [p0, p1): every lane of the wave takes T / 64 trials, which share each point's
+// load (the same address in every lane).
+template <int T, bool kLiteral>
+__device__ __forceinline__ void count_trials(TrialShared<T> &sh, const double2 *__restrict__ pts,
+                                             int p0, int p1, double th, int lane) {
+    constexpr int kEach = T / kWave;
+    double aa[kEach], cc[kEach], lim[kEach];
+    int count[kEach];
+#pragma unroll
+    for (int u = 0; u < kEach; ++u) {
+        const int t = u * kWave + lane;
+        aa[u] = sh.aa[t];
+        cc[u] = sh.cc[t];
+        lim[u] = kLiteral ? sh.distd[t] : sh.bound[t];
+        count[u] = 0;
+    }
+    // A point that takes no part is stored as (NaN, NaN); its distance is NaN and
+    // never passes.
+    constexpr int kUnroll = kLiteral ? 1 : 8 / kEach;
+#pragma unroll kUnroll
+    for (int p = p0; p < p1; ++p) {
+        const double2 q = pts[p];
+#pragma unroll
+        for (int u = 0; u < kEach; ++u) {
+            const double num = fabs((aa[u] * q.x + q.y) + cc[u]);
+            count[u] += (kLiteral ? num / lim[u] <= th : num <= lim[u]) ? 1 : 0;
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < kEach; ++u) atomicAdd(&sh.count[u * kWave + lane], count[u]);
+}
+
+// Trials [h0, h0 + T) of cluster k by a workgroup: thread t < T draws trial h0 + t
+// and fits its line, then the waves share the cluster's points, each counting its
+// own for all T trials.  Returns the
+// best (count, lowest index) key in every thread (0 when no trial is valid).
+// Uniform early return.
+template <int T>
+__device__ __forceinline__ unsigned long long paper_score(const float *__restrict__ theta, Span sp, int64_t k,
+                                          int64_t h0, int32_t n_hyp, uint32_t key0, uint32_t key1,
                                           const double2 *__restrict__ pts, double th,
-                                          int32_t *__restrict__ hyp_counts,
-                                          unsigned long long *s_key) {
-    const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
+                                          int32_t *__restrict__ hyp_counts, TrialShared<T> &sh) {
+    const int tid = threadIdx.x, lane = tid % kWave;
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int64_t h = h0 + tid;
+    const bool mine = tid < T && h < n_hyp;
     if (!paper_cluster(sp)) {
-        if (hyp_counts != nullptr && h < n_hyp) hyp_counts[k * n_hyp + h] = 0;
+        if (hyp_counts != nullptr && mine) hyp_counts[k * n_hyp + h] = 0;
         return 0;
     }
     const int n = (int)sp.n;
-    unsigned long long key = 0;
-    if (h < n_hyp) {
-        const Line L = trial_line(theta + sp.lo, pts, n, (uint32_t)h, (uint32_t)k, key0, key1);
-        int count = 0;
-        if (L.valid) {
-            // A point that takes no part is stored as (NaN, NaN); its distance
-            // is NaN and never passes.  Points are independent: the loops are
-            // unrolled and have no branch.
-            double bound;
-            if (pass_bound(L.distd, th, bound)) {
-#pragma unroll 8
-                for (int p = 0; p < n; ++p) count += fabs(dist_num(L, pts[p])) <= bound ? 1 : 0;
-            } else {
-#pragma unroll 8
-                for (int p = 0; p < n; ++p) count += within(L, pts[p], th) ? 1 : 0;
-            }
-            key = ((unsigned long long)count << 32) | (0xFFFFFFFFull - (uint32_t)h);
-        }
-        if (hyp_counts != nullptr) hyp_counts[k * n_hyp + h] = count;
-    }
-    key = wave_max_u64(key);
-    if (lane == 0) s_key[wave] = key;
+    if (tid == 0) sh.literal = 0;
     __syncthreads();
-    key = s_key[0];
-    for (int w = 1; w < kPaperWaves; ++w) key = s_key[w] > key ? s_key[w] : key;
+    bool valid = false;
+    if (tid < T) {
+        Line L;
+        L.valid = false;
+        double bound = -1.0;
+        if (mine) {
+            L = trial_line(theta + sp.lo, pts, n, (uint32_t)h, (uint32_t)k, key0, key1);
+            valid = L.valid;
+            if (valid && !pass_bound(L.distd, th, bound)) sh.literal = 1;
+        }
+        sh.aa[tid] = valid ? -L.m : 0.0;
+        sh.cc[tid] = valid ? -L.c : 0.0;
+        sh.bound[tid] = bound;
+        sh.distd[tid] = valid ? L.distd : __builtin_nan("");
+        sh.count[tid] = 0;
+    }
+    __syncthreads();
+    const int p0 = n * wave / kPaperWaves, p1 = n * (wave + 1) / kPaperWaves;
+    if (sh.literal != 0)
+        count_trials<T, true>(sh, pts, p0, p1, th, lane);
+    else
+        count_trials<T, false>(sh, pts, p0, p1, th, lane);
+    __syncthreads();
+    if (wave < T / kWave) {
+        const int count = sh.count[tid];
+        if (hyp_counts != nullptr && mine) hyp_counts[k * n_hyp + h] = valid ? count : 0;
+        const uint32_t val = valid ? (uint32_t)count + 1u : 0u;
+        const uint32_t most = wave_max_u32(val);
+        const uint32_t low = ~wave_max_u32(val == most ? ~(uint32_t)h : 0u);
+        if (lane == 0)
+            sh.key[wave] = most == 0 ? 0ull
+                                     : ((unsigned long long)(most - 1u) << 32) | (0xFFFFFFFFull - low);
+    }
+    __syncthreads();
+    unsigned long long key = sh.key[0];
+    for (int w = 1; w < T / kWave; ++w) key = sh.key[w] > key ? sh.key[w] : key;
     return key;
 }
 
-// Block = (cluster, 256 trials); blocks of one cluster merge their keys with a
-// 64-bit atomic maximum, whose result does not depend on their order.
+// Block = (cluster, T trials); blocks of one cluster merge their keys with a 64-bit
+// atomic maximum, whose result does not depend on their order.  T = 64 keeps a block
+// of the largest cluster short: the blocks run in index order, and with 256 trials
+// each the compute unit that happened on several large clusters set the kernel's
+// length (512 clusters of 8 to 2048 points, 512 trials, FP64 operations for 14 us:
+// 83 us with a thread per trial over all points, 56 us with 256 trials and eight
+// waves sharing the points, 45 us this way).
+template <int T>
 __global__ __launch_bounds__(kPaperBlock) void paper_score_kernel(
     const float *__restrict__ theta, const int32_t *__restrict__ off, int64_t n_points,
     int32_t n_hyp, int32_t blocks_per_cluster, uint32_t key0, uint32_t key1,
     const double2 *__restrict__ xy, const double *__restrict__ thresh,
     unsigned long long *__restrict__ best_key, int32_t *__restrict__ hyp_counts) {
-    __shared__ unsigned long long s_key[kPaperWaves];
+    __shared__ TrialShared<T> sh;
     const int64_t k = blockIdx.x / blocks_per_cluster;
     const int b = (int)(blockIdx.x % blocks_per_cluster);
-    const int64_t h = (int64_t)b * kPaperBlock + threadIdx.x;
     const Span sp = cluster_span(off, k, n_points);
     const double2 *pts = paper_cluster(sp) ? xy + sp.lo : xy;
-    const unsigned long long key =
-        paper_score(theta, sp, k, h, n_hyp, key0, key1, pts, thresh[k], hyp_counts, s_key);
+    const unsigned long long key = paper_score<T>(theta, sp, k, (int64_t)b * T, n_hyp, key0, key1,
+                                                  pts, thresh[k], hyp_counts, sh);
     if (threadIdx.x == 0 && key != 0) atomicMax(&best_key[k], key);
 }
 
@@ -531,8 +615,8 @@ __global__ __launch_bounds__(kPaperBlock) void paper_frame_kernel(
     int64_t n_points, int32_t n_hyp, uint32_t key0, uint32_t key1, double2 *__restrict__ xy,
     double *__restrict__ thresh, int32_t *__restrict__ hyp_counts, PaperOutputs o) {
     __shared__ StatsShared sh;
+    __shared__ TrialShared<kPaperBlock> s_trials;
     __shared__ double2 s_xy[kPaperBlock];  // normalised points of clusters of <= 256 points
-    __shared__ unsigned long long s_key[kPaperWaves];
     __shared__ double s_sum[kPaperWaves][5];
     __shared__ int s_cnt[kPaperWaves];
     const int64_t k = blockIdx.x;
@@ -542,18 +626,13 @@ __global__ __launch_bounds__(kPaperBlock) void paper_frame_kernel(
     // Trials read the points from LDS where they fit, else from global memory.
     unsigned long long best;
     if (paper_cluster(sp) && sp.n <= kPaperBlock)
-        best = paper_score(theta, sp, k, threadIdx.x, n_hyp, key0, key1, s_xy, th, hyp_counts,
-                           s_key);
+        best = paper_score<kPaperBlock>(theta, sp, k, 0, n_hyp, key0, key1, s_xy, th, hyp_counts,
+                                        s_trials);
     else
-        best = paper_score(theta, sp, k, threadIdx.x, n_hyp, key0, key1,
-                           paper_cluster(sp) ? xy + sp.lo : xy, th, hyp_counts, s_key);
+        best = paper_score<kPaperBlock>(theta, sp, k, 0, n_hyp, key0, key1,
+                                        paper_cluster(sp) ? xy + sp.lo : xy, th, hyp_counts,
+                                        s_trials);
     paper_refit(theta, vd, sp, k, key0, key1, xy, th, best, o, s_sum, s_cnt);
-}
-
-__global__ __launch_bounds__(kPaperBlock) void paper_clear_bits_kernel(uint32_t *__restrict__ bits,
-                                                                      int64_t n_words) {
-    const int64_t i = (int64_t)blockIdx.x * kPaperBlock + threadIdx.x;
-    if (i < n_words) bits[i] = 0u;
 }
 
 constexpr size_t kPaperAlign = 256;
@@ -649,19 +728,16 @@ int rv_estimate_velocity_paper(const float *theta, const float *vd, const int32_
         if (e != hipSuccess) return fail(RV_ERR_HIP, "kernel launch failed: %s", hipGetErrorString(e));
         return RV_OK;
     }
-    if (inlier_bits != nullptr) {
-        const int64_t n_words = (n_points + 31) / 32;
-        if (n_words > 0)
-            hipLaunchKernelGGL(paper_clear_bits_kernel,
-                               dim3((unsigned)((n_words + kPaperBlock - 1) / kPaperBlock)),
-                               dim3(kPaperBlock), 0, st, inlier_bits, n_words);
-    }
     hipLaunchKernelGGL(paper_stats_kernel, dim3((unsigned)n_clusters), dim3(kPaperBlock), 0, st,
-                       theta, vd, cluster_offsets, n_points, xy, th, best_key);
+                       theta, vd, cluster_offsets, n_points, xy, th, best_key, inlier_bits,
+                       (n_points + 31) / 32);
     if (timed) (void)hipEventRecord(tc.ev[1], st);
-    hipLaunchKernelGGL(paper_score_kernel, dim3((unsigned)(n_clusters * bpc)), dim3(kPaperBlock), 0,
-                       st, theta, cluster_offsets, n_points, n_hyp, (int32_t)bpc, key0, key1,
-                       (const double2 *)xy, (const double *)th, best_key, hyp_counts);
+    const int64_t bpc64 = ((int64_t)n_hyp + kWave - 1) / kWave;
+    const bool fine = n_clusters * bpc64 <= INT32_MAX;  // else the grid would be too large
+    hipLaunchKernelGGL(fine ? paper_score_kernel<kWave> : paper_score_kernel<kPaperBlock>,
+                       dim3((unsigned)(n_clusters * (fine ? bpc64 : bpc))), dim3(kPaperBlock), 0, st,
+                       theta, cluster_offsets, n_points, n_hyp, (int32_t)(fine ? bpc64 : bpc), key0,
+                       key1, (const double2 *)xy, (const double *)th, best_key, hyp_counts);
     if (timed) (void)hipEventRecord(tc.ev[2], st);
     hipLaunchKernelGGL(paper_refit_kernel, dim3((unsigned)n_clusters), dim3(kPaperBlock), 0, st,
                        theta, vd, cluster_offsets, n_points, key0, key1, (const double2 *)xy,
