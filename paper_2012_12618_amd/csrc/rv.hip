@@ -517,6 +517,16 @@ __device__ __forceinline__ PointLoad load_point(const Points &pts, int64_t first
     return L;
 }
 
+// Point p of a cluster's n (its last one past the end: in bounds, not used).
+__device__ __forceinline__ PointLoad load_at(const StagedPoint *points, uint32_t p, uint32_t n) {
+    const StagedPoint &q = points[p < n ? p : n - 1];
+    PointLoad L;
+    L.c = q.c;
+    L.s = q.s;
+    L.v = q.v;
+    return L;
+}
+
 // Stores the points of load_point into LDS as float4 quads, padded to a
 // multiple of four with (0, 0, +inf), a point that never counts; the caller's
 // next block barrier publishes them.
@@ -902,8 +912,8 @@ __device__ __forceinline__ uint32_t fp16_counts(Span sp, const Points &pts, int 
 // Only the hypothesis with the most inliers is kept, so a hypothesis need not
 // be counted once its count is known to be below another's.  Per workgroup
 // (one cluster, up to kPruneHyp hypotheses):
-//   1. reference r: among the first hypotheses, one per thread, the one with the
-//      most inliers in a strided sample of the points;
+//   1. reference r: among the first 64 hypotheses the one with the most inliers in
+//      a strided sample of the points;
 //   2. one sweep over the cluster counts r exactly (T) and sorts the points
 //      into a table of direction (kAngleBins) x signed residual under r;
 //   3. every hypothesis h gets an upper bound of its count from the table: a
@@ -940,6 +950,7 @@ __device__ __forceinline__ uint32_t fp16_counts(Span sp, const Points &pts, int 
 // ---------------------------------------------------------------------------
 
 constexpr int kPruneHyp = 1024;     // hypotheses per workgroup, at most
+constexpr int kSample = 32;         // points of the sample
 
 // Smallest cluster scored this way, by blocks of 256 hypotheses per workgroup
 // (at least 1).  The table is made once per workgroup, so the more blocks share it
@@ -959,7 +970,7 @@ constexpr float kPruneMaxSpeed = 1e15f;  // references beyond it are not used
 template <int B>
 struct PruneShared {
     float4 hyp[kPruneHyp / 2];  // (vx, vy) pairs
-    LaneTile<kWave> sample;
+    LaneTile<kSample> sample;
     float4 dir[kAngleBins];     // centre (cos, sin), half width w, w^2 / 2
     union {
         uint32_t hist[kAngleBins * kResidualRow];
@@ -1015,6 +1026,24 @@ __device__ __forceinline__ float uniform_f(float v) {
     return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, v)));
 }
 
+// body(point, in) for the block's share of a cluster's points, every thread one
+// point in B, kSweepLoads of them loaded before the first is used (in: the point is
+// one of the n; past the end the last one is loaded again).
+template <int B, typename Body>
+__device__ __forceinline__ void sweep_points(const StagedPoint *points, uint32_t n,
+                                             const Body &body) {
+    constexpr int kSweepLoads = 4;
+    for (uint32_t base = 0; base < n; base += kSweepLoads * B) {
+        PointLoad u[kSweepLoads];
+#pragma unroll
+        for (int i = 0; i < kSweepLoads; ++i)
+            u[i] = load_at(points, base + i * B + threadIdx.x, n);
+#pragma unroll
+        for (int i = 0; i < kSweepLoads; ++i)
+            if (base + i * B < n) body(u[i], base + i * B + threadIdx.x < n);  // uniform
+    }
+}
+
 // Scoring of hypotheses [h_first, h_first + nh), nh <= kPruneHyp, of a cluster
 // with at least kWave points.  Returns the best key among the hypotheses, or,
 // where a key of best_key (the cluster's so far, shared by its workgroups;
@@ -1037,23 +1066,18 @@ __device__ __forceinline__ unsigned long long score_pruned(
     const StagedPoint *points = pts.staged + sp.lo;
     float2 *hyp = reinterpret_cast<float2 *>(sh.hyp);
 
-    // The sample: 64 points spread over the cluster.
+    // The sample, spread over the cluster.
     if (wave == 0) {
-        const StagedPoint &u = points[(uint32_t)(((uint64_t)lane * n) / kWave)];
-        PointLoad L;
-        L.c = u.c;
-        L.s = u.s;
-        L.v = u.v;
-        store_points(L, kWave, sh.sample.c, sh.sample.s, sh.sample.v);
+        const PointLoad L = load_at(points, (uint32_t)(((uint64_t)lane * n) / kSample), n);
+        store_points(L, kSample, sh.sample.c, sh.sample.s, sh.sample.v);
     }
     // Range of the points' directions.
     float qlo = __builtin_inff(), qhi = -__builtin_inff();
-#pragma unroll 2
-    for (uint32_t p = tid; p < n; p += B) {
-        const float q = direction_key(points[p].c, points[p].s);  // NaN for a non-finite point (0, 0)
+    sweep_points<B>(points, n, [&](const PointLoad &u, bool) {
+        const float q = direction_key(u.c, u.s);  // NaN for a non-finite point (0, 0)
         qlo = fminf(qlo, q);
         qhi = fmaxf(qhi, q);
-    }
+    });
     for (int i = tid; i < kAngleBins * kResidualRow; i += B) sh.u.hist[i] = 0;
     // The hypotheses, two at a time so that their seed loads overlap (NaN for a
     // degenerate pair and past the last).
@@ -1080,9 +1104,12 @@ __device__ __forceinline__ unsigned long long score_pruned(
     }
     __syncthreads();
 
-    // 1. Reference.
-    {
-        const uint32_t cnt = tail_count(sh.sample, kWave, own.x, own.y, tau);
+    // 1. Reference (the other waves have none: 64 hypotheses over 32 points leave as
+    // many hypotheses after step 4 as 256 over 64).
+    if (wave > 0) {
+        if (lane == 0) sh.key[wave] = 0;
+    } else {
+        const uint32_t cnt = tail_count(sh.sample, kSample, own.x, own.y, tau);
         const bool usable = __builtin_fabsf(own.x) + __builtin_fabsf(own.y) < kPruneMaxSpeed;  // not NaN
         const unsigned long long key = wave_best(usable ? cnt + 1u : 0u, (uint32_t)tid);
         if (lane == 0) sh.key[wave] = key;
@@ -1123,16 +1150,15 @@ __device__ __forceinline__ unsigned long long score_pruned(
         const float sigma = uniform_f(residual_scale(tau));
         const float scale = 1.0f / width;
         uint32_t t = 0;
-#pragma unroll 2
-        for (uint32_t p = tid; p < n; p += B) {
-            const StagedPoint &u = points[p];
+        sweep_points<B>(points, n, [&](const PointLoad &u, bool in) {
             const float e = __builtin_fmaf(-ry, u.s, __builtin_fmaf(-rx, u.c, u.v));
-            t += __builtin_fabsf(e) < tau ? 1u : 0u;
+            t += in && __builtin_fabsf(e) < tau ? 1u : 0u;
             int b = (int)((direction_key(u.c, u.s) - q0) * scale);
             b = b < kAngleBins - 1 ? b : kAngleBins - 1;
             b = b > 0 ? b : 0;
-            if (u.v < __builtin_inff()) atomicAdd(&sh.u.hist[b * kResidualRow + residual_bin(e * sigma)], 1u);
-        }
+            if (in && u.v < __builtin_inff())
+                atomicAdd(&sh.u.hist[b * kResidualRow + residual_bin(e * sigma)], 1u);
+        });
         t = (uint32_t)wave_sum_i((int)t);
         if (lane == 0) sh.n[wave] = t;
         __syncthreads();
@@ -1179,7 +1205,7 @@ __device__ __forceinline__ unsigned long long score_pruned(
                 const float band = __builtin_fmaf(__builtin_fabsf(dx) + __builtin_fabsf(dy), w2,
                                                   (tau + 0x1p-18f * (tau + m)) * sigma);
                 uint32_t bound = 0;
-#pragma unroll 1
+#pragma unroll 4
                 for (int b = 0; b < kAngleBins; ++b) {
                     const float4 d = sh.dir[b];
                     const float f = __builtin_fmaf(dx, d.x, dy * d.y);
@@ -1318,27 +1344,148 @@ __device__ __forceinline__ unsigned long long score_pruned(
     return best;
 }
 
+// ---------------------------------------------------------------------------
+// Small clusters, every hypothesis of the workgroup at once: lanes = hypotheses,
+// each thread with up to four of them, the cluster's points broadcast from LDS.  A
+// point's three broadcasts serve them all (with one hypothesis per thread the
+// LDS, not the vector unit, set the rate: 15 cycles per point and 64 hypotheses).
+// The compare, which issues at half the rate of an FMA, is a third FMA instead:
+// (tau - |e|) 2^k with the result clamped to [0, 1] is exactly 1.0 when |e| < tau
+// and 0 otherwise (NaN clamps to 0), for k such that one unit in the last place of
+// tau times 2^k is at least 1; the product and tau 2^k are exact and the sum is
+// rounded once, so its sign is that of tau - |e|.  The ones are added as integers,
+// three operands an instruction, and their sum names the count: m times the bit
+// pattern of 1.0f is 127 m 2^23, and 127 is odd.  The residual e is the rows form's,
+// so every count is the same bit for bit.
+// ---------------------------------------------------------------------------
+
+constexpr uint32_t kInverse127 = 383;  // 127 * 383 = 1 mod 512: counts up to 511
+static_assert((127u * kInverse127) % 512u == 1u && kLaneTile < 512, "counts are recovered mod 512");
+
+template <int B>
+struct SmallShared {
+    float4 hyp[kPruneHyp / 2];
+    LaneTile<kLaneTile> tile;
+    unsigned long long key[B / kWave];
+};
+
+template <int H>
+__device__ __forceinline__ void count_small(const LaneTile<kLaneTile> &tile, int n,
+                                            const float2 *hyp, int stride, float tau,
+                                            uint32_t (&count)[4]) {
+    const uint32_t exponent = (__builtin_bit_cast(uint32_t, tau) >> 23) & 255u;  // tau is normal
+    const float scale = __builtin_bit_cast(float, (127u + 127u + 25u - exponent) << 23);
+    const float limit = tau * scale;
+    float hx[H], hy[H];
+    uint32_t sum[H];
+#pragma unroll
+    for (int k = 0; k < H; ++k) {
+        hx[k] = hyp[k * stride].x;
+        hy[k] = hyp[k * stride].y;
+        sum[k] = 0;
+    }
+#pragma unroll 1
+    for (int q = 0; q < (n + 3) / 4; ++q) {
+        const float4 c = tile.c[q], sn = tile.s[q], v = tile.v[q];
+        const float cc[4] = {c.x, c.y, c.z, c.w}, ss[4] = {sn.x, sn.y, sn.z, sn.w};
+        const float vv[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+        for (int k = 0; k < H; ++k) {
+            uint32_t one[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const float e = __builtin_fmaf(-hy[k], ss[u], __builtin_fmaf(-hx[k], cc[u], vv[u]));
+                one[u] = __builtin_bit_cast(
+                    uint32_t, __builtin_amdgcn_fmed3f(
+                                  __builtin_fmaf(-__builtin_fabsf(e), scale, limit), 0.0f, 1.0f));
+            }
+            sum[k] = sum[k] + one[0] + one[1];
+            sum[k] = sum[k] + one[2] + one[3];
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < H; ++k) count[k] = ((sum[k] >> 23) * kInverse127) & 511u;
+}
+
+// Hypotheses [h_first, h_first + nh), nh <= kPruneHyp, of a cluster with 2 <= n <=
+// kLaneTile points; tau in the range of prune_from.  The best key, the same in
+// every thread.  Called by all threads of the block, also from the persistent loop.
+template <int B>
+__device__ __forceinline__ unsigned long long score_small(Span sp, ClusterId id, int64_t h_first,
+                                                          int nh, int32_t n_hyp, const Points &pts,
+                                                          float tau, SmallShared<B> &sh,
+                                                          int32_t *__restrict__ hyp_counts) {
+    const int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int lane = tid % kWave;
+    const int n = (int)sp.n, rounds = (nh + B - 1) / B;
+    float2 *hyp = reinterpret_cast<float2 *>(sh.hyp);
+    const PointLoad tl = load_point(pts, sp.lo, n);
+#pragma unroll 1
+    for (int q = 0; q < rounds; ++q) {
+        const int hl = q * B + tid;
+        const Hypothesis y =
+            make_hypothesis(pts, sp, (uint32_t)(h_first + hl), id.local, id.key0, id.key1);
+        const float qnan = __builtin_nanf("");
+        hyp[hl] = hl < nh ? make_float2((float)y.vx, (float)y.vy) : make_float2(qnan, qnan);
+    }
+    store_points(tl, n, sh.tile.c, sh.tile.s, sh.tile.v);
+    __syncthreads();
+    uint32_t val = 0, h = 0;  // the thread's best: count + 1 of a valid hypothesis, its index
+#pragma unroll 1
+    for (int q0 = 0; q0 < rounds; q0 += 4) {
+        uint32_t count[4] = {0, 0, 0, 0};
+        const int left = rounds - q0;
+        if (left == 1)
+            count_small<1>(sh.tile, n, hyp + q0 * B + tid, B, tau, count);
+        else if (left == 2)
+            count_small<2>(sh.tile, n, hyp + q0 * B + tid, B, tau, count);
+        else
+            count_small<4>(sh.tile, n, hyp + q0 * B + tid, B, tau, count);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int hl = (q0 + k) * B + tid;
+            if (q0 + k < rounds && hl < nh) {
+                if (hyp_counts != nullptr) hyp_counts[id.out * n_hyp + h_first + hl] = (int32_t)count[k];
+                if (count[k] + 1u > val && !__builtin_isnan(hyp[hl].x)) {
+                    val = count[k] + 1u;
+                    h = (uint32_t)h_first + (uint32_t)hl;
+                }
+            }
+        }
+    }
+    const unsigned long long key = wave_best(val, h);
+    if (lane == 0) sh.key[wave] = key;
+    __syncthreads();
+    return block_key<B>(sh.key);
+}
+
 // Workgroup LDS of the scoring forms: a workgroup uses one at a time.
 template <int B>
 struct ScoreShared {
     static constexpr size_t kBytes = sizeof(PruneShared<B>);
-    static_assert(sizeof(RowsShared<B>) <= kBytes && sizeof(Fp16Shared) <= kBytes, "the largest");
+    static_assert(sizeof(RowsShared<B>) <= kBytes && sizeof(Fp16Shared) <= kBytes &&
+                  sizeof(SmallShared<B>) <= kBytes, "the largest");
     alignas(16) unsigned char bytes[kBytes];
     __device__ RowsShared<B> &rows() { return *reinterpret_cast<RowsShared<B> *>(bytes); }
     __device__ Fp16Shared &fp16() { return *reinterpret_cast<Fp16Shared *>(bytes); }
+    __device__ SmallShared<B> &small() { return *reinterpret_cast<SmallShared<B> *>(bytes); }
     __device__ PruneShared<B> &prune() { return *reinterpret_cast<PruneShared<B> *>(bytes); }
 };
 
 // Float32 scoring of hypotheses [h_first, h_first + nh) of one cluster by one
 // workgroup (h_first a multiple of B), in the form its size asks for; the best
-// key, the same in every thread.  lanes_max: clusters of at most this many points
-// take lanes = hypotheses; prune: clusters of at least this many points count
-// only possible winners (nh <= kPruneHyp).
+// key, the same in every thread.  small_max: clusters of at most this many points
+// (and at least two) take score_small; prune: clusters of at least this many points
+// count only possible winners; otherwise clusters of at most lanes_max points take
+// lanes = hypotheses and the others lanes = points.
 template <int B>
 __device__ __forceinline__ unsigned long long score_hypotheses(
     Span sp, ClusterId id, int64_t h_first, int nh, int32_t n_hyp, const Points &pts, float tau,
-    int rows_max, int lanes_max, int64_t prune, ScoreShared<B> &sh,
+    int rows_max, int lanes_max, int small_max, int64_t prune, ScoreShared<B> &sh,
     const unsigned long long *best_key, int32_t *__restrict__ hyp_counts) {
+    if (sp.n >= 2 && sp.n <= small_max)
+        return score_small<B>(sp, id, h_first, nh, n_hyp, pts, tau, sh.small(), hyp_counts);
     if (sp.n >= prune) return score_pruned<B>(sp, id, h_first, nh, pts, tau, sh.prune(), best_key);
     const int b0 = (int)(h_first / B), blocks = (nh + B - 1) / B;
     unsigned long long best = 0;
@@ -1700,8 +1847,8 @@ __device__ __forceinline__ void refit_cluster(Span sp, ClusterId id, unsigned lo
 __global__ __launch_bounds__(kScoreBlock) __attribute__((amdgpu_waves_per_eu(8))) void score_kernel(
     const int32_t *__restrict__ off, const int32_t *__restrict__ order, int64_t n_clusters,
     int64_t n_points, int32_t n_hyp, int32_t rounds, int32_t parts, uint32_t key0, uint32_t key1,
-    uint32_t cluster_base, int64_t point_base, int64_t prune, Points pts, float tau,
-    unsigned long long *__restrict__ best_key, int32_t *__restrict__ hyp_counts) {
+    uint32_t cluster_base, int64_t point_base, int32_t small_max, int64_t prune, Points pts,
+    float tau, unsigned long long *__restrict__ best_key, int32_t *__restrict__ hyp_counts) {
     __shared__ ScoreShared<kScoreBlock> s;
     const uint32_t xcd = blockIdx.x % kXcds;
     const uint32_t r = blockIdx.x / kXcds;
@@ -1719,7 +1866,7 @@ __global__ __launch_bounds__(kScoreBlock) __attribute__((amdgpu_waves_per_eu(8))
     const int64_t left = n_hyp - first;
     const unsigned long long key = score_hypotheses<kScoreBlock>(
         sp, id, first, left < most ? (int)left : most, n_hyp, pts, tau, kRowsMax, kSingleLanesMax,
-        prune, s, &best_key[k], hyp_counts);
+        small_max, prune, s, &best_key[k], hyp_counts);
     merge_key(&best_key[k], key, __builtin_amdgcn_readfirstlane(threadIdx.x / kWave),
               threadIdx.x % kWave);
 }
@@ -1803,7 +1950,8 @@ __global__ __launch_bounds__(kRefitBlock) void refit_kernel(
 __global__ __launch_bounds__(kScoreBlock) __attribute__((amdgpu_waves_per_eu(8))) void cluster_kernel(
     const float *__restrict__ theta, const float *__restrict__ vd, const int32_t *__restrict__ off,
     int64_t n_points, int32_t n_hyp, uint32_t key0, uint32_t key1, uint32_t cluster_base,
-    int64_t point_base, int64_t prune, float tau, StagedPoint *staged, Outputs o) {
+    int64_t point_base, int32_t small_max, int64_t prune, float tau, StagedPoint *staged,
+    Outputs o) {
     const Points pts = {staged, theta};
     __shared__ ScoreShared<kScoreBlock> s;
     __shared__ RefitShared s_refit;
@@ -1819,7 +1967,7 @@ __global__ __launch_bounds__(kScoreBlock) __attribute__((amdgpu_waves_per_eu(8))
     id.key1 = key1;
     const unsigned long long best =
         score_hypotheses<kScoreBlock>(sp, id, 0, n_hyp, n_hyp, pts, tau, kRowsMax, kSingleLanesMax,
-                                      prune, s, nullptr, o.hyp_counts);
+                                      small_max, prune, s, nullptr, o.hyp_counts);
     refit_cluster(sp, id, best, pts, tau, o, __builtin_amdgcn_readfirstlane(threadIdx.x / kWave),
                   kScoreBlock / kWave, s_refit);
 }
@@ -1836,11 +1984,12 @@ struct Tuning {
     int32_t rows[RV_TUNE_BUCKETS];
     int32_t fp16_min;   // clusters of at least this many points use the FP16 form; 0: none
     int32_t lanes_max;  // clusters of at most this many points score with lanes = hypotheses
+    int32_t small_max;  // clusters of at most this many points take score_small
     int64_t prune;      // clusters of at least this many points count only possible winners
 };
 
 // Scoring form of a cluster (ItemDesc::form).
-enum : int16_t { kFormRows = 0, kFormFp16 = 1, kFormLanes = 2, kFormPruned = 3 };
+enum : int16_t { kFormRows = 0, kFormFp16 = 1, kFormLanes = 2, kFormPruned = 3, kFormSmall = 4 };
 
 // Everything the scoring and refit workgroups need about one cluster, at its
 // position in the dispatch order: one 32-byte load instead of a chain of
@@ -2013,7 +2162,9 @@ __global__ __launch_bounds__(kPrepBlock) void batch_scatter_kernel(
     d.ok = sp.ok ? 1 : 0;
     d.rows = (int16_t)tune.rows[size_bucket(sp.n)];
     d.form = kFormRows;
-    if (sp.ok && sp.n >= 2 && sp.n <= tune.lanes_max)
+    if (sp.n >= 2 && sp.n <= tune.small_max)
+        d.form = kFormSmall;
+    else if (sp.ok && sp.n >= 2 && sp.n <= tune.lanes_max)
         d.form = kFormLanes;
     else if (tune.fp16_min > 0 && sp.ok && sp.n >= 2 && sp.n >= tune.fp16_min)
         d.form = kFormFp16;
@@ -2070,7 +2221,7 @@ __global__ __launch_bounds__(kScoreBlock) __attribute__((amdgpu_waves_per_eu(kFp
         }
         const unsigned long long key = score_hypotheses<kScoreBlock>(
             desc_span(d), desc_id(d), first, nh, n_hyp, pts, tau, d.rows, desc_lanes(d),
-            desc_prune(d), s, &best_key[d.out], hyp_counts);
+            d.form == kFormSmall ? kLaneTile : 0, desc_prune(d), s, &best_key[d.out], hyp_counts);
         merge_key(&best_key[d.out], key, wave, lane);
     });
 }
@@ -2243,9 +2394,26 @@ int32_t score_rounds(int64_t n_clusters, int64_t blocks_per_cluster) {
 // Smallest cluster that counts only possible winners: none when the caller asks
 // for every hypothesis's count, or tau is so extreme that the residual bins'
 // scale leaves the normal range.
+bool ordinary_tau(float tau) { return tau > 1e-15f && tau < 1e15f; }
+
 int64_t prune_from(int32_t rounds, float tau, const int32_t *hyp_counts) {
-    if (hyp_counts != nullptr || !(tau > 1e-15f) || !(tau < 1e15f)) return INT64_MAX;
-    return prune_min(rounds);
+    return hyp_counts != nullptr || !ordinary_tau(tau) ? INT64_MAX : prune_min(rounds);
+}
+
+// Largest cluster that takes score_small; lanes_max: what the tuning lets take
+// lanes = hypotheses (0: none).  Where a table pays (prune_min) that takes over:
+// 32,768 clusters at 512 hypotheses, scoring stage this way 129, 161, 195 us at 64,
+// 96 and 128 points (198, 245 and 256 us with lanes = points above 64 and one
+// hypothesis per thread below), with a table 236 and 241 us at 128 and 192.  With one
+// block per workgroup a broadcast serves one hypothesis and LDS sets the rate, yet
+// up to 200 points it is still the shorter chain (frame of 64 clusters of 20 to 200
+// points 10.8 and 10.1 us; 1021 clusters in 3-degree windows 44.0 and 43.2 us).
+constexpr int32_t kSmallAlone = 200;
+
+int32_t small_to(int32_t rounds, float tau, int32_t lanes_max) {
+    if (lanes_max == 0 || !ordinary_tau(tau)) return 0;
+    const int32_t most = rounds == 1 ? kSmallAlone : prune_min(rounds) - 1;
+    return most > lanes_max ? most : lanes_max;
 }
 
 // Frames small enough that launch latency dominates take one launch
@@ -2334,6 +2502,9 @@ int launch_batch(const BatchArgs &a, unsigned grid, hipStream_t st, bool allow_t
     tune.lanes_max = a.tuning.lanes_max_points;
     const int32_t rounds = batch_rounds(a), parts = batch_parts(a);
     tune.prune = prune_from(rounds, a.tau, a.o.hyp_counts);
+    tune.small_max = small_to(rounds, a.tau, a.tuning.lanes_max_points);
+    if (a.tuning.fp16_min_points > 0 && tune.small_max >= a.tuning.fp16_min_points)
+        tune.small_max = a.tuning.fp16_min_points - 1;
     const int64_t n_words = a.o.bits != nullptr ? (a.n_points + 31) / 32 : 0;
     int64_t prep_items = a.n_points > n_words ? a.n_points : n_words;
     prep_items = prep_items > a.n_clusters ? prep_items : a.n_clusters;
@@ -2474,7 +2645,8 @@ int estimate_frame(const float *theta, const float *vd, const int32_t *cluster_o
         if (timed) (void)hipEventRecord(tc.ev[1], st);
         hipLaunchKernelGGL(cluster_kernel, dim3((unsigned)n_clusters), dim3(kScoreBlock), 0, st,
                            theta, vd, cluster_offsets, n_points, n_hyp, key0, key1, first_cluster,
-                           first_point, prune_from(1, tau, hyp_counts), tau, staged, o);
+                           first_point, small_to(1, tau, kSingleLanesMax), prune_from(1, tau, hyp_counts),
+                           tau, staged, o);
         if (timed) {
             (void)hipEventRecord(tc.ev[2], st);
             (void)hipEventRecord(tc.ev[3], st);
@@ -2496,7 +2668,8 @@ int estimate_frame(const float *theta, const float *vd, const int32_t *cluster_o
     hipLaunchKernelGGL(score_kernel, dim3((unsigned)(clusters_xcd * parts)), dim3(kScoreBlock), 0,
                        st, cluster_offsets, (const int32_t *)order, n_clusters, n_points, n_hyp,
                        rounds, (int32_t)parts, key0, key1, first_cluster, first_point,
-                       prune_from(rounds, tau, hyp_counts), pts, tau, best_key, hyp_counts);
+                       small_to(rounds, tau, kSingleLanesMax), prune_from(rounds, tau, hyp_counts),
+                       pts, tau, best_key, hyp_counts);
     if (timed) (void)hipEventRecord(tc.ev[2], st);
     launch_refit(false, cluster_offsets, order, nullptr, n_clusters,
                  order != nullptr ? (const int64_t *)n_big : nullptr, n_points, key0, key1,

@@ -16,6 +16,11 @@ constexpr uint32_t kPhiloxW0 = 0x9E3779B9u;
 constexpr uint32_t kPhiloxW1 = 0xBB67AE85u;
 
 
+// a ^ b ^ c in one instruction (truth table of the three-way exclusive or).
+__device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
+    return (uint32_t)__builtin_amdgcn_bitop3_b32((int)a, (int)b, (int)c, 0x96);
+}
+
 // Philox4x32-10 (Salmon et al., SC'11): ten rounds of two 32x32->64 products
 // mixed into the counter words, key advanced by the Weyl constants between rounds.
 __device__ __forceinline__ uint4 philox4x32_10(uint4 x, uint32_t k0, uint32_t k1) {
@@ -28,8 +33,8 @@ __device__ __forceinline__ uint4 philox4x32_10(uint4 x, uint32_t k0, uint32_t k1
         // one 32x32->64 multiply-add instruction per product
         const uint64_t p0 = (uint64_t)kPhiloxM0 * x.x;
         const uint64_t p1 = (uint64_t)kPhiloxM1 * x.z;
-        x = make_uint4((uint32_t)(p1 >> 32) ^ x.y ^ k0, (uint32_t)p1,
-                       (uint32_t)(p0 >> 32) ^ x.w ^ k1, (uint32_t)p0);
+        x = make_uint4(xor3((uint32_t)(p1 >> 32), x.y, k0), (uint32_t)p1,
+                       xor3((uint32_t)(p0 >> 32), x.w, k1), (uint32_t)p0);
     }
     return x;
 }

@@ -150,3 +150,54 @@ def test_long_cluster_and_batch(rv):
             assert np.array_equal(out[k].cpu().numpy().view(np.int32), single[k].view(np.int32)), k
         for k in ("n_inliers", "status", "n_near_tau", "inlier_bits"):
             assert np.array_equal(out[k].cpu().numpy(), single[k]), k
+
+
+@pytest.mark.parametrize("n_hyp,tau", [(1, 0.15), (255, 0.15), (256, 0.15), (512, 0.01), (700, 3.0),
+                                       (1024, 0.15), (1100, 0.15), (512, 0.25), (512, 1e-31),
+                                       (512, 1e16), (300, 1e-14), (300, 9e14)])
+def test_small_clusters(rv, n_hyp, tau):
+    """Clusters of 2 to 256 points (score_small: every hypothesis of a workgroup at
+    once, the compare as a clamped FMA) against lanes = points (no such form allowed),
+    per-hypothesis counts included, with edge clusters and tau at powers of two and
+    where the form does not apply."""
+    import torch
+
+    sizes = list(range(2, 10)) + [31, 32, 33, 63, 64, 65, 95, 127, 128, 129, 159, 160, 199, 200,
+                                  201, 255, 256]
+    clusters = [cluster(n, 700 + n, p_uniform=0.2) for n in sizes]
+    t, v = (a.copy() for a in cluster(90, 31, p_uniform=0.2))
+    t[::7], v[::11], v[::13] = np.nan, np.inf, -np.inf
+    clusters.append((t, v))
+    # Doppler values at exactly tau, and one unit in the last place either side, from
+    # the hypotheses of the others.
+    th = np.zeros(60, np.float32)
+    th[1::2] = 0.5
+    e = np.float32(tau)
+    clusters.append((th, np.where(np.arange(60) % 3 == 0, np.nextafter(e, np.float32(0)), e)))
+    clusters.append((np.full(40, 0.3), np.linspace(-1, 1, 40)))
+    theta, vd, off = frame_of(clusters)
+    t, v, o = (torch.from_numpy(a).cuda() for a in (theta, vd, off))
+    K = len(off) - 1
+    # Enough clusters for several blocks of hypotheses per workgroup.
+    copies = 2048 // K + 1
+    N = len(theta)
+    big_t, big_v = t.repeat(copies), v.repeat(copies)
+    base = torch.arange(copies, device="cuda", dtype=torch.int32)[:, None] * N
+    big_o = torch.cat([(o[:-1][None] + base).reshape(-1), base[-1:, 0] + N])
+    out = {}
+    for lanes_max in (0, 64):
+        for copy in (False, True):
+            tuning = rv.rv_tuning_default()
+            tuning.lanes_max_points = lanes_max
+            print(f"[gpu] small clusters H={n_hyp} tau={tau} lanes_max={lanes_max} many={copy}", flush=True)
+            a, b, c = (big_t, big_v, big_o) if copy else (t, v, o)
+            fo = torch.tensor([0, len(c) - 1], dtype=torch.int32, device="cuda")
+            seeds = torch.tensor([41], dtype=torch.int64, device="cuda")
+            r = rv.rv_estimate_velocity_batch(a, b, c, fo, seeds, n_hyp, tau, tuning=tuning,
+                                              want_bits=True, debug=True)
+            torch.cuda.synchronize()
+            out[lanes_max, copy] = {k: x.cpu().numpy() for k, x in r.items()}
+    for copy in (False, True):
+        for k, x in out[0, copy].items():
+            y = out[64, copy][k]
+            assert np.array_equal(x.view(np.uint8), y.view(np.uint8)), (k, copy)
