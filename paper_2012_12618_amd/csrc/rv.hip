@@ -102,7 +102,15 @@ namespace {
 constexpr int kScoreBlock = 256;        // score: 4 waves x 64 hypotheses, one per thread
 constexpr int kRefitBlock = 256;
 constexpr int kRefitWaves = kRefitBlock / 64;  // clusters per refit workgroup
-constexpr int kRefitBigClass = 41;             // size class of 1024 points: a workgroup each
+// Clusters from this size on are refit by a whole workgroup, smaller ones by a wave
+// each.  Many clusters (more than fit the chip at eight workgroups per CU): from
+// 1024 points, a wave alone being the cheaper form until its chain is the longest
+// thing left.  Fewer: from 256 points, where only the chain counts (700 clusters of
+// 8 to 1024 points: refit 14.2 us from 1024 on, 9.2 us from 256 on).
+constexpr int kRefitManyClusters = 2048;
+constexpr int kRefitBigPoints = 1024;
+constexpr int kRefitBigClass = 41;     // size class of 1024 points
+constexpr int kRefitBigClassFew = 33;  // and of 256 points
 constexpr int kXcds = 8;                // MI355X: 8 XCDs, workgroups dealt round-robin
 constexpr int kPrepBlock = 256;
 constexpr int kRowsMax = 16;            // register rows per pass, the most a tuning may name
@@ -233,7 +241,7 @@ __device__ __forceinline__ uint32_t wave_exclusive_sum(uint32_t x, int lane) {
 
 // Start of each size class in the dispatch order (largest class first) and the
 // number of clusters refit by a whole workgroup; the first wave of the block.
-__device__ __forceinline__ void plan_scan(const uint32_t *count, uint32_t *start,
+__device__ __forceinline__ void plan_scan(const uint32_t *count, uint32_t *start, int big_class,
                                           int64_t *__restrict__ n_big) {
     if (threadIdx.x < kWave) {
         // Position q = 0, 1, ... in the dispatch order is class kSizeClasses - 1 - q.
@@ -243,15 +251,15 @@ __device__ __forceinline__ void plan_scan(const uint32_t *count, uint32_t *start
         const uint32_t excl = wave_exclusive_sum(a + b, lane);
         start[c_hi] = excl;
         start[c_lo] = excl + a;
-        // Clusters refit by a whole workgroup: classes kRefitBigClass and up.
-        if (c_hi == kRefitBigClass) *n_big = excl + a;
-        if (c_lo == kRefitBigClass) *n_big = excl + a + b;
+        // Clusters refit by a whole workgroup: classes big_class and up.
+        if (c_hi == big_class) *n_big = excl + a;
+        if (c_lo == big_class) *n_big = excl + a + b;
     }
 }
 
 constexpr int kPlanUnroll = 16;
 __device__ void plan_order(const int32_t *__restrict__ off, int64_t point_base, int64_t n_clusters,
-                           int64_t n_points, int32_t *__restrict__ order,
+                           int64_t n_points, int big_class, int32_t *__restrict__ order,
                            int64_t *__restrict__ n_big) {
     __shared__ uint32_t count[kSizeClasses];
     __shared__ uint32_t start[kSizeClasses];
@@ -272,7 +280,7 @@ __device__ void plan_order(const int32_t *__restrict__ off, int64_t point_base, 
         for (int u = 0; u < kPlanUnroll; ++u)
             if (cls[u] >= 0) atomicAdd(&count[cls[u]], 1u);
         __syncthreads();
-        plan_scan(count, start, n_big);
+        plan_scan(count, start, big_class, n_big);
         __syncthreads();
 #pragma unroll
         for (int u = 0; u < kPlanUnroll; ++u) {
@@ -295,7 +303,7 @@ __device__ void plan_order(const int32_t *__restrict__ off, int64_t point_base, 
             if (cls[u] >= 0) atomicAdd(&count[cls[u]], 1u);
     }
     __syncthreads();
-    plan_scan(count, start, n_big);
+    plan_scan(count, start, big_class, n_big);
     __syncthreads();
     for (int64_t k0 = threadIdx.x; k0 < n_clusters; k0 += group) {
         int cls[kPlanUnroll];
@@ -343,10 +351,11 @@ __global__ __launch_bounds__(kPrepBlock) void prep_kernel(
     const float *__restrict__ theta, const float *__restrict__ vd, int64_t n_points,
     StagedPoint *__restrict__ staged, uint32_t *__restrict__ bits,
     int64_t n_words, const int32_t *__restrict__ off, int64_t point_base, int64_t n_clusters,
-    int32_t *__restrict__ order, int64_t *__restrict__ n_big,
+    int32_t big_class, int32_t *__restrict__ order, int64_t *__restrict__ n_big,
     unsigned long long *__restrict__ best_key) {
     if (blockIdx.x == 0) {
-        if (order != nullptr) plan_order(off, point_base, n_clusters, n_points, order, n_big);
+        if (order != nullptr)
+            plan_order(off, point_base, n_clusters, n_points, big_class, order, n_big);
         return;
     }
     const int64_t p = (int64_t)(blockIdx.x - 1) * kPrepBlock + threadIdx.x;
@@ -1839,6 +1848,15 @@ __device__ __forceinline__ void refit_cluster(Span sp, ClusterId id, unsigned lo
 
 // ---- single frame ---------------------------------------------------------
 
+// refit_big (a workgroup has all hypotheses of a cluster, clusters are many): the
+// workgroup refits its cluster itself from kRefitBigPoints on.  The points are still
+// in the XCD's L2 and the work runs beside other clusters' scoring.  Smaller ones
+// are cheaper a wave each (refit_planned): here they would hold a whole workgroup for
+// the refit's chain of latencies.  4096 clusters of 8 to 4096 points, 1024
+// hypotheses: score and refit 69.7 + 16.9 us apart, 73.8 + 10.9 us so (call 94.4 and
+// 92.5 us); from 512 points on, 4096 clusters of 512 points take 97.4 us for 91.9.
+// The batched kernel does not: its registers spill (256 frames 2369 to 2426 us).
+//
 // Work item = (cluster, `rounds` blocks of 256 hypotheses).  Block i takes the
 // item that keeps clusters in the planned order while all items of one cluster
 // run on the same XCD (blocks are dealt to the 8 XCDs round-robin), sharing that
@@ -1848,8 +1866,9 @@ __global__ __launch_bounds__(kScoreBlock) __attribute__((amdgpu_waves_per_eu(8))
     const int32_t *__restrict__ off, const int32_t *__restrict__ order, int64_t n_clusters,
     int64_t n_points, int32_t n_hyp, int32_t rounds, int32_t parts, uint32_t key0, uint32_t key1,
     uint32_t cluster_base, int64_t point_base, int32_t small_max, int64_t prune, Points pts,
-    float tau, unsigned long long *__restrict__ best_key, int32_t *__restrict__ hyp_counts) {
+    float tau, unsigned long long *__restrict__ best_key, Outputs o, bool refit_big) {
     __shared__ ScoreShared<kScoreBlock> s;
+    __shared__ RefitShared s_refit;
     const uint32_t xcd = blockIdx.x % kXcds;
     const uint32_t r = blockIdx.x / kXcds;
     const int64_t j = xcd + (int64_t)kXcds * (r / (uint32_t)parts);
@@ -1866,25 +1885,30 @@ __global__ __launch_bounds__(kScoreBlock) __attribute__((amdgpu_waves_per_eu(8))
     const int64_t left = n_hyp - first;
     const unsigned long long key = score_hypotheses<kScoreBlock>(
         sp, id, first, left < most ? (int)left : most, n_hyp, pts, tau, kRowsMax, kSingleLanesMax,
-        small_max, prune, s, &best_key[k], hyp_counts);
-    merge_key(&best_key[k], key, __builtin_amdgcn_readfirstlane(threadIdx.x / kWave),
-              threadIdx.x % kWave);
+        small_max, prune, s, &best_key[k], o.hyp_counts);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    if (refit_big && sp.n >= kRefitBigPoints)
+        refit_cluster(sp, id, key, pts, tau, o, wave, kScoreBlock / kWave, s_refit);
+    else
+        merge_key(&best_key[k], key, wave, threadIdx.x % kWave);
 }
 
 // Refit of a frame's or batch's clusters over their planned (largest-first)
 // positions, in one launch: workgroups [0, n_big) take the first n_big
-// clusters (size class >= kRefitBigClass, i.e. >= 1024 points), one each with
+// clusters (kRefitBigPoints or more, see there for frames of few), one each with
 // all four waves; the following workgroups take the other
 // clusters four at a time, one per wave.  n_big is counted on the
 // device by the ordering pass; without an order (n_big == nullptr) every
 // cluster gets a workgroup.  The grid is an upper bound (one workgroup per
-// cluster); surplus workgroups exit at once.
+// cluster); surplus workgroups exit at once.  big_done: the first n_big clusters
+// were refit by their scoring workgroups.
 template <typename ClusterAt>
 __device__ __forceinline__ void refit_planned(int64_t n_clusters, const int64_t *n_big,
                                               const ClusterAt &at, const Points &pts, float tau,
-                                              const Outputs &o, RefitShared &sh) {
-    const int64_t b = blockIdx.x;
+                                              const Outputs &o, RefitShared &sh,
+                                              bool big_done) {
     const int64_t big = n_big != nullptr ? *n_big : n_clusters;
+    const int64_t b = big_done ? blockIdx.x + big : blockIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const bool all = b < big;  // the whole workgroup on one cluster
     const int64_t j = all ? b : big + (b - big) * kRefitWaves + wave;
@@ -1919,11 +1943,11 @@ __global__ __launch_bounds__(kRefitBlock) void refit_kernel(
     const int32_t *__restrict__ off, const int32_t *__restrict__ order, int64_t n_clusters,
     const int64_t *__restrict__ n_big, int64_t n_points, uint32_t key0, uint32_t key1,
     uint32_t cluster_base, int64_t point_base, Points pts,
-    const unsigned long long *__restrict__ best_key, float tau, Outputs o) {
+    const unsigned long long *__restrict__ best_key, float tau, Outputs o, bool big_done) {
     __shared__ RefitShared s_refit;
     const FrameClusterAt at = {off, order, n_points, key0, key1, cluster_base, point_base,
                                best_key};
-    refit_planned(n_clusters, n_big, at, pts, tau, o, s_refit);
+    refit_planned(n_clusters, n_big, at, pts, tau, o, s_refit, big_done);
 }
 
 // ---- many frames in one launch sequence ----------------------------------
@@ -2240,7 +2264,7 @@ __global__ __launch_bounds__(kRefitBlock) void batch_refit_kernel(
     Points pts, const unsigned long long *__restrict__ best_key, float tau, Outputs o) {
     __shared__ RefitShared s_refit;
     const BatchClusterAt at = {desc, best_key};
-    refit_planned(n_clusters, n_big, at, pts, tau, o, s_refit);
+    refit_planned(n_clusters, n_big, at, pts, tau, o, s_refit, false);
 }
 
 __global__ __launch_bounds__(kPrepBlock) void philox_kernel(const uint32_t *__restrict__ ctr,
@@ -2444,7 +2468,7 @@ int32_t batch_parts(const BatchArgs &a) {
 void launch_refit(bool batch, const int32_t *off, const int32_t *order, const ItemDesc *desc,
                   int64_t n_clusters, const int64_t *n_big, int64_t n_points, uint32_t key0,
                   uint32_t key1, uint32_t cluster_base, int64_t point_base, const Points &pts,
-                  const unsigned long long *best_key, float tau, const Outputs &o,
+                  const unsigned long long *best_key, float tau, const Outputs &o, bool big_done,
                   hipStream_t st) {
     if (batch)
         hipLaunchKernelGGL(batch_refit_kernel, dim3((unsigned)n_clusters), dim3(kRefitBlock), 0, st,
@@ -2452,7 +2476,7 @@ void launch_refit(bool batch, const int32_t *off, const int32_t *order, const It
     else
         hipLaunchKernelGGL(refit_kernel, dim3((unsigned)n_clusters), dim3(kRefitBlock), 0, st, off,
                            order, n_clusters, n_big, n_points, key0, key1, cluster_base,
-                           point_base, pts, best_key, tau, o);
+                           point_base, pts, best_key, tau, o, big_done);
 }
 
 // Persistent grid of the batched scoring kernel on the current device.
@@ -2531,7 +2555,7 @@ int launch_batch(const BatchArgs &a, unsigned grid, hipStream_t st, bool allow_t
                            a.tau, queues, best_key, a.o.hyp_counts);
     if (timed) (void)hipEventRecord(tc.ev[2], st);
     launch_refit(true, nullptr, nullptr, (const ItemDesc *)desc, a.n_clusters, n_big,
-                 a.n_points, 0, 0, 0, 0, pts, best_key, a.tau, a.o, st);
+                 a.n_points, 0, 0, 0, 0, pts, best_key, a.tau, a.o, false, st);
     if (timed) {
         (void)hipEventRecord(tc.ev[3], st);
         keep_timed_call(tc);
@@ -2658,22 +2682,25 @@ int estimate_frame(const float *theta, const float *vd, const int32_t *cluster_o
     }
     const int32_t rounds = score_rounds(n_clusters, blocks_per_cluster);
     const int64_t parts = (blocks_per_cluster + rounds - 1) / rounds;
+    const bool many = n_clusters >= kRefitManyClusters;
+    const bool refit_big = parts == 1 && many && order != nullptr;  // the order counts them
     int64_t prep_items = n_points > n_words ? n_points : n_words;
     prep_items = prep_items > n_clusters ? prep_items : n_clusters;
     const int64_t prep_blocks = (prep_items + kPrepBlock - 1) / kPrepBlock + 1;  // + planner
     hipLaunchKernelGGL(prep_kernel, dim3((unsigned)prep_blocks), dim3(kPrepBlock), 0, st, theta,
                        vd, n_points, staged, inlier_bits, n_words, cluster_offsets,
-                       first_point, n_clusters, order, n_big, best_key);
+                       first_point, n_clusters, many ? kRefitBigClass : kRefitBigClassFew,
+                       order, n_big, best_key);
     if (timed) (void)hipEventRecord(tc.ev[1], st);
     hipLaunchKernelGGL(score_kernel, dim3((unsigned)(clusters_xcd * parts)), dim3(kScoreBlock), 0,
                        st, cluster_offsets, (const int32_t *)order, n_clusters, n_points, n_hyp,
                        rounds, (int32_t)parts, key0, key1, first_cluster, first_point,
                        small_to(rounds, tau, kSingleLanesMax), prune_from(rounds, tau, hyp_counts),
-                       pts, tau, best_key, hyp_counts);
+                       pts, tau, best_key, o, refit_big);
     if (timed) (void)hipEventRecord(tc.ev[2], st);
     launch_refit(false, cluster_offsets, order, nullptr, n_clusters,
                  order != nullptr ? (const int64_t *)n_big : nullptr, n_points, key0, key1,
-                 first_cluster, first_point, pts, best_key, tau, o, st);
+                 first_cluster, first_point, pts, best_key, tau, o, refit_big, st);
     if (timed) {
         (void)hipEventRecord(tc.ev[3], st);
         keep_timed_call(tc);
