@@ -101,7 +101,7 @@ namespace {
 
 constexpr int kScoreBlock = 256;        // score: 4 waves x 64 hypotheses, one per thread
 constexpr int kRefitBlock = 256;
-constexpr int kRefitWaves = kRefitBlock / 64;  // clusters per refit workgroup
+constexpr int kLongBlock = 1024;        // score and refit of long clusters (long_clusters)
 // Clusters from this size on are refit by a whole workgroup, smaller ones by a wave
 // each.  Many clusters (more than fit the chip at eight workgroups per CU): from
 // 1024 points, a wave alone being the cheaper form until its chain is the longest
@@ -924,7 +924,7 @@ __device__ __forceinline__ uint32_t fp16_counts(Span sp, const Points &pts, int 
 //   1. reference r: among the first 64 hypotheses the one with the most inliers in
 //      a strided sample of the points;
 //   2. one sweep over the cluster counts r exactly (T) and sorts the points
-//      into a table of direction (kAngleBins) x signed residual under r;
+//      into a table of direction (kAngleBins<B>) x signed residual under r;
 //   3. every hypothesis h gets an upper bound of its count from the table: a
 //      point with direction u is an inlier of h only if its residual under r
 //      lies within tau of (h - r).u, and over one direction bin (h - r).u
@@ -946,7 +946,7 @@ __device__ __forceinline__ uint32_t fp16_counts(Span sp, const Points &pts, int 
 // frames of equal clusters, 4.2M hypotheses: 4096 clusters of 512 points 152 and
 // 78 us, 1024 of 2048 points 151 and 52 us; the 4096-cluster frame of 8 to 4096
 // points 193 and 84 us; 64 clusters of 65,536 points at 4096 hypotheses 1.40 and
-// 0.33 ms.
+// 0.10 ms (0.27 ms in small workgroups, see long_clusters).
 //
 // Rounding.  A point with |float32 residual under h| < tau has an exact
 // residual (of the float32 cos, sin, v_d and velocities) within
@@ -971,7 +971,14 @@ constexpr int kSample = 32;         // points of the sample
 __host__ __device__ constexpr int prune_min(int rounds) {
     return rounds == 1 ? 320 : rounds == 2 ? 160 : 128;
 }
-constexpr int kAngleBins = 8;
+
+// Direction bins.  A long cluster's time is its sweeps and counts, and its large
+// workgroup (long_clusters) has the LDS for four times as many: 64 clusters of 65,536
+// points, 1024 of their 4096 hypotheses per workgroup, 39 to count for 58 (modelled),
+// call 180 us with 32 directions, 199 us with 16, 226 us with 8.  Twice the residual
+// bins as well: 177 us, but 130 for 122 us at 128 clusters of 16,384 points.
+template <int B>
+constexpr int kAngleBins = B == kLongBlock ? 32 : 8;
 constexpr int kResidualBins = 256;  // 128 per sign, 16 per octave of |e| + unit (residual_bin)
 constexpr int kResidualRow = kResidualBins + 1;
 constexpr float kPruneMaxSpeed = 1e15f;  // references beyond it are not used
@@ -980,9 +987,9 @@ template <int B>
 struct PruneShared {
     float4 hyp[kPruneHyp / 2];  // (vx, vy) pairs
     LaneTile<kSample> sample;
-    float4 dir[kAngleBins];     // centre (cos, sin), half width w, w^2 / 2
+    float4 dir[kAngleBins<B>];     // centre (cos, sin), half width w, w^2 / 2
     union {
-        uint32_t hist[kAngleBins * kResidualRow];
+        uint32_t hist[kAngleBins<B> * kResidualRow];
         struct {
             uint32_t part[B / kWave][kWave];
             float list[2 * kWave] __attribute__((aligned(16)));
@@ -1067,6 +1074,7 @@ __device__ __forceinline__ unsigned long long score_pruned(
     Span sp, ClusterId id, int64_t h_first, int nh, const Points &pts, float tau,
     PruneShared<B> &sh, const unsigned long long *best_key) {
     constexpr int kPruneRounds = kPruneHyp / B;
+    constexpr int kDirs = kAngleBins<B>;
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int lane = tid % kWave;
@@ -1087,7 +1095,7 @@ __device__ __forceinline__ unsigned long long score_pruned(
         qlo = fminf(qlo, q);
         qhi = fmaxf(qhi, q);
     });
-    for (int i = tid; i < kAngleBins * kResidualRow; i += B) sh.u.hist[i] = 0;
+    for (int i = tid; i < kDirs * kResidualRow; i += B) sh.u.hist[i] = 0;
     // The hypotheses, two at a time so that their seed loads overlap (NaN for a
     // degenerate pair and past the last).
     float2 own = make_float2(0.0f, 0.0f);  // the thread's first
@@ -1129,13 +1137,13 @@ __device__ __forceinline__ unsigned long long score_pruned(
         q0 = fminf(q0, sh.lo[w]);
         q1 = fmaxf(q1, sh.hi[w]);
     }
-    const float width = fmaxf(q1 - q0, 1e-6f) * (1.0f / kAngleBins);
-    if (tid < kAngleBins) {
+    const float width = fmaxf(q1 - q0, 1e-6f) * (1.0f / kDirs);
+    if (tid < kDirs) {
         // A direction bin's centre and half width (asin x <= 1.05 x up to half
         // a radian: bins are narrower than 60 degrees), widened for the
         // rounding of direction_key.
         const float2 a = key_direction(q0 + tid * width);
-        const float2 b = key_direction(tid == kAngleBins - 1 ? q1 : q0 + (tid + 1) * width);
+        const float2 b = key_direction(tid == kDirs - 1 ? q1 : q0 + (tid + 1) * width);
         const float dx = b.x - a.x, dy = b.y - a.y;
         const float w = 0.53f * __builtin_amdgcn_sqrtf(dx * dx + dy * dy) + 0x1p-15f;
         const float mx = a.x + b.x, my = a.y + b.y;
@@ -1163,7 +1171,7 @@ __device__ __forceinline__ unsigned long long score_pruned(
             const float e = __builtin_fmaf(-ry, u.s, __builtin_fmaf(-rx, u.c, u.v));
             t += in && __builtin_fabsf(e) < tau ? 1u : 0u;
             int b = (int)((direction_key(u.c, u.s) - q0) * scale);
-            b = b < kAngleBins - 1 ? b : kAngleBins - 1;
+            b = b < kDirs - 1 ? b : kDirs - 1;
             b = b > 0 ? b : 0;
             if (in && u.v < __builtin_inff())
                 atomicAdd(&sh.u.hist[b * kResidualRow + residual_bin(e * sigma)], 1u);
@@ -1177,9 +1185,9 @@ __device__ __forceinline__ unsigned long long score_pruned(
         best = uniform_u64(hyp_key(t, h_first + r_local));
         // Prefix sums along each row: 32 threads per row, eight bins each.
         constexpr int kRowThreads = 32;
-        static_assert(kAngleBins * kRowThreads <= B && kAngleBins * kRowThreads % kWave == 0 &&
+        static_assert(kDirs * kRowThreads <= B && kDirs * kRowThreads % kWave == 0 &&
                       kResidualBins == kRowThreads * 8, "one pass of whole waves");
-        if (wave < kAngleBins * kRowThreads / kWave) {
+        if (wave < kDirs * kRowThreads / kWave) {
             uint32_t *row =
                 sh.u.hist + (tid / kRowThreads) * kResidualRow + (tid % kRowThreads) * 8;
             uint32_t x[8], sum = 0;
@@ -1202,7 +1210,7 @@ __device__ __forceinline__ unsigned long long score_pruned(
         // 3. Bounds.
         float w2 = sh.dir[0].w;
 #pragma unroll
-        for (int b = 1; b < kAngleBins; ++b) w2 = fmaxf(w2, sh.dir[b].w);
+        for (int b = 1; b < kDirs; ++b) w2 = fmaxf(w2, sh.dir[b].w);
 #pragma unroll
         for (int q = 0; q < kPruneRounds; ++q) {
             ub[q] = 0;
@@ -1215,7 +1223,7 @@ __device__ __forceinline__ unsigned long long score_pruned(
                                                   (tau + 0x1p-18f * (tau + m)) * sigma);
                 uint32_t bound = 0;
 #pragma unroll 4
-                for (int b = 0; b < kAngleBins; ++b) {
+                for (int b = 0; b < kDirs; ++b) {
                     const float4 d = sh.dir[b];
                     const float f = __builtin_fmaf(dx, d.x, dy * d.y);
                     const float g = __builtin_fmaf(dy, d.x, -dx * d.y);
@@ -1862,12 +1870,13 @@ __device__ __forceinline__ void refit_cluster(Span sp, ClusterId id, unsigned lo
 // run on the same XCD (blocks are dealt to the 8 XCDs round-robin), sharing that
 // XCD's L2 copy of the cluster's points.  Eight waves per SIMD: the scoring loop
 // fits in 64 VGPRs.
-__global__ __launch_bounds__(kScoreBlock) __attribute__((amdgpu_waves_per_eu(8))) void score_kernel(
+template <int B>
+__global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(B == kLongBlock ? 4 : 8))) void score_kernel(
     const int32_t *__restrict__ off, const int32_t *__restrict__ order, int64_t n_clusters,
     int64_t n_points, int32_t n_hyp, int32_t rounds, int32_t parts, uint32_t key0, uint32_t key1,
     uint32_t cluster_base, int64_t point_base, int32_t small_max, int64_t prune, Points pts,
     float tau, unsigned long long *__restrict__ best_key, Outputs o, bool refit_big) {
-    __shared__ ScoreShared<kScoreBlock> s;
+    __shared__ ScoreShared<B> s;
     __shared__ RefitShared s_refit;
     const uint32_t xcd = blockIdx.x % kXcds;
     const uint32_t r = blockIdx.x / kXcds;
@@ -1880,15 +1889,15 @@ __global__ __launch_bounds__(kScoreBlock) __attribute__((amdgpu_waves_per_eu(8))
     id.key0 = key0;
     id.key1 = key1;
     const Span sp = cluster_span(off, k, n_points, point_base);
-    const int most = rounds * kScoreBlock;
+    const int most = rounds * B;
     const int64_t first = (int64_t)(r % (uint32_t)parts) * most;
     const int64_t left = n_hyp - first;
-    const unsigned long long key = score_hypotheses<kScoreBlock>(
+    const unsigned long long key = score_hypotheses<B>(
         sp, id, first, left < most ? (int)left : most, n_hyp, pts, tau, kRowsMax, kSingleLanesMax,
         small_max, prune, s, &best_key[k], o.hyp_counts);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     if (refit_big && sp.n >= kRefitBigPoints)
-        refit_cluster(sp, id, key, pts, tau, o, wave, kScoreBlock / kWave, s_refit);
+        refit_cluster(sp, id, key, pts, tau, o, wave, B / kWave, s_refit);
     else
         merge_key(&best_key[k], key, wave, threadIdx.x % kWave);
 }
@@ -1902,19 +1911,20 @@ __global__ __launch_bounds__(kScoreBlock) __attribute__((amdgpu_waves_per_eu(8))
 // cluster gets a workgroup.  The grid is an upper bound (one workgroup per
 // cluster); surplus workgroups exit at once.  big_done: the first n_big clusters
 // were refit by their scoring workgroups.
-template <typename ClusterAt>
+template <int B, typename ClusterAt>
 __device__ __forceinline__ void refit_planned(int64_t n_clusters, const int64_t *n_big,
                                               const ClusterAt &at, const Points &pts, float tau,
                                               const Outputs &o, RefitShared &sh,
                                               bool big_done) {
+    constexpr int kWaves = B / kWave;
     const int64_t big = n_big != nullptr ? *n_big : n_clusters;
     const int64_t b = big_done ? blockIdx.x + big : blockIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const bool all = b < big;  // the whole workgroup on one cluster
-    const int64_t j = all ? b : big + (b - big) * kRefitWaves + wave;
+    const int64_t j = all ? b : big + (b - big) * kWaves + wave;
     if (j >= n_clusters) return;
     refit_cluster(at.span(j), at.id(j), at.best(j), pts, tau, o, all ? wave : 0,
-                  all ? kRefitWaves : 1, sh);
+                  all ? kWaves : 1, sh);
 }
 
 // Cluster at planned position j of a single frame.
@@ -1939,7 +1949,8 @@ struct FrameClusterAt {
     }
 };
 
-__global__ __launch_bounds__(kRefitBlock) void refit_kernel(
+template <int B>
+__global__ __launch_bounds__(B) void refit_kernel(
     const int32_t *__restrict__ off, const int32_t *__restrict__ order, int64_t n_clusters,
     const int64_t *__restrict__ n_big, int64_t n_points, uint32_t key0, uint32_t key1,
     uint32_t cluster_base, int64_t point_base, Points pts,
@@ -1947,7 +1958,7 @@ __global__ __launch_bounds__(kRefitBlock) void refit_kernel(
     __shared__ RefitShared s_refit;
     const FrameClusterAt at = {off, order, n_points, key0, key1, cluster_base, point_base,
                                best_key};
-    refit_planned(n_clusters, n_big, at, pts, tau, o, s_refit, big_done);
+    refit_planned<B>(n_clusters, n_big, at, pts, tau, o, s_refit, big_done);
 }
 
 // ---- many frames in one launch sequence ----------------------------------
@@ -2207,32 +2218,35 @@ __global__ __launch_bounds__(kPrepBlock) void batch_scatter_kernel(
 // of rows, measured 1-2 % faster than seven waves without them); kFp16: the
 // instantiation that also runs FP16-form items (launched only when the tuning
 // enables that form, so that the float32-only kernel keeps its own register
-// allocation), at seven waves per SIMD.
-template <bool kFp16>
-__global__ __launch_bounds__(kScoreBlock) __attribute__((amdgpu_waves_per_eu(kFp16 ? 7 : 8))) void batch_score_kernel(
+// allocation), at seven waves per SIMD.  The large workgroups of long clusters come
+// one to a CU, so they have the registers of four waves per SIMD.
+template <bool kFp16, int B>
+__global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(B == kLongBlock ? 4 : kFp16 ? 7 : 8))) void batch_score_kernel(
     const ItemDesc *__restrict__ desc, int64_t n_clusters, int32_t n_hyp,
     int32_t rounds, int32_t parts, int64_t prune, Points pts, float tau,
     unsigned long long *__restrict__ queues, unsigned long long *__restrict__ best_key,
     int32_t *__restrict__ hyp_counts) {
-    __shared__ ScoreShared<kScoreBlock> s;
+    __shared__ ScoreShared<B> s;
     __shared__ unsigned long long s_item;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int lane = threadIdx.x % kWave;
     const uint32_t home = blockIdx.x % kXcds;
     for_each_item(queues, n_clusters, parts, home, wave, lane, s_item, [&](int64_t j, int part) {
         const ItemDesc d = desc[j];
-        const int most = rounds * kScoreBlock;
+        const int most = rounds * B;
         const int64_t first = (int64_t)part * most;
         const int64_t left = n_hyp - first;
         const int nh = left < most ? (int)left : most;
         if constexpr (kFp16) {
             if (d.form == kFormFp16 && d.n >= prune) {
                 const unsigned long long key =
-                    score_pruned<kScoreBlock, true>(desc_span(d), desc_id(d), first, nh, pts, tau,
-                                                    s.prune(), &best_key[d.out]);
+                    score_pruned<B, true>(desc_span(d), desc_id(d), first, nh, pts, tau, s.prune(),
+                                          &best_key[d.out]);
                 merge_key(&best_key[d.out], key, wave, lane);
                 return;
             }
+        }
+        if constexpr (kFp16 && B == kScoreBlock) {
             if (d.form == kFormFp16) {
                 const int b0 = part * rounds;
                 for (int b = b0; b < b0 + (nh + kScoreBlock - 1) / kScoreBlock; ++b) {
@@ -2243,7 +2257,7 @@ __global__ __launch_bounds__(kScoreBlock) __attribute__((amdgpu_waves_per_eu(kFp
                 return;
             }
         }
-        const unsigned long long key = score_hypotheses<kScoreBlock>(
+        const unsigned long long key = score_hypotheses<B>(
             desc_span(d), desc_id(d), first, nh, n_hyp, pts, tau, d.rows, desc_lanes(d),
             d.form == kFormSmall ? kLaneTile : 0, desc_prune(d), s, &best_key[d.out], hyp_counts);
         merge_key(&best_key[d.out], key, wave, lane);
@@ -2259,12 +2273,13 @@ struct BatchClusterAt {
     __device__ unsigned long long best(int64_t j) const { return best_key[desc[j].out]; }
 };
 
-__global__ __launch_bounds__(kRefitBlock) void batch_refit_kernel(
+template <int B>
+__global__ __launch_bounds__(B) void batch_refit_kernel(
     const ItemDesc *__restrict__ desc, int64_t n_clusters, const int64_t *__restrict__ n_big,
     Points pts, const unsigned long long *__restrict__ best_key, float tau, Outputs o) {
     __shared__ RefitShared s_refit;
     const BatchClusterAt at = {desc, best_key};
-    refit_planned(n_clusters, n_big, at, pts, tau, o, s_refit, false);
+    refit_planned<B>(n_clusters, n_big, at, pts, tau, o, s_refit, false);
 }
 
 __global__ __launch_bounds__(kPrepBlock) void philox_kernel(const uint32_t *__restrict__ ctr,
@@ -2453,14 +2468,70 @@ bool use_cluster_path(int64_t n_clusters, int64_t n_points, int32_t n_hyp,
            n_clusters <= kSmallFrameMaxClusters;
 }
 
-int32_t batch_rounds(const BatchArgs &a) {
-    return score_rounds(a.n_clusters, blocks_of(a.n_hyp));
+// Split of a call's scoring: workgroups of `block` threads, each with `rounds` blocks
+// of hypotheses of a cluster, `parts` of them per cluster; the pruned form's smallest
+// and score_small's largest cluster.
+struct ScorePlan {
+    int32_t block, rounds, parts, small_max;
+    int64_t prune;
+};
+
+// Few and long clusters (the mean length is what the host knows; the choice is one
+// for speed alone) are scored by workgroups of 1024 threads with up to 1024 hypotheses
+// each and refit by such.  In the small workgroups every 256 hypotheses of a cluster
+// sweep all its points for their own table: 64 clusters of 65,536 points at 4096
+// hypotheses, 16 workgroups each, score in 270 us and refit in 57 us, 4 and 1 large
+// ones in 105 and 29 us (call 378 and 180 us, in the FP16 form 460 and 201 us).
+// The line: scoring of 64 clusters at 1024 hypotheses 44.7 and 35.3 us at 8192 points,
+// 28.0 and 28.8 us at 4096.  Beyond a workgroup per CU a large one's share is too
+// coarse (320 x 8192 points at 300 hypotheses 53 and 65 us) unless it takes the place
+// of four (512 x 16,384 points at 1024 hypotheses 188 and 140 us, 700 x 8192 points
+// 120 and 110 us); refit of 256 clusters of 8192 points 14.6 and 14.4 us, of 512
+// 18.9 and 23.6 us.
+constexpr int64_t kLongPoints = 8192;
+constexpr int64_t kLongClusters = 256;
+
+bool long_clusters(int64_t n_clusters, int64_t n_points) {
+    return n_clusters > 0 && n_points / n_clusters >= kLongPoints;
 }
 
-// Work items per cluster.
-int32_t batch_parts(const BatchArgs &a) {
-    const int32_t rounds = batch_rounds(a);
-    return (int32_t)((blocks_of(a.n_hyp) + rounds - 1) / rounds);
+ScorePlan plan_score(int64_t n_clusters, int64_t n_points, int32_t n_hyp, float tau,
+                     const int32_t *hyp_counts, int32_t lanes_max, int32_t fp16_min) {
+    ScorePlan p;
+    p.block = kScoreBlock;
+    p.rounds = score_rounds(n_clusters, blocks_of(n_hyp));
+    const auto parts = [n_hyp](int64_t each) { return (int32_t)((n_hyp + each - 1) / each); };
+    p.parts = parts(kScoreBlock * p.rounds);
+    int32_t blocks = p.rounds;  // of 256 hypotheses, per workgroup
+    // The large workgroups have no FP16 form of a full count: only where every
+    // cluster of that form is pruned.
+    constexpr int32_t kLongBlocks = kLongBlock / kScoreBlock;
+    if (long_clusters(n_clusters, n_points) &&
+        (n_clusters <= kLongClusters || p.parts >= 4 * parts(kLongBlock)) &&
+        prune_from(kLongBlocks, tau, hyp_counts) != INT64_MAX &&
+        (fp16_min <= 0 || fp16_min >= prune_min(kLongBlocks))) {
+        p.block = kLongBlock;
+        p.rounds = 1;
+        p.parts = parts(kLongBlock);
+        blocks = kLongBlocks;
+    }
+    p.prune = prune_from(blocks, tau, hyp_counts);
+    p.small_max = small_to(blocks, tau, lanes_max);
+    if (fp16_min > 0 && p.small_max >= fp16_min) p.small_max = fp16_min - 1;
+    return p;
+}
+
+ScorePlan batch_plan(const BatchArgs &a) {
+    return plan_score(a.n_clusters, a.n_points, a.n_hyp, a.tau, a.o.hyp_counts,
+                      a.tuning.lanes_max_points, a.tuning.fp16_min_points);
+}
+
+using BatchScore = void (*)(const ItemDesc *, int64_t, int32_t, int32_t, int32_t, int64_t, Points,
+                            float, unsigned long long *, unsigned long long *, int32_t *);
+BatchScore batch_score(bool fp16, int32_t block) {
+    if (block == kLongBlock)
+        return fp16 ? batch_score_kernel<true, kLongBlock> : batch_score_kernel<false, kLongBlock>;
+    return fp16 ? batch_score_kernel<true, kScoreBlock> : batch_score_kernel<false, kScoreBlock>;
 }
 
 // The refit kernel over planned positions; n_big (device, nullable) is the
@@ -2470,13 +2541,17 @@ void launch_refit(bool batch, const int32_t *off, const int32_t *order, const It
                   uint32_t key1, uint32_t cluster_base, int64_t point_base, const Points &pts,
                   const unsigned long long *best_key, float tau, const Outputs &o, bool big_done,
                   hipStream_t st) {
+    const bool large = long_clusters(n_clusters, n_points) && n_clusters <= kLongClusters;
+    const dim3 block(large ? kLongBlock : kRefitBlock);
     if (batch)
-        hipLaunchKernelGGL(batch_refit_kernel, dim3((unsigned)n_clusters), dim3(kRefitBlock), 0, st,
-                           desc, n_clusters, n_big, pts, best_key, tau, o);
+        hipLaunchKernelGGL(large ? batch_refit_kernel<kLongBlock> : batch_refit_kernel<kRefitBlock>,
+                           dim3((unsigned)n_clusters), block, 0, st, desc, n_clusters, n_big, pts,
+                           best_key, tau, o);
     else
-        hipLaunchKernelGGL(refit_kernel, dim3((unsigned)n_clusters), dim3(kRefitBlock), 0, st, off,
-                           order, n_clusters, n_big, n_points, key0, key1, cluster_base,
-                           point_base, pts, best_key, tau, o, big_done);
+        hipLaunchKernelGGL(large ? refit_kernel<kLongBlock> : refit_kernel<kRefitBlock>,
+                           dim3((unsigned)n_clusters), block, 0, st, off, order, n_clusters, n_big,
+                           n_points, key0, key1, cluster_base, point_base, pts, best_key, tau, o,
+                           big_done);
 }
 
 // Persistent grid of the batched scoring kernel on the current device.
@@ -2485,16 +2560,15 @@ int persistent_blocks(const BatchArgs &a, unsigned *grid) {
     if (a.n_clusters == 0) return RV_OK;
     int fit = 0;
     const int cus = device_cus();
-    const hipError_t e =
-        a.tuning.fp16_min_points > 0
-            ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&fit, batch_score_kernel<true>, kScoreBlock, 0)
-            : hipOccupancyMaxActiveBlocksPerMultiprocessor(&fit, batch_score_kernel<false>, kScoreBlock, 0);
+    const ScorePlan plan = batch_plan(a);
+    const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
+        &fit, batch_score(a.tuning.fp16_min_points > 0, plan.block), plan.block, 0);
     if (cus <= 0 || e != hipSuccess)
         return fail(RV_ERR_HIP, "device query failed");
     const int asked = a.tuning.blocks_per_cu;
     int per_cu = asked > 0 && asked < fit ? asked : fit;
     if (per_cu < 1) per_cu = 1;
-    const int64_t items = a.n_clusters * batch_parts(a);
+    const int64_t items = a.n_clusters * plan.parts;
     int64_t g = (int64_t)cus * per_cu;
     if (g > items) g = items;
     *grid = (unsigned)(g > 0 ? g : 1);
@@ -2524,11 +2598,9 @@ int launch_batch(const BatchArgs &a, unsigned grid, hipStream_t st, bool allow_t
     for (int b = 0; b < RV_TUNE_BUCKETS; ++b) tune.rows[b] = a.tuning.rows_max[b];
     tune.fp16_min = a.tuning.fp16_min_points;
     tune.lanes_max = a.tuning.lanes_max_points;
-    const int32_t rounds = batch_rounds(a), parts = batch_parts(a);
-    tune.prune = prune_from(rounds, a.tau, a.o.hyp_counts);
-    tune.small_max = small_to(rounds, a.tau, a.tuning.lanes_max_points);
-    if (a.tuning.fp16_min_points > 0 && tune.small_max >= a.tuning.fp16_min_points)
-        tune.small_max = a.tuning.fp16_min_points - 1;
+    const ScorePlan plan = batch_plan(a);
+    tune.prune = plan.prune;
+    tune.small_max = plan.small_max;
     const int64_t n_words = a.o.bits != nullptr ? (a.n_points + 31) / 32 : 0;
     int64_t prep_items = a.n_points > n_words ? a.n_points : n_words;
     prep_items = prep_items > a.n_clusters ? prep_items : a.n_clusters;
@@ -2545,14 +2617,10 @@ int launch_batch(const BatchArgs &a, unsigned grid, hipStream_t st, bool allow_t
                        dim3((unsigned)((a.n_clusters + kPrepBlock - 1) / kPrepBlock)),
                        dim3(kPrepBlock), 0, st, a.off, a.n_clusters, a.n_points, bt, tune, hist, desc);
     if (timed) (void)hipEventRecord(tc.ev[1], st);
-    if (a.tuning.fp16_min_points > 0)
-        hipLaunchKernelGGL(batch_score_kernel<true>, dim3(grid), dim3(kScoreBlock), 0, st,
-                           (const ItemDesc *)desc, a.n_clusters, a.n_hyp, rounds, parts, tune.prune, pts,
-                           a.tau, queues, best_key, a.o.hyp_counts);
-    else
-        hipLaunchKernelGGL(batch_score_kernel<false>, dim3(grid), dim3(kScoreBlock), 0, st,
-                           (const ItemDesc *)desc, a.n_clusters, a.n_hyp, rounds, parts, tune.prune, pts,
-                           a.tau, queues, best_key, a.o.hyp_counts);
+    hipLaunchKernelGGL(batch_score(a.tuning.fp16_min_points > 0, plan.block), dim3(grid),
+                       dim3(plan.block), 0, st, (const ItemDesc *)desc, a.n_clusters, a.n_hyp,
+                       plan.rounds, plan.parts, plan.prune, pts, a.tau, queues, best_key,
+                       a.o.hyp_counts);
     if (timed) (void)hipEventRecord(tc.ev[2], st);
     launch_refit(true, nullptr, nullptr, (const ItemDesc *)desc, a.n_clusters, n_big,
                  a.n_points, 0, 0, 0, 0, pts, best_key, a.tau, a.o, false, st);
@@ -2680,10 +2748,10 @@ int estimate_frame(const float *theta, const float *vd, const int32_t *cluster_o
         if (e != hipSuccess) return fail(RV_ERR_HIP, "kernel launch failed: %s", hipGetErrorString(e));
         return RV_OK;
     }
-    const int32_t rounds = score_rounds(n_clusters, blocks_per_cluster);
-    const int64_t parts = (blocks_per_cluster + rounds - 1) / rounds;
+    const ScorePlan plan =
+        plan_score(n_clusters, n_points, n_hyp, tau, hyp_counts, kSingleLanesMax, 0);
     const bool many = n_clusters >= kRefitManyClusters;
-    const bool refit_big = parts == 1 && many && order != nullptr;  // the order counts them
+    const bool refit_big = plan.parts == 1 && many && order != nullptr;  // the order counts them
     int64_t prep_items = n_points > n_words ? n_points : n_words;
     prep_items = prep_items > n_clusters ? prep_items : n_clusters;
     const int64_t prep_blocks = (prep_items + kPrepBlock - 1) / kPrepBlock + 1;  // + planner
@@ -2692,11 +2760,12 @@ int estimate_frame(const float *theta, const float *vd, const int32_t *cluster_o
                        first_point, n_clusters, many ? kRefitBigClass : kRefitBigClassFew,
                        order, n_big, best_key);
     if (timed) (void)hipEventRecord(tc.ev[1], st);
-    hipLaunchKernelGGL(score_kernel, dim3((unsigned)(clusters_xcd * parts)), dim3(kScoreBlock), 0,
-                       st, cluster_offsets, (const int32_t *)order, n_clusters, n_points, n_hyp,
-                       rounds, (int32_t)parts, key0, key1, first_cluster, first_point,
-                       small_to(rounds, tau, kSingleLanesMax), prune_from(rounds, tau, hyp_counts),
-                       pts, tau, best_key, o, refit_big);
+    hipLaunchKernelGGL(plan.block == kLongBlock ? score_kernel<kLongBlock>
+                                                : score_kernel<kScoreBlock>,
+                       dim3((unsigned)(clusters_xcd * plan.parts)), dim3(plan.block), 0, st,
+                       cluster_offsets, (const int32_t *)order, n_clusters, n_points, n_hyp,
+                       plan.rounds, plan.parts, key0, key1, first_cluster, first_point,
+                       plan.small_max, plan.prune, pts, tau, best_key, o, refit_big);
     if (timed) (void)hipEventRecord(tc.ev[2], st);
     launch_refit(false, cluster_offsets, order, nullptr, n_clusters,
                  order != nullptr ? (const int64_t *)n_big : nullptr, n_points, key0, key1,
