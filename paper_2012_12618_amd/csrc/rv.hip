@@ -2116,10 +2116,18 @@ __device__ __forceinline__ void for_each_item(unsigned long long *__restrict__ q
     }
 }
 
-// Clears the size-class histogram and the work queues.
+// Places taken so far of size class c in the dispatch order: a counter in the
+// second half of the queues' 256-byte lines.
+__device__ __forceinline__ uint32_t *class_cursor(unsigned long long *queues, int c) {
+    static_assert(kSizeClasses == 16 * kXcds && kQueueStride == 32, "16 classes a queue");
+    return reinterpret_cast<uint32_t *>(queues + (c / 16) * kQueueStride + kQueueStride / 2) + c % 16;
+}
+
+// Clears the size-class histogram, the classes' cursors and the work queues.
 __global__ __launch_bounds__(kSizeClasses) void batch_init_kernel(
     uint32_t *__restrict__ hist, unsigned long long *__restrict__ queues) {
     hist[threadIdx.x] = 0;
+    *class_cursor(queues, threadIdx.x) = 0;
     if (threadIdx.x < kXcds) queues[threadIdx.x * kQueueStride] = 0;
 }
 
@@ -2145,32 +2153,25 @@ __global__ __launch_bounds__(kPrepBlock) void batch_prep_kernel(
         if (local[c] != 0) atomicAdd(&hist[c], local[c]);
 }
 
-// Start of each size class in the dispatch order (largest class first).
-__global__ __launch_bounds__(kWave) void batch_scan_kernel(uint32_t *__restrict__ hist,
-                                                           int64_t *__restrict__ n_big) {
-    // One wave, two classes per lane (position q in the dispatch order is class
-    // kSizeClasses - 1 - q); each lane reads and rewrites only its own two.
-    const int lane = threadIdx.x;
-    const int c_hi = kSizeClasses - 1 - 2 * lane, c_lo = c_hi - 1;
-    const uint32_t a = hist[c_hi], b = hist[c_lo];
-    const uint32_t excl = wave_exclusive_sum(a + b, lane);
-    hist[c_hi] = excl;
-    hist[c_lo] = excl + a;
-    // Clusters refit by a whole workgroup: classes kRefitBigClass and up.
-    if (c_hi == kRefitBigClass) *n_big = excl + a;
-    if (c_lo == kRefitBigClass) *n_big = excl + a + b;
-}
-
 // Places every cluster in the dispatch order (one global atomic per class and
 // block reserves a range, LDS atomics rank the block's clusters inside it) and
-// writes its descriptor there.
+// writes its descriptor there.  Every block scans the histogram for the classes'
+// starts itself (a launch of one wave for it: 1.5 us more of every batch).
 __global__ __launch_bounds__(kPrepBlock) void batch_scatter_kernel(
     const int32_t *__restrict__ off, int64_t n_clusters, int64_t n_points, Batch bt, Tuning tune,
-    uint32_t *__restrict__ start, ItemDesc *__restrict__ desc) {
+    const uint32_t *__restrict__ hist, unsigned long long *__restrict__ queues,
+    int64_t *__restrict__ n_big, ItemDesc *__restrict__ desc) {
+    __shared__ uint32_t total[kSizeClasses];
+    __shared__ uint32_t start[kSizeClasses];
     __shared__ uint32_t count[kSizeClasses];
     __shared__ uint32_t base[kSizeClasses];
-    for (int c = threadIdx.x; c < kSizeClasses; c += kPrepBlock) count[c] = 0;
+    __shared__ int64_t s_big;
+    for (int c = threadIdx.x; c < kSizeClasses; c += kPrepBlock) {
+        count[c] = 0;
+        total[c] = hist[c];
+    }
     __syncthreads();
+    plan_scan(total, start, kRefitBigClass, &s_big);
     const int64_t k = (int64_t)blockIdx.x * kPrepBlock + threadIdx.x;
     int cls = -1;
     uint32_t rank = 0;
@@ -2182,7 +2183,8 @@ __global__ __launch_bounds__(kPrepBlock) void batch_scatter_kernel(
     }
     __syncthreads();
     for (int c = threadIdx.x; c < kSizeClasses; c += kPrepBlock)
-        base[c] = count[c] != 0 ? atomicAdd(&start[c], count[c]) : 0u;
+        base[c] = count[c] != 0 ? start[c] + atomicAdd(class_cursor(queues, c), count[c]) : 0u;
+    if (blockIdx.x == 0 && threadIdx.x == 0) *n_big = s_big;
     __syncthreads();
     if (cls < 0) return;
     const int64_t f = frame_of_cluster(bt.frame_off, bt.n_frames, k);
@@ -2612,10 +2614,10 @@ int launch_batch(const BatchArgs &a, unsigned grid, hipStream_t st, bool allow_t
     hipLaunchKernelGGL(batch_prep_kernel, dim3((unsigned)((prep_items + kPrepBlock - 1) / kPrepBlock)),
                        dim3(kPrepBlock), 0, st, a.theta, a.vd, a.n_points, staged,
                        a.o.bits, n_words, a.off, a.n_clusters, best_key, hist);
-    hipLaunchKernelGGL(batch_scan_kernel, dim3(1), dim3(64), 0, st, hist, n_big);
     hipLaunchKernelGGL(batch_scatter_kernel,
                        dim3((unsigned)((a.n_clusters + kPrepBlock - 1) / kPrepBlock)),
-                       dim3(kPrepBlock), 0, st, a.off, a.n_clusters, a.n_points, bt, tune, hist, desc);
+                       dim3(kPrepBlock), 0, st, a.off, a.n_clusters, a.n_points, bt, tune,
+                       (const uint32_t *)hist, queues, n_big, desc);
     if (timed) (void)hipEventRecord(tc.ev[1], st);
     hipLaunchKernelGGL(batch_score(a.tuning.fp16_min_points > 0, plan.block), dim3(grid),
                        dim3(plan.block), 0, st, (const ItemDesc *)desc, a.n_clusters, a.n_hyp,
