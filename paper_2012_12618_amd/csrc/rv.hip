@@ -111,6 +111,10 @@ constexpr int kRefitManyClusters = 2048;
 constexpr int kRefitBigPoints = 1024;
 constexpr int kRefitBigClass = 41;     // size class of 1024 points
 constexpr int kRefitBigClassFew = 33;  // and of 256 points
+
+__host__ __device__ constexpr int refit_big_class(int64_t n_clusters) {
+    return n_clusters >= kRefitManyClusters ? kRefitBigClass : kRefitBigClassFew;
+}
 constexpr int kXcds = 8;                // MI355X: 8 XCDs, workgroups dealt round-robin
 constexpr int kPrepBlock = 256;
 constexpr int kRowsMax = 16;            // register rows per pass, the most a tuning may name
@@ -2211,7 +2215,7 @@ __device__ void plan_batch(const int32_t *__restrict__ off, int64_t n_clusters, 
     for (int u = 0; u < kPlanBatchEach; ++u)
         if (cls[u] >= 0) atomicAdd(&count[cls[u]], 1u);
     __syncthreads();
-    plan_scan(count, start, kRefitBigClass, n_big);
+    plan_scan(count, start, refit_big_class(n_clusters), n_big);
     __syncthreads();
     for (int64_t k = threadIdx.x; k < n_clusters; k += kPrepBlock) {
         const Span sp = cluster_span(off, k, n_points);
@@ -2254,7 +2258,7 @@ __global__ __launch_bounds__(kPrepBlock) void batch_scatter_kernel(
         total[c] = hist[c];
     }
     __syncthreads();
-    plan_scan(total, start, kRefitBigClass, &s_big);
+    plan_scan(total, start, refit_big_class(n_clusters), &s_big);
     const int64_t k = (int64_t)blockIdx.x * kPrepBlock + threadIdx.x;
     int cls = -1;
     uint32_t rank = 0;
@@ -2829,7 +2833,7 @@ int estimate_frame(const float *theta, const float *vd, const int32_t *cluster_o
     const int64_t prep_blocks = (prep_items + kPrepBlock - 1) / kPrepBlock + 1;  // + planner
     hipLaunchKernelGGL(prep_kernel, dim3((unsigned)prep_blocks), dim3(kPrepBlock), 0, st, theta,
                        vd, n_points, staged, inlier_bits, n_words, cluster_offsets,
-                       first_point, n_clusters, many ? kRefitBigClass : kRefitBigClassFew,
+                       first_point, n_clusters, refit_big_class(n_clusters),
                        order, n_big, best_key);
     if (timed) (void)hipEventRecord(tc.ev[1], st);
     hipLaunchKernelGGL(plan.block == kLongBlock ? score_kernel<kLongBlock>
