@@ -242,7 +242,8 @@ int rv_estimate_velocity_noalloc(const float *theta, const float *vd,
 #define RV_TUNE_BUCKETS 8
 
 typedef struct {
-    /* register rows of 64 points scored per pass, 1..16, per size bucket */
+    /* register rows of 64 points scored per pass, 1..16 (more than 12 as 12), per
+       size bucket, where every hypothesis is counted with lanes = points */
     int32_t rows_max[RV_TUNE_BUCKETS];
     /* persistent scoring grid: workgroups per compute unit; 0 = as many as fit */
     int32_t blocks_per_cu;
@@ -256,11 +257,11 @@ typedef struct {
        there it holds the FP16 counts, upper bounds of the float32 counts. */
     int32_t fp16_min_points;
     /* clusters of at most this many points (0..256) score with lanes =
-       hypotheses: each thread keeps the hypothesis it solved, the cluster's
-       points are staged in LDS and read as broadcasts, and each lane counts its
-       own inliers (four vector instructions per point and 64 hypotheses, no
-       lanes idle for a cluster smaller than 64 points).  Same arithmetic, so
-       the same results bit for bit; it takes precedence over the FP16 form. */
+       hypotheses: the cluster's points are staged in LDS and read as broadcasts,
+       and each lane counts its own hypotheses' inliers.  Same arithmetic, so the
+       same results bit for bit; it takes precedence over the FP16 form.  Any value
+       above 0 also lets the library take that form for somewhat larger clusters
+       where it is the faster one; 0 forbids it. */
     int32_t lanes_max_points;
 } rv_tuning_t;
 

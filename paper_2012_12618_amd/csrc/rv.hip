@@ -8,24 +8,24 @@
 //           clears the optional frame-wide inlier bitmask and the per-cluster
 //           best keys.  Its first workgroup plans the dispatch order: clusters
 //           by decreasing size.
-//   score   the hot loop.  Workgroup = (cluster, block of 256 hypotheses).
-//           Each thread draws one Philox4x32-10 seed pair and solves the 2x2
-//           system in FP64 (Sec. 3.1, Alg. 1: seeds, slope and intercept, as the
-//           velocity profile of Sec. 3.2, Eq. 6); the float32 (vx, vy) go to LDS.
-//           Each wave then owns 64 hypotheses: lanes hold the cluster's points in
-//           registers (rows of 64 points), every lane reads the same hypothesis
-//           from LDS, and per point two float32 FMAs and one compare produce a
-//           64-lane ballot that the scalar unit popcounts (Alg. 1's distance test
-//           and inlier count).  The last n mod 64 points of a cluster, when
-//           fewer than 32, and whole clusters of at most 64 points are scored
-//           with lanes = hypotheses instead (points broadcast from LDS, each
-//           lane counting its own inliers; same arithmetic, same counts).  The
-//           best (count, lowest index) key of the block is merged per cluster
-//           with a 64-bit atomic maximum (Sec. 3.1: the trial with the most
-//           inliers is kept).
-//   refit   one wave per cluster, or the whole workgroup for clusters of
-//           1024 points or more: FP64 re-classification under the kept
-//           hypothesis, FP64 normal-equation sums in a fixed reduction tree,
+//   score   the hot loop.  Workgroup = (cluster, up to 1024 hypotheses).  Each
+//           thread draws Philox4x32-10 seed pairs and solves the 2x2 systems in FP64
+//           (Sec. 3.1, Alg. 1: seeds, slope and intercept, as the velocity profile
+//           of Sec. 3.2, Eq. 6); the float32 (vx, vy) go to LDS.  By the cluster's
+//           size:
+//           small (score_small): the points in LDS, a thread holds up to four
+//           hypotheses and counts their inliers point by point (Alg. 1's distance
+//           test, two float32 FMAs, and a clamped FMA as the compare);
+//           larger (score_pruned): a table of the points under a good hypothesis
+//           bounds every other one's count, and only those that can still win are
+//           counted, lanes = points, with a ballot and a scalar popcount;
+//           calls that ask for every hypothesis's count, and tau beyond the bound's
+//           range, take lanes = points for all (score_block).
+//           The best (count, lowest index) key is merged per cluster with a 64-bit
+//           atomic maximum (Sec. 3.1: the trial with the most inliers is kept).
+//   refit   one wave per cluster, or a whole workgroup for large ones (in dense
+//           frames the scoring workgroup itself): FP64 re-classification under the
+//           kept hypothesis, FP64 normal-equation sums in a fixed reduction tree,
 //           2x2 solve (Sec. 3.2, Eq. 7, Alg. 2) and atan2 heading (Eq. 8).
 // Small frames without an inlier mask take one launch (cluster_kernel)
 // that runs the same three steps per cluster in one workgroup.  A part of a
@@ -34,7 +34,8 @@
 // frame in host memory can be copied and estimated part by part.  The batched
 // form stages, orders and describes the clusters of many frames, scores them
 // from per-XCD work queues in one persistent launch (optionally in the FP16
-// residual form) and refits them in one more launch.
+// residual form) and refits them in one more launch.  Long clusters take
+// workgroups of 1024 threads in both forms.
 //
 // No floating-point atomics and fixed reduction orders: results are bitwise
 // reproducible run to run and independent of the other clusters in the frame.
@@ -401,31 +402,6 @@ __device__ __forceinline__ uint32_t count_rows(const float (&c)[R], const float 
         }
     }
     return counts;
-}
-
-// count_rows on the points from cs_chunk, v_chunk on (npts of them, the rest of
-// the rows padded with a point that never counts).
-template <int R, bool kScalarLoop = false>
-__device__ __forceinline__ uint32_t score_rows(const float2 *__restrict__ cs_chunk,
-                                               const float *__restrict__ v_chunk, int npts,
-                                               int lane, const float4 *hp, int ng, float tau) {
-    float c[R], s[R], v[R];
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-        // Uniform row base and row length, one lane offset: no per-row address
-        // registers.
-        const int len = npts - r * kWave;
-        c[r] = 0.0f;
-        s[r] = 0.0f;
-        v[r] = __builtin_inff();
-        if (lane < len) {
-            const float2 q = cs_chunk[r * kWave + lane];
-            c[r] = q.x;
-            s[r] = q.y;
-            v[r] = v_chunk[r * kWave + lane];
-        }
-    }
-    return count_rows<R, kScalarLoop>(c, s, v, hp, ng, tau);
 }
 
 // count_rows on the npts points from `chunk` on (the rest of the rows padded with
@@ -1965,19 +1941,6 @@ __global__ __launch_bounds__(B) void refit_kernel(
     refit_planned<B>(n_clusters, n_big, at, pts, tau, o, s_refit, big_done);
 }
 
-// ---- many frames in one launch sequence ----------------------------------
-//
-// The frames share one CSR: frame f owns clusters [frame_off[f], frame_off[f+1]).
-// A cluster draws its hypotheses with its frame's seed and its index within
-// the frame, so its result is bitwise the one a single-frame call gives.  The
-// scoring kernel is persistent: a fixed grid drains device work queues of
-// (cluster, 256-hypothesis block) items, clusters largest first.  There is one
-// queue per XCD (its own 256-byte line): cluster j of the dispatch order
-// belongs to queue j % 8, and workgroup b serves queue b % 8 first (workgroups
-// are dispatched to the XCDs round-robin), so a cluster's blocks share one L2
-// and no counter is hammered by the whole chip; a workgroup whose queue is
-// empty takes items from the others.
-
 // Small frames (see use_cluster_path): one workgroup per cluster stages the
 // cluster's own points, scores its hypotheses (at most 256) and refits, in a
 // single launch.  The arithmetic is the three-kernel path's, so every output is
@@ -2010,6 +1973,19 @@ __global__ __launch_bounds__(kScoreBlock) __attribute__((amdgpu_waves_per_eu(8))
     refit_cluster(sp, id, best, pts, tau, o, __builtin_amdgcn_readfirstlane(threadIdx.x / kWave),
                   kScoreBlock / kWave, s_refit);
 }
+
+// ---- many frames in one launch sequence ----------------------------------
+//
+// The frames share one CSR: frame f owns clusters [frame_off[f], frame_off[f+1]).
+// A cluster draws its hypotheses with its frame's seed and its index within
+// the frame, so its result is bitwise the one a single-frame call gives.  The
+// scoring kernel is persistent: a fixed grid drains device work queues of
+// (cluster, up to 1024 hypotheses) items, clusters largest first.  There is one
+// queue per XCD (its own 256-byte line): cluster j of the dispatch order
+// belongs to queue j % 8, and workgroup b serves queue b % 8 first (workgroups
+// are dispatched to the XCDs round-robin), so a cluster's blocks share one L2
+// and no counter is hammered by the whole chip; a workgroup whose queue is
+// empty takes items from the others.
 
 struct Batch {
     const int32_t *frame_off;  // [n_frames + 1]
@@ -2590,7 +2566,10 @@ ScorePlan plan_score(int64_t n_clusters, int64_t n_points, int32_t n_hyp, float 
                      const int32_t *hyp_counts, int32_t lanes_max, int32_t fp16_min) {
     ScorePlan p;
     p.block = kScoreBlock;
-    p.rounds = score_rounds(n_clusters, blocks_of(n_hyp));
+    // A full count has little to share between blocks and wants the finer split (frame
+    // of 4096 clusters of 8 to 4096 points with hyp_counts: 312 us with four blocks per workgroup, 244 us with one).
+    const bool pruned = prune_from(1, tau, hyp_counts) != INT64_MAX;
+    p.rounds = pruned ? score_rounds(n_clusters, blocks_of(n_hyp)) : 1;
     const auto parts = [n_hyp](int64_t each) { return (int32_t)((n_hyp + each - 1) / each); };
     p.parts = parts(kScoreBlock * p.rounds);
     int32_t blocks = p.rounds;  // of 256 hypotheses, per workgroup
@@ -2599,8 +2578,7 @@ ScorePlan plan_score(int64_t n_clusters, int64_t n_points, int32_t n_hyp, float 
     constexpr int32_t kLongBlocks = kLongBlock / kScoreBlock;
     if (long_clusters(n_clusters, n_points) &&
         (n_clusters <= kLongClusters || p.parts >= 4 * parts(kLongBlock)) &&
-        prune_from(kLongBlocks, tau, hyp_counts) != INT64_MAX &&
-        (fp16_min <= 0 || fp16_min >= prune_min(kLongBlocks))) {
+        pruned && (fp16_min <= 0 || fp16_min >= prune_min(kLongBlocks))) {
         p.block = kLongBlock;
         p.rounds = 1;
         p.parts = parts(kLongBlock);
