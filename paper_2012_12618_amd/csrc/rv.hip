@@ -128,20 +128,33 @@ constexpr int64_t kPlanMaxClusters = 1 << 16;  // above this, clusters run in in
 // ---------------------------------------------------------------------------
 
 // One staged point: float32 (cos, sin) and v_d for scoring (v_d = +inf marks a
-// point whose azimuth or Doppler value is not finite) and the float32 low parts
-// of the FP64 (cos, sin) for the solves and the refit (cs64() below).  All
-// twenty bytes in one record: a hypothesis's seeds are gathered at random, and
-// what a gather costs is the cache lines it touches.
+// point whose azimuth or Doppler value is not finite), and beside them, in an array
+// of their own, the float32 low parts of the FP64 (cos, sin) for the solves and the
+// refit (cs64() below).  The sweeps over a cluster's points read the 12-byte records
+// only, and of large clusters they miss L2 (2048 resident workgroups); the seeds'
+// gathers and the refit read both.  In one 20-byte record a seed is fewer cache lines,
+// but every sweep reads all of it: 256 frames 2357 us, split 2251 us; the dense frame
+// 92.9 and 88.8 us (scoring 257 MB a launch from beyond L2 with the record); clusters
+// of 64 points, all gathers, 276 and 284 us.
 struct StagedPoint {
     float c, s, v;
-    float clo, slo;
 };
-static_assert(sizeof(StagedPoint) == 20, "packed");
+struct StagedLow {
+    float c, s;
+};
+static_assert(sizeof(StagedPoint) == 12 && sizeof(StagedLow) == 8, "packed");
+
+// Where points are staged.
+struct Staging {
+    StagedPoint *points;
+    StagedLow *low;
+};
 
 // A frame's staged points and the caller's azimuths (for the seed-separation
 // test).
 struct Points {
     const StagedPoint *staged;
+    const StagedLow *low;
     const float *theta;
 };
 
@@ -149,8 +162,8 @@ struct Points {
 // part, c = hi + lo (an exact FP64 sum), within 2^-49 of the FP64 sincos.
 // Staging 8 bytes per point for the low parts instead of 16 for the FP64 pair
 // shortens the staging kernel, which is bound by its bytes.
-__device__ __forceinline__ double2 cs64(const StagedPoint &p) {
-    return make_double2((double)p.c + (double)p.clo, (double)p.s + (double)p.slo);
+__device__ __forceinline__ double2 cs64(const StagedPoint &p, const StagedLow &low) {
+    return make_double2((double)p.c + (double)low.c, (double)p.s + (double)low.s);
 }
 
 struct Hypothesis {
@@ -162,6 +175,7 @@ struct Hypothesis {
 struct Seeds {
     int64_t pi, pj;
     StagedPoint a, b;
+    StagedLow al, bl;
 };
 
 // Seed pair of hypothesis h of cluster k.  No branch: all loads are in flight
@@ -176,6 +190,8 @@ __device__ __forceinline__ Seeds draw_seeds(const Points &pts, Span sp, uint32_t
     d.pj = sp.lo + j;
     d.a = pts.staged[d.pi];
     d.b = pts.staged[d.pj];
+    d.al = pts.low[d.pi];
+    d.bl = pts.low[d.pj];
     return d;
 }
 
@@ -183,7 +199,7 @@ __device__ __forceinline__ Seeds draw_seeds(const Points &pts, Span sp, uint32_t
 // (Cramer's rule); an invalid pair's solve (possibly inf or NaN) is replaced by
 // NaN.
 __device__ __forceinline__ Hypothesis solve_seeds(const Points &pts, const Seeds &d) {
-    const double2 ai = cs64(d.a), bj = cs64(d.b);
+    const double2 ai = cs64(d.a, d.al), bj = cs64(d.b, d.bl);
     const double ci = ai.x, si = ai.y, cj = bj.x, sj = bj.y;
     const double dvi = d.a.v, dvj = d.b.v;
     const double det = ci * sj - si * cj;
@@ -334,7 +350,7 @@ __device__ void plan_order(const int32_t *__restrict__ off, int64_t point_base, 
 // below tau, and +inf marks it for the solves and the refit.
 __device__ __forceinline__ void stage_point(const float *__restrict__ theta,
                                             const float *__restrict__ vd, int64_t p,
-                                            StagedPoint *__restrict__ staged) {
+                                            const Staging &staged) {
     const float t = theta[p], v = vd[p];
     double s, c;
     sincos((double)t, &s, &c);
@@ -344,9 +360,11 @@ __device__ __forceinline__ void stage_point(const float *__restrict__ theta,
     q.c = ch;
     q.s = sh;
     q.v = ok ? v : __builtin_inff();
-    q.clo = ok ? (float)(c - (double)ch) : 0.0f;
-    q.slo = ok ? (float)(s - (double)sh) : 0.0f;
-    staged[p] = q;
+    StagedLow low;
+    low.c = ok ? (float)(c - (double)ch) : 0.0f;
+    low.s = ok ? (float)(s - (double)sh) : 0.0f;
+    staged.points[p] = q;
+    staged.low[p] = low;
 }
 
 // Block 0 plans the order (when `order` is non-null); it is dispatched first,
@@ -354,7 +372,7 @@ __device__ __forceinline__ void stage_point(const float *__restrict__ theta,
 // points and clear the per-cluster best keys.
 __global__ __launch_bounds__(kPrepBlock) void prep_kernel(
     const float *__restrict__ theta, const float *__restrict__ vd, int64_t n_points,
-    StagedPoint *__restrict__ staged, uint32_t *__restrict__ bits,
+    Staging staged, uint32_t *__restrict__ bits,
     int64_t n_words, const int32_t *__restrict__ off, int64_t point_base, int64_t n_clusters,
     int32_t big_class, int32_t *__restrict__ order, int64_t *__restrict__ n_big,
     unsigned long long *__restrict__ best_key) {
@@ -1025,10 +1043,12 @@ __device__ __forceinline__ float uniform_f(float v) {
 // body(point, in) for the block's share of a cluster's points, every thread one
 // point in B, kSweepLoads of them loaded before the first is used (in: the point is
 // one of the n; past the end the last one is loaded again).
+// A large workgroup has the registers for eight (64 clusters of 65,536 points: 172 us
+// with four ahead, 168 us with eight).
 template <int B, typename Body>
 __device__ __forceinline__ void sweep_points(const StagedPoint *points, uint32_t n,
                                              const Body &body) {
-    constexpr int kSweepLoads = 4;
+    constexpr int kSweepLoads = B == kLongBlock ? 8 : 4;
     for (uint32_t base = 0; base < n; base += kSweepLoads * B) {
         PointLoad u[kSweepLoads];
 #pragma unroll
@@ -1727,6 +1747,7 @@ __device__ __forceinline__ void refit_points(int64_t p0, bool in_range, float v,
 // valid index.
 struct RefitLoad {
     StagedPoint p;
+    StagedLow low;
     bool in;
 };
 
@@ -1734,7 +1755,9 @@ __device__ __forceinline__ RefitLoad refit_load(Span sp, int64_t p0, const Point
     const int64_t p = p0 + lane;
     RefitLoad L;
     L.in = p >= sp.lo && p < sp.lo + sp.n;
-    L.p = pts.staged[L.in ? p : sp.lo];
+    const int64_t at = L.in ? p : sp.lo;
+    L.p = pts.staged[at];
+    L.low = pts.low[at];
     return L;
 }
 
@@ -1799,9 +1822,9 @@ __device__ __forceinline__ void refit_cluster(Span sp, ClusterId id, unsigned lo
     for (; p0 < end; p0 += 2 * stride) {
         const RefitLoad b0 = refit_load(sp, p0 + 2 * stride, pts, lane);
         const RefitLoad b1 = refit_load(sp, p0 + 3 * stride, pts, lane);
-        refit_points(p0, a0.in, a0.p.v, cs64(a0.p), hy, (double)tau, a, o, lane);
+        refit_points(p0, a0.in, a0.p.v, cs64(a0.p, a0.low), hy, (double)tau, a, o, lane);
         if (p0 + stride < end)
-            refit_points(p0 + stride, a1.in, a1.p.v, cs64(a1.p), hy, (double)tau, a, o, lane);
+            refit_points(p0 + stride, a1.in, a1.p.v, cs64(a1.p, a1.low), hy, (double)tau, a, o, lane);
         a0 = b0;
         a1 = b1;
     }
@@ -1952,9 +1975,9 @@ __global__ __launch_bounds__(B) void refit_kernel(
 __global__ __launch_bounds__(kScoreBlock) __attribute__((amdgpu_waves_per_eu(8))) void cluster_kernel(
     const float *__restrict__ theta, const float *__restrict__ vd, const int32_t *__restrict__ off,
     int64_t n_points, int32_t n_hyp, uint32_t key0, uint32_t key1, uint32_t cluster_base,
-    int64_t point_base, int32_t small_max, int64_t prune, float tau, StagedPoint *staged,
+    int64_t point_base, int32_t small_max, int64_t prune, float tau, Staging staged,
     Outputs o) {
-    const Points pts = {staged, theta};
+    const Points pts = {staged.points, staged.low, theta};
     __shared__ ScoreShared<kScoreBlock> s;
     __shared__ RefitShared s_refit;
     const int64_t k = blockIdx.x;
@@ -2163,7 +2186,7 @@ __global__ __launch_bounds__(kSizeClasses) void batch_init_kernel(
 // one global atomic per class and block).
 __global__ __launch_bounds__(kPrepBlock) void batch_prep_kernel(
     const float *__restrict__ theta, const float *__restrict__ vd, int64_t n_points,
-    StagedPoint *__restrict__ staged, uint32_t *__restrict__ bits, int64_t n_words,
+    Staging staged, uint32_t *__restrict__ bits, int64_t n_words,
     const int32_t *__restrict__ off, int64_t n_clusters, unsigned long long *__restrict__ best_key, uint32_t *__restrict__ hist) {
     __shared__ uint32_t local[kSizeClasses];
     for (int c = threadIdx.x; c < kSizeClasses; c += kPrepBlock) local[c] = 0;
@@ -2224,7 +2247,7 @@ __device__ void plan_batch(const int32_t *__restrict__ off, int64_t n_clusters, 
 
 __global__ __launch_bounds__(kPrepBlock) void batch_plan_prep_kernel(
     const float *__restrict__ theta, const float *__restrict__ vd, int64_t n_points,
-    StagedPoint *__restrict__ staged, uint32_t *__restrict__ bits, int64_t n_words,
+    Staging staged, uint32_t *__restrict__ bits, int64_t n_words,
     const int32_t *__restrict__ off, int64_t n_clusters, Batch bt, Tuning tune,
     unsigned long long *__restrict__ best_key, unsigned long long *__restrict__ queues,
     int64_t *__restrict__ n_big, ItemDesc *__restrict__ desc) {
@@ -2383,14 +2406,15 @@ constexpr size_t kAlign = 256;
 size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
 struct Layout {
-    size_t staged, order, best_key, n_big, total;
+    size_t staged, low, order, best_key, n_big, total;
 };
 
 Layout make_layout(int64_t n_clusters, int64_t n_points) {
     Layout L;
     const size_t np = (size_t)n_points;
     size_t at = 0;
-    L.staged = at; at = align_up(at + np * sizeof(StagedPoint));
+    L.staged = at; at = align_up(align_up(at + np * 2 * sizeof(float)) + np * sizeof(float));
+    L.low = at; at = align_up(at + np * sizeof(StagedLow));
     L.order = at; at = align_up(at + (size_t)n_clusters * sizeof(int32_t));
     L.best_key = at; at = align_up(at + (size_t)n_clusters * sizeof(unsigned long long));
     L.n_big = at; at = align_up(at + sizeof(int64_t));
@@ -2402,14 +2426,15 @@ Layout make_layout(int64_t n_clusters, int64_t n_points) {
 
 
 struct BatchLayout {
-    size_t staged, desc, best_key, hist, queues, n_big, total;
+    size_t staged, low, desc, best_key, hist, queues, n_big, total;
 };
 
 BatchLayout make_batch_layout(int64_t n_clusters, int64_t n_points) {
     BatchLayout L;
     const size_t np = (size_t)n_points, nc = (size_t)n_clusters;
     size_t at = 0;
-    L.staged = at; at = align_up(at + np * sizeof(StagedPoint));
+    L.staged = at; at = align_up(align_up(at + np * 2 * sizeof(float)) + np * sizeof(float));
+    L.low = at; at = align_up(at + np * sizeof(StagedLow));
     L.desc = at; at = align_up(at + nc * sizeof(ItemDesc));
     L.best_key = at; at = align_up(at + nc * sizeof(unsigned long long));
     L.hist = at; at = align_up(at + kSizeClasses * sizeof(uint32_t));
@@ -2651,14 +2676,15 @@ int launch_batch(const BatchArgs &a, unsigned grid, hipStream_t st, bool allow_t
     if (a.n_clusters == 0) return RV_OK;
     const BatchLayout L = make_batch_layout(a.n_clusters, a.n_points);
     char *ws = (char *)a.workspace;
-    StagedPoint *staged = (StagedPoint *)(ws + L.staged);
+    const Staging staged = {(StagedPoint *)(ws + L.staged), (StagedLow *)(ws + L.low)};
     ItemDesc *desc = (ItemDesc *)(ws + L.desc);
     unsigned long long *best_key = (unsigned long long *)(ws + L.best_key);
     uint32_t *hist = (uint32_t *)(ws + L.hist);
     unsigned long long *queues = (unsigned long long *)(ws + L.queues);
     int64_t *n_big = (int64_t *)(ws + L.n_big);
     Points pts;
-    pts.staged = staged;
+    pts.staged = staged.points;
+    pts.low = staged.low;
     pts.theta = a.theta;
     Batch bt;
     bt.frame_off = a.frame_off;
@@ -2784,9 +2810,10 @@ int estimate_frame(const float *theta, const float *vd, const int32_t *cluster_o
     if (n_clusters == 0) return RV_OK;
 
     char *ws = (char *)workspace;
-    StagedPoint *staged = (StagedPoint *)(ws + L.staged);
+    const Staging staged = {(StagedPoint *)(ws + L.staged), (StagedLow *)(ws + L.low)};
     Points pts;
-    pts.staged = staged;
+    pts.staged = staged.points;
+    pts.low = staged.low;
     pts.theta = theta;
     int32_t *order = n_clusters <= kPlanMaxClusters ? (int32_t *)(ws + L.order) : nullptr;
     int64_t *n_big = (int64_t *)(ws + L.n_big);
