@@ -997,6 +997,7 @@ struct PruneShared {
         } count;
     } u;
     unsigned long long key[B / kWave];
+    unsigned long long top_key[B / kWave];
     float lo[B / kWave], hi[B / kWave];
     uint32_t n[B / kWave];
     uint32_t top[B / kWave];
@@ -1264,14 +1265,16 @@ __device__ __forceinline__ unsigned long long score_pruned(
         top = wave_best(most != 0 ? most + 1u : 0u, (uint32_t)h_first + at);
         top = top > floor_key ? top : 0ull;
     }
-    if (lane == 0) sh.key[wave] = top;
+    // Into an array of its own: without a reference no barrier lies between the reads
+    // of sh.key above and here.
+    if (lane == 0) sh.top_key[wave] = top;
     __syncthreads();  // also the last use of the table
     int nl = 0;
     {
         int before = 0;
 #pragma unroll
         for (int w = 0; w < B / kWave; ++w) {
-            const int has = sh.key[w] != 0 ? 1 : 0;
+            const int has = sh.top_key[w] != 0 ? 1 : 0;
             before += w < wave ? has : 0;
             nl += has;
         }

@@ -1,0 +1,144 @@
+// The device code of csrc/rv.hip on the CPU (tests/emulator; the test that builds this
+// passes its device half as RV_DEVICE_SOURCE): the scoring of a large cluster under
+// many orders of its workgroup's waves, against the count of every hypothesis.
+//   score_host_check no-reference | other-workgroups
+#include RV_DEVICE_SOURCE
+
+namespace {
+
+struct Cluster {
+    std::vector<float> theta, vd;
+    std::vector<StagedPoint> staged;
+    std::vector<StagedLow> low;
+    Points pts;
+    Span sp;
+    void stage() {
+        staged.resize(theta.size());
+        low.resize(theta.size());
+        for (size_t p = 0; p < theta.size(); ++p)
+            stage_point(theta.data(), vd.data(), (int64_t)p, Staging{staged.data(), low.data()});
+        pts = {staged.data(), low.data(), theta.data()};
+        sp = {0, (int64_t)theta.size(), true};
+    }
+};
+
+Cluster make_cluster(int n, uint32_t seed, double outliers, double finite) {
+    std::mt19937 rng(seed);
+    std::uniform_real_distribution<double> u(0, 1);
+    std::normal_distribution<double> g(0, 0.05);
+    Cluster c;
+    for (int i = 0; i < n; ++i) {
+        const double t = 2 * u(rng) - 1;
+        double v = 12 * cos(t) - 7 * sin(t) + g(rng);
+        if (u(rng) < outliers) v = 80 * u(rng) - 40;
+        c.theta.push_back((float)t);
+        c.vd.push_back(u(rng) < finite ? (float)v : NAN);
+    }
+    c.stage();
+    return c;
+}
+
+constexpr float kTau = 0.15f;
+
+// Count of hypothesis h as the rows form makes it, -1 for an invalid one.
+int64_t count_of(const Cluster &c, ClusterId id, uint32_t h) {
+    const Hypothesis y = make_hypothesis(c.pts, c.sp, h, id.local, id.key0, id.key1);
+    const float hx = (float)y.vx, hy = (float)y.vy;
+    if (std::isnan(hx)) return -1;
+    int64_t n = 0;
+    for (const StagedPoint &q : c.staged)
+        n += fabsf(fmaf(-hy, q.s, fmaf(-hx, q.c, q.v))) < kTau ? 1 : 0;
+    return n;
+}
+
+unsigned long long full_key(const Cluster &c, ClusterId id, int64_t first, int nh) {
+    unsigned long long best = 0;
+    for (int64_t h = first; h < first + nh; ++h) {
+        const int64_t n = count_of(c, id, (uint32_t)h);
+        if (n >= 0 && hyp_key((uint32_t)n, h) > best) best = hyp_key((uint32_t)n, h);
+    }
+    return best;
+}
+
+ClusterId cluster_id(uint32_t seed) { return {0, 3, seed, 77}; }
+
+PruneShared<kScoreBlock> shared;
+
+template <bool kHalf>
+unsigned long long pruned(const Cluster &c, ClusterId id, int64_t first, int nh, uint32_t order,
+                          unsigned long long *best_key) {
+    unsigned long long keys[kScoreBlock];
+    memset((void *)&shared, 0xFF, sizeof shared);  // what an earlier workgroup left: NaN, -1
+    emu::run(kScoreBlock, order, [&] {
+        const uint32_t t = threadIdx.x;
+        const unsigned long long k =
+            score_pruned<kScoreBlock, kHalf>(c.sp, id, first, nh, c.pts, kTau, shared, best_key);
+        keys[t] = k;
+    });
+    for (int t = 1; t < kScoreBlock; ++t)
+        if (keys[t] != keys[0]) emu::fail("the threads' keys differ, thread, order", t, (int)order);
+    return keys[0];
+}
+
+void check(bool ok, const char *what, int a, int b) {
+    if (!ok) emu::fail(what, a, b);
+}
+
+// No usable hypothesis among the workgroup's first 64 (one point in a dozen is
+// finite), a few after them.
+void no_reference() {
+    int cases = 0;
+    for (uint32_t seed = 0; cases < 12; ++seed) {
+        const Cluster c = make_cluster(330 + (int)seed % 90, seed, 0.2, 0.08);
+        const ClusterId id = cluster_id(seed);
+        const int64_t first = seed % 2 ? 512 : 0;
+        const int nh = seed % 3 ? 256 : 700;
+        bool usable = false;
+        for (int h = 0; h < kWave; ++h) usable |= count_of(c, id, (uint32_t)(first + h)) >= 0;
+        const unsigned long long want = full_key(c, id, first, nh);
+        if (usable || want == 0) continue;
+        ++cases;
+        for (uint32_t order = 0; order < 40; ++order)
+            check(pruned<false>(c, id, first, nh, order, nullptr) == want,
+                  "no reference: wrong key, seed, order", (int)seed, (int)order);
+    }
+}
+
+// Another workgroup of the cluster merges a key just below this one's best after some
+// of the waves have read the cluster's, before the others do.
+template <bool kHalf>
+void other_workgroups() {
+    for (uint32_t seed = 0; seed < 8; ++seed) {
+        const Cluster c = make_cluster(700 + 37 * (int)seed, 100 + seed, 0.35, 1.0);
+        const ClusterId id = cluster_id(seed);
+        const unsigned long long want = full_key(c, id, 256, 256);
+        for (uint32_t order = 0; order < 24; ++order) {
+            unsigned long long best_key = 0;
+            uint32_t loads = 0;
+            emu::on_load = [&] {
+                if (loads++ == (order % 4) * kWave) best_key = want - 1;
+            };
+            const unsigned long long got = pruned<kHalf>(c, id, 256, 256, order, &best_key);
+            emu::on_load = nullptr;
+            check(loads > 0, "no load of the cluster's key", (int)seed, (int)order);
+            check(got == want, kHalf ? "FP16 form: winner lost, seed, order"
+                                     : "winner lost, seed, order", (int)seed, (int)order);
+        }
+    }
+}
+
+}  // namespace
+
+int main(int argc, char **argv) {
+    const char *what = argc > 1 ? argv[1] : "";
+    if (!strcmp(what, "no-reference")) {
+        no_reference();
+    } else if (!strcmp(what, "other-workgroups")) {
+        other_workgroups<false>();
+        other_workgroups<true>();
+    } else {
+        return 2;
+    }
+    printf("ok\n");
+    return 0;
+}

@@ -1,0 +1,33 @@
+"""GPU: clusters that score_pruned (csrc/rv.hip) handles without a reference, and the
+batched FP16 form with many workgroups per cluster, against the full count, bit for
+bit.  tests/test_score_host.py runs the same code on the CPU under many orders of the
+waves.  Tolerance: none."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+from test_gpu_pruned import cluster, compare, frame_of, rv  # noqa: F401 (fixture)
+
+pytestmark = pytest.mark.gpu
+
+
+def sparse(n, seed, finite):
+    """A cluster with a share `finite` of finite points."""
+    t, v = (a.copy() for a in cluster(n, seed, p_uniform=0.2))
+    v[np.random.default_rng(seed).random(n) >= finite] = np.nan
+    return t, v
+
+
+@pytest.mark.parametrize("n_hyp", [256, 700, 1024, 2500])
+def test_few_finite_points(rv, n_hyp):  # noqa: F811
+    clusters = [sparse(330 + 61 * i, 500 + i, f) for i, f in
+                enumerate([0.02, 0.05, 0.08, 0.1, 0.12, 0.2] * 12)]
+    # One azimuth but for a few points: nearly every pair degenerate.
+    for i in range(8):
+        t, v = (a.copy() for a in cluster(600, 600 + i, p_uniform=0.2))
+        t[20:] = 0.4
+        clusters.append((t, v))
+    compare(rv, *frame_of(clusters), n_hyp, 0.15, 21, f"few finite points H={n_hyp}")
+    compare(rv, *frame_of(clusters + [sparse(900000, 9, 0.06)]), n_hyp, 0.15, 22,
+            f"few finite points, long H={n_hyp}")
