@@ -998,6 +998,7 @@ struct PruneShared {
     } u;
     unsigned long long key[B / kWave];
     unsigned long long top_key[B / kWave];
+    unsigned long long floor_key;
     float lo[B / kWave], hi[B / kWave];
     uint32_t n[B / kWave];
     uint32_t top[B / kWave];
@@ -1266,9 +1267,13 @@ __device__ __forceinline__ unsigned long long score_pruned(
         top = top > floor_key ? top : 0ull;
     }
     // Into an array of its own: without a reference no barrier lies between the reads
-    // of sh.key above and here.
+    // of sh.key above and here.  From here on every wave goes by the first one's floor:
+    // each loaded the cluster's key at its own moment, and what they keep together has
+    // to be decided by one.
     if (lane == 0) sh.top_key[wave] = top;
+    if (wave == 0) sh.floor_key = floor_key;  // the same value from every lane
     __syncthreads();  // also the last use of the table
+    floor_key = uniform_u64(sh.floor_key);
     int nl = 0;
     {
         int before = 0;

@@ -31,3 +31,28 @@ def test_few_finite_points(rv, n_hyp):  # noqa: F811
     compare(rv, *frame_of(clusters), n_hyp, 0.15, 21, f"few finite points H={n_hyp}")
     compare(rv, *frame_of(clusters + [sparse(900000, 9, 0.06)]), n_hyp, 0.15, 22,
             f"few finite points, long H={n_hyp}")
+
+
+@pytest.mark.parametrize("points", [1500, 20000])
+def test_fp16_form_with_many_workgroups_per_cluster(rv, points):  # noqa: F811
+    """16 (in the large workgroups 4) workgroups of a cluster share its best key."""
+    import torch
+
+    theta, vd, off = frame_of([cluster(points + 13 * i, 800 + i, p_uniform=0.3, p_band=0.2)
+                               for i in range(24)])
+    t, v, o = (torch.from_numpy(a).cuda() for a in (theta, vd, off))
+    fo = torch.tensor([0, len(off) - 1], dtype=torch.int32, device="cuda")
+    for seed in range(12):
+        got = {}
+        for fp16_min in (0, 512):
+            tuning = rv.rv_tuning_default()
+            tuning.fp16_min_points = fp16_min
+            print(f"[gpu] fp16 workgroups points={points} seed={seed} fp16_min={fp16_min}", flush=True)
+            out = rv.allocate_batch_outputs(1, len(off) - 1, len(theta), 4096, t.device, debug=True)
+            del out["hyp_counts"]
+            rv.rv_estimate_velocity_batch(t, v, o, fo, torch.tensor([seed], device="cuda"), 4096, 0.15,
+                                          tuning=tuning, out=out)
+            torch.cuda.synchronize()
+            got[fp16_min] = {k: x.cpu().numpy() for k, x in out.items()}
+        for k, x in got[0].items():
+            assert np.array_equal(x.view(np.uint8), got[512][k].view(np.uint8)), (seed, k)
