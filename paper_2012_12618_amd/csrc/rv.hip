@@ -104,10 +104,11 @@ constexpr int kScoreBlock = 256;        // score: 4 waves x 64 hypotheses, one p
 constexpr int kRefitBlock = 256;
 constexpr int kLongBlock = 1024;        // score and refit of long clusters (long_clusters)
 // Clusters from this size on are refit by a whole workgroup, smaller ones by a wave
-// each.  Many clusters (more than fit the chip at eight workgroups per CU): from
-// 1024 points, a wave alone being the cheaper form until its chain is the longest
-// thing left.  Fewer: from 256 points, where only the chain counts (700 clusters of
-// 8 to 1024 points: refit 14.2 us from 1024 on, 9.2 us from 256 on).
+// each, with the same bits (see refit_cluster).  Many clusters (more than fit the chip
+// at eight workgroups per CU): from 1024 points, a wave alone being the cheaper form
+// until its chain is the longest thing left.  Fewer: from 256 points, where only the chain
+// counts (refit of 700 clusters of 8 to 1024 points 10.8 us from 1024 on, 8.1 us from 256
+// on; of 300 clusters of 512 points 9.8 and 8.2, of 1000 of 256 points 8.8 and 8.7).
 constexpr int kRefitManyClusters = 2048;
 constexpr int kRefitBigPoints = 1024;
 constexpr int kRefitBigClass = 41;     // size class of 1024 points
@@ -1485,10 +1486,22 @@ __device__ __forceinline__ unsigned long long score_small(Span sp, ClusterId id,
     return block_key<B>(sh.key);
 }
 
-// Workgroup LDS of the scoring forms: a workgroup uses one at a time.
+// Streams of a cluster's sums in the refit, per-lane sums of its waves (refit_cluster).
+constexpr int kRefitStreams = 4;
+constexpr int64_t kRefitLongPoints = 8192;
+
+template <int kWaves>
+struct RefitShared {
+    double sum[kWaves][5][kWave];
+    int cnt[kWaves][2][kWave];
+};
+
+// Workgroup LDS of the scoring forms and of the refit behind them: a workgroup uses one
+// at a time.
 template <int B>
 struct ScoreShared {
-    static constexpr size_t kBytes = sizeof(PruneShared<B>);
+    static constexpr size_t kBytes = sizeof(PruneShared<B>) > sizeof(RefitShared<B / kWave>)
+                                         ? sizeof(PruneShared<B>) : sizeof(RefitShared<B / kWave>);
     static_assert(sizeof(RowsShared<B>) <= kBytes && sizeof(Fp16Shared) <= kBytes &&
                   sizeof(SmallShared<B>) <= kBytes, "the largest");
     alignas(16) unsigned char bytes[kBytes];
@@ -1496,6 +1509,7 @@ struct ScoreShared {
     __device__ Fp16Shared &fp16() { return *reinterpret_cast<Fp16Shared *>(bytes); }
     __device__ SmallShared<B> &small() { return *reinterpret_cast<SmallShared<B> *>(bytes); }
     __device__ PruneShared<B> &prune() { return *reinterpret_cast<PruneShared<B> *>(bytes); }
+    __device__ RefitShared<B / kWave> &refit() { return *reinterpret_cast<RefitShared<B / kWave> *>(bytes); }
 };
 
 // Float32 scoring of hypotheses [h_first, h_first + nh) of one cluster by one
@@ -1718,10 +1732,10 @@ struct RefitSums {
     int n_in = 0, n_near = 0;
 };
 
-// Re-classification of one 64-aligned block of points [p0, p0 + 64) under h*
-// (one wave, wave-uniform call): lane point p = p0 + lane counts when it lies
-// in [lo, end) and its v_d is finite (+inf marks a non-finite point); the
-// block's ballot fills two words of the frame-wide mask.  v and cs are loaded
+// Re-classification of 64 points [p0, p0 + 64) of a cluster under h* (one wave,
+// wave-uniform call): lane point p0 + lane counts when it is one of the cluster's and
+// its v_d is finite (+inf marks a non-finite point); the block's ballot goes to the
+// two or three words of the frame-wide mask that it lies in.  v and cs are loaded
 // by the caller, so that the loads of several blocks are in flight together.
 __device__ __forceinline__ void refit_points(int64_t p0, bool in_range, float v, double2 cs,
                                              const Hypothesis &hy, double dtau, RefitSums &a,
@@ -1744,9 +1758,15 @@ __device__ __forceinline__ void refit_points(int64_t p0, bool in_range, float v,
     if (o.bits != nullptr) {
         const uint64_t m = __builtin_amdgcn_ballot_w64(inlier);
         if (lane == 0) {
-            const uint32_t w0 = (uint32_t)m, w1 = (uint32_t)(m >> 32);
+            // A word holds no bit beyond the cluster's last point, so none outside the
+            // mask is touched.
+            const int sh = (int)(p0 & 31);
+            const uint64_t low = m << sh;
+            const uint32_t w0 = (uint32_t)low, w1 = (uint32_t)(low >> 32);
+            const uint32_t w2 = sh != 0 ? (uint32_t)(m >> (64 - sh)) : 0u;
             if (w0) atomicOr(&o.bits[p0 >> 5], w0);
             if (w1) atomicOr(&o.bits[(p0 >> 5) + 1], w1);
+            if (w2) atomicOr(&o.bits[(p0 >> 5) + 2], w2);
         }
     }
 }
@@ -1762,7 +1782,7 @@ struct RefitLoad {
 __device__ __forceinline__ RefitLoad refit_load(Span sp, int64_t p0, const Points &pts, int lane) {
     const int64_t p = p0 + lane;
     RefitLoad L;
-    L.in = p >= sp.lo && p < sp.lo + sp.n;
+    L.in = p < sp.lo + sp.n;
     const int64_t at = L.in ? p : sp.lo;
     L.p = pts.staged[at];
     L.low = pts.low[at];
@@ -1785,26 +1805,38 @@ __device__ __forceinline__ void wave_sum_all(RefitSums &a) {
     }
 }
 
-// Refit of one cluster by `waves` waves (1, or all of the workgroup's at most
-// kMaxWaves; `wave` is this one's index among them): the kept hypothesis (from its
-// best key), FP64 re-classification of every point under it, least-squares refit
-// on its inliers (Sec. 3.2, Eq. 7, Alg. 2: normal equations A^T A v = A^T v_d,
-// summed per lane over the wave's 64-point blocks, across the wave in a fixed
-// tree, then over the waves in order) and heading atan2(vy, vx) (Eq. 8).
+__device__ __forceinline__ void add_sums(RefitSums &a, const RefitSums &b) {
+    a.scc += b.scc;
+    a.scs += b.scs;
+    a.sss += b.sss;
+    a.scv += b.scv;
+    a.ssv += b.ssv;
+    a.n_in += b.n_in;
+    a.n_near += b.n_near;
+}
+
+// Refit of one cluster by `waves` waves (1, 4 or 16: all of a workgroup's; `wave` is
+// this one's index among them): the kept hypothesis (from its best key), FP64
+// re-classification of every point under it, least-squares refit on its inliers
+// (Sec. 3.2, Eq. 7, Alg. 2: normal equations A^T A v = A^T v_d) and heading
+// atan2(vy, vx) (Eq. 8).
+//
+// The order of the sums follows from the cluster's own points alone, whatever runs
+// them, so a cluster has the same bits in a frame, a part of it, a batch of any size,
+// and in every kernel that refits.  Per lane the 64-point blocks, counted from the
+// cluster's first point, form kRefitStreams streams (every fourth block each), or from
+// kRefitLongPoints points on sixteen; stream i + 4, i + 8 and i + 12 are added to stream i,
+// then streams 0 to 3 in order, then the lanes in a fixed tree.  A wave walks its streams one
+// after the other: one wave all four, one of four waves one or four, one of sixteen one.
 //
 // What bounds it on a few clusters is the code: every compute unit that runs it
 // once fetches each of its lines once, at more than a hundred cycles a line.  So
-// the sums and the point loop are rolled and both workgroup shapes share one copy.
-// Wave-uniform branches only around the barrier (it is called from the persistent
-// loop, see batch_score_kernel).
-struct RefitShared {
-    double sum[1024 / kWave][5];
-    int cnt[1024 / kWave][2];
-};
-
+// the sums and the point loop are rolled and the workgroup shapes share one copy.
+// Wave-uniform branches only around the barriers.
+template <int kWaves>
 __device__ __forceinline__ void refit_cluster(Span sp, ClusterId id, unsigned long long best,
                                               const Points &pts, float tau, const Outputs &o,
-                                              int wave, int waves, RefitShared &sh) {
+                                              int wave, int waves, RefitShared<kWaves> &sh) {
     const int lane = threadIdx.x % kWave;
     const int64_t k = id.out;
     if (!sp.ok || sp.n < 2 || best == 0) {
@@ -1816,53 +1848,81 @@ __device__ __forceinline__ void refit_cluster(Span sp, ClusterId id, unsigned lo
         }
         return;
     }
-    // Waves walk 64-aligned global blocks so one wave ballot maps onto two
-    // words of the frame-wide bitmask.
-    const int64_t end = sp.lo + sp.n, stride = (int64_t)waves * kWave;
-    int64_t p0 = (sp.lo & ~(int64_t)(kWave - 1)) + (int64_t)wave * kWave;
+    const int streams = sp.n >= kRefitLongPoints ? 4 * kRefitStreams : kRefitStreams;
+    waves = waves < streams ? waves : streams;
+    if (wave >= waves) return;
+    const int64_t end = sp.lo + sp.n, stride = (int64_t)streams * kWave;
+    int stream = wave;  // of the block after p
+    // The block after the one at p: the next of its stream, then the wave's next stream.
+    const auto after = [&](int64_t p) {
+        p += stride;
+        if (p >= end && stream + waves < streams) {
+            stream += waves;
+            p = sp.lo + (int64_t)stream * kWave;
+        }
+        return p;
+    };
     // Two blocks' loads in flight while the two before them are summed (the first
     // pair during the solve).
-    RefitLoad a0 = refit_load(sp, p0, pts, lane), a1 = refit_load(sp, p0 + stride, pts, lane);
+    int64_t p0 = sp.lo + (int64_t)wave * kWave, p1 = after(p0);
+    RefitLoad a0 = refit_load(sp, p0, pts, lane), a1 = refit_load(sp, p1, pts, lane);
     const uint32_t hbest = 0xFFFFFFFFu - (uint32_t)(best & 0xFFFFFFFFull);
     const Hypothesis hy = make_hypothesis(pts, sp, hbest, id.local, id.key0, id.key1);
-    RefitSums a;
+    RefitSums a, stream_sums;
 #pragma unroll 1
-    for (; p0 < end; p0 += 2 * stride) {
-        const RefitLoad b0 = refit_load(sp, p0 + 2 * stride, pts, lane);
-        const RefitLoad b1 = refit_load(sp, p0 + 3 * stride, pts, lane);
-        refit_points(p0, a0.in, a0.p.v, cs64(a0.p, a0.low), hy, (double)tau, a, o, lane);
-        if (p0 + stride < end)
-            refit_points(p0 + stride, a1.in, a1.p.v, cs64(a1.p, a1.low), hy, (double)tau, a, o, lane);
+    while (p0 < end) {
+        const int64_t p2 = p1 < end ? after(p1) : p1;
+        const RefitLoad b0 = refit_load(sp, p2, pts, lane);
+        const int64_t p3 = p2 < end ? after(p2) : p2;
+        const RefitLoad b1 = refit_load(sp, p3, pts, lane);
+        refit_points(p0, a0.in, a0.p.v, cs64(a0.p, a0.low), hy, (double)tau, stream_sums, o, lane);
+        if (p1 != p0 + stride) {
+            add_sums(a, stream_sums);
+            stream_sums = RefitSums();
+        }
+        if (p1 < end) {
+            refit_points(p1, a1.in, a1.p.v, cs64(a1.p, a1.low), hy, (double)tau, stream_sums, o, lane);
+            if (p2 != p1 + stride) {
+                add_sums(a, stream_sums);
+                stream_sums = RefitSums();
+            }
+        }
         a0 = b0;
         a1 = b1;
+        p0 = p2;
+        p1 = p3;
+    }
+    add_sums(a, stream_sums);
+    if (waves > 1) {
+        __syncthreads();  // sh may lie where other LDS was read until now
+        sh.sum[wave][0][lane] = a.scc;
+        sh.sum[wave][1][lane] = a.scs;
+        sh.sum[wave][2][lane] = a.sss;
+        sh.sum[wave][3][lane] = a.scv;
+        sh.sum[wave][4][lane] = a.ssv;
+        sh.cnt[wave][0][lane] = a.n_in;
+        sh.cnt[wave][1][lane] = a.n_near;
+        __syncthreads();
+        if (wave > 0) return;
+        a = RefitSums();
+#pragma unroll 1
+        for (int w = 0; w < kRefitStreams; ++w) {
+            RefitSums t;
+#pragma unroll 1
+            for (int q = w; q < waves; q += kRefitStreams) {
+                t.scc += sh.sum[q][0][lane];
+                t.scs += sh.sum[q][1][lane];
+                t.sss += sh.sum[q][2][lane];
+                t.scv += sh.sum[q][3][lane];
+                t.ssv += sh.sum[q][4][lane];
+                t.n_in += sh.cnt[q][0][lane];
+                t.n_near += sh.cnt[q][1][lane];
+            }
+            add_sums(a, t);
+        }
     }
     wave_sum_all(a);
-    if (waves > 1) {
-        if (lane == 0) {
-            sh.sum[wave][0] = a.scc;
-            sh.sum[wave][1] = a.scs;
-            sh.sum[wave][2] = a.sss;
-            sh.sum[wave][3] = a.scv;
-            sh.sum[wave][4] = a.ssv;
-            sh.cnt[wave][0] = a.n_in;
-            sh.cnt[wave][1] = a.n_near;
-        }
-        __syncthreads();
-#pragma unroll 1
-        for (int w = 1; w < waves; ++w) {
-            a.scc += sh.sum[w][0];
-            a.scs += sh.sum[w][1];
-            a.sss += sh.sum[w][2];
-            a.scv += sh.sum[w][3];
-            a.ssv += sh.sum[w][4];
-            a.n_in += sh.cnt[w][0];
-            a.n_near += sh.cnt[w][1];
-        }
-    }
-    if (wave == 0) {
-        if (lane == 0)
-            write_refit(o, k, hbest, a.n_in, a.n_near, a.scc, a.scs, a.sss, a.scv, a.ssv);
-    }
+    if (lane == 0) write_refit(o, k, hbest, a.n_in, a.n_near, a.scc, a.scs, a.sss, a.scv, a.ssv);
 }
 
 // ---- single frame ---------------------------------------------------------
@@ -1888,7 +1948,6 @@ __global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(B == kLongBlo
     uint32_t cluster_base, int64_t point_base, int32_t small_max, int64_t prune, Points pts,
     float tau, unsigned long long *__restrict__ best_key, Outputs o, bool refit_big) {
     __shared__ ScoreShared<B> s;
-    __shared__ RefitShared s_refit;
     const uint32_t xcd = blockIdx.x % kXcds;
     const uint32_t r = blockIdx.x / kXcds;
     const int64_t j = xcd + (int64_t)kXcds * (r / (uint32_t)parts);
@@ -1908,7 +1967,7 @@ __global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(B == kLongBlo
         small_max, prune, s, &best_key[k], o.hyp_counts);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     if (refit_big && sp.n >= kRefitBigPoints)
-        refit_cluster(sp, id, key, pts, tau, o, wave, B / kWave, s_refit);
+        refit_cluster(sp, id, key, pts, tau, o, wave, B / kWave, s.refit());
     else
         merge_key(&best_key[k], key, wave, threadIdx.x % kWave);
 }
@@ -1916,8 +1975,7 @@ __global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(B == kLongBlo
 // Refit of a frame's or batch's clusters over their planned (largest-first)
 // positions, in one launch: workgroups [0, n_big) take the first n_big
 // clusters (kRefitBigPoints or more, see there for frames of few), one each with
-// all four waves; the following workgroups take the other
-// clusters four at a time, one per wave.  n_big is counted on the
+// all its waves; the following workgroups take the other clusters one per wave.  n_big is counted on the
 // device by the ordering pass; without an order (n_big == nullptr) every
 // cluster gets a workgroup.  The grid is an upper bound (one workgroup per
 // cluster); surplus workgroups exit at once.  big_done: the first n_big clusters
@@ -1925,7 +1983,7 @@ __global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(B == kLongBlo
 template <int B, typename ClusterAt>
 __device__ __forceinline__ void refit_planned(int64_t n_clusters, const int64_t *n_big,
                                               const ClusterAt &at, const Points &pts, float tau,
-                                              const Outputs &o, RefitShared &sh,
+                                              const Outputs &o, RefitShared<B / kWave> &sh,
                                               bool big_done) {
     constexpr int kWaves = B / kWave;
     const int64_t big = n_big != nullptr ? *n_big : n_clusters;
@@ -1966,7 +2024,7 @@ __global__ __launch_bounds__(B) void refit_kernel(
     const int64_t *__restrict__ n_big, int64_t n_points, uint32_t key0, uint32_t key1,
     uint32_t cluster_base, int64_t point_base, Points pts,
     const unsigned long long *__restrict__ best_key, float tau, Outputs o, bool big_done) {
-    __shared__ RefitShared s_refit;
+    __shared__ RefitShared<B / kWave> s_refit;
     const FrameClusterAt at = {off, order, n_points, key0, key1, cluster_base, point_base,
                                best_key};
     refit_planned<B>(n_clusters, n_big, at, pts, tau, o, s_refit, big_done);
@@ -1987,7 +2045,6 @@ __global__ __launch_bounds__(kScoreBlock) __attribute__((amdgpu_waves_per_eu(8))
     Outputs o) {
     const Points pts = {staged.points, staged.low, theta};
     __shared__ ScoreShared<kScoreBlock> s;
-    __shared__ RefitShared s_refit;
     const int64_t k = blockIdx.x;
     const Span sp = cluster_span(off, k, n_points, point_base);
     for (int64_t p = sp.lo + threadIdx.x; p < sp.lo + sp.n; p += kScoreBlock)
@@ -2002,7 +2059,7 @@ __global__ __launch_bounds__(kScoreBlock) __attribute__((amdgpu_waves_per_eu(8))
         score_hypotheses<kScoreBlock>(sp, id, 0, n_hyp, n_hyp, pts, tau, kRowsMax, kSingleLanesMax,
                                       small_max, prune, s, nullptr, o.hyp_counts);
     refit_cluster(sp, id, best, pts, tau, o, __builtin_amdgcn_readfirstlane(threadIdx.x / kWave),
-                  kScoreBlock / kWave, s_refit);
+                  kScoreBlock / kWave, s.refit());
 }
 
 // ---- many frames in one launch sequence ----------------------------------
@@ -2375,7 +2432,7 @@ template <int B>
 __global__ __launch_bounds__(B) void batch_refit_kernel(
     const ItemDesc *__restrict__ desc, int64_t n_clusters, const int64_t *__restrict__ n_big,
     Points pts, const unsigned long long *__restrict__ best_key, float tau, Outputs o) {
-    __shared__ RefitShared s_refit;
+    __shared__ RefitShared<B / kWave> s_refit;
     const BatchClusterAt at = {desc, best_key};
     refit_planned<B>(n_clusters, n_big, at, pts, tau, o, s_refit, false);
 }

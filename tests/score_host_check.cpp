@@ -1,7 +1,8 @@
 // The device code of csrc/rv.hip on the CPU (tests/emulator; the test that builds this
 // passes its device half as RV_DEVICE_SOURCE): the scoring of a large cluster under
-// many orders of its workgroup's waves, against the count of every hypothesis.
-//   score_host_check no-reference | other-workgroups
+// many orders of its workgroup's waves, against the count of every hypothesis; the refit
+// by one wave, four and sixteen.
+//   score_host_check no-reference | other-workgroups | refit-order
 #include RV_DEVICE_SOURCE
 
 namespace {
@@ -127,6 +128,71 @@ void other_workgroups() {
     }
 }
 
+struct Refit {
+    float vx, vy, heading;
+    int32_t n_inliers, n_near;
+    uint8_t status;
+    uint32_t bits[512];
+};
+
+// The cluster's refit by `waves` waves of a workgroup of kWaves, its points from `at` on.
+template <int kWaves>
+Refit refit(const Cluster &c, int waves, int64_t at, uint32_t order) {
+    static RefitShared<kWaves> sh;
+    memset((void *)&sh, 0xFF, sizeof sh);
+    std::vector<StagedPoint> staged(at, {NAN, NAN, NAN});
+    std::vector<StagedLow> low(at, {NAN, NAN});
+    std::vector<float> theta(at, NAN);
+    staged.insert(staged.end(), c.staged.begin(), c.staged.end());
+    low.insert(low.end(), c.low.begin(), c.low.end());
+    theta.insert(theta.end(), c.theta.begin(), c.theta.end());
+    const Points pts = {staged.data(), low.data(), theta.data()};
+    const Span sp = {at, c.sp.n, true};
+    const ClusterId id = cluster_id(5);
+    unsigned long long best = 0;
+    for (uint32_t h = 0; h < 64 && best == 0; ++h)
+        if (count_of(c, id, h) >= 0) best = hyp_key(1, h);
+    check(best != 0, "no valid pair, points", (int)c.sp.n, 0);
+    Refit r;
+    memset(&r, 0, sizeof r);
+    const Outputs o = {&r.vx, &r.vy, &r.heading, &r.n_inliers, &r.status, &r.n_near, nullptr,
+                       nullptr, at + c.sp.n <= 512 * 32 ? r.bits : nullptr};
+    emu::run(waves * kWave, order, [&] {
+        refit_cluster<kWaves>(sp, id, best, pts, 1.0f, o, (int)threadIdx.x / kWave, waves, sh);
+    });
+    return r;
+}
+
+// Nearly all points share one azimuth, so that another order of the sums shows.
+void refit_order() {
+    for (int n : {2, 63, 64, 65, 130, 255, 256, 257, 700, 1023, 1024, 1025, 4097, 8191, 8192, 9001}) {
+        std::mt19937 rng(n);
+        std::normal_distribution<double> g(0, 1);
+        Cluster c;
+        for (int i = 0; i < n; ++i) {
+            const double t = 0.3 + 1e-6 * g(rng) + (i % 3 == 1 ? 1.5e-3 : 0.0);
+            c.theta.push_back((float)t);
+            c.vd.push_back((float)(9 * cos(t) - 4 * sin(t) + 0.05 * g(rng)));
+        }
+        c.stage();
+        const Refit want = refit<4>(c, 4, 0, 1);
+        check(want.n_inliers > n / 2, "few inliers, points", n, want.n_inliers);
+        const auto same = [&](const Refit &r, int64_t at, int waves) {
+            check(!memcmp(&r, &want, offsetof(Refit, bits)), "refit differs, points, waves", n, waves);
+            if (at + n <= 512 * 32)
+                for (int i = 0; i < n; ++i)
+                    check(((r.bits[(at + i) / 32] >> ((at + i) % 32)) & 1) ==
+                              ((want.bits[i / 32] >> (i % 32)) & 1),
+                          "mask differs, points, waves", n, waves);
+        };
+        for (int64_t at : {0, 1, 31, 77}) {
+            same(refit<4>(c, 4, at, 2), at, 4);
+            same(refit<16>(c, 16, at, 3), at, 16);
+            if (n < kRefitBigPoints) same(refit<4>(c, 1, at, 4), at, 1);
+        }
+    }
+}
+
 }  // namespace
 
 int main(int argc, char **argv) {
@@ -136,6 +202,8 @@ int main(int argc, char **argv) {
     } else if (!strcmp(what, "other-workgroups")) {
         other_workgroups<false>();
         other_workgroups<true>();
+    } else if (!strcmp(what, "refit-order")) {
+        refit_order();
     } else {
         return 2;
     }
