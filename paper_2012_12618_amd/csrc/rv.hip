@@ -388,6 +388,13 @@ __global__ __launch_bounds__(kPrepBlock) void prep_kernel(
     if (bits != nullptr && p < n_words) bits[p] = 0u;
 }
 
+// The point at byte offset `at` of a row (a wave-uniform base, so that the load takes
+// it from scalar registers; indexing the row by the lane cost a 64-bit vector
+// multiply-add for every row).
+__device__ __forceinline__ const StagedPoint &row_point(const StagedPoint *row, uint32_t at) {
+    return *reinterpret_cast<const StagedPoint *>(reinterpret_cast<const char *>(row) + at);
+}
+
 // R rows of 64 points per lane (registers) against ng groups of kHypGroup
 // hypotheses read from LDS (broadcast reads: every lane gets the same (vx, vy));
 // returns the count of hypothesis q of the wave in lane q.  kScalarLoop: the
@@ -429,16 +436,17 @@ template <int R, bool kScalarLoop = false>
 __device__ __forceinline__ uint32_t score_rows(const StagedPoint *__restrict__ chunk, int npts,
                                                int lane, const float4 *hp, int ng, float tau) {
     float c[R], s[R], v[R];
+    const uint32_t at = (uint32_t)lane * (uint32_t)sizeof(StagedPoint);
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-        // Uniform row base and row length, one lane offset: no per-row address
-        // registers.
+        // Uniform row base and row length, one 32-bit lane offset: no per-row address
+        // arithmetic on the vector unit.
         const int len = npts - r * kWave;
         c[r] = 0.0f;
         s[r] = 0.0f;
         v[r] = __builtin_inff();
         if (lane < len) {
-            const StagedPoint &q = chunk[r * kWave + lane];
+            const StagedPoint &q = row_point(chunk + r * kWave, at);
             c[r] = q.c;
             s[r] = q.s;
             v[r] = q.v;
@@ -784,13 +792,14 @@ __device__ __forceinline__ uint32_t score_rows_fp16(const StagedPoint *__restric
     static_assert(R % 4 == 0, "rows come in blocks of four");
     uint32_t cs[R];
     float w[R];
+    const uint32_t at = (uint32_t)lane * (uint32_t)sizeof(StagedPoint);
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         const int len = npts - r * kWave;
         cs[r] = 0u;
         w[r] = __builtin_inff();
         if (lane < len) {
-            const StagedPoint &q = chunk[r * kWave + lane];
+            const StagedPoint &q = row_point(chunk + r * kWave, at);
             cs[r] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(q.c, q.s));
             w[r] = __builtin_fmaf(-ry, q.s, __builtin_fmaf(-rx, q.c, q.v));
         }
