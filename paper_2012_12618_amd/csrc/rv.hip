@@ -2611,9 +2611,11 @@ int64_t prune_from(int32_t rounds, float tau, const int32_t *hyp_counts) {
 // 96 and 128 points (198, 245 and 256 us with lanes = points above 64 and one
 // hypothesis per thread below), with a table 236 and 241 us at 128 and 192.  With one
 // block per workgroup a broadcast serves one hypothesis and LDS sets the rate, yet
-// up to 200 points it is still the shorter chain (frame of 64 clusters of 20 to 200
-// points 10.8 and 10.1 us; 1021 clusters in 3-degree windows 44.0 and 43.2 us).
-constexpr int32_t kSmallAlone = 200;
+// nearly as far as the tile goes it is the shorter chain (call this way and with lanes =
+// points: 4096 clusters of 210 points at 256 hypotheses 54.1 and 59.5 us, 1000 of 230 points
+// at 512 28.0 and 30.7, 64 of 230 points 18.6 and 18.5; of 256 points 58.7 and 63.7,
+// 29.3 and 30.8, but 18.4 and 17.4).
+constexpr int32_t kSmallAlone = 240;
 
 int32_t small_to(int32_t rounds, float tau, int32_t lanes_max) {
     if (lanes_max == 0 || !ordinary_tau(tau)) return 0;
