@@ -603,6 +603,19 @@ __device__ __forceinline__ unsigned long long block_key(const unsigned long long
     return uniform_u64(key);
 }
 
+// A cluster's key while other workgroups may merge into it (some value it had lately),
+// the same in every lane.
+__device__ __forceinline__ unsigned long long load_key(const unsigned long long *key) {
+    return uniform_u64(__hip_atomic_load(key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+}
+
+// A cluster's key with every merge that came before, the same in every lane.
+__device__ __forceinline__ unsigned long long read_key(unsigned long long *key) {
+    unsigned long long k = 0;
+    if (threadIdx.x % kWave == 0) k = atomicMax(key, 0ull);
+    return uniform_u64(k);
+}
+
 // Merges a block's best key into the cluster's: a 64-bit atomic maximum, whose
 // result does not depend on the order of the blocks.  Called by the whole block
 // (the guard is wave-uniform: it may sit in a loop with barriers, see
@@ -614,27 +627,29 @@ __device__ __forceinline__ void merge_key(unsigned long long *best_key, unsigned
     }
 }
 
+constexpr int kPruneHyp = 1024;  // hypotheses per workgroup, at most
+
 // Workgroup LDS of the rows form.
 template <int B>
 struct RowsShared {
-    float4 hyp[B / 2];  // (vx, vy) pairs, two per float4
+    float4 hyp[kPruneHyp / 2];  // (vx, vy) pairs, two per float4
     unsigned long long key[B / kWave];
     LaneTile<kLaneTile> tile;
 };
 
 // One scoring block: hypotheses [b B, b B + B) of one cluster, B threads.  Each
-// thread draws and solves one hypothesis into LDS; each wave then scores 64 of
-// them against every point of the cluster: lanes = points over the cluster's full
+// thread draws and solves one hypothesis into LDS (drawn: they are there, at entry q B
+// of its list); each wave then scores 64 of them against every point of the cluster: lanes = points over the cluster's full
 // rows, lanes = hypotheses over its tail, or over the whole cluster when it has at
 // most lanes_max (<= kLaneTile) points.  Returns the block's best (count, lowest
 // index) key over its valid hypotheses, the same in every thread.  Called by all
 // threads of the block, also from the persistent loop (every branch around a
 // barrier is on a wave-uniform value).
 template <int B>
-__device__ __forceinline__ unsigned long long score_block(Span sp, ClusterId id, int b,
-                                                          int32_t n_hyp, const Points &pts,
-                                                          float tau, int rows_max, int lanes_max,
-                                                          RowsShared<B> &sh,
+__device__ __forceinline__ unsigned long long score_block(Span sp, ClusterId id, int b, int q,
+                                                          bool drawn, int32_t n_hyp,
+                                                          const Points &pts, float tau, int rows_max,
+                                                          int lanes_max, RowsShared<B> &sh,
                                                           int32_t *__restrict__ hyp_counts) {
     static_assert(kLaneTile <= B, "a thread stages a point");
     const int tid = threadIdx.x;
@@ -644,17 +659,20 @@ __device__ __forceinline__ unsigned long long score_block(Span sp, ClusterId id,
         return 0;
     }
     const int tail = sp.n <= lanes_max ? (int)sp.n : lanes_tail(sp.n);  // the same for the block
+    const float4 *hyp = sh.hyp + q * (B / 2);
     float2 own = make_float2(__builtin_nanf(""), __builtin_nanf(""));
     {
         // The tail points' loads go out before the hypothesis's seed loads and
         // are stored after its solve, so the two latencies overlap.
         PointLoad tl;
         if (tail > 0) tl = load_point(pts, sp.lo + sp.n - tail, tail);
-        if (h < n_hyp) {
-            const Hypothesis hyp = make_hypothesis(pts, sp, (uint32_t)h, id.local, id.key0, id.key1);
-            own = make_float2((float)hyp.vx, (float)hyp.vy);  // NaN exactly when degenerate
+        if (!drawn) {
+            if (h < n_hyp) {
+                const Hypothesis y = make_hypothesis(pts, sp, (uint32_t)h, id.local, id.key0, id.key1);
+                own = make_float2((float)y.vx, (float)y.vy);  // NaN exactly when degenerate
+            }
+            reinterpret_cast<float2 *>(sh.hyp)[q * B + tid] = own;
         }
-        reinterpret_cast<float2 *>(sh.hyp)[tid] = own;
         if (tail > 0) store_points(tl, tail, sh.tile.c, sh.tile.s, sh.tile.v);
     }
     __syncthreads();
@@ -668,13 +686,12 @@ __device__ __forceinline__ unsigned long long score_block(Span sp, ClusterId id,
         Span rows = sp;
         rows.n -= tail;
         uint32_t cnt = 0;
-        if (rows.n > 0) {
-            cnt = score_cluster<kPassRows, true>(pts, rows, lane, sh.hyp + wave * (kWave / 2), nh,
-                                                 tau, rows_max);
-            // The lane's own hypothesis is re-read from LDS rather than kept in
-            // registers through the scoring loop.
-            own = reinterpret_cast<const float2 *>(sh.hyp)[tid];
-        }
+        if (rows.n > 0)
+            cnt = score_cluster<kPassRows, true>(pts, rows, lane, hyp + wave * (kWave / 2), nh, tau,
+                                                 rows_max);
+        // The lane's own hypothesis is re-read from LDS rather than kept in
+        // registers through the scoring loop.
+        own = reinterpret_cast<const float2 *>(hyp)[tid];
         cnt += tail_count(sh.tile, tail, own.x, own.y, tau);
         if (lane < nh) {
             if (hyp_counts != nullptr) hyp_counts[id.out * n_hyp + h] = (int32_t)cnt;
@@ -966,8 +983,46 @@ __device__ __forceinline__ uint32_t fp16_counts(Span sp, const Points &pts, int 
 // widened by 2^-18 (tau + M).
 // ---------------------------------------------------------------------------
 
-constexpr int kPruneHyp = 1024;     // hypotheses per workgroup, at most
 constexpr int kSample = 32;         // points of the sample
+
+// Clusters of at least this many points in a long frame of few workgroups are deferred
+// when the table would exclude too little (plan_score); the mark in such a cluster's key.
+constexpr int64_t kDeferPoints = 1024;
+constexpr uint32_t kGiveUpPoints = 2048;
+constexpr unsigned long long kDeferred = 1ull << 63;
+
+// When the table would exclude too little, every hypothesis is counted after all: when
+// the reference holds fewer than `sample` of the 32 sampled points, seen before the
+// table is made, or fewer than share / 64 of the cluster's points, seen after it.  The
+// hypotheses are drawn already; what is lost are one or two sweeps.  Scoring stage in us
+// at 1024 hypotheses: always with the table, by this rule, and before there was a table:
+//   outliers             60 %            70 %             90 %
+//   3177 of 330 points   85,  86,  92    140, 121, 92     190, 112, 93
+//   2048 of 512 points   73,  75,  81    116,  99, 81     140, 100, 81
+//   5242 of 200 points  100,  99, 109    158, 112, 110    225,  95, 109
+// Small clusters (score_small is their other form) gain least from the table.  From 1024
+// points on it still halves the time at 60 % (256 of 4096 points 63, 63, 97 us) and
+// makes no difference at 70 % (98, 98, 97), and a workgroup that gives up by the chance of
+// its sample alone sets the end of the call (4096 clusters of 8 to 4096 points at 60 %: 124
+// us, 146 with the line of 1024 points for all): only the hopeless are told.  A few
+// hypotheses are not given up either: the list's count shares the points between all
+// waves (16 clusters of 4096 points, 64 hypotheses, 85 %: call 47 and 87 us).
+// A long cluster that a single compute unit would be counting is given up sooner, since
+// it is spread over the chip then (64 of 30,000 points 59, 56, 467 us; 374, 214, 468;
+// 721, 214, 468 with the refit).
+struct GiveUp {
+    uint32_t sample, share;
+};
+
+// (enough: more than half of the workgroup's waves would have hypotheses to count.)
+__device__ __forceinline__ GiveUp give_up(uint32_t n, bool enough, bool defer) {
+    if (!enough) return {0, 0};
+    if (n <= kLaneTile) return {13, 17};
+    if (n < kDeferPoints) return {8, 17};
+    if (defer) return {6, 20};
+    if (n < kGiveUpPoints) return {6, 12};
+    return {3, 0};
+}
 
 // Smallest cluster scored this way, by blocks of 256 hypotheses per workgroup
 // (at least 1).  The table is made once per workgroup, so the more blocks share it
@@ -1078,13 +1133,15 @@ __device__ __forceinline__ void sweep_points(const StagedPoint *points, uint32_t
 // nullptr: none) beats them all, some key not above it.  Called by all threads
 // of the block, also from the persistent loop: every branch around a barrier is
 // on a wave-uniform value.
+// full: the table excludes too little (give_up) and nothing was counted; the
+// hypotheses lie in LDS (sh.hyp, NaN for a degenerate pair and past the last).
 // kHalf: the remaining hypotheses are first counted in the FP16 residual form (see
 // below; r as its reference velocity), 64 at a time, and only those whose upper
 // count still reaches the best key are counted in float32.
 template <int B, bool kHalf = false>
 __device__ __forceinline__ unsigned long long score_pruned(
     Span sp, ClusterId id, int64_t h_first, int nh, const Points &pts, float tau,
-    PruneShared<B> &sh, const unsigned long long *best_key) {
+    PruneShared<B> &sh, const unsigned long long *best_key, bool defer, bool &full) {
     constexpr int kPruneRounds = kPruneHyp / B;
     constexpr int kDirs = kAngleBins<B>;
     const int tid = threadIdx.x;
@@ -1111,18 +1168,25 @@ __device__ __forceinline__ unsigned long long score_pruned(
     // The hypotheses, two at a time so that their seed loads overlap (NaN for a
     // degenerate pair and past the last).
     float2 own = make_float2(0.0f, 0.0f);  // the thread's first
-    for (int q = 0; q < rounds; q += 2) {
-        const int h0 = q * B + tid, h1 = h0 + B;
-        const Seeds d0 = draw_seeds(pts, sp, (uint32_t)(h_first + h0), id.local, id.key0, id.key1);
-        const Seeds d1 = draw_seeds(pts, sp, (uint32_t)(h_first + h1), id.local, id.key0, id.key1);
-        const Hypothesis y0 = solve_seeds(pts, d0);
-        const float qnan = __builtin_nanf("");
-        const float2 f0 = h0 < nh ? make_float2((float)y0.vx, (float)y0.vy) : make_float2(qnan, qnan);
-        hyp[h0] = f0;
-        if (q == 0) own = f0;
-        if (q + 1 < rounds) {
-            const Hypothesis y1 = solve_seeds(pts, d1);
-            hyp[h1] = h1 < nh ? make_float2((float)y1.vx, (float)y1.vy) : make_float2(qnan, qnan);
+    const float2 none = make_float2(__builtin_nanf(""), __builtin_nanf(""));
+    if (kPruneRounds == 1 || rounds == 1) {
+        const Hypothesis y =
+            make_hypothesis(pts, sp, (uint32_t)(h_first + tid), id.local, id.key0, id.key1);
+        own = tid < nh ? make_float2((float)y.vx, (float)y.vy) : none;
+        hyp[tid] = own;
+    } else {
+        for (int q = 0; q < rounds; q += 2) {
+            const int h0 = q * B + tid, h1 = h0 + B;
+            const Seeds d0 = draw_seeds(pts, sp, (uint32_t)(h_first + h0), id.local, id.key0, id.key1);
+            const Seeds d1 = draw_seeds(pts, sp, (uint32_t)(h_first + h1), id.local, id.key0, id.key1);
+            const Hypothesis y0 = solve_seeds(pts, d0);
+            const float2 f0 = h0 < nh ? make_float2((float)y0.vx, (float)y0.vy) : none;
+            hyp[h0] = f0;
+            if (q == 0) own = f0;
+            if (q + 1 < rounds) {
+                const Hypothesis y1 = solve_seeds(pts, d1);
+                hyp[h1] = h1 < nh ? make_float2((float)y1.vx, (float)y1.vy) : none;
+            }
         }
     }
     qlo = wave_min_f(qlo);
@@ -1168,10 +1232,17 @@ __device__ __forceinline__ unsigned long long score_pruned(
     for (int w = 0; w < B / kWave; ++w) ref = sh.key[w] > ref ? sh.key[w] : ref;
     ref = uniform_u64(ref);
 
+    const GiveUp rule = give_up(n, nh > B / 2, B == kLongBlock && defer);
+    full = ref == 0 || (uint32_t)(ref >> 32) < rule.sample;
+    if (full) {
+        __syncthreads();  // the caller puts other data there
+        return 0;
+    }
+
     unsigned long long best = 0;  // best known (count, hypothesis) key, the same in every lane
     uint32_t ub[kPruneRounds];
     float rx = 0.0f, ry = 0.0f;
-    if (ref != 0) {
+    {
         // 2. Table of the points under r.
         const uint32_t r_local = 0xFFFFFFFFu - (uint32_t)ref;
         rx = uniform_f(hyp[r_local].x);
@@ -1195,6 +1266,11 @@ __device__ __forceinline__ unsigned long long score_pruned(
 #pragma unroll
         for (int w = 1; w < B / kWave; ++w) t += sh.n[w];
         best = uniform_u64(hyp_key(t, h_first + r_local));
+        full = (uint32_t)(best >> 32) < (uint32_t)(((uint64_t)n * rule.share) >> 6);
+        if (full) {
+            __syncthreads();
+            return 0;
+        }
         // Prefix sums along each row: 32 threads per row, eight bins each.
         constexpr int kRowThreads = 32;
         static_assert(kDirs * kRowThreads <= B && kDirs * kRowThreads % kWave == 0 &&
@@ -1249,18 +1325,13 @@ __device__ __forceinline__ unsigned long long score_pruned(
                 ub[q] = __builtin_isnan(h.x) || (q == 0 && tid == (int)r_local) ? 0u : bound;
             }
         }
-    } else {
-#pragma unroll
-        for (int q = 0; q < kPruneRounds; ++q)
-            ub[q] = q < rounds && !__builtin_isnan(hyp[q * B + tid].x) ? n : 0u;
     }
 
     // 4. The largest bound of each wave's hypotheses above the best key known
     // (this workgroup's r, or another workgroup's of the same cluster).
     unsigned long long floor_key = best;
     if (best_key != nullptr) {
-        const unsigned long long other = uniform_u64(
-            __hip_atomic_load(best_key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+        const unsigned long long other = load_key(best_key);
         floor_key = other > best ? other : best;
     }
     unsigned long long top = 0;
@@ -1447,8 +1518,9 @@ __device__ __forceinline__ void count_small(const LaneTile<kLaneTile> &tile, int
 // every thread.  Called by all threads of the block, also from the persistent loop.
 template <int B>
 __device__ __forceinline__ unsigned long long score_small(Span sp, ClusterId id, int64_t h_first,
-                                                          int nh, int32_t n_hyp, const Points &pts,
-                                                          float tau, SmallShared<B> &sh,
+                                                          int nh, bool drawn, int32_t n_hyp,
+                                                          const Points &pts, float tau,
+                                                          SmallShared<B> &sh,
                                                           int32_t *__restrict__ hyp_counts) {
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
@@ -1457,7 +1529,7 @@ __device__ __forceinline__ unsigned long long score_small(Span sp, ClusterId id,
     float2 *hyp = reinterpret_cast<float2 *>(sh.hyp);
     const PointLoad tl = load_point(pts, sp.lo, n);
 #pragma unroll 1
-    for (int q = 0; q < rounds; ++q) {
+    for (int q = drawn ? rounds : 0; q < rounds; ++q) {
         const int hl = q * B + tid;
         const Hypothesis y =
             make_hypothesis(pts, sp, (uint32_t)(h_first + hl), id.local, id.key0, id.key1);
@@ -1521,25 +1593,39 @@ struct ScoreShared {
     __device__ RefitShared<B / kWave> &refit() { return *reinterpret_cast<RefitShared<B / kWave> *>(bytes); }
 };
 
-// Float32 scoring of hypotheses [h_first, h_first + nh) of one cluster by one
+// Scoring of hypotheses [h_first, h_first + nh) of one cluster by one
 // workgroup (h_first a multiple of B), in the form its size asks for; the best
 // key, the same in every thread.  small_max: clusters of at most this many points
 // (and at least two) take score_small; prune: clusters of at least this many points
-// count only possible winners; otherwise clusters of at most lanes_max points take
-// lanes = hypotheses and the others lanes = points.
-template <int B>
+// count only possible winners (half: behind the FP16 form); where that excludes too
+// little, those up to the tile's size take score_small (unless small_max is 0), and
+// with `defer` those of kDeferPoints points or more get kDeferred for a key; otherwise
+// clusters of at most lanes_max points take lanes = hypotheses and the others
+// lanes = points.
+template <int B, bool kFp16 = false>
 __device__ __forceinline__ unsigned long long score_hypotheses(
     Span sp, ClusterId id, int64_t h_first, int nh, int32_t n_hyp, const Points &pts, float tau,
-    int rows_max, int lanes_max, int small_max, int64_t prune, ScoreShared<B> &sh,
+    int rows_max, int lanes_max, int small_max, int64_t prune, bool half, bool defer,
+    ScoreShared<B> &sh,
     const unsigned long long *best_key, int32_t *__restrict__ hyp_counts) {
+    bool drawn = false;  // the hypotheses lie in LDS
+    if (sp.n >= prune && sp.n > small_max) {
+        unsigned long long key;
+        if (kFp16 && half)
+            key = score_pruned<B, kFp16>(sp, id, h_first, nh, pts, tau, sh.prune(), best_key, defer, drawn);
+        else
+            key = score_pruned<B>(sp, id, h_first, nh, pts, tau, sh.prune(), best_key, defer, drawn);
+        if (!drawn) return key;
+        if (B == kLongBlock && defer && sp.n >= kDeferPoints) return kDeferred;
+        if (small_max > 0 && sp.n <= kLaneTile) small_max = kLaneTile;
+    }
     if (sp.n >= 2 && sp.n <= small_max)
-        return score_small<B>(sp, id, h_first, nh, n_hyp, pts, tau, sh.small(), hyp_counts);
-    if (sp.n >= prune) return score_pruned<B>(sp, id, h_first, nh, pts, tau, sh.prune(), best_key);
+        return score_small<B>(sp, id, h_first, nh, drawn, n_hyp, pts, tau, sh.small(), hyp_counts);
     const int b0 = (int)(h_first / B), blocks = (nh + B - 1) / B;
     unsigned long long best = 0;
-    for (int b = b0; b < b0 + blocks; ++b) {
-        const unsigned long long key = score_block<B>(sp, id, b, n_hyp, pts, tau, rows_max,
-                                                      lanes_max, sh.rows(), hyp_counts);
+    for (int q = 0; q < blocks; ++q) {
+        const unsigned long long key = score_block<B>(sp, id, b0 + q, q, drawn, n_hyp, pts, tau,
+                                                      rows_max, lanes_max, sh.rows(), hyp_counts);
         best = key > best ? key : best;
     }
     return best;
@@ -1858,59 +1944,67 @@ __device__ __forceinline__ void refit_cluster(Span sp, ClusterId id, unsigned lo
         return;
     }
     const int streams = sp.n >= kRefitLongPoints ? 4 * kRefitStreams : kRefitStreams;
-    waves = waves < streams ? waves : streams;
-    if (wave >= waves) return;
-    const int64_t end = sp.lo + sp.n, stride = (int64_t)streams * kWave;
-    int stream = wave;  // of the block after p
-    // The block after the one at p: the next of its stream, then the wave's next stream.
-    const auto after = [&](int64_t p) {
-        p += stride;
-        if (p >= end && stream + waves < streams) {
-            stream += waves;
-            p = sp.lo + (int64_t)stream * kWave;
-        }
-        return p;
-    };
-    // Two blocks' loads in flight while the two before them are summed (the first
-    // pair during the solve).
-    int64_t p0 = sp.lo + (int64_t)wave * kWave, p1 = after(p0);
-    RefitLoad a0 = refit_load(sp, p0, pts, lane), a1 = refit_load(sp, p1, pts, lane);
+    const bool shared = waves > 1;
+    // Where there are more waves than streams, the others only come to the barriers.
+    constexpr bool kMore = kWaves > kRefitStreams;
+    if (kMore && waves > streams) waves = streams;
     const uint32_t hbest = 0xFFFFFFFFu - (uint32_t)(best & 0xFFFFFFFFull);
-    const Hypothesis hy = make_hypothesis(pts, sp, hbest, id.local, id.key0, id.key1);
-    RefitSums a, stream_sums;
+    RefitSums a;
+    if (!kMore || wave < waves) {
+        const int64_t end = sp.lo + sp.n, stride = (int64_t)streams * kWave;
+        int stream = wave;  // of the block after p
+        // The block after the one at p: the next of its stream, then the wave's next stream.
+        const auto after = [&](int64_t p) {
+            p += stride;
+            if (p >= end && stream + waves < streams) {
+                stream += waves;
+                p = sp.lo + (int64_t)stream * kWave;
+            }
+            return p;
+        };
+        // Two blocks' loads in flight while the two before them are summed (the first
+        // pair during the solve).
+        int64_t p0 = sp.lo + (int64_t)wave * kWave, p1 = after(p0);
+        RefitLoad a0 = refit_load(sp, p0, pts, lane), a1 = refit_load(sp, p1, pts, lane);
+        const Hypothesis hy = make_hypothesis(pts, sp, hbest, id.local, id.key0, id.key1);
+        RefitSums stream_sums;
 #pragma unroll 1
-    while (p0 < end) {
-        const int64_t p2 = p1 < end ? after(p1) : p1;
-        const RefitLoad b0 = refit_load(sp, p2, pts, lane);
-        const int64_t p3 = p2 < end ? after(p2) : p2;
-        const RefitLoad b1 = refit_load(sp, p3, pts, lane);
-        refit_points(p0, a0.in, a0.p.v, cs64(a0.p, a0.low), hy, (double)tau, stream_sums, o, lane);
-        if (p1 != p0 + stride) {
-            add_sums(a, stream_sums);
-            stream_sums = RefitSums();
-        }
-        if (p1 < end) {
-            refit_points(p1, a1.in, a1.p.v, cs64(a1.p, a1.low), hy, (double)tau, stream_sums, o, lane);
-            if (p2 != p1 + stride) {
+        while (p0 < end) {
+            const int64_t p2 = p1 < end ? after(p1) : p1;
+            const RefitLoad b0 = refit_load(sp, p2, pts, lane);
+            const int64_t p3 = p2 < end ? after(p2) : p2;
+            const RefitLoad b1 = refit_load(sp, p3, pts, lane);
+            refit_points(p0, a0.in, a0.p.v, cs64(a0.p, a0.low), hy, (double)tau, stream_sums, o, lane);
+            if (p1 != p0 + stride) {
                 add_sums(a, stream_sums);
                 stream_sums = RefitSums();
             }
+            if (p1 < end) {
+                refit_points(p1, a1.in, a1.p.v, cs64(a1.p, a1.low), hy, (double)tau, stream_sums, o,
+                             lane);
+                if (p2 != p1 + stride) {
+                    add_sums(a, stream_sums);
+                    stream_sums = RefitSums();
+                }
+            }
+            a0 = b0;
+            a1 = b1;
+            p0 = p2;
+            p1 = p3;
         }
-        a0 = b0;
-        a1 = b1;
-        p0 = p2;
-        p1 = p3;
+        add_sums(a, stream_sums);
     }
-    add_sums(a, stream_sums);
-    if (waves > 1) {
+    if (shared) {
         __syncthreads();  // sh may lie where other LDS was read until now
-        sh.sum[wave][0][lane] = a.scc;
-        sh.sum[wave][1][lane] = a.scs;
-        sh.sum[wave][2][lane] = a.sss;
-        sh.sum[wave][3][lane] = a.scv;
-        sh.sum[wave][4][lane] = a.ssv;
-        sh.cnt[wave][0][lane] = a.n_in;
-        sh.cnt[wave][1][lane] = a.n_near;
+        if (!kMore || wave < waves) {
+            sh.sum[wave][0][lane] = a.scc;
+            sh.sum[wave][1][lane] = a.scs;
+            sh.sum[wave][2][lane] = a.sss;
+            sh.sum[wave][3][lane] = a.scv;
+            sh.sum[wave][4][lane] = a.ssv;
+            sh.cnt[wave][0][lane] = a.n_in;
+            sh.cnt[wave][1][lane] = a.n_near;
+        }
         __syncthreads();
         if (wave > 0) return;
         a = RefitSums();
@@ -1936,6 +2030,53 @@ __device__ __forceinline__ void refit_cluster(Span sp, ClusterId id, unsigned lo
 
 // ---- single frame ---------------------------------------------------------
 
+// Merges the workgroup's key into cluster j's and returns 1 in every lane of the calling
+// wave when all `parts` of the cluster have done so, else 0.  The workgroups exchange
+// nothing but the two words, both by atomic operations of the whole device: the merge has
+// returned before the count is raised, so the last one's read sees every merge.  (A fence
+// would also invalidate the XCD's L2: scoring of 4096 mixed clusters 146 us for 74.)
+template <typename ClusterAt>
+__device__ __forceinline__ uint32_t merge_part(const ClusterAt &at, int64_t j, unsigned long long key,
+                                               uint32_t parts, int lane) {
+    uint32_t last = 0;
+    if (lane == 0) {
+        const unsigned long long before = atomicMax(at.key(j), key);
+        __builtin_amdgcn_s_waitcnt(0);
+        last = at.arrive(j) == parts - 1 && before != ~0ull ? 1u : 0u;
+    }
+    return __builtin_amdgcn_readfirstlane(last);
+}
+
+// Cluster at planned position j of a single frame.
+struct FrameClusterAt {
+    const int32_t *off;
+    int32_t *order;
+    int64_t n_points;
+    uint32_t key0, key1, cluster_base;
+    int64_t point_base;
+    unsigned long long *best_key;
+    // The upper half of an entry counts the cluster's parts that are done, where the last
+    // one refits it (there is an order for up to 65,536 clusters).
+    __device__ int64_t index(int64_t j) const { return order != nullptr ? order[j] & 0xFFFF : j; }
+    __device__ uint32_t arrive(int64_t j) const {
+        return atomicAdd(reinterpret_cast<uint32_t *>(order) + j, 1u << 16) >> 16;
+    }
+    __device__ Span span(int64_t j) const {
+        return cluster_span(off, index(j), n_points, point_base);
+    }
+    __device__ unsigned long long best(int64_t j) const { return best_key[index(j)]; }
+    __device__ unsigned long long *key(int64_t j) const { return &best_key[index(j)]; }
+    __device__ unsigned long long merged(int64_t j) const { return read_key(key(j)); }
+    __device__ ClusterId id(int64_t j) const {
+        ClusterId c;
+        c.out = index(j);
+        c.local = cluster_base + (uint32_t)c.out;
+        c.key0 = key0;
+        c.key1 = key1;
+        return c;
+    }
+};
+
 // refit_big (a workgroup has all hypotheses of a cluster, clusters are many): the
 // workgroup refits its cluster itself from kRefitBigPoints on.  The points are still
 // in the XCD's L2 and the work runs beside other clusters' scoring.  Smaller ones
@@ -1952,33 +2093,129 @@ __device__ __forceinline__ void refit_cluster(Span sp, ClusterId id, unsigned lo
 // fits in 64 VGPRs.
 template <int B>
 __global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(B == kLongBlock ? 4 : 8))) void score_kernel(
-    const int32_t *__restrict__ off, const int32_t *__restrict__ order, int64_t n_clusters,
+    const int32_t *__restrict__ off, int32_t *order, int64_t n_clusters,
     int64_t n_points, int32_t n_hyp, int32_t rounds, int32_t parts, uint32_t key0, uint32_t key1,
     uint32_t cluster_base, int64_t point_base, int32_t small_max, int64_t prune, Points pts,
-    float tau, unsigned long long *__restrict__ best_key, Outputs o, bool refit_big) {
+    float tau, unsigned long long *__restrict__ best_key, Outputs o, bool refit_big, bool defer) {
     __shared__ ScoreShared<B> s;
     const uint32_t xcd = blockIdx.x % kXcds;
     const uint32_t r = blockIdx.x / kXcds;
     const int64_t j = xcd + (int64_t)kXcds * (r / (uint32_t)parts);
     if (j >= n_clusters) return;
-    const int64_t k = order != nullptr ? order[j] : j;
-    ClusterId id;
-    id.out = k;
-    id.local = cluster_base + (uint32_t)k;
-    id.key0 = key0;
-    id.key1 = key1;
-    const Span sp = cluster_span(off, k, n_points, point_base);
+    const FrameClusterAt at = {off, order, n_points, key0, key1, cluster_base, point_base,
+                               best_key};
+    const int64_t k = at.index(j);
+    const ClusterId id = at.id(j);
+    const Span sp = at.span(j);
     const int most = rounds * B;
     const int64_t first = (int64_t)(r % (uint32_t)parts) * most;
     const int64_t left = n_hyp - first;
     const unsigned long long key = score_hypotheses<B>(
         sp, id, first, left < most ? (int)left : most, n_hyp, pts, tau, kRowsMax, kSingleLanesMax,
-        small_max, prune, s, &best_key[k], o.hyp_counts);
+        small_max, prune, false, defer, s, &best_key[k], o.hyp_counts);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     if (refit_big && sp.n >= kRefitBigPoints)
         refit_cluster(sp, id, key, pts, tau, o, wave, B / kWave, s.refit());
     else
         merge_key(&best_key[k], key, wave, threadIdx.x % kWave);
+}
+
+// Workgroup LDS of a refit kernel.
+template <int B>
+struct DeferredShared {
+    float4 hyp[kScoreBlock / 2];
+    uint32_t count[B / kScoreBlock][kScoreBlock];
+    unsigned long long key[kScoreBlock / kWave];
+    uint32_t last;
+};
+
+template <int B>
+struct RefitSpace {
+    static constexpr size_t kBytes = sizeof(RefitShared<B / kWave>);
+    static_assert(sizeof(DeferredShared<B>) <= kBytes, "the larger");
+    alignas(16) unsigned char bytes[kBytes];
+    __device__ RefitShared<B / kWave> &refit() { return *reinterpret_cast<RefitShared<B / kWave> *>(bytes); }
+    __device__ DeferredShared<B> &deferred() { return *reinterpret_cast<DeferredShared<B> *>(bytes); }
+};
+
+// Counts hypotheses [b 256, b 256 + 256) of a cluster in full: four waves with 64
+// hypotheses each, or in a large workgroup four such groups with a quarter of the
+// points each.  The best key, the same in every thread of the first four waves.
+template <int B>
+__device__ __forceinline__ unsigned long long count_block(Span sp, ClusterId id, int b, int32_t n_hyp,
+                                                          const Points &pts, float tau, int wave,
+                                                          DeferredShared<B> &sh) {
+    constexpr int kGroups = B / kScoreBlock, kWaves = kScoreBlock / kWave;
+    const int tid = threadIdx.x, lane = tid % kWave;
+    const int64_t h = (int64_t)b * kScoreBlock + tid;
+    float2 *hyp = reinterpret_cast<float2 *>(sh.hyp);
+    if (wave < kWaves) {
+        float2 own = make_float2(__builtin_nanf(""), __builtin_nanf(""));
+        if (h < n_hyp) {
+            const Hypothesis y = make_hypothesis(pts, sp, (uint32_t)h, id.local, id.key0, id.key1);
+            own = make_float2((float)y.vx, (float)y.vy);
+        }
+        hyp[tid] = own;
+    }
+    __syncthreads();
+    const int group = wave / kWaves, w = wave % kWaves;
+    const int64_t rows = (sp.n + kWave - 1) / kWave;
+    const int64_t r0 = rows * group / kGroups, r1 = rows * (group + 1) / kGroups;
+    Span part;
+    part.lo = sp.lo + r0 * kWave;
+    part.n = (r1 * kWave < sp.n ? r1 * kWave : sp.n) - r0 * kWave;
+    part.ok = true;
+    sh.count[group][w * kWave + lane] = score_cluster<kPassRows, true>(
+        pts, part, lane, sh.hyp + w * (kWave / 2), kWave, tau, kPassRows);
+    __syncthreads();
+    if (wave < kWaves) {
+        uint32_t cnt = 0;
+#pragma unroll
+        for (int g = 0; g < kGroups; ++g) cnt += sh.count[g][tid];
+        const unsigned long long key = wave_best(__builtin_isnan(hyp[tid].x) ? 0u : cnt + 1u, (uint32_t)h);
+        if (lane == 0) sh.key[wave] = key;
+    }
+    __syncthreads();
+    return block_key<kScoreBlock>(sh.key);
+}
+
+// The deferred clusters (see score_pruned), counted in full in items of 256 hypotheses,
+// dealt round the workgroups [n_clusters, gridDim.x) of a refit kernel in the planned
+// order (largest first), a cluster's on one XCD.  A workgroup looks at 64 of its items
+// at a time; one that ends the last item of a cluster refits it, so none waits for
+// another.  These workgroups start when the others' refits are under way: a call without
+// deferred clusters hardly sees them, as a launch of their own it would have
+// (4096 mixed clusters 84 us of scoring for 75).
+template <int B, typename ClusterAt>
+__device__ __forceinline__ void refit_deferred(int64_t n_clusters, int32_t n_hyp,
+                                               const ClusterAt &at, const Points &pts, float tau,
+                                               const Outputs &o, int wave, RefitSpace<B> &space) {
+    DeferredShared<B> &sh = space.deferred();
+    const int lane = threadIdx.x % kWave;
+    const uint32_t xcd = blockIdx.x % kXcds;
+    const uint32_t step = (uint32_t)(gridDim.x - n_clusters) / kXcds;  // a multiple of kXcds
+    const uint32_t blocks = ((uint32_t)n_hyp + kScoreBlock - 1) / kScoreBlock;
+    const int64_t clusters = n_clusters > (int64_t)xcd ? (n_clusters - xcd + kXcds - 1) / kXcds : 0;
+    const int64_t items = clusters * blocks;
+    for (int64_t first = (blockIdx.x - n_clusters) / kXcds; first < items;
+         first += (int64_t)step * kWave) {
+        const int64_t mine = first + (int64_t)lane * step;
+        const bool here = mine < items && at.best(xcd + kXcds * (mine / blocks)) >= kDeferred;
+        for (uint64_t m = __builtin_amdgcn_ballot_w64(here); m != 0; m &= m - 1) {
+            const int64_t item = first + (int64_t)__builtin_ctzll(m) * step;
+            const int64_t j = xcd + kXcds * (item / blocks);
+            const Span sp = at.span(j);
+            const ClusterId id = at.id(j);
+            const unsigned long long key =
+                count_block<B>(sp, id, (int)(item % blocks), n_hyp, pts, tau, wave, sh);
+            if (wave == 0) sh.last = merge_part(at, j, key | kDeferred, blocks, lane);
+            __syncthreads();
+            if (__builtin_amdgcn_readfirstlane(sh.last) != 0)
+                refit_cluster(sp, id, at.merged(j) & ~kDeferred, pts, tau, o, wave, B / kWave,
+                              space.refit());
+            __syncthreads();
+        }
+    }
 }
 
 // Refit of a frame's or batch's clusters over their planned (largest-first)
@@ -1989,54 +2226,43 @@ __global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(B == kLongBlo
 // cluster gets a workgroup.  The grid is an upper bound (one workgroup per
 // cluster); surplus workgroups exit at once.  big_done: the first n_big clusters
 // were refit by their scoring workgroups.
+//
+// Behind them, where clusters may have been deferred: gridDim.x - n_clusters workgroups
+// that count and refit those (refit_deferred).
 template <int B, typename ClusterAt>
 __device__ __forceinline__ void refit_planned(int64_t n_clusters, const int64_t *n_big,
-                                              const ClusterAt &at, const Points &pts, float tau,
-                                              const Outputs &o, RefitShared<B / kWave> &sh,
+                                              const ClusterAt &at, int32_t n_hyp, const Points &pts,
+                                              float tau, const Outputs &o, RefitSpace<B> &space,
                                               bool big_done) {
     constexpr int kWaves = B / kWave;
+    RefitShared<kWaves> &sh = space.refit();
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    if constexpr (B == kLongBlock) {
+        if (blockIdx.x >= n_clusters) {
+            refit_deferred<B>(n_clusters, n_hyp, at, pts, tau, o, wave, space);
+            return;
+        }
+    }
     const int64_t big = n_big != nullptr ? *n_big : n_clusters;
     const int64_t b = big_done ? blockIdx.x + big : blockIdx.x;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const bool all = b < big;  // the whole workgroup on one cluster
     const int64_t j = all ? b : big + (b - big) * kWaves + wave;
     if (j >= n_clusters) return;
-    refit_cluster(at.span(j), at.id(j), at.best(j), pts, tau, o, all ? wave : 0,
-                  all ? kWaves : 1, sh);
+    const unsigned long long best = at.best(j);
+    if (B == kLongBlock && best >= kDeferred) return;
+    refit_cluster(at.span(j), at.id(j), best, pts, tau, o, all ? wave : 0, all ? kWaves : 1, sh);
 }
-
-// Cluster at planned position j of a single frame.
-struct FrameClusterAt {
-    const int32_t *off, *order;
-    int64_t n_points;
-    uint32_t key0, key1, cluster_base;
-    int64_t point_base;
-    const unsigned long long *best_key;
-    __device__ int64_t index(int64_t j) const { return order != nullptr ? order[j] : j; }
-    __device__ Span span(int64_t j) const {
-        return cluster_span(off, index(j), n_points, point_base);
-    }
-    __device__ unsigned long long best(int64_t j) const { return best_key[index(j)]; }
-    __device__ ClusterId id(int64_t j) const {
-        ClusterId c;
-        c.out = index(j);
-        c.local = cluster_base + (uint32_t)c.out;
-        c.key0 = key0;
-        c.key1 = key1;
-        return c;
-    }
-};
 
 template <int B>
 __global__ __launch_bounds__(B) void refit_kernel(
-    const int32_t *__restrict__ off, const int32_t *__restrict__ order, int64_t n_clusters,
-    const int64_t *__restrict__ n_big, int64_t n_points, uint32_t key0, uint32_t key1,
-    uint32_t cluster_base, int64_t point_base, Points pts,
-    const unsigned long long *__restrict__ best_key, float tau, Outputs o, bool big_done) {
-    __shared__ RefitShared<B / kWave> s_refit;
+    const int32_t *__restrict__ off, int32_t *order, int64_t n_clusters,
+    const int64_t *__restrict__ n_big, int64_t n_points, int32_t n_hyp, uint32_t key0, uint32_t key1,
+    uint32_t cluster_base, int64_t point_base, Points pts, unsigned long long *best_key, float tau,
+    Outputs o, bool big_done) {
+    __shared__ RefitSpace<B> s_refit;
     const FrameClusterAt at = {off, order, n_points, key0, key1, cluster_base, point_base,
                                best_key};
-    refit_planned<B>(n_clusters, n_big, at, pts, tau, o, s_refit, big_done);
+    refit_planned<B>(n_clusters, n_big, at, n_hyp, pts, tau, o, s_refit, big_done);
 }
 
 // Small frames (see use_cluster_path): one workgroup per cluster stages the
@@ -2066,7 +2292,7 @@ __global__ __launch_bounds__(kScoreBlock) __attribute__((amdgpu_waves_per_eu(8))
     id.key1 = key1;
     const unsigned long long best =
         score_hypotheses<kScoreBlock>(sp, id, 0, n_hyp, n_hyp, pts, tau, kRowsMax, kSingleLanesMax,
-                                      small_max, prune, s, nullptr, o.hyp_counts);
+                                      small_max, prune, false, false, s, nullptr, o.hyp_counts);
     refit_cluster(sp, id, best, pts, tau, o, __builtin_amdgcn_readfirstlane(threadIdx.x / kWave),
                   kScoreBlock / kWave, s.refit());
 }
@@ -2101,7 +2327,14 @@ struct Tuning {
 };
 
 // Scoring form of a cluster (ItemDesc::form).
-enum : int16_t { kFormRows = 0, kFormFp16 = 1, kFormLanes = 2, kFormPruned = 3, kFormSmall = 4 };
+enum : uint8_t {
+    kFormRows = 0,
+    kFormFp16 = 1,
+    kFormLanes = 2,
+    kFormPruned = 3,
+    kFormSmall = 4,
+    kFormPrunedSmall = 5  // pruned; if that excludes too little, as kFormSmall
+};
 
 // Everything the scoring and refit workgroups need about one cluster, at its
 // position in the dispatch order: one 32-byte load instead of a chain of
@@ -2111,9 +2344,10 @@ struct alignas(32) ItemDesc {
     int32_t out;           // output index (the cluster's index in the batch)
     uint32_t local;        // counter word 1: index within its frame
     uint32_t key0, key1;   // Philox key: its frame's seed
-    int32_t ok;            // offsets valid
+    uint32_t done;         // parts of a deferred cluster's count that are done
+    uint8_t ok;            // offsets valid
+    uint8_t form;          // kFormRows etc.
     int16_t rows;          // register rows per pass for its size
-    int16_t form;          // kFormRows, kFormFp16 or kFormLanes
 };
 
 constexpr int kQueueStride = 32;  // 64-bit counters: 256 bytes between queues
@@ -2160,8 +2394,12 @@ __device__ __forceinline__ int desc_lanes(const ItemDesc &d) {
     return d.form == kFormLanes ? kLaneTile : 0;
 }
 
+__device__ __forceinline__ int desc_small(const ItemDesc &d) {
+    return d.form == kFormSmall ? kLaneTile : d.form == kFormPrunedSmall ? 1 : 0;
+}
+
 __device__ __forceinline__ int64_t desc_prune(const ItemDesc &d) {
-    return d.form == kFormPruned ? 0 : INT64_MAX;
+    return d.form == kFormPruned || d.form == kFormPrunedSmall ? 0 : INT64_MAX;
 }
 
 // Runs body(cluster position, part) for every item this workgroup takes from the
@@ -2226,6 +2464,7 @@ __device__ __forceinline__ void write_desc(int64_t k, const Span &sp, int64_t f,
     d.local = (uint32_t)(k - bt.frame_off[f]);
     d.key0 = (uint32_t)(seed & 0xFFFFFFFFu);
     d.key1 = (uint32_t)(seed >> 32);
+    d.done = 0;
     d.ok = sp.ok ? 1 : 0;
     d.rows = (int16_t)tune.rows[size_bucket(sp.n)];
     d.form = kFormRows;
@@ -2236,7 +2475,7 @@ __device__ __forceinline__ void write_desc(int64_t k, const Span &sp, int64_t f,
     else if (tune.fp16_min > 0 && sp.ok && sp.n >= 2 && sp.n >= tune.fp16_min)
         d.form = kFormFp16;
     else if (sp.n >= tune.prune)
-        d.form = kFormPruned;
+        d.form = tune.small_max > 0 && sp.n <= kLaneTile ? kFormPrunedSmall : kFormPruned;
     at = d;
 }
 
@@ -2387,7 +2626,7 @@ __global__ __launch_bounds__(kPrepBlock) void batch_scatter_kernel(
 template <bool kFp16, int B>
 __global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(B == kLongBlock ? 4 : kFp16 ? 7 : 8))) void batch_score_kernel(
     const ItemDesc *__restrict__ desc, int64_t n_clusters, int32_t n_hyp,
-    int32_t rounds, int32_t parts, int64_t prune, Points pts, float tau,
+    int32_t rounds, int32_t parts, int64_t prune, bool defer, Points pts, float tau,
     unsigned long long *__restrict__ queues, unsigned long long *__restrict__ best_key,
     int32_t *__restrict__ hyp_counts) {
     __shared__ ScoreShared<B> s;
@@ -2401,17 +2640,9 @@ __global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(B == kLongBlo
         const int64_t first = (int64_t)part * most;
         const int64_t left = n_hyp - first;
         const int nh = left < most ? (int)left : most;
-        if constexpr (kFp16) {
-            if (d.form == kFormFp16 && d.n >= prune) {
-                const unsigned long long key =
-                    score_pruned<B, true>(desc_span(d), desc_id(d), first, nh, pts, tau, s.prune(),
-                                          &best_key[d.out]);
-                merge_key(&best_key[d.out], key, wave, lane);
-                return;
-            }
-        }
+        const bool half = kFp16 && d.form == kFormFp16 && d.n >= prune;
         if constexpr (kFp16 && B == kScoreBlock) {
-            if (d.form == kFormFp16) {
+            if (d.form == kFormFp16 && !half) {
                 const int b0 = part * rounds;
                 for (int b = b0; b < b0 + (nh + kScoreBlock - 1) / kScoreBlock; ++b) {
                     score_block_fp16(desc_span(d), desc_id(d), b, n_hyp, pts, tau, d.rows, s.fp16(),
@@ -2421,29 +2652,33 @@ __global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(B == kLongBlo
                 return;
             }
         }
-        const unsigned long long key = score_hypotheses<B>(
+        const unsigned long long key = score_hypotheses<B, kFp16>(
             desc_span(d), desc_id(d), first, nh, n_hyp, pts, tau, d.rows, desc_lanes(d),
-            d.form == kFormSmall ? kLaneTile : 0, desc_prune(d), s, &best_key[d.out], hyp_counts);
+            desc_small(d), half ? 0 : desc_prune(d), half, defer, s,
+            &best_key[d.out], hyp_counts);
         merge_key(&best_key[d.out], key, wave, lane);
     });
 }
 
 // Cluster at dispatch position j of a batch (its descriptor).
 struct BatchClusterAt {
-    const ItemDesc *desc;
-    const unsigned long long *best_key;
+    ItemDesc *desc;
+    unsigned long long *best_key;
     __device__ Span span(int64_t j) const { return desc_span(desc[j]); }
     __device__ ClusterId id(int64_t j) const { return desc_id(desc[j]); }
     __device__ unsigned long long best(int64_t j) const { return best_key[desc[j].out]; }
+    __device__ unsigned long long *key(int64_t j) const { return &best_key[desc[j].out]; }
+    __device__ unsigned long long merged(int64_t j) const { return read_key(key(j)); }
+    __device__ uint32_t arrive(int64_t j) const { return atomicAdd(&desc[j].done, 1u); }
 };
 
 template <int B>
 __global__ __launch_bounds__(B) void batch_refit_kernel(
-    const ItemDesc *__restrict__ desc, int64_t n_clusters, const int64_t *__restrict__ n_big,
-    Points pts, const unsigned long long *__restrict__ best_key, float tau, Outputs o) {
-    __shared__ RefitShared<B / kWave> s_refit;
+    ItemDesc *desc, int64_t n_clusters, const int64_t *__restrict__ n_big, int32_t n_hyp, Points pts,
+    unsigned long long *best_key, float tau, Outputs o) {
+    __shared__ RefitSpace<B> s_refit;
     const BatchClusterAt at = {desc, best_key};
-    refit_planned<B>(n_clusters, n_big, at, pts, tau, o, s_refit, false);
+    refit_planned<B>(n_clusters, n_big, at, n_hyp, pts, tau, o, s_refit, false);
 }
 
 __global__ __launch_bounds__(kPrepBlock) void philox_kernel(const uint32_t *__restrict__ ctr,
@@ -2636,12 +2871,21 @@ bool use_cluster_path(int64_t n_clusters, int64_t n_points, int32_t n_hyp,
            n_clusters <= kSmallFrameMaxClusters;
 }
 
+// Workgroups behind a refit kernel's own that count deferred clusters (a multiple of
+// kXcds), and the most scoring workgroups of a call that defers: with a workgroup for
+// every second compute unit, spreading a cluster over the chip still makes up for
+// counting it twice in part (100 clusters of 8192 points, 90 % outliers: call 238 us
+// counted in place, 142 us deferred; 200 clusters 206 and 262 us).
+constexpr int kDeferredBlocks = 256;
+constexpr int64_t kDeferItems = 128;
+
 // Split of a call's scoring: workgroups of `block` threads, each with `rounds` blocks
 // of hypotheses of a cluster, `parts` of them per cluster; the pruned form's smallest
 // and score_small's largest cluster.
 struct ScorePlan {
     int32_t block, rounds, parts, small_max;
     int64_t prune;
+    bool defer;
 };
 
 // Few and long clusters (the mean length is what the host knows; the choice is one
@@ -2653,9 +2897,9 @@ struct ScorePlan {
 // The line: scoring of 64 clusters at 1024 hypotheses 44.7 and 35.3 us at 8192 points,
 // 28.0 and 28.8 us at 4096.  Beyond a workgroup per CU a large one's share is too
 // coarse (320 x 8192 points at 300 hypotheses 53 and 65 us) unless it takes the place
-// of four (512 x 16,384 points at 1024 hypotheses 188 and 140 us, 700 x 8192 points
-// 120 and 110 us); refit of 256 clusters of 8192 points 14.6 and 14.4 us, of 512
-// 18.9 and 23.6 us.
+// of four and the clusters are twice as long (512 x 16,384 points at 1024 hypotheses 153
+// and 114 us, 90 % outliers 641 and 730; 300 x 8192 points 67 and 68 us, and with 90 %
+// outliers 238 and 368).
 constexpr int64_t kLongPoints = 8192;
 constexpr int64_t kLongClusters = 256;
 
@@ -2678,7 +2922,8 @@ ScorePlan plan_score(int64_t n_clusters, int64_t n_points, int32_t n_hyp, float 
     // cluster of that form is pruned.
     constexpr int32_t kLongBlocks = kLongBlock / kScoreBlock;
     if (long_clusters(n_clusters, n_points) &&
-        (n_clusters <= kLongClusters || p.parts >= 4 * parts(kLongBlock)) &&
+        (n_clusters <= kLongClusters || (p.parts >= 4 * parts(kLongBlock) &&
+                                         n_points / n_clusters >= 2 * kLongPoints)) &&
         pruned && (fp16_min <= 0 || fp16_min >= prune_min(kLongBlocks))) {
         p.block = kLongBlock;
         p.rounds = 1;
@@ -2688,6 +2933,7 @@ ScorePlan plan_score(int64_t n_clusters, int64_t n_points, int32_t n_hyp, float 
     p.prune = prune_from(blocks, tau, hyp_counts);
     p.small_max = small_to(blocks, tau, lanes_max);
     if (fp16_min > 0 && p.small_max >= fp16_min) p.small_max = fp16_min - 1;
+    p.defer = p.block == kLongBlock && n_clusters * p.parts <= kDeferItems;
     return p;
 }
 
@@ -2696,7 +2942,7 @@ ScorePlan batch_plan(const BatchArgs &a) {
                       a.tuning.lanes_max_points, a.tuning.fp16_min_points);
 }
 
-using BatchScore = void (*)(const ItemDesc *, int64_t, int32_t, int32_t, int32_t, int64_t, Points,
+using BatchScore = void (*)(const ItemDesc *, int64_t, int32_t, int32_t, int32_t, int64_t, bool, Points,
                             float, unsigned long long *, unsigned long long *, int32_t *);
 BatchScore batch_score(bool fp16, int32_t block) {
     if (block == kLongBlock)
@@ -2706,22 +2952,20 @@ BatchScore batch_score(bool fp16, int32_t block) {
 
 // The refit kernel over planned positions; n_big (device, nullable) is the
 // ordering pass's count of big clusters.
-void launch_refit(bool batch, const int32_t *off, const int32_t *order, const ItemDesc *desc,
-                  int64_t n_clusters, const int64_t *n_big, int64_t n_points, uint32_t key0,
-                  uint32_t key1, uint32_t cluster_base, int64_t point_base, const Points &pts,
-                  const unsigned long long *best_key, float tau, const Outputs &o, bool big_done,
-                  hipStream_t st) {
-    const bool large = long_clusters(n_clusters, n_points) && n_clusters <= kLongClusters;
+void launch_refit(bool batch, const int32_t *off, int32_t *order, ItemDesc *desc,
+                  int64_t n_clusters, const int64_t *n_big, int64_t n_points, int32_t n_hyp,
+                  uint32_t key0, uint32_t key1, uint32_t cluster_base, int64_t point_base,
+                  const Points &pts, unsigned long long *best_key, float tau, const Outputs &o,
+                  bool big_done, bool large, bool defer, hipStream_t st) {
     const dim3 block(large ? kLongBlock : kRefitBlock);
+    const dim3 grid((unsigned)(n_clusters + (defer ? kDeferredBlocks : 0)));
     if (batch)
         hipLaunchKernelGGL(large ? batch_refit_kernel<kLongBlock> : batch_refit_kernel<kRefitBlock>,
-                           dim3((unsigned)n_clusters), block, 0, st, desc, n_clusters, n_big, pts,
-                           best_key, tau, o);
+                           grid, block, 0, st, desc, n_clusters, n_big, n_hyp, pts, best_key, tau, o);
     else
         hipLaunchKernelGGL(large ? refit_kernel<kLongBlock> : refit_kernel<kRefitBlock>,
-                           dim3((unsigned)n_clusters), block, 0, st, off, order, n_clusters, n_big,
-                           n_points, key0, key1, cluster_base, point_base, pts, best_key, tau, o,
-                           big_done);
+                           grid, block, 0, st, off, order, n_clusters, n_big, n_points, n_hyp, key0,
+                           key1, cluster_base, point_base, pts, best_key, tau, o, big_done);
 }
 
 // Persistent grid of the batched scoring kernel on the current device.
@@ -2798,11 +3042,11 @@ int launch_batch(const BatchArgs &a, unsigned grid, hipStream_t st, bool allow_t
     if (timed) (void)hipEventRecord(tc.ev[1], st);
     hipLaunchKernelGGL(batch_score(a.tuning.fp16_min_points > 0, plan.block), dim3(grid),
                        dim3(plan.block), 0, st, (const ItemDesc *)desc, a.n_clusters, a.n_hyp,
-                       plan.rounds, plan.parts, plan.prune, pts, a.tau, queues, best_key,
+                       plan.rounds, plan.parts, plan.prune, plan.defer, pts, a.tau, queues, best_key,
                        a.o.hyp_counts);
     if (timed) (void)hipEventRecord(tc.ev[2], st);
-    launch_refit(true, nullptr, nullptr, (const ItemDesc *)desc, a.n_clusters, n_big,
-                 a.n_points, 0, 0, 0, 0, pts, best_key, a.tau, a.o, false, st);
+    launch_refit(true, nullptr, nullptr, desc, a.n_clusters, n_big, a.n_points, a.n_hyp, 0, 0, 0, 0,
+                 pts, best_key, a.tau, a.o, false, plan.block == kLongBlock, plan.defer, st);
     if (timed) {
         (void)hipEventRecord(tc.ev[3], st);
         keep_timed_call(tc);
@@ -2932,6 +3176,7 @@ int estimate_frame(const float *theta, const float *vd, const int32_t *cluster_o
         plan_score(n_clusters, n_points, n_hyp, tau, hyp_counts, kSingleLanesMax, 0);
     const bool many = n_clusters >= kRefitManyClusters;
     const bool refit_big = plan.parts == 1 && many && order != nullptr;  // the order counts them
+    const bool defer = plan.defer && order != nullptr;
     int64_t prep_items = n_points > n_words ? n_points : n_words;
     prep_items = prep_items > n_clusters ? prep_items : n_clusters;
     const int64_t prep_blocks = (prep_items + kPrepBlock - 1) / kPrepBlock + 1;  // + planner
@@ -2943,13 +3188,13 @@ int estimate_frame(const float *theta, const float *vd, const int32_t *cluster_o
     hipLaunchKernelGGL(plan.block == kLongBlock ? score_kernel<kLongBlock>
                                                 : score_kernel<kScoreBlock>,
                        dim3((unsigned)(clusters_xcd * plan.parts)), dim3(plan.block), 0, st,
-                       cluster_offsets, (const int32_t *)order, n_clusters, n_points, n_hyp,
+                       cluster_offsets, order, n_clusters, n_points, n_hyp,
                        plan.rounds, plan.parts, key0, key1, first_cluster, first_point,
-                       plan.small_max, plan.prune, pts, tau, best_key, o, refit_big);
+                       plan.small_max, plan.prune, pts, tau, best_key, o, refit_big, defer);
     if (timed) (void)hipEventRecord(tc.ev[2], st);
     launch_refit(false, cluster_offsets, order, nullptr, n_clusters,
-                 order != nullptr ? (const int64_t *)n_big : nullptr, n_points, key0, key1,
-                 first_cluster, first_point, pts, best_key, tau, o, refit_big, st);
+                 order != nullptr ? (const int64_t *)n_big : nullptr, n_points, n_hyp, key0, key1,
+                 first_cluster, first_point, pts, best_key, tau, o, refit_big, plan.block == kLongBlock, defer, st);
     if (timed) {
         (void)hipEventRecord(tc.ev[3], st);
         keep_timed_call(tc);

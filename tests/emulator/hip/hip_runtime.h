@@ -220,6 +220,7 @@ template <typename T, typename U> T atomicMax(T *p, U v) { const T old = *p; if 
 #define __builtin_amdgcn_mbcnt_hi(m, c) \
     ((c) + (uint32_t)__builtin_popcountll(((uint64_t)(m) << 32) & ((1ull << emu::lane()) - 1)))
 #define __builtin_amdgcn_sched_barrier(x) ((void)0)
+#define __builtin_amdgcn_s_waitcnt(x) ((void)0)
 #define __builtin_amdgcn_bitop3_b32(a, b, c, table) ((a) ^ (b) ^ (c))
 #define __builtin_amdgcn_fmed3f(a, b, c) emu::med3(a, b, c)
 #define __builtin_amdgcn_rcpf(x) (1.0f / (x))

@@ -2,7 +2,9 @@
 // passes its device half as RV_DEVICE_SOURCE): the scoring of a large cluster under
 // many orders of its workgroup's waves, against the count of every hypothesis; the refit
 // by one wave, four and sixteen.
-//   score_host_check no-reference | other-workgroups | refit-order
+//   score_host_check no-reference | other-workgroups | refit-order | deferred
+#include <algorithm>
+
 #include RV_DEVICE_SOURCE
 
 namespace {
@@ -63,7 +65,7 @@ unsigned long long full_key(const Cluster &c, ClusterId id, int64_t first, int n
 
 ClusterId cluster_id(uint32_t seed) { return {0, 3, seed, 77}; }
 
-PruneShared<kScoreBlock> shared;
+ScoreShared<kScoreBlock> shared;
 
 template <bool kHalf>
 unsigned long long pruned(const Cluster &c, ClusterId id, int64_t first, int nh, uint32_t order,
@@ -72,8 +74,9 @@ unsigned long long pruned(const Cluster &c, ClusterId id, int64_t first, int nh,
     memset((void *)&shared, 0xFF, sizeof shared);  // what an earlier workgroup left: NaN, -1
     emu::run(kScoreBlock, order, [&] {
         const uint32_t t = threadIdx.x;
-        const unsigned long long k =
-            score_pruned<kScoreBlock, kHalf>(c.sp, id, first, nh, c.pts, kTau, shared, best_key);
+        const unsigned long long k = score_hypotheses<kScoreBlock, kHalf>(
+            c.sp, id, first, nh, (int32_t)first + nh, c.pts, kTau, kRowsMax, 0, 0, 0, kHalf, false, shared,
+            best_key, nullptr);
         keys[t] = k;
     });
     for (int t = 1; t < kScoreBlock; ++t)
@@ -99,7 +102,7 @@ void no_reference() {
         const unsigned long long want = full_key(c, id, first, nh);
         if (usable || want == 0) continue;
         ++cases;
-        for (uint32_t order = 0; order < 40; ++order)
+        for (uint32_t order = 0; order < 12; ++order)
             check(pruned<false>(c, id, first, nh, order, nullptr) == want,
                   "no reference: wrong key, seed, order", (int)seed, (int)order);
     }
@@ -193,6 +196,85 @@ void refit_order() {
     }
 }
 
+// A refit kernel over clusters of which some are deferred, its workgroups one after the
+// other in a drawn order, against the refit of the full count's key.
+template <int B>
+void deferred(int32_t n_hyp, uint32_t seed) {
+    std::mt19937 rng(seed);
+    std::vector<Cluster> clusters;
+    for (int n : {9000, 4200, 2050, 1500, 1024, 1023, 300, 64, 2, 1})
+        clusters.push_back(make_cluster(n, seed * 31 + n, 0.8, n == 2050 ? 0.0 : 1.0));
+    const int64_t K = (int64_t)clusters.size();
+    Cluster all;
+    std::vector<int32_t> off(1, 0), order;
+    for (const Cluster &c : clusters) {
+        all.theta.insert(all.theta.end(), c.theta.begin(), c.theta.end());
+        all.vd.insert(all.vd.end(), c.vd.begin(), c.vd.end());
+        off.push_back((int32_t)all.theta.size());
+        order.push_back((int32_t)order.size());
+    }
+    all.stage();
+    const int64_t n_big[2] = {5, 0};  // of kRefitBigPoints points or more, in the order
+    std::vector<Refit> got(K);
+    std::vector<float> vx(K), vy(K), heading(K);
+    std::vector<int32_t> n_inliers(K), n_near(K), best_hyp(K);
+    std::vector<uint8_t> status(K);
+    std::vector<uint32_t> bits(all.theta.size() / 32 + 1);
+    const Outputs o = {vx.data(), vy.data(), heading.data(), n_inliers.data(), status.data(),
+                       n_near.data(), best_hyp.data(), nullptr, bits.data()};
+    std::vector<unsigned long long> keys(K), want(K);
+    const FrameClusterAt at = {off.data(), order.data(), (int64_t)all.theta.size(), seed, 3, 0, 0,
+                               keys.data()};
+    int n_deferred = 0;
+    for (int64_t k = 0; k < K; ++k) {
+        const Span sp = at.span(k);
+        const ClusterId id = at.id(k);
+        Cluster c = clusters[k];
+        want[k] = sp.n < 2 ? 0 : full_key(c, id, 0, n_hyp);
+        const bool defer = sp.n >= kRefitBigPoints && (k < 3 || rng() % 2);
+        n_deferred += defer;
+        keys[k] = defer ? kDeferred | (rng() % 2 ? want[k] & ~1ull : 0) : want[k];
+    }
+    const auto run = [&](const std::vector<uint32_t> &blocks, uint32_t grid) {
+        gridDim.x = grid;
+        for (uint32_t b : blocks) {
+            blockIdx.x = b;
+            static RefitSpace<B> space;
+            memset((void *)&space, 0xFF, sizeof space);
+            emu::run(B, rng(), [&] {
+                refit_planned<B>(K, n_big, at, n_hyp, all.pts, 1.0f * kTau, o, space, false);
+            });
+        }
+    };
+    const uint32_t extra = 8 * (1 + rng() % 3);
+    std::vector<uint32_t> blocks(K + extra);
+    for (uint32_t b = 0; b < blocks.size(); ++b) blocks[b] = b;
+    std::shuffle(blocks.begin(), blocks.end(), rng);
+    run(blocks, (uint32_t)blocks.size());
+    const auto vx1 = vx, vy1 = vy, heading1 = heading;
+    const auto n1 = n_inliers, near1 = n_near, best1 = best_hyp;
+    const auto status1 = status;
+    const auto bits1 = bits;
+    keys = want;
+    for (int64_t k = 0; k < K; ++k) order[k] = (int32_t)k;
+    std::fill(bits.begin(), bits.end(), 0);
+    std::fill(status.begin(), status.end(), 99);
+    blocks.resize(K);
+    for (uint32_t b = 0; b < blocks.size(); ++b) blocks[b] = b;
+    run(blocks, (uint32_t)K);
+    const auto same = [&](const void *a, const void *b, size_t n, const char *what) {
+        check(!memcmp(a, b, n), what, (int)seed, n_deferred);
+    };
+    same(vx1.data(), vx.data(), K * 4, "deferred: vx, seed, deferred clusters");
+    same(vy1.data(), vy.data(), K * 4, "deferred: vy, seed, deferred clusters");
+    same(heading1.data(), heading.data(), K * 4, "deferred: heading, seed, deferred clusters");
+    same(n1.data(), n_inliers.data(), K * 4, "deferred: n_inliers, seed, deferred clusters");
+    same(near1.data(), n_near.data(), K * 4, "deferred: n_near, seed, deferred clusters");
+    same(best1.data(), best_hyp.data(), K * 4, "deferred: best, seed, deferred clusters");
+    same(status1.data(), status.data(), K, "deferred: status, seed, deferred clusters");
+    same(bits1.data(), bits.data(), bits.size() * 4, "deferred: mask, seed, deferred clusters");
+}
+
 }  // namespace
 
 int main(int argc, char **argv) {
@@ -204,6 +286,8 @@ int main(int argc, char **argv) {
         other_workgroups<true>();
     } else if (!strcmp(what, "refit-order")) {
         refit_order();
+    } else if (!strcmp(what, "deferred")) {
+        for (uint32_t seed = 0; seed < 3; ++seed) deferred<kLongBlock>(seed % 2 ? 512 : 257, seed + 50);
     } else {
         return 2;
     }

@@ -46,6 +46,6 @@ def check(tmp_path_factory):
     return run
 
 
-@pytest.mark.parametrize("what", ["no-reference", "other-workgroups", "refit-order"])
+@pytest.mark.parametrize("what", ["no-reference", "other-workgroups", "refit-order", "deferred"])
 def test_any_order_of_the_waves(check, what):
     check(what)
