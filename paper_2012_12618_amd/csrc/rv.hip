@@ -118,6 +118,22 @@ __host__ __device__ constexpr int refit_big_class(int64_t n_clusters) {
     return n_clusters >= kRefitManyClusters ? kRefitBigClass : kRefitBigClassFew;
 }
 constexpr int kXcds = 8;                // MI355X: 8 XCDs, workgroups dealt round-robin
+// Where a scoring workgroup has all hypotheses of a cluster (1024 in four blocks, see
+// score_rounds), clusters from this size on are split between two: the largest
+// workgroup sets the end of a frame whose workgroups are few more than fit the chip.
+// Scoring and refit of 4096 clusters of 8 to 4096 points at 20, 60 and 90 % outliers 81,
+// 182 and 312 us unsplit, 81, 137 and 234 us split; 2100 of 16 to 8192 points 110, 290
+// and 560 us, 79, 227 and 292 us; but 2100 of 2048 points each 100 and 104 us at 20 %.
+constexpr int64_t kSplitPoints = 2048;
+constexpr int kSplitClass = 45;         // size class of kSplitPoints
+constexpr int32_t kSplitParts = 2;
+
+// The most clusters that are split (the grid has room for them), a multiple of kXcds.
+// More than n_points / kSplitPoints can be that large where offsets are not ascending.
+__host__ __device__ constexpr int64_t split_max(int64_t n_clusters, int64_t n_points) {
+    const int64_t room = n_points / kSplitPoints < n_clusters ? n_points / kSplitPoints : n_clusters;
+    return (room + kXcds - 1) / kXcds * kXcds;
+}
 constexpr int kPrepBlock = 256;
 constexpr int kRowsMax = 16;            // register rows per pass, the most a tuning may name
 constexpr int kPassRows = 12;           // register rows per pass, the most the float32 loop holds
@@ -261,10 +277,11 @@ __device__ __forceinline__ uint32_t wave_exclusive_sum(uint32_t x, int lane) {
     return incl - x;
 }
 
-// Start of each size class in the dispatch order (largest class first) and the
-// number of clusters refit by a whole workgroup; the first wave of the block.
+// Start of each size class in the dispatch order (largest class first), the
+// number of clusters refit by a whole workgroup (n_big[0]) and split between scoring
+// workgroups (n_big[1]); the first wave of the block.
 __device__ __forceinline__ void plan_scan(const uint32_t *count, uint32_t *start, int big_class,
-                                          int64_t *__restrict__ n_big) {
+                                          int64_t most_split, int64_t *__restrict__ n_big) {
     if (threadIdx.x < kWave) {
         // Position q = 0, 1, ... in the dispatch order is class kSizeClasses - 1 - q.
         const int lane = threadIdx.x;
@@ -273,9 +290,15 @@ __device__ __forceinline__ void plan_scan(const uint32_t *count, uint32_t *start
         const uint32_t excl = wave_exclusive_sum(a + b, lane);
         start[c_hi] = excl;
         start[c_lo] = excl + a;
-        // Clusters refit by a whole workgroup: classes big_class and up.
-        if (c_hi == big_class) *n_big = excl + a;
-        if (c_lo == big_class) *n_big = excl + a + b;
+        // Clusters refit by a whole workgroup: classes big_class and up; clusters split
+        // between scoring workgroups, a multiple of kXcds.
+        if (c_hi == big_class) n_big[0] = excl + a;
+        if (c_lo == big_class) n_big[0] = excl + a + b;
+        if (c_hi == kSplitClass || c_lo == kSplitClass) {
+            const int64_t n = excl + a + (c_lo == kSplitClass ? b : 0u);
+            const int64_t whole = (n + kXcds - 1) / kXcds * kXcds;
+            n_big[1] = whole < most_split ? whole : most_split;
+        }
     }
 }
 
@@ -302,7 +325,7 @@ __device__ void plan_order(const int32_t *__restrict__ off, int64_t point_base, 
         for (int u = 0; u < kPlanUnroll; ++u)
             if (cls[u] >= 0) atomicAdd(&count[cls[u]], 1u);
         __syncthreads();
-        plan_scan(count, start, big_class, n_big);
+        plan_scan(count, start, big_class, split_max(n_clusters, n_points), n_big);
         __syncthreads();
 #pragma unroll
         for (int u = 0; u < kPlanUnroll; ++u) {
@@ -325,7 +348,7 @@ __device__ void plan_order(const int32_t *__restrict__ off, int64_t point_base, 
             if (cls[u] >= 0) atomicAdd(&count[cls[u]], 1u);
     }
     __syncthreads();
-    plan_scan(count, start, big_class, n_big);
+    plan_scan(count, start, big_class, split_max(n_clusters, n_points), n_big);
     __syncthreads();
     for (int64_t k0 = threadIdx.x; k0 < n_clusters; k0 += group) {
         int cls[kPlanUnroll];
@@ -2086,6 +2109,10 @@ struct FrameClusterAt {
 // 92.5 us); from 512 points on, 4096 clusters of 512 points take 97.4 us for 91.9.
 // The batched kernel does not: its registers spill (256 frames 2369 to 2426 us).
 //
+// n_split (nullable; with refit_big): the first *n_split clusters are split between `parts`
+// workgroups of `rounds` blocks (see kSplitPoints), which do not refit them, and each
+// other cluster has one workgroup, behind them.
+//
 // Work item = (cluster, `rounds` blocks of 256 hypotheses).  Block i takes the
 // item that keeps clusters in the planned order while all items of one cluster
 // run on the same XCD (blocks are dealt to the 8 XCDs round-robin), sharing that
@@ -2096,11 +2123,20 @@ __global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(B == kLongBlo
     const int32_t *__restrict__ off, int32_t *order, int64_t n_clusters,
     int64_t n_points, int32_t n_hyp, int32_t rounds, int32_t parts, uint32_t key0, uint32_t key1,
     uint32_t cluster_base, int64_t point_base, int32_t small_max, int64_t prune, Points pts,
-    float tau, unsigned long long *__restrict__ best_key, Outputs o, bool refit_big, bool defer) {
+    float tau, unsigned long long *__restrict__ best_key, Outputs o, bool refit_big,
+    const int64_t *__restrict__ n_split, bool defer) {
     __shared__ ScoreShared<B> s;
     const uint32_t xcd = blockIdx.x % kXcds;
     const uint32_t r = blockIdx.x / kXcds;
-    const int64_t j = xcd + (int64_t)kXcds * (r / (uint32_t)parts);
+    int64_t j = xcd + (int64_t)kXcds * (r / (uint32_t)parts);
+    uint32_t part = r % (uint32_t)parts;
+    const int64_t split = n_split != nullptr ? *n_split : 0;
+    const bool whole = n_split != nullptr && blockIdx.x >= split * parts;  // not split
+    if (whole) {
+        j = blockIdx.x - split * (parts - 1);
+        part = 0;
+        rounds *= parts;
+    }
     if (j >= n_clusters) return;
     const FrameClusterAt at = {off, order, n_points, key0, key1, cluster_base, point_base,
                                best_key};
@@ -2108,13 +2144,13 @@ __global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(B == kLongBlo
     const ClusterId id = at.id(j);
     const Span sp = at.span(j);
     const int most = rounds * B;
-    const int64_t first = (int64_t)(r % (uint32_t)parts) * most;
+    const int64_t first = (int64_t)part * most;
     const int64_t left = n_hyp - first;
     const unsigned long long key = score_hypotheses<B>(
         sp, id, first, left < most ? (int)left : most, n_hyp, pts, tau, kRowsMax, kSingleLanesMax,
         small_max, prune, false, defer, s, &best_key[k], o.hyp_counts);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    if (refit_big && sp.n >= kRefitBigPoints)
+    if (refit_big && (n_split == nullptr || whole) && sp.n >= kRefitBigPoints)
         refit_cluster(sp, id, key, pts, tau, o, wave, B / kWave, s.refit());
     else
         merge_key(&best_key[k], key, wave, threadIdx.x % kWave);
@@ -2218,14 +2254,18 @@ __device__ __forceinline__ void refit_deferred(int64_t n_clusters, int32_t n_hyp
     }
 }
 
+// Clusters that their scoring workgroups have refit: none, those of kRefitBigPoints
+// points or more, or of these the ones that are not split.
+enum RefitDone : int32_t { kNoneDone = 0, kBigDone = 1, kUnsplitDone = 2 };
+
 // Refit of a frame's or batch's clusters over their planned (largest-first)
 // positions, in one launch: workgroups [0, n_big) take the first n_big
 // clusters (kRefitBigPoints or more, see there for frames of few), one each with
 // all its waves; the following workgroups take the other clusters one per wave.  n_big is counted on the
 // device by the ordering pass; without an order (n_big == nullptr) every
 // cluster gets a workgroup.  The grid is an upper bound (one workgroup per
-// cluster); surplus workgroups exit at once.  big_done: the first n_big clusters
-// were refit by their scoring workgroups.
+// cluster); surplus workgroups exit at once.  done: which of the
+// big clusters were refit by their scoring workgroups.
 //
 // Behind them, where clusters may have been deferred: gridDim.x - n_clusters workgroups
 // that count and refit those (refit_deferred).
@@ -2233,7 +2273,7 @@ template <int B, typename ClusterAt>
 __device__ __forceinline__ void refit_planned(int64_t n_clusters, const int64_t *n_big,
                                               const ClusterAt &at, int32_t n_hyp, const Points &pts,
                                               float tau, const Outputs &o, RefitSpace<B> &space,
-                                              bool big_done) {
+                                              RefitDone done) {
     constexpr int kWaves = B / kWave;
     RefitShared<kWaves> &sh = space.refit();
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
@@ -2243,8 +2283,12 @@ __device__ __forceinline__ void refit_planned(int64_t n_clusters, const int64_t 
             return;
         }
     }
-    const int64_t big = n_big != nullptr ? *n_big : n_clusters;
-    const int64_t b = big_done ? blockIdx.x + big : blockIdx.x;
+    const int64_t big = n_big != nullptr ? n_big[0] : n_clusters;
+    int64_t b = blockIdx.x;
+    if (done != kNoneDone) {
+        const int64_t from = done == kBigDone ? 0 : n_big[1] < big ? n_big[1] : big;
+        if (b >= from) b += big - from;
+    }
     const bool all = b < big;  // the whole workgroup on one cluster
     const int64_t j = all ? b : big + (b - big) * kWaves + wave;
     if (j >= n_clusters) return;
@@ -2258,11 +2302,11 @@ __global__ __launch_bounds__(B) void refit_kernel(
     const int32_t *__restrict__ off, int32_t *order, int64_t n_clusters,
     const int64_t *__restrict__ n_big, int64_t n_points, int32_t n_hyp, uint32_t key0, uint32_t key1,
     uint32_t cluster_base, int64_t point_base, Points pts, unsigned long long *best_key, float tau,
-    Outputs o, bool big_done) {
+    Outputs o, RefitDone done) {
     __shared__ RefitSpace<B> s_refit;
     const FrameClusterAt at = {off, order, n_points, key0, key1, cluster_base, point_base,
                                best_key};
-    refit_planned<B>(n_clusters, n_big, at, n_hyp, pts, tau, o, s_refit, big_done);
+    refit_planned<B>(n_clusters, n_big, at, n_hyp, pts, tau, o, s_refit, done);
 }
 
 // Small frames (see use_cluster_path): one workgroup per cluster stages the
@@ -2549,7 +2593,7 @@ __device__ void plan_batch(const int32_t *__restrict__ off, int64_t n_clusters, 
     for (int u = 0; u < kPlanBatchEach; ++u)
         if (cls[u] >= 0) atomicAdd(&count[cls[u]], 1u);
     __syncthreads();
-    plan_scan(count, start, refit_big_class(n_clusters), n_big);
+    plan_scan(count, start, refit_big_class(n_clusters), 0, n_big);
     __syncthreads();
     for (int64_t k = threadIdx.x; k < n_clusters; k += kPrepBlock) {
         const Span sp = cluster_span(off, k, n_points);
@@ -2586,13 +2630,13 @@ __global__ __launch_bounds__(kPrepBlock) void batch_scatter_kernel(
     __shared__ uint32_t start[kSizeClasses];
     __shared__ uint32_t count[kSizeClasses];
     __shared__ uint32_t base[kSizeClasses];
-    __shared__ int64_t s_big;
+    __shared__ int64_t s_big[2];
     for (int c = threadIdx.x; c < kSizeClasses; c += kPrepBlock) {
         count[c] = 0;
         total[c] = hist[c];
     }
     __syncthreads();
-    plan_scan(total, start, refit_big_class(n_clusters), &s_big);
+    plan_scan(total, start, refit_big_class(n_clusters), 0, s_big);
     const int64_t k = (int64_t)blockIdx.x * kPrepBlock + threadIdx.x;
     int cls = -1;
     uint32_t rank = 0;
@@ -2605,7 +2649,7 @@ __global__ __launch_bounds__(kPrepBlock) void batch_scatter_kernel(
     __syncthreads();
     for (int c = threadIdx.x; c < kSizeClasses; c += kPrepBlock)
         base[c] = count[c] != 0 ? start[c] + atomicAdd(class_cursor(queues, c), count[c]) : 0u;
-    if (blockIdx.x == 0 && threadIdx.x == 0) *n_big = s_big;
+    if (blockIdx.x == 0 && threadIdx.x == 0) n_big[0] = s_big[0];
     __syncthreads();
     if (cls < 0) return;
     write_desc(k, sp, frame_of_cluster(bt.frame_off, bt.n_frames, k), bt, tune, desc[base[cls] + rank]);
@@ -2678,7 +2722,7 @@ __global__ __launch_bounds__(B) void batch_refit_kernel(
     unsigned long long *best_key, float tau, Outputs o) {
     __shared__ RefitSpace<B> s_refit;
     const BatchClusterAt at = {desc, best_key};
-    refit_planned<B>(n_clusters, n_big, at, n_hyp, pts, tau, o, s_refit, false);
+    refit_planned<B>(n_clusters, n_big, at, n_hyp, pts, tau, o, s_refit, kNoneDone);
 }
 
 __global__ __launch_bounds__(kPrepBlock) void philox_kernel(const uint32_t *__restrict__ ctr,
@@ -2726,7 +2770,7 @@ Layout make_layout(int64_t n_clusters, int64_t n_points) {
     L.low = at; at = align_up(at + np * sizeof(StagedLow));
     L.order = at; at = align_up(at + (size_t)n_clusters * sizeof(int32_t));
     L.best_key = at; at = align_up(at + (size_t)n_clusters * sizeof(unsigned long long));
-    L.n_big = at; at = align_up(at + sizeof(int64_t));
+    L.n_big = at; at = align_up(at + 2 * sizeof(int64_t));
     L.total = at;
     return L;
 }
@@ -2748,7 +2792,7 @@ BatchLayout make_batch_layout(int64_t n_clusters, int64_t n_points) {
     L.best_key = at; at = align_up(at + nc * sizeof(unsigned long long));
     L.hist = at; at = align_up(at + kSizeClasses * sizeof(uint32_t));
     L.queues = at; at = align_up(at + kXcds * kQueueStride * sizeof(unsigned long long));
-    L.n_big = at; at = align_up(at + sizeof(int64_t));
+    L.n_big = at; at = align_up(at + 2 * sizeof(int64_t));
     L.total = at;
     return L;
 }
@@ -2956,7 +3000,7 @@ void launch_refit(bool batch, const int32_t *off, int32_t *order, ItemDesc *desc
                   int64_t n_clusters, const int64_t *n_big, int64_t n_points, int32_t n_hyp,
                   uint32_t key0, uint32_t key1, uint32_t cluster_base, int64_t point_base,
                   const Points &pts, unsigned long long *best_key, float tau, const Outputs &o,
-                  bool big_done, bool large, bool defer, hipStream_t st) {
+                  RefitDone done, bool large, bool defer, hipStream_t st) {
     const dim3 block(large ? kLongBlock : kRefitBlock);
     const dim3 grid((unsigned)(n_clusters + (defer ? kDeferredBlocks : 0)));
     if (batch)
@@ -2965,7 +3009,7 @@ void launch_refit(bool batch, const int32_t *off, int32_t *order, ItemDesc *desc
     else
         hipLaunchKernelGGL(large ? refit_kernel<kLongBlock> : refit_kernel<kRefitBlock>,
                            grid, block, 0, st, off, order, n_clusters, n_big, n_points, n_hyp, key0,
-                           key1, cluster_base, point_base, pts, best_key, tau, o, big_done);
+                           key1, cluster_base, point_base, pts, best_key, tau, o, done);
 }
 
 // Persistent grid of the batched scoring kernel on the current device.
@@ -3046,7 +3090,7 @@ int launch_batch(const BatchArgs &a, unsigned grid, hipStream_t st, bool allow_t
                        a.o.hyp_counts);
     if (timed) (void)hipEventRecord(tc.ev[2], st);
     launch_refit(true, nullptr, nullptr, desc, a.n_clusters, n_big, a.n_points, a.n_hyp, 0, 0, 0, 0,
-                 pts, best_key, a.tau, a.o, false, plan.block == kLongBlock, plan.defer, st);
+                 pts, best_key, a.tau, a.o, kNoneDone, plan.block == kLongBlock, plan.defer, st);
     if (timed) {
         (void)hipEventRecord(tc.ev[3], st);
         keep_timed_call(tc);
@@ -3176,6 +3220,10 @@ int estimate_frame(const float *theta, const float *vd, const int32_t *cluster_o
         plan_score(n_clusters, n_points, n_hyp, tau, hyp_counts, kSingleLanesMax, 0);
     const bool many = n_clusters >= kRefitManyClusters;
     const bool refit_big = plan.parts == 1 && many && order != nullptr;  // the order counts them
+    const bool split = refit_big && plan.rounds == kPruneHyp / kScoreBlock;
+    const int32_t parts = split ? kSplitParts : plan.parts;
+    int64_t score_blocks = clusters_xcd * parts;
+    if (split) score_blocks = n_clusters + (parts - 1) * split_max(n_clusters, n_points);
     const bool defer = plan.defer && order != nullptr;
     int64_t prep_items = n_points > n_words ? n_points : n_words;
     prep_items = prep_items > n_clusters ? prep_items : n_clusters;
@@ -3187,14 +3235,16 @@ int estimate_frame(const float *theta, const float *vd, const int32_t *cluster_o
     if (timed) (void)hipEventRecord(tc.ev[1], st);
     hipLaunchKernelGGL(plan.block == kLongBlock ? score_kernel<kLongBlock>
                                                 : score_kernel<kScoreBlock>,
-                       dim3((unsigned)(clusters_xcd * plan.parts)), dim3(plan.block), 0, st,
+                       dim3((unsigned)score_blocks), dim3(plan.block), 0, st,
                        cluster_offsets, order, n_clusters, n_points, n_hyp,
-                       plan.rounds, plan.parts, key0, key1, first_cluster, first_point,
-                       plan.small_max, plan.prune, pts, tau, best_key, o, refit_big, defer);
+                       split ? plan.rounds / parts : plan.rounds, parts, key0, key1, first_cluster,
+                       first_point, plan.small_max, plan.prune, pts, tau, best_key, o, refit_big,
+                       split ? (const int64_t *)n_big + 1 : nullptr, defer);
     if (timed) (void)hipEventRecord(tc.ev[2], st);
     launch_refit(false, cluster_offsets, order, nullptr, n_clusters,
                  order != nullptr ? (const int64_t *)n_big : nullptr, n_points, n_hyp, key0, key1,
-                 first_cluster, first_point, pts, best_key, tau, o, refit_big, plan.block == kLongBlock, defer, st);
+                 first_cluster, first_point, pts, best_key, tau, o, 
+                 !refit_big ? kNoneDone : split ? kUnsplitDone : kBigDone, plan.block == kLongBlock, defer, st);
     if (timed) {
         (void)hipEventRecord(tc.ev[3], st);
         keep_timed_call(tc);

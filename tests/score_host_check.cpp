@@ -242,7 +242,7 @@ void deferred(int32_t n_hyp, uint32_t seed) {
             static RefitSpace<B> space;
             memset((void *)&space, 0xFF, sizeof space);
             emu::run(B, rng(), [&] {
-                refit_planned<B>(K, n_big, at, n_hyp, all.pts, 1.0f * kTau, o, space, false);
+                refit_planned<B>(K, n_big, at, n_hyp, all.pts, 1.0f * kTau, o, space, kNoneDone);
             });
         }
     };

@@ -1,8 +1,9 @@
 """GPU: clusters in which the bound of score_pruned (csrc/rv.hip) excludes too little:
 many outliers, a threshold far below the noise, no structure at all.  They are counted
 in full after all, in place, by score_small, or deferred to the workgroups behind the
-refit (few, long clusters).  As in test_gpu_pruned, every output equals, bit for bit,
-that of the call which counts every hypothesis.  Tolerance: none."""
+refit (few, long clusters); large clusters of dense frames are split between two scoring
+workgroups.  As in test_gpu_pruned, every output equals, bit for bit, that of the call
+which counts every hypothesis.  Tolerance: none."""
 from __future__ import annotations
 
 import numpy as np
@@ -27,7 +28,7 @@ def test_few_clusters(rv, n_hyp, tau):  # noqa: F811
 
 @pytest.mark.parametrize("n_hyp", [512, 600, 1024, 1025])
 def test_many_clusters(rv, n_hyp):  # noqa: F811
-    """Two and four blocks of hypotheses per workgroup."""
+    """Two and four blocks of hypotheses per workgroup, split and whole clusters."""
     part = noisy(SIZES, 400)
     few = [cluster(40, 5)] * (2100 - 2 * len(part))
     compare(rv, *frame_of(part + few + part), n_hyp, 0.15, 32, f"give up, many H={n_hyp}")
@@ -99,3 +100,11 @@ def test_graph_of_deferred_clusters(rv):  # noqa: F811
                     assert np.array_equal(a.view(np.uint8), b.view(np.uint8)), (rep, k)
     finally:
         graph.destroy()
+
+
+def test_more_large_clusters_than_points_allow(rv):  # noqa: F811
+    """Offsets that go back again and again: more clusters of 2048 points than fit the
+    points one after the other (each is a valid range, so each is estimated)."""
+    theta, vd = cluster(4096, 77, p_uniform=0.3)
+    off = np.resize(np.array([0, 2048, 4096], np.int32), 3001)
+    compare(rv, theta, vd, off, 1024, 0.15, 34, "ranges again and again", bits=False)
