@@ -733,7 +733,8 @@ int rv_estimate_velocity_paper(const float *theta, const float *vd, const int32_
                        (n_points + 31) / 32);
     if (timed) (void)hipEventRecord(tc.ev[1], st);
     const int64_t bpc64 = ((int64_t)n_hyp + kWave - 1) / kWave;
-    const bool fine = n_clusters * bpc64 <= INT32_MAX;  // else the grid would be too large
+    // A grid's threads have to stay below 2^32 (HIP refuses it otherwise).
+    const bool fine = n_clusters * bpc64 <= (int64_t)UINT32_MAX / kPaperBlock;
     hipLaunchKernelGGL(fine ? paper_score_kernel<kWave> : paper_score_kernel<kPaperBlock>,
                        dim3((unsigned)(n_clusters * (fine ? bpc64 : bpc))), dim3(kPaperBlock), 0, st,
                        theta, cluster_offsets, n_points, n_hyp, (int32_t)(fine ? bpc64 : bpc), key0,
