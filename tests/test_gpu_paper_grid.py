@@ -1,5 +1,6 @@
-"""GPU: the paper-literal variant with more trials than a grid of 64 each has room for (a
-grid's threads stay below 2^32).  Tolerance: none."""
+"""GPU: the paper-literal variant's launches at the ends of their sizes: more trials than
+a grid of 64 each has room for (a grid's threads stay below 2^32), and a frame-wide mask
+far larger than its clusters' points.  Tolerance: none."""
 import numpy as np
 import pytest
 
@@ -32,3 +33,21 @@ def test_most_trials_of_many_clusters(rv):
     for k in ("vx", "vy", "heading", "n_inliers", "status", "inlier_bits"):
         assert torch.equal(got[k], few[k]), k
     assert int(got["status"].max()) == 0
+
+
+@pytest.mark.parametrize("points", [31, 4096, 40_000_000])
+def test_mask_beyond_the_clusters_points(rv, points):
+    """Every word of the mask is cleared, also those of points in no cluster."""
+    theta = torch.zeros(points, device="cuda")
+    vd = torch.zeros(points, device="cuda")
+    theta[:20] = torch.linspace(-1, 1, 20)
+    vd[:20] = 3 * torch.cos(theta[:20])
+    off = torch.tensor([0, 20], dtype=torch.int32, device="cuda")
+    print(f"[gpu] paper variant, mask of {points} points", flush=True)
+    out = rv.allocate_paper_outputs(1, points, 100, theta.device, want_bits=True)
+    out["inlier_bits"].fill_(-1)
+    rv.rv_estimate_velocity_paper(theta, vd, off, 100, 3, out=out)
+    torch.cuda.synchronize()
+    bits = out["inlier_bits"]
+    assert bin(int(bits[0]) & 0xFFFFFFFF).count("1") == int(out["n_inliers"][0])
+    assert int(bits[0]) >> 20 == 0 and int(bits[1:].ne(0).sum()) == 0
