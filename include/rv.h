@@ -234,7 +234,7 @@ int rv_estimate_velocity_noalloc(const float *theta, const float *vd,
  * (h, k - frame_offsets[f], 0, 0): every cluster's outputs are bitwise those
  * rv_estimate_velocity gives for its frame alone with seed seeds[f].  The
  * scoring runs as one persistent launch that drains a device work queue of
- * (cluster, block of 256 hypotheses) items, largest clusters first.
+ * (cluster, up to 1024 hypotheses) items, largest clusters first.
  */
 
 /* Cluster-size buckets of the tuning table: bucket 0 holds n < 64, bucket b
@@ -242,8 +242,9 @@ int rv_estimate_velocity_noalloc(const float *theta, const float *vd,
 #define RV_TUNE_BUCKETS 8
 
 typedef struct {
-    /* register rows of 64 points scored per pass, 1..16 (more than 12 as 12), per
-       size bucket, where every hypothesis is counted with lanes = points */
+    /* register rows of 64 points scored per pass, 1..16 (more than 12 as 12; in the
+       FP16 form rounded up to a multiple of four), per size bucket, where every
+       hypothesis is counted with lanes = points */
     int32_t rows_max[RV_TUNE_BUCKETS];
     /* persistent scoring grid: workgroups per compute unit; 0 = as many as fit */
     int32_t blocks_per_cu;

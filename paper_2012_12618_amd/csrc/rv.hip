@@ -137,6 +137,10 @@ __host__ __device__ constexpr int64_t split_max(int64_t n_clusters, int64_t n_po
 constexpr int kPrepBlock = 256;
 constexpr int kRowsMax = 16;            // register rows per pass, the most a tuning may name
 constexpr int kPassRows = 12;           // register rows per pass, the most the float32 loop holds
+// And in the single-frame kernels, which with twelve spill (a wave that uses scratch starts
+// later): full count of 4096 clusters of 256 points 35.9 and 33.7 us, of 64 of 65,536 points
+// 1110 and 1135 us a call.
+constexpr int kFrameRows = 10;
 constexpr int kHypGroup = 4;            // hypotheses per LDS fetch in the scoring loop
 constexpr int kSizeClasses = 128;       // quarter-octave size classes for the dispatch order
 constexpr int64_t kPlanMaxClusters = 1 << 16;  // above this, clusters run in index order
@@ -668,7 +672,7 @@ struct RowsShared {
 // index) key over its valid hypotheses, the same in every thread.  Called by all
 // threads of the block, also from the persistent loop (every branch around a
 // barrier is on a wave-uniform value).
-template <int B>
+template <int B, int kRows>
 __device__ __forceinline__ unsigned long long score_block(Span sp, ClusterId id, int b, int q,
                                                           bool drawn, int32_t n_hyp,
                                                           const Points &pts, float tau, int rows_max,
@@ -710,8 +714,8 @@ __device__ __forceinline__ unsigned long long score_block(Span sp, ClusterId id,
         rows.n -= tail;
         uint32_t cnt = 0;
         if (rows.n > 0)
-            cnt = score_cluster<kPassRows, true>(pts, rows, lane, hyp + wave * (kWave / 2), nh, tau,
-                                                 rows_max);
+            cnt = score_cluster<kRows, true>(pts, rows, lane, hyp + wave * (kWave / 2), nh, tau,
+                                             rows_max);
         // The lane's own hypothesis is re-read from LDS rather than kept in
         // registers through the scoring loop.
         own = reinterpret_cast<const float2 *>(hyp)[tid];
@@ -1625,7 +1629,7 @@ struct ScoreShared {
 // with `defer` those of kDeferPoints points or more get kDeferred for a key; otherwise
 // clusters of at most lanes_max points take lanes = hypotheses and the others
 // lanes = points.
-template <int B, bool kFp16 = false>
+template <int B, int kRows, bool kFp16 = false>
 __device__ __forceinline__ unsigned long long score_hypotheses(
     Span sp, ClusterId id, int64_t h_first, int nh, int32_t n_hyp, const Points &pts, float tau,
     int rows_max, int lanes_max, int small_max, int64_t prune, bool half, bool defer,
@@ -1647,7 +1651,7 @@ __device__ __forceinline__ unsigned long long score_hypotheses(
     const int b0 = (int)(h_first / B), blocks = (nh + B - 1) / B;
     unsigned long long best = 0;
     for (int q = 0; q < blocks; ++q) {
-        const unsigned long long key = score_block<B>(sp, id, b0 + q, q, drawn, n_hyp, pts, tau,
+        const unsigned long long key = score_block<B, kRows>(sp, id, b0 + q, q, drawn, n_hyp, pts, tau,
                                                       rows_max, lanes_max, sh.rows(), hyp_counts);
         best = key > best ? key : best;
     }
@@ -2146,7 +2150,7 @@ __global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(B == kLongBlo
     const int most = rounds * B;
     const int64_t first = (int64_t)part * most;
     const int64_t left = n_hyp - first;
-    const unsigned long long key = score_hypotheses<B>(
+    const unsigned long long key = score_hypotheses<B, B == kLongBlock ? kPassRows : kFrameRows>(
         sp, id, first, left < most ? (int)left : most, n_hyp, pts, tau, kRowsMax, kSingleLanesMax,
         small_max, prune, false, defer, s, &best_key[k], o.hyp_counts);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
@@ -2335,7 +2339,7 @@ __global__ __launch_bounds__(kScoreBlock) __attribute__((amdgpu_waves_per_eu(8))
     id.key0 = key0;
     id.key1 = key1;
     const unsigned long long best =
-        score_hypotheses<kScoreBlock>(sp, id, 0, n_hyp, n_hyp, pts, tau, kRowsMax, kSingleLanesMax,
+        score_hypotheses<kScoreBlock, kFrameRows>(sp, id, 0, n_hyp, n_hyp, pts, tau, kRowsMax, kSingleLanesMax,
                                       small_max, prune, false, false, s, nullptr, o.hyp_counts);
     refit_cluster(sp, id, best, pts, tau, o, __builtin_amdgcn_readfirstlane(threadIdx.x / kWave),
                   kScoreBlock / kWave, s.refit());
@@ -2696,7 +2700,7 @@ __global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(B == kLongBlo
                 return;
             }
         }
-        const unsigned long long key = score_hypotheses<B, kFp16>(
+        const unsigned long long key = score_hypotheses<B, kPassRows, kFp16>(
             desc_span(d), desc_id(d), first, nh, n_hyp, pts, tau, d.rows, desc_lanes(d),
             desc_small(d), half ? 0 : desc_prune(d), half, defer, s,
             &best_key[d.out], hyp_counts);

@@ -74,7 +74,7 @@ unsigned long long pruned(const Cluster &c, ClusterId id, int64_t first, int nh,
     memset((void *)&shared, 0xFF, sizeof shared);  // what an earlier workgroup left: NaN, -1
     emu::run(kScoreBlock, order, [&] {
         const uint32_t t = threadIdx.x;
-        const unsigned long long k = score_hypotheses<kScoreBlock, kHalf>(
+        const unsigned long long k = score_hypotheses<kScoreBlock, kPassRows, kHalf>(
             c.sp, id, first, nh, (int32_t)first + nh, c.pts, kTau, kRowsMax, 0, 0, 0, kHalf, false, shared,
             best_key, nullptr);
         keys[t] = k;
