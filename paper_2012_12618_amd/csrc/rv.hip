@@ -137,9 +137,9 @@ __host__ __device__ constexpr int64_t split_max(int64_t n_clusters, int64_t n_po
 constexpr int kPrepBlock = 256;
 constexpr int kRowsMax = 16;            // register rows per pass, the most a tuning may name
 constexpr int kPassRows = 12;           // register rows per pass, the most the float32 loop holds
-// And in the single-frame kernels, which with twelve spill (a wave that uses scratch starts
-// later): full count of 4096 clusters of 256 points 35.9 and 33.7 us, of 64 of 65,536 points
-// 1110 and 1135 us a call.
+// And in score_kernel, which with twelve spills (a wave that uses scratch starts later): full
+// count of 4096 clusters of 256 points 35.9 and 33.7 us, of 64 of 65,536 points 1110 and
+// 1135 us a call.  (cluster_kernel spills either way: 10.3 us with twelve, 10.5 with ten.)
 constexpr int kFrameRows = 10;
 constexpr int kHypGroup = 4;            // hypotheses per LDS fetch in the scoring loop
 constexpr int kSizeClasses = 128;       // quarter-octave size classes for the dispatch order
@@ -2339,8 +2339,9 @@ __global__ __launch_bounds__(kScoreBlock) __attribute__((amdgpu_waves_per_eu(8))
     id.key0 = key0;
     id.key1 = key1;
     const unsigned long long best =
-        score_hypotheses<kScoreBlock, kFrameRows>(sp, id, 0, n_hyp, n_hyp, pts, tau, kRowsMax, kSingleLanesMax,
-                                      small_max, prune, false, false, s, nullptr, o.hyp_counts);
+        score_hypotheses<kScoreBlock, kPassRows>(sp, id, 0, n_hyp, n_hyp, pts, tau, kRowsMax,
+                                                 kSingleLanesMax, small_max, prune, false, false, s,
+                                                 nullptr, o.hyp_counts);
     refit_cluster(sp, id, best, pts, tau, o, __builtin_amdgcn_readfirstlane(threadIdx.x / kWave),
                   kScoreBlock / kWave, s.refit());
 }
