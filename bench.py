@@ -25,10 +25,13 @@ if ROOT not in sys.path:
 METRIC = "clusters/s + hyp-point evals/s (% FP32 VALU peak); p50/p99 frame latency"
 FP32_VECTOR_PEAK_TFLOPS = 157.3  # MI355X: 256 CUs x 4 SIMD x 16 lanes x 2 x 2 x 2.4 GHz
 HBM_PEAK_GBPS = 8000.0  # MI355X HBM3E
-# An evaluation is a (hypothesis, point) pair that the estimate decides.  The kernels
-# compute only part of them (a bound shows that a hypothesis cannot win), so the rates
-# are of nominal work and may exceed the peak.
-NOMINAL_NOTE = ("achieved is nominal: 4 FLOP for every hypothesis-point pair decided; in larger "
+# An evaluation is a (hypothesis, point) pair that the estimate decides.  In larger
+# clusters the kernels compute only part of them (a bound shows that a hypothesis cannot
+# win), so 4 FLOP for each of them is nominal work: its rate may exceed the peak and says
+# nothing of the vector units.  `frac_fp32_valu_peak` and `roofline.frac` are of calls
+# that compute every pair, and null where no such call was timed; the nominal rate is
+# kept apart, as `roofline.nominal`.
+NOMINAL_NOTE = ("4 FLOP for every hypothesis-point pair decided, over the timed steps; in larger "
                 "clusters most hypotheses are excluded by a bound and not computed")
 # Algorithmic HBM bytes of the two other stages of the three-kernel path: the
 # staging reads theta and v_d and writes float32 (cos, sin), v_d and the low
@@ -70,6 +73,22 @@ WORKLOAD_TEXT["issue-rates"] = (
     "generation's v_mad_u64_u32, v_mul_hi_u32 and v_fma_f64, eight waves per SIMD "
     "(_lib/issue_probe)")
 FRAME_WORKLOADS = ("dense", "small")
+
+
+def alu_roofline(kernel: str, evals: int, kernel_ms: float, full_ms: float | None, **more) -> dict:
+    """The scoring kernel against the FP32 vector peak.  kernel_ms: of the timed
+    steps; full_ms: of the same work with every pair computed (None: not timed)."""
+    def rate(ms):
+        return FLOP_PER_EVAL * evals / (ms / 1e3) / 1e12 if ms else None
+
+    def frac(ms):
+        return rate(ms) / FP32_VECTOR_PEAK_TFLOPS if ms else None
+
+    return {"bound": "alu", "kernel": kernel, "achieved": rate(full_ms),
+            "peak": FP32_VECTOR_PEAK_TFLOPS, "unit": "TFLOP/s", "frac": frac(full_ms),
+            "full_count_kernel_ms": full_ms, "kernel_ms": kernel_ms,
+            "nominal": {"achieved": rate(kernel_ms), "frac": frac(kernel_ms), "note": NOMINAL_NOTE},
+            "algorithmic_flop_per_launch": FLOP_PER_EVAL * evals, **more}
 
 
 def kernel_code_sha256(path: str) -> str:
@@ -492,7 +511,8 @@ def batch_bench(args, torch, binding, synth, dev) -> dict:
     stage_ms, n_calls = binding.rv_stage_times()
     stage_avg = [x / max(n_calls, 1) for x in stage_ms]
     score_ms = stage_avg[binding.STAGE_NAMES.index("score")]
-    achieved_tflops = FLOP_PER_EVAL * evals / (score_ms / 1e3) / 1e12
+    roofline = alu_roofline("batch_score_kernel", evals, score_ms, None,
+                            traffic=profiled_traffic(name, "batch_score_kernel"))
 
     # The plain per-frame form on the same frames, one call per frame.
     print("[bench] per-frame form on the same frames", file=sys.stderr, flush=True)
@@ -552,19 +572,13 @@ def batch_bench(args, torch, binding, synth, dev) -> dict:
                    "n_hyp": n_hyp, "tau": tau, "evals_per_step": evals,
                    "tuning": tuning.to_dict() if tuning is not None else "default"},
         "clusters_per_s": K / sec,
-        "frac_fp32_valu_peak": achieved_tflops / FP32_VECTOR_PEAK_TFLOPS,
-        "frac_fp32_valu_peak_note": NOMINAL_NOTE,
+        "frac_fp32_valu_peak": roofline["frac"],
         "per_frame_form": {"ms_per_batch": per_frame_ms, "clusters_per_s": K / (per_frame_ms / 1e3),
                            "evals_per_s": evals / (per_frame_ms / 1e3),
                            "scope": "rv_estimate_velocity once per frame, same frames, one stream"},
         "stage_ms": dict(zip(binding.STAGE_NAMES, stage_avg)),
         "wall_ms_per_step": wall * 1e3 / args.steps,
-        "roofline": {"bound": "alu", "kernel": "batch_score_kernel", "achieved": achieved_tflops,
-                     "peak": FP32_VECTOR_PEAK_TFLOPS, "unit": "TFLOP/s",
-                     "frac": achieved_tflops / FP32_VECTOR_PEAK_TFLOPS,
-                     "traffic": profiled_traffic(name, "batch_score_kernel"),
-                     "algorithmic_flop_per_launch": FLOP_PER_EVAL * evals,
-                     "kernel_ms": score_ms, "note": NOMINAL_NOTE},
+        "roofline": roofline,
         "cpu_baseline": cpu,
     }
     return line
@@ -648,7 +662,9 @@ def served_bench(args, torch, binding, synth, dev, extra_fp16: int = 0,
     paced_f, sat_f, _ = out["per_frame"]
     stage_ms, n_calls = out["stages"]
     score_ms_total = stage_ms[binding.STAGE_NAMES.index("score")]
-    achieved_tflops = FLOP_PER_EVAL * sat.evals / (score_ms_total / 1e3) / 1e12 if score_ms_total else 0.0
+    launches = max(n_calls, 1)
+    roofline = alu_roofline("batch_score_kernel", sat.evals / launches, score_ms_total / launches, None,
+                            traffic=None, launches=n_calls)
 
     cpu = None
     if not args.no_cpu_baseline:
@@ -693,15 +709,8 @@ def served_bench(args, torch, binding, synth, dev, extra_fp16: int = 0,
         "served_form": brief(paced_s, sat_s),
         "per_frame_form": brief(paced_f, sat_f),
         "server": sat_s["server"],
-        "frac_fp32_valu_peak": achieved_tflops / FP32_VECTOR_PEAK_TFLOPS,
-        "frac_fp32_valu_peak_note": NOMINAL_NOTE,
-        "roofline": {"bound": "alu", "kernel": "batch_score_kernel", "achieved": achieved_tflops,
-                     "peak": FP32_VECTOR_PEAK_TFLOPS, "unit": "TFLOP/s",
-                     "frac": achieved_tflops / FP32_VECTOR_PEAK_TFLOPS,
-                     "traffic": None,
-                     "algorithmic_flop_per_launch": FLOP_PER_EVAL * sat.evals / max(n_calls, 1),
-                     "kernel_ms": score_ms_total / max(n_calls, 1), "launches": n_calls,
-                     "note": NOMINAL_NOTE},
+        "frac_fp32_valu_peak": roofline["frac"],
+        "roofline": roofline,
         "cpu_baseline": cpu,
     }
     if extra_fp16 > 0:
@@ -900,7 +909,10 @@ def precision_bench(args, torch, binding, synth, dev, oracle_budget_s: float = 1
     recount = fp16_recount_stats(f16["res"]["hyp_counts"], f32["res"]["hyp_counts"],
                                  np.diff(frame.offsets), n_hyp)
     score16 = f16["stage_ms"]["score"]
-    achieved = FLOP_PER_EVAL * evals / (score16 / 1e3) / 1e12
+    # The step asks for hyp_counts: every pair is computed.
+    roofline = alu_roofline("batch_score_kernel", evals, score16, score16,
+                            traffic=profiled_traffic("precision", "batch_score_kernel"),
+                            note="the MI355X vector FP16 and FP32 peaks are the same 157.3 TFLOP/s")
     sec = f16["ms_per_step"] / 1e3
     line = {
         "metric": METRIC,
@@ -927,13 +939,7 @@ def precision_bench(args, torch, binding, synth, dev, oracle_budget_s: float = 1
         "oracle_error": dict(err, scope="FP16-form results (bitwise the float32 form's) against "
                                          "the FP64 oracle, per cluster"),
         "stage_ms": f16["stage_ms"],
-        "roofline": {"bound": "alu", "kernel": "batch_score_kernel", "achieved": achieved,
-                     "peak": FP32_VECTOR_PEAK_TFLOPS, "unit": "TFLOP/s",
-                     "frac": achieved / FP32_VECTOR_PEAK_TFLOPS,
-                     "traffic": profiled_traffic("precision", "batch_score_kernel"),
-                     "algorithmic_flop_per_launch": FLOP_PER_EVAL * evals, "kernel_ms": score16,
-                     "note": "the MI355X vector FP16 and FP32 peaks are the same 157.3 TFLOP/s; "
-                             + NOMINAL_NOTE},
+        "roofline": roofline,
         "cpu_baseline": cpu,
     }
     return line
@@ -1093,13 +1099,17 @@ def frame_bench(args, torch, binding, synth, dev, name) -> dict:
     clusters_per_s = K / sec
     stage_avg = [x / max(n_calls, 1) for x in stage_ms]
     score_ms = stage_avg[binding.STAGE_NAMES.index("score")]
-    achieved_tflops = FLOP_PER_EVAL * evals / (score_ms / 1e3) / 1e12
     # The library's rule for its one-launch path (no inlier mask is requested
     # here): the whole estimate is then one kernel, timed as the scoring stage.
     small_path = n_hyp <= 256 and N <= (1 << 16) and K <= (1 << 16)
     kernel = "cluster_kernel" if small_path else "score_kernel"
-    full_ms = None if small_path or args.no_extras else full_count_score_ms(
+    # The one-launch kernel computes every pair of clusters this small.
+    full_ms = score_ms if small_path else None if args.no_extras else full_count_score_ms(
         torch, binding, theta, vd, offsets, n_hyp, tau, dev)
+    roofline = alu_roofline(
+        kernel, evals, score_ms, full_ms,
+        traffic=None if small_path else profiled_traffic(name), kernel_events_on_steps=n_calls,
+        valu_issue=None if small_path else profiled_valu_issue(name))
 
     # Frame latency: pinned host frame -> device -> estimate -> results in host memory.
     print(f"[bench] latency over {args.latency_frames} distinct frames", file=sys.stderr, flush=True)
@@ -1163,11 +1173,7 @@ def frame_bench(args, torch, binding, synth, dev, name) -> dict:
         "config": {"workload": WORKLOAD_TEXT[name], "clusters": K, "points": N, "n_hyp": n_hyp,
                    "tau": tau, "evals_per_frame": evals},
         "clusters_per_s": clusters_per_s,
-        "frac_fp32_valu_peak": (achieved_tflops if full_ms is None else
-                                FLOP_PER_EVAL * evals / (full_ms / 1e3) / 1e12)
-                               / FP32_VECTOR_PEAK_TFLOPS,
-        "frac_fp32_valu_peak_note": NOMINAL_NOTE if full_ms is None else
-                                    "of the full count (roofline.full_count): every pair computed",
+        "frac_fp32_valu_peak": roofline["frac"],
         "latency_ms": ({"p50": percentile(lat, 50), "p99": percentile(lat, 99), "frames": len(lat),
                         "distinct_frames": len(lat), "frames_recipe": lat_recipe,
                         "scope": "pinned host frame -> H2D -> estimate -> D2H of per-cluster results"}
@@ -1190,20 +1196,7 @@ def frame_bench(args, torch, binding, synth, dev, name) -> dict:
                     "scope": "single steps, a second pass with an event between steps"},
         "stage_ms": dict(zip(binding.STAGE_NAMES, stage_avg)),
         "wall_ms_per_step": wall * 1e3 / args.steps,
-        "roofline": {"bound": "alu", "kernel": kernel, "achieved": achieved_tflops,
-                     "peak": FP32_VECTOR_PEAK_TFLOPS, "unit": "TFLOP/s",
-                     "frac": achieved_tflops / FP32_VECTOR_PEAK_TFLOPS,
-                     "traffic": profiled_traffic(name) if kernel == "score_kernel" else None,
-                     "algorithmic_flop_per_launch": FLOP_PER_EVAL * evals,
-                     "kernel_ms": score_ms, "kernel_events_on_steps": n_calls,
-                     "note": NOMINAL_NOTE,
-                     "full_count": None if full_ms is None else {
-                         "kernel_ms": full_ms,
-                         "achieved": FLOP_PER_EVAL * evals / (full_ms / 1e3) / 1e12,
-                         "frac": FLOP_PER_EVAL * evals / (full_ms / 1e3) / 1e12
-                                 / FP32_VECTOR_PEAK_TFLOPS,
-                         "scope": "the same frame with hyp_counts requested: every pair computed"},
-                     "valu_issue": profiled_valu_issue(name) if kernel == "score_kernel" else None},
+        "roofline": roofline,
         "stage_roofline": None if small_path else {
             st: {"bound": "hbm", "achieved": b / (ms * 1e-3) / 1e9, "peak": HBM_PEAK_GBPS,
                  "unit": "GB/s", "frac": b / (ms * 1e-3) / 1e9 / HBM_PEAK_GBPS,
@@ -1251,7 +1244,7 @@ def default_extras(args, torch, binding, synth, dev) -> dict:
         "workload": WORKLOAD_TEXT["batched"], "ms_per_step": b["ms_per_step"],
         "clusters_per_s": b["clusters_per_s"], "evals_per_s": b["value"],
         "frames": b["config"]["frames"], "clusters": b["config"]["clusters"],
-        "frac_fp32_valu_peak": b["frac_fp32_valu_peak"], "stage_ms": b["stage_ms"],
+        "nominal_frac_fp32_valu_peak": b["roofline"]["nominal"]["frac"], "stage_ms": b["stage_ms"],
         "per_frame_form": b["per_frame_form"],
         "batched_over_per_frame_clusters_per_s":
             b["clusters_per_s"] / b["per_frame_form"]["clusters_per_s"]}
