@@ -2767,11 +2767,19 @@ struct Layout {
     size_t staged, low, order, best_key, n_big, total;
 };
 
+// The points' 12-byte records, with the room of two aligned arrays of 8 and 4 bytes
+// a point: rv_workspace_bytes has always answered with that size, and callers keep
+// workspaces by it.
+size_t staged_bytes(size_t n_points) {
+    static_assert(sizeof(StagedPoint) == 3 * sizeof(float), "12-byte records");
+    return align_up(align_up(n_points * 2 * sizeof(float)) + n_points * sizeof(float));
+}
+
 Layout make_layout(int64_t n_clusters, int64_t n_points) {
     Layout L;
     const size_t np = (size_t)n_points;
     size_t at = 0;
-    L.staged = at; at = align_up(align_up(at + np * 2 * sizeof(float)) + np * sizeof(float));
+    L.staged = at; at += staged_bytes(np);
     L.low = at; at = align_up(at + np * sizeof(StagedLow));
     L.order = at; at = align_up(at + (size_t)n_clusters * sizeof(int32_t));
     L.best_key = at; at = align_up(at + (size_t)n_clusters * sizeof(unsigned long long));
@@ -2791,7 +2799,7 @@ BatchLayout make_batch_layout(int64_t n_clusters, int64_t n_points) {
     BatchLayout L;
     const size_t np = (size_t)n_points, nc = (size_t)n_clusters;
     size_t at = 0;
-    L.staged = at; at = align_up(align_up(at + np * 2 * sizeof(float)) + np * sizeof(float));
+    L.staged = at; at += staged_bytes(np);
     L.low = at; at = align_up(at + np * sizeof(StagedLow));
     L.desc = at; at = align_up(at + nc * sizeof(ItemDesc));
     L.best_key = at; at = align_up(at + nc * sizeof(unsigned long long));

@@ -317,8 +317,8 @@ int launch_slot(rv_server *s, Slot &sl) {
     char *o = d + p.out;
     int rc;
     // A batch of one frame in float32 takes the single-frame launch sequence
-    // (three kernels, or one for a small frame, against the batched form's
-    // six): the same results bit for bit, fewer launches on the frame's path.
+    // (three kernels, or one for a small frame, against the batched form's five
+    // or three): the same results bit for bit, fewer launches on the frame's path.
     // Its workspace fits in the batched one (fewer bytes per cluster).
     if (F == 1 && s->cfg.tuning.fp16_min_points == 0 &&
         rv_workspace_bytes(sl.K, sl.N, s->cfg.n_hyp) <= p.ws_bytes)
